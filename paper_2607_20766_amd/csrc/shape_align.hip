@@ -170,7 +170,8 @@ __global__ __launch_bounds__(kAlignThreads) void k_align(AlignArgs a) {
           for (int s = 0; s < kAS; ++s) {
             // S <- S (1 - o) + o P c  written as  S + o (c P - S): two fused
             // operations per component, and P <- P - o P
-            const float oj = occupancy_x(b, aj, rx[s], ry[s], rz[s], r2[s]);
+            const float oj =
+                __builtin_amdgcn_exp2f(-exponent_x(b, aj, rx[s], ry[s], rz[s], r2[s]));
             S0[s] = fmaf(oj, fmaf(cj.w, P[s], -S0[s]), S0[s]);
             Sx[s] = fmaf(oj, fmaf(cj.x, P[s], -Sx[s]), Sx[s]);
             Sy[s] = fmaf(oj, fmaf(cj.y, P[s], -Sy[s]), Sy[s]);

@@ -371,8 +371,7 @@ __global__ __launch_bounds__(256) void k_query_cache(Prepared Qp, const int* __r
 // library molecules (xcd_chunk).  Per round, `round_side` samples on each side:
 //   side A (query samples, from the cache): f1 = w_A u_B, f2 = w_A u_A
 //   side B (library samples, drawn here):   f1 = w_B u_A, f2 = w_B u_B
-// FP32 in-lane sums per round, FP64 lane accumulators across rounds, wave
-// butterflies for the pair totals (every lane ends with the same value).
+// FP32 in-lane sums per round, summed across the wave and added in FP64.
 // Adaptive mode takes the stopping decision on SE(T) in FP64 after every
 // round; the decision is read from the first lane so the branch is scalar.
 // ---------------------------------------------------------------------------
@@ -406,208 +405,59 @@ __device__ __forceinline__ double se_tanimoto(double n, double Za, double Zb, do
   return fabs(S / (D * D)) * se_O;
 }
 
-template <int kSA, int kSB>
-__global__ __launch_bounds__(64) void k_screen(ScreenArgs a) {
-  // No implicit multiply-add contraction: the fused operations are written
-  // out, so every tile variant rounds identically.
+// A pair's six running sums (sum f1, sum f1^2, sum f2 of side A, then of side
+// B), FP64: lane j < 6 holds sum j.  add() takes one round's per-lane FP32
+// partials, sums each across the wave (DPP) and adds the six totals in one
+// FP64 instruction; get(j) reads sum j in every lane.
+struct RoundSums {
+  double s = 0.0;
+  __device__ __forceinline__ void add(const float (&fa)[3], const float (&fb)[3]) {
+    const int lane = threadIdx.x & (kWave - 1);
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      const float t = wave_sum_dpp(j < 3 ? fa[j] : fb[j - 3]);
+      v = lane == j ? t : v;
+    }
+    s += (double)v;
+  }
+  __device__ __forceinline__ double get(int j) const { return readlane_f64(s, j); }
+};
+
+// Whether a pair stops after n_side samples per side.  Adaptive: at the cap,
+// or once its seeded budget is spent and SE(T) <= tau.  That test needs no
+// division or root: with n independent terms per side, S' = Za a2 + Zb b2,
+// D' = S' - (Za a1 + Zb b1)/2 and V = n a11 - a1^2 (clamped at 0), the
+// delta-method SE satisfies
+//   SE(T)^2 = S'^2 (Za^2 Va + Zb^2 Vb) / (4 (n-1) D'^4),
+// so the test is S'^2 (Za^2 Va + Zb^2 Vb) <= 4 tau^2 (n-1) D'^4 with
+// D' != 0 (NaN sums never stop).
+__device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSums& S,
+                                             int64_t n_side, int64_t first_check, bool anti,
+                                             double Za, double Zb) {
 #pragma clang fp contract(off)
-  // LDS (per pair, n = atoms):
-  //   sBF   [max_b] Atom          library atoms in the library frame (sampling)
-  //   sBS   [max_b] AtomSampling  their sampling records
-  //   sBB   [max_b] AtomRec + a2  library atoms, library frame (own density)
-  //   sBA   [max_b] AtomRec + a2  library atoms, query frame (side A partner)
-  //   sAB   [max_q] AtomRec + a2  query atoms, library frame (side B partner)
-  //   guide [kGuideSize] int      the library molecule's component guide
-  // 16-byte records first, then the 8-byte, then the 4-byte arrays, so every
-  // array is aligned to its element size whatever the atom counts.
-  extern __shared__ __align__(16) unsigned char smem[];
-  Atom* sBF = reinterpret_cast<Atom*>(smem);
-  AtomRec* sBB = reinterpret_cast<AtomRec*>(sBF + a.max_b);
-  AtomRec* sBA = sBB + a.max_b;
-  AtomRec* sAB = sBA + a.max_b;
-  AtomSampling* sBS = reinterpret_cast<AtomSampling*>(sAB + a.max_q);
-  float* aBB = reinterpret_cast<float*>(sBS + a.max_b);
-  float* aBA = aBB + a.max_b;
-  float* aAB = aBA + a.max_b;
-  int* guide = reinterpret_cast<int*>(aAB + a.max_q);  // [kGuideSize] of the library molecule
-  const int lane = threadIdx.x;
-  // grid = n_pairs; a launch order, when given, is a permutation of the pairs
-  const int p = a.order ? a.order[blockIdx.x] : xcd_chunk(blockIdx.x, gridDim.x);
-  if (p < 0 || p >= a.n_pairs) return;
-  const int m = a.pairs ? a.pairs[p] : p;
-  const bool bad = a.Q.bad[0] != 0 || m < 0 || m >= a.n_lib || a.L.bad[m] != 0;
-  if (bad) {
-    if (lane == 0) {
-      const float nanv = __builtin_nanf("");
-      a.T[p] = nanv;
-      a.se_T[p] = nanv;
-      if (a.O_ab) a.O_ab[p] = nanv;
-      if (a.O_aa) a.O_aa[p] = nanv;
-      if (a.O_bb) a.O_bb[p] = nanv;
-      if (a.n_used) a.n_used[p] = 0;
-    }
-    return;
-  }
-  const int q0 = a.offQ[0], nq = a.offQ[1] - a.offQ[0];
-  const int b0 = a.offL[m], nb = a.offL[m + 1] - b0;
-  const float4 cA = a.Q.centre[0];
-  const float4 cB = a.L.centre[m];
-  for (int i = lane; i < nq; i += kWave) make_rec(a.Q.atom[q0 + i], cB.x, cB.y, cB.z, sAB[i], aAB[i]);
-  for (int i = lane; i < nb; i += kWave) {
-    const Atom at = a.L.atom[b0 + i];
-    Atom f = at;
-    f.x = at.x - cB.x;
-    f.y = at.y - cB.y;
-    f.z = at.z - cB.z;
-    sBF[i] = f;
-    sBS[i] = a.L.samp[b0 + i];
-    make_rec(at, cB.x, cB.y, cB.z, sBB[i], aBB[i]);
-    make_rec(at, cA.x, cA.y, cA.z, sBA[i], aBA[i]);
-  }
-  __syncthreads();
-  build_guide(sBS, nb, guide, lane, kWave);
-  __syncthreads();
-  const double Za = a.Q.Z[0];
-  const uint32_t idb = a.L.id[m];
-  const double Zb = a.L.Z[m];
-  const int rs = a.round_side;
-  const int per_lane = rs / kWave;
-  // Running sums over both sides, identical in every lane: per round each
-  // lane's FP32 partials are summed across the wave (DPP) and added in FP64.
-  // S[0..2] = sum f1, sum f1^2, sum f2 on side A; S[3..5] the same on side B.
-  double S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  int64_t n_side = 0;
-  const int64_t first_check = a.n_start ? (int64_t)a.n_start[p] : 0;
+  if (a.mode != SHAPE_SCREEN_ADAPTIVE) return n_side >= a.n_fixed;
+  if (2 * n_side >= a.cap_pair) return true;
+  if (2 * n_side < first_check) return false;  // below the pair's seeded budget: no test yet
   const double tau2x4 = 4.0 * a.tau * a.tau;
-  // Slot i of a lane in a round holds sample n_side + lane + 64 i (i.i.d.),
-  // or for antithetic sampling member i & 1 of pair n_side/2 + lane +
-  // 64 (i >> 1), i.e. sample n_side + 2 lane + 128 (i >> 1) + (i & 1); the
-  // pair's two members sit in consecutive slots of one lane and enter the
-  // sums as one term, their mean (pend* holds the first member).
-  const bool anti = a.anti != 0;
-  float pa1 = 0.f, pa2 = 0.f, pb1 = 0.f, pb2 = 0.f;
-  for (;;) {
-    float fa[3] = {0.f, 0.f, 0.f};
-    float fb[3] = {0.f, 0.f, 0.f};
-    // side A: query samples from the cache (query frame), partner = library
-    for (int t = 0; t < per_lane; t += kSA) {
-      float rx[kSA], ry[kSA], rz[kSA], r2[kSA], w[kSA], f2[kSA], q[kSA], valid[kSA];
-#pragma unroll
-      for (int s = 0; s < kSA; ++s) {
-        const bool ok = (t + s) < per_lane;
-        const int i = ok ? t + s : t;
-        const int k = anti ? (int)n_side + 2 * lane + 2 * kWave * (i >> 1) + (i & 1)
-                           : (int)n_side + lane + kWave * i;
-        const float4 c = a.qs[k];
-        rx[s] = c.x; ry[s] = c.y; rz[s] = c.z; w[s] = c.w;
-        r2[s] = norm2(c.x, c.y, c.z);
-        f2[s] = a.qf2[k];
-        q[s] = 1.0f;
-        valid[s] = ok ? 1.0f : 0.0f;
-      }
-      eval_union_x<kSA>(sBA, aBA, nb, rx, ry, rz, r2, q);
-#pragma unroll
-      for (int s = 0; s < kSA; ++s) {
-        const float f1 = w[s] * (1.0f - q[s]) * valid[s];
-        if (!anti) {
-          fa[0] += f1; fa[1] = fmaf(f1, f1, fa[1]);
-          fa[2] = fmaf(f2[s], valid[s], fa[2]);
-        } else if (((t + s) & 1) == 0) {
-          pa1 = f1;
-          pa2 = f2[s] * valid[s];
-        } else {
-          const float g1 = 0.5f * (pa1 + f1), g2 = 0.5f * (pa2 + f2[s] * valid[s]);
-          fa[0] += g1; fa[1] = fmaf(g1, g1, fa[1]);
-          fa[2] += g2;
-        }
-      }
-    }
-    // side B: library samples drawn here (library frame), partner = query
-    for (int t = 0; t < per_lane; t += kSB) {
-      float rx[kSB], ry[kSB], rz[kSB], r2[kSB], mb[kSB], qb[kSB], qa[kSB], valid[kSB];
-#pragma unroll
-      for (int s = 0; s < kSB; ++s) {
-        const bool ok = (t + s) < per_lane;
-        const int i = ok ? t + s : t;
-        if (!anti) {
-          const int64_t k = n_side + (int64_t)lane + (int64_t)kWave * i;
-          sample_point(sBF, sBS, nb, idb, (uint64_t)k, a.key, rx[s], ry[s], rz[s], guide);
-        } else if (kSB % 2 == 0) {
-          // both members of the pair from one Philox block (t and s even)
-          if ((s & 1) == 0) {
-            const int64_t pr = n_side / 2 + (int64_t)lane + (int64_t)kWave * (i >> 1);
-            sample_pair(sBF, sBS, nb, idb, (uint64_t)pr, a.key, rx[s], ry[s], rz[s],
-                        rx[s + 1 < kSB ? s + 1 : s], ry[s + 1 < kSB ? s + 1 : s],
-                        rz[s + 1 < kSB ? s + 1 : s], guide);
-          }
-        } else {
-          const int64_t k = n_side + 2 * (int64_t)lane + 2 * (int64_t)kWave * (i >> 1) + (i & 1);
-          sample_point_anti(sBF, sBS, nb, idb, (uint64_t)k, a.key, rx[s], ry[s], rz[s], guide);
-        }
-        valid[s] = ok ? 1.0f : 0.0f;
-      }
-#pragma unroll
-      for (int s = 0; s < kSB; ++s) {
-        r2[s] = norm2(rx[s], ry[s], rz[s]);
-        mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
-      }
-      eval_density_x<kSB>(sBB, aBB, nb, rx, ry, rz, r2, mb, qb);
-      eval_union_x<kSB>(sAB, aAB, nq, rx, ry, rz, r2, qa);
-#pragma unroll
-      for (int s = 0; s < kSB; ++s) {
-        const float ub = 1.0f - qb[s];
-        const float w = bounded_weight(ub, mb[s]) * valid[s];
-        const float f1 = w * (1.0f - qa[s]);
-        if (!anti) {
-          fb[0] += f1; fb[1] = fmaf(f1, f1, fb[1]);
-          fb[2] = fmaf(w, ub, fb[2]);
-        } else if (((t + s) & 1) == 0) {
-          pb1 = f1;
-          pb2 = w * ub;
-        } else {
-          const float g1 = 0.5f * (pb1 + f1), g2 = 0.5f * (pb2 + w * ub);
-          fb[0] += g1; fb[1] = fmaf(g1, g1, fb[1]);
-          fb[2] += g2;
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      S[j] += (double)wave_sum_dpp(fa[j]);
-      S[3 + j] += (double)wave_sum_dpp(fb[j]);
-    }
-    n_side += rs;
-    int stop;
-    if (a.mode == SHAPE_SCREEN_ADAPTIVE) {
-      if (2 * n_side >= a.cap_pair) {
-        stop = 1;
-      } else if (2 * n_side < first_check) {
-        stop = 0;  // below the pair's seeded budget: no test yet
-      } else {
-        // SE(T) <= tau without divisions or roots: with n samples per side,
-        // S' = Za a2 + Zb b2, D' = S' - (Za a1 + Zb b1)/2 and
-        // V = n a11 - a1^2 (clamped at 0), the delta-method SE satisfies
-        //   SE(T)^2 = S'^2 (Za^2 Va + Zb^2 Vb) / (4 (n-1) D'^4),
-        // so the test is S'^2 (Za^2 Va + Zb^2 Vb) <= 4 tau^2 (n-1) D'^4 with
-        // D' != 0 (NaN sums never stop).
-        const double n = (double)(anti ? n_side / 2 : n_side);  // independent terms
-        const double Sp = Za * S[2] + Zb * S[5];
-        const double Dp = Sp - 0.5 * (Za * S[0] + Zb * S[3]);
-        const double Va = fmax(n * S[1] - S[0] * S[0], 0.0);
-        const double Vb = fmax(n * S[4] - S[3] * S[3], 0.0);
-        const double lhs = Sp * Sp * (Za * Za * Va + Zb * Zb * Vb);
-        const double D2 = Dp * Dp;
-        stop = (Dp != 0.0 && lhs <= tau2x4 * (n - 1.0) * D2 * D2) ? 1 : 0;
-      }
-    } else {
-      stop = n_side >= a.n_fixed ? 1 : 0;
-    }
-    if (__builtin_amdgcn_readfirstlane(stop)) break;
-  }
-  if (lane == 0) {
-    double T, O_ab, O_aa, O_bb;
-    const double se = se_tanimoto((double)(anti ? n_side / 2 : n_side), Za, Zb, S[0], S[1],
-                                  S[2], S[3], S[4], S[5], &T, &O_ab, &O_aa, &O_bb);
+  const double n = (double)(anti ? n_side / 2 : n_side);  // independent terms
+  const double a1 = S.get(0), a11 = S.get(1), b1 = S.get(3), b11 = S.get(4);
+  const double Sp = Za * S.get(2) + Zb * S.get(5);
+  const double Dp = Sp - 0.5 * (Za * a1 + Zb * b1);
+  const double Va = fmax(n * a11 - a1 * a1, 0.0);
+  const double Vb = fmax(n * b11 - b1 * b1, 0.0);
+  const double lhs = Sp * Sp * (Za * Za * Va + Zb * Zb * Vb);
+  const double D2 = Dp * Dp;
+  return Dp != 0.0 && lhs <= tau2x4 * (n - 1.0) * D2 * D2;
+}
+
+// A pair's outputs from its sums (one lane).
+__device__ __forceinline__ void screen_write(const ScreenArgs& a, int p, const RoundSums& S,
+                                             int64_t n_side, bool anti, double Za, double Zb) {
+  double T, O_ab, O_aa, O_bb;
+  const double se = se_tanimoto((double)(anti ? n_side / 2 : n_side), Za, Zb, S.get(0), S.get(1),
+                                S.get(2), S.get(3), S.get(4), S.get(5), &T, &O_ab, &O_aa, &O_bb);
+  if (threadIdx.x == 0) {
     a.T[p] = (float)T;
     a.se_T[p] = (float)se;
     if (a.O_ab) a.O_ab[p] = (float)O_ab;
@@ -615,6 +465,243 @@ __global__ __launch_bounds__(64) void k_screen(ScreenArgs a) {
     if (a.O_bb) a.O_bb[p] = (float)O_bb;
     if (a.n_used) a.n_used[p] = (int)(2 * n_side);
   }
+}
+
+__device__ __forceinline__ void screen_write_nan(const ScreenArgs& a, int p) {
+  if (threadIdx.x == 0) {
+    const float nanv = __builtin_nanf("");
+    a.T[p] = nanv;
+    a.se_T[p] = nanv;
+    if (a.O_ab) a.O_ab[p] = nanv;
+    if (a.O_aa) a.O_aa[p] = nanv;
+    if (a.O_bb) a.O_bb[p] = nanv;
+    if (a.n_used) a.n_used[p] = 0;
+  }
+}
+
+// The kernel's arguments, read again from the kernel-argument segment: what
+// only the end of a pair needs then takes no scalar registers during its
+// rounds (they would be spilled into lanes of vector registers, which the
+// kernel has none to spare of).
+__device__ __forceinline__ const ScreenArgs& screen_args_again() {
+  auto k = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(k));
+  return *(const ScreenArgs*)k;
+}
+
+// LDS of one pair (n = atoms):
+//   sBF   [max_b] Atom          library atoms in the library frame (sampling)
+//   sBB   [max_b] AtomRec + a2  library atoms, library frame (own density)
+//   sBA   [max_b] AtomRec + a2  library atoms, query frame (side A partner)
+//   sAB   [max_q] AtomRec + a2  query atoms, library frame (side B partner)
+//   sBS   [max_b] AtomSampling  the library atoms' sampling records
+//   guide [kGuideSize] uint8_t  the library molecule's component guide
+// 16-byte records first, then the 8-byte, the 4-byte and the 1-byte arrays,
+// so every array is aligned to its element size whatever the atom counts.
+struct ScreenLds {
+  Atom* BF;
+  AtomRec *BB, *BA, *AB;
+  AtomSampling* BS;
+  float *aBB, *aBA, *aAB;
+  uint8_t* guide;
+  __device__ ScreenLds(unsigned char* smem, int max_q, int max_b) {
+    BF = reinterpret_cast<Atom*>(smem);
+    BB = reinterpret_cast<AtomRec*>(BF + max_b);
+    BA = BB + max_b;
+    AB = BA + max_b;
+    BS = reinterpret_cast<AtomSampling*>(AB + max_q);
+    aBB = reinterpret_cast<float*>(BS + max_b);
+    aBA = aBB + max_b;
+    aAB = aBA + max_b;
+    guide = reinterpret_cast<uint8_t*>(aAB + max_q);
+  }
+  // the records of a pair, staged by the whole workgroup
+  __device__ __forceinline__ void stage(const ScreenArgs& a, int m, int q0, int nq, int b0,
+                                        int nb) const {
+    const float4 cA = a.Q.centre[0];
+    const float4 cB = a.L.centre[m];
+    for (int i = threadIdx.x; i < nq; i += blockDim.x)
+      make_rec(a.Q.atom[q0 + i], cB.x, cB.y, cB.z, AB[i], aAB[i]);
+    for (int i = threadIdx.x; i < nb; i += blockDim.x) {
+      const Atom at = a.L.atom[b0 + i];
+      Atom f = at;
+      f.x = at.x - cB.x;
+      f.y = at.y - cB.y;
+      f.z = at.z - cB.z;
+      BF[i] = f;
+      BS[i] = a.L.samp[b0 + i];
+      make_rec(at, cB.x, cB.y, cB.z, BB[i], aBB[i]);
+      make_rec(at, cA.x, cA.y, cA.z, BA[i], aBA[i]);
+    }
+    __syncthreads();
+    build_guide(BS, nb, guide, threadIdx.x, blockDim.x);
+    __syncthreads();
+  }
+};
+
+// Slot i of a lane in a round holds sample n_side + lane + 64 i (i.i.d.), or
+// for antithetic sampling member i & 1 of pair n_side/2 + lane + 64 (i >> 1),
+// i.e. sample n_side + 2 lane + 128 (i >> 1) + (i & 1); the pair's two
+// members sit in consecutive slots of one lane and enter the sums as one
+// term, their mean (held in pend1, pend2 from the first member on).
+template <bool kAnti>
+struct SideSums {
+  float f[3] = {0.f, 0.f, 0.f};
+  float pend1 = 0.f, pend2 = 0.f;
+  // slot i's term: f1, and f2 = f2a f2b (a product, fused into the sum)
+  __device__ __forceinline__ void term(int i, float f1, float f2a, float f2b) {
+#pragma clang fp contract(off)
+    if constexpr (!kAnti) {
+      f[0] += f1;
+      f[1] = fmaf(f1, f1, f[1]);
+      f[2] = fmaf(f2a, f2b, f[2]);
+    } else if ((i & 1) == 0) {
+      pend1 = f1;
+      pend2 = f2a * f2b;
+    } else {
+      const float g1 = 0.5f * (pend1 + f1), g2 = 0.5f * (pend2 + f2a * f2b);
+      f[0] += g1;
+      f[1] = fmaf(g1, g1, f[1]);
+      f[2] += g2;
+    }
+  }
+};
+
+// A lane's points for slots t .. t + S - 1 of a round that starts at sample
+// n_side of the library molecule (a slot past the round's last repeats slot
+// t): the points sample_point, or sample_point_anti, draws.  All steps of the
+// S points go together; sample numbers stay below 2^32 (at most 2^20 per
+// side), so the Philox counter's second word is zero.  Antithetic pairs sit
+// in consecutive slots and share one block where S is even.
+template <int S, bool kAnti>
+__device__ __forceinline__ void screen_draw(const ScreenLds& lds, int nb, uint32_t id,
+                                            uint32_t n_side, int t, int per_lane, uint2 key,
+                                            float (&rx)[S], float (&ry)[S], float (&rz)[S]) {
+  constexpr bool kPairs = kAnti && S % 2 == 0;
+  constexpr int D = kPairs ? S / 2 : S;
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  uint32_t w0[D], wz[3 * D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const int s = kPairs ? 2 * d : d;
+    const uint32_t i = (t + s) < per_lane ? t + s : t;
+    const uint32_t blk = kAnti ? n_side / 2 + lane + kWave * (i >> 1) : n_side + lane + kWave * i;
+    const uint4 x = philox4x32_10(make_uint4(blk, 0u, id, 0u), key);
+    w0[d] = x.x;
+    wz[3 * d] = x.y; wz[3 * d + 1] = x.z; wz[3 * d + 2] = x.w;
+  }
+  int j[D];
+  select_components_guided<D>(lds.BS, lds.guide, nb, w0, j);
+  float z[3 * D];
+  normals_from_bits<3 * D>(wz, z);
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const Atom c = lds.BF[j[d]];
+    const float sd = lds.BS[j[d]].sd;
+    if constexpr (kPairs) {
+      rx[2 * d] = fmaf(z[3 * d], sd, c.x);
+      ry[2 * d] = fmaf(z[3 * d + 1], sd, c.y);
+      rz[2 * d] = fmaf(z[3 * d + 2], sd, c.z);
+      rx[2 * d + 1] = fmaf(-z[3 * d], sd, c.x);
+      ry[2 * d + 1] = fmaf(-z[3 * d + 1], sd, c.y);
+      rz[2 * d + 1] = fmaf(-z[3 * d + 2], sd, c.z);
+    } else {
+      // the odd member of an antithetic pair (a slot's parity is its sample's)
+      const int i = (t + d) < per_lane ? t + d : t;
+      const float sg = kAnti && (i & 1) ? -1.0f : 1.0f;
+      rx[d] = fmaf(sg * z[3 * d], sd, c.x);
+      ry[d] = fmaf(sg * z[3 * d + 1], sd, c.y);
+      rz[d] = fmaf(sg * z[3 * d + 2], sd, c.z);
+    }
+  }
+}
+
+// VALU issue bounds this kernel (per evaluation 5 or 6 FP32 instructions and
+// one exponential, about a sixth more for drawing the library's points).  Its
+// registers are held to 64, for eight waves per SIMD: the more waves, the
+// more often two of them stand at FP32 instructions that can be issued
+// together (trans_group); a density loop alone measured 21.6, 24.3 and 28.2
+// cycles per evaluation with eight, six and four waves.  100,000 molecules of
+// 10-50 atoms, 30-atom query, SE(T) <= 0.005: 8.07 ms with the exponentials
+// among the other instructions (76 registers), 7.15 ms with them grouped, 7.01
+// ms with the drawing steps of a lane's points grouped too; fixed 4,096 per
+// side, 7,003 molecules: 0.60 -> 0.53 ms.
+template <int kSA, int kSB, bool kAnti>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSA >= 8 ? 4 : 8)))
+void k_screen(ScreenArgs a) {
+  // No implicit multiply-add contraction: the fused operations are written
+  // out, so every tile variant rounds identically.
+#pragma clang fp contract(off)
+  extern __shared__ __align__(16) unsigned char smem[];
+  const ScreenLds lds(smem, a.max_q, a.max_b);
+  const int lane = threadIdx.x;
+  // grid = n_pairs; a launch order, when given, is a permutation of the pairs
+  const int p = a.order ? a.order[blockIdx.x] : xcd_chunk(blockIdx.x, gridDim.x);
+  if (p < 0 || p >= a.n_pairs) return;
+  const int m = a.pairs ? a.pairs[p] : p;
+  if (a.Q.bad[0] != 0 || m < 0 || m >= a.n_lib || a.L.bad[m] != 0) {
+    screen_write_nan(a, p);
+    return;
+  }
+  const int q0 = a.offQ[0], nq = a.offQ[1] - q0;
+  const int b0 = a.offL[m], nb = a.offL[m + 1] - b0;
+  lds.stage(a, m, q0, nq, b0, nb);
+  const uint32_t idb = a.L.id[m];
+  const int rs = a.round_side;
+  const int per_lane = rs / kWave;
+  RoundSums S;
+  int64_t n_side = 0;
+  for (;;) {
+    SideSums<kAnti> A, B;
+    // side A: query samples from the cache (query frame), partner = library
+    for (int t = 0; t < per_lane; t += kSA) {
+      float rx[kSA], ry[kSA], rz[kSA], r2[kSA], w[kSA], f2[kSA], q[kSA];
+#pragma unroll
+      for (int s = 0; s < kSA; ++s) {
+        const int i = (t + s) < per_lane ? t + s : t;
+        const int k = kAnti ? (int)n_side + 2 * lane + 2 * kWave * (i >> 1) + (i & 1)
+                            : (int)n_side + lane + kWave * i;
+        const float4 c = a.qs[k];
+        rx[s] = c.x; ry[s] = c.y; rz[s] = c.z; w[s] = c.w;
+        r2[s] = norm2(c.x, c.y, c.z);
+        f2[s] = a.qf2[k];
+        q[s] = 1.0f;
+      }
+      eval_union_x<kSA>(lds.BA, lds.aBA, nb, rx, ry, rz, r2, q);
+#pragma unroll
+      for (int s = 0; s < kSA; ++s) {
+        const float valid = (t + s) < per_lane ? 1.0f : 0.0f;
+        A.term(t + s, w[s] * (1.0f - q[s]) * valid, f2[s], valid);
+      }
+    }
+    // side B: library samples drawn here (library frame), partner = query
+    for (int t = 0; t < per_lane; t += kSB) {
+      float rx[kSB], ry[kSB], rz[kSB], r2[kSB], mb[kSB], qb[kSB], qa[kSB];
+      screen_draw<kSB, kAnti>(lds, nb, idb, (uint32_t)n_side, t, per_lane, a.key, rx, ry, rz);
+#pragma unroll
+      for (int s = 0; s < kSB; ++s) {
+        r2[s] = norm2(rx[s], ry[s], rz[s]);
+        mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
+      }
+      eval_density_x<kSB>(lds.BB, lds.aBB, nb, rx, ry, rz, r2, mb, qb);
+      eval_union_x<kSB>(lds.AB, lds.aAB, nq, rx, ry, rz, r2, qa);
+#pragma unroll
+      for (int s = 0; s < kSB; ++s) {
+        const float valid = (t + s) < per_lane ? 1.0f : 0.0f;
+        const float ub = 1.0f - qb[s];
+        const float w = bounded_weight(ub, mb[s]) * valid;
+        B.term(t + s, w * (1.0f - qa[s]), w, ub);
+      }
+    }
+    S.add(A.f, B.f);
+    n_side += rs;
+    const ScreenArgs& r = screen_args_again();
+    const bool stop = screen_stops(r, S, n_side, r.n_start ? (int64_t)r.n_start[p] : 0, kAnti,
+                                   r.Q.Z[0], r.L.Z[m]);
+    if (__builtin_amdgcn_readfirstlane(stop)) break;
+  }
+  const ScreenArgs& r = screen_args_again();
+  screen_write(r, p, S, n_side, kAnti, r.Q.Z[0], r.L.Z[m]);
 }
 
 // ---------------------------------------------------------------------------
@@ -633,7 +720,7 @@ __global__ __launch_bounds__(256) void k_sample_points(Prepared P, const int* __
                                                        uint32_t* __restrict__ words,
                                                        int* __restrict__ comp,
                                                        float* __restrict__ r) {
-  __shared__ int guide[kGuideSize];  // the screening kernel's table, one entry per thread
+  __shared__ uint8_t guide[kGuideSize];  // the screening kernel's table, one entry per thread
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int a0 = off[mol], na = off[mol + 1] - a0;
   const Atom* atoms = P.atom + a0;
@@ -896,13 +983,17 @@ hipError_t launch_work_order(const OrderArgs& o, int* order, int* work, hipStrea
 size_t screen_lds_bytes(int max_q, int max_b) {
   return (size_t)max_b * (sizeof(Atom) + 2 * (sizeof(AtomRec) + sizeof(float)) +
                           sizeof(AtomSampling)) +
-         (size_t)max_q * (sizeof(AtomRec) + sizeof(float)) + kGuideSize * sizeof(int);
+         (size_t)max_q * (sizeof(AtomRec) + sizeof(float)) + kGuideSize * sizeof(uint8_t);
 }
 
 template <int A, int B>
 static void launch_screen_t(const ScreenArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((k_screen<A, B>), dim3((unsigned)a.n_pairs), dim3(kWave),
-                     screen_lds_bytes(a.max_q, a.max_b), st, a);
+  const dim3 grid((unsigned)a.n_pairs), block(kWave);
+  const size_t lds = screen_lds_bytes(a.max_q, a.max_b);
+  if (a.anti)
+    hipLaunchKernelGGL((k_screen<A, B, true>), grid, block, lds, st, a);
+  else
+    hipLaunchKernelGGL((k_screen<A, B, false>), grid, block, lds, st, a);
 }
 
 hipError_t launch_screen(const ScreenArgs& a, int variant, hipStream_t st) {

@@ -68,6 +68,33 @@ def test_all_variants_bit_identical(eng, data, kw):
     assert np.all(np.isfinite(ref["T"]))
 
 
+@pytest.mark.parametrize("round_per_pair, anti", [(128, False), (256, False), (384, False),
+                                                  (640, False), (1280, False), (256, True),
+                                                  (1280, True)])
+def test_round_sizes_every_variant(eng, data, round_per_pair, anti):
+    """Rounds of 1, 2, 3, 5 and 10 points per lane: whole, partial and
+    single-point tiles of every variant give the bits of the smallest tile,
+    with a fixed number of rounds and adaptively."""
+    Q, lib = data
+    print(f"case: rounds of {round_per_pair}, anti {anti}", flush=True)
+    eng.sampling(anti)
+    try:
+        for tau in (1e-9, 0.02):
+            kw = dict(mode=SHAPE_SCREEN_ADAPTIVE, round_per_pair=round_per_pair,
+                      cap_per_pair=4 * round_per_pair, tau=tau, seed=5)
+            ref = None
+            for v in (5, 0, 1, 2, 3, 4, 6, 7, -1):
+                eng.screen_variant(v)
+                got = _np(eng.shape_screen(Q, lib, **kw))
+                assert np.all(np.isfinite(got["T"]))
+                if ref is None:
+                    ref = got
+                _same(got, ref)
+    finally:
+        eng.screen_variant(-1)
+        eng.sampling(False)
+
+
 def test_tuner_picks_a_variant(eng, data):
     Q, lib = data
     tune_cache_clear()
