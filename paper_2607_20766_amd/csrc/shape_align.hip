@@ -15,13 +15,12 @@
 // and dT/dq follows from dtheta = 2 (w dv - dw v + v x dv) for q = (w, v).
 #include "shape_kernels.hpp"
 
+#include <algorithm>
+#include <type_traits>
+
 #include <math.h>
 
 namespace shape {
-
-constexpr int kAlignThreads = 256;
-constexpr int kAlignWaves = kAlignThreads / kWave;
-constexpr int kAS = 4;  // points per lane evaluated together
 
 __device__ __forceinline__ void quat_rotation(float qw, float qx, float qy, float qz,
                                               float (&R)[9], float& inv_norm) {
@@ -31,6 +30,34 @@ __device__ __forceinline__ void quat_rotation(float qw, float qx, float qy, floa
   R[0] = 1.f - 2.f * (y * y + z * z); R[1] = 2.f * (x * y - w * z); R[2] = 2.f * (x * z + w * y);
   R[3] = 2.f * (x * y + w * z); R[4] = 1.f - 2.f * (x * x + z * z); R[5] = 2.f * (y * z - w * x);
   R[6] = 2.f * (x * z - w * y); R[7] = 2.f * (y * z + w * x); R[8] = 1.f - 2.f * (x * x + y * y);
+}
+
+// A molecule's samples k0 .. k1 - 1 and their weights, drawn by the whole
+// workgroup two per thread at a time: put(k, x, y, z, w, u) for each of them.
+// The molecule's records are in its own frame.
+template <class Put>
+__device__ __forceinline__ void weigh_samples(const Atom* AF, const AtomSampling* AS,
+                                              const AtomRec* AR, const float* Aa, int na,
+                                              uint32_t id, int k0, int k1, uint2 key, Put put) {
+  constexpr int D = 2;
+  for (int i = k0 + threadIdx.x; i < k1; i += D * blockDim.x) {
+    uint32_t k[D];
+    float rx[D], ry[D], rz[D], r2[D], m[D], u[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      k[d] = min(i + d * (int)blockDim.x, k1 - 1);  // past the end: the last sample again
+      m[d] = 0.f;
+      u[d] = 0.f;
+    }
+    sample_points<D>(AF, AS, na, id, k, key, rx, ry, rz);
+#pragma unroll
+    for (int d = 0; d < D; ++d) r2[d] = norm2(rx[d], ry[d], rz[d]);
+    eval_density_u_x<D>(AR, Aa, na, rx, ry, rz, r2, m, u);
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (i + d * (int)blockDim.x < k1)
+        put((int)k[d], rx[d], ry[d], rz[d], bounded_weight(u[d], m[d]), u[d]);
+  }
 }
 
 // Phase 1 (whole workgroup): A's samples in A's frame and their weights.
@@ -49,214 +76,425 @@ __device__ void align_samples(const AlignArgs& a, int pair, float4* sSamp, Atom*
     make_rec(at, cA.x, cA.y, cA.z, sAR[i], sAa[i]);
   }
   __syncthreads();
-  const uint32_t ida = a.A.id[pair];
-  for (int k = threadIdx.x; k < a.n_samples; k += blockDim.x) {
-    float rx[1], ry[1], rz[1], r2[1], m[1] = {0.f}, u[1] = {0.f};
-    sample_point(sAF, sAS, na, ida, (uint64_t)k, a.key, rx[0], ry[0], rz[0]);
-    r2[0] = norm2(rx[0], ry[0], rz[0]);
-    eval_density_u_x<1>(sAR, sAa, na, rx, ry, rz, r2, m, u);
-    sSamp[k] = make_float4(rx[0], ry[0], rz[0], bounded_weight(u[0], m[0]));
-  }
+  weigh_samples(sAF, sAS, sAR, sAa, na, a.A.id[pair], 0, a.n_samples, a.key,
+                [&](int k, float x, float y, float z, float w, float) {
+                  sSamp[k] = make_float4(x, y, z, w);
+                });
   __syncthreads();
 }
 
-// One Adam (Kingma and Ba) ascent step on T for a pose x[7] with moments
-// m, v: step number t (from 1), gradient dT; the quaternion is renormalised.
-// Shared by the fused optimisation in k_align and by k_adam_pose, so both
-// take the same roundings.
-__device__ __forceinline__ void adam_pose_step(float (&x)[7], float (&m)[7], float (&v)[7],
-                                               const float (&dT)[7], int t, float lr, float b1,
-                                               float b2, float eps) {
+// One Adam (Kingma and Ba) ascent step on T for component c of a pose, with
+// moments m, v: bias corrections c1, c2, gradient dT; the caller renormalises
+// the quaternion.  Shared by the fused optimisation in the alignment kernels
+// and by k_adam_pose, so both take the same roundings.
+__device__ __forceinline__ float adam_component(float x, float& m, float& v, float dT, float c1,
+                                                float c2, float lr, float b1, float b2,
+                                                float eps) {
 #pragma clang fp contract(off)
-  const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
-  float xn[7];
-#pragma unroll
-  for (int c = 0; c < 7; ++c) {
-    const float g = -dT[c];  // minimise -T
-    m[c] = fmaf(b1, m[c], (1.f - b1) * g);
-    v[c] = fmaf(b2, v[c], (1.f - b2) * g * g);
-    xn[c] = x[c] - lr * (m[c] / c1) / (sqrtf(v[c] / c2) + eps);
-  }
-  const float inv = rsqrtf(xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3]);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) x[c] = xn[c] * inv;
-#pragma unroll
-  for (int c = 4; c < 7; ++c) x[c] = xn[c];
+  const float g = -dT;  // minimise -T
+  m = fmaf(b1, m, (1.f - b1) * g);
+  v = fmaf(b2, v, (1.f - b2) * g * g);
+  return x - lr * (m / c1) / (sqrtf(v / c2) + eps);
+}
+__device__ __forceinline__ float quat_inv_norm(float a, float b, float c, float d) {
+#pragma clang fp contract(off)
+  return rsqrtf(a * a + b * b + c * c + d * d);
 }
 
-__global__ __launch_bounds__(kAlignThreads) void k_align(AlignArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  // 16-byte arrays first, then 8-byte, then 4-byte: each stays aligned.
-  float4* sSamp = reinterpret_cast<float4*>(smem);                    // [n_samples]
-  AtomRec* sAR = reinterpret_cast<AtomRec*>(sSamp + a.n_samples);     // [max_a]
-  Atom* sAF = reinterpret_cast<Atom*>(sAR + a.max_a);                 // [max_a]
-  float4* sBC = reinterpret_cast<float4*>(sAF + a.max_a);             // [waves][max_b]
-  AtomRec* sBR = reinterpret_cast<AtomRec*>(sBC + kAlignWaves * a.max_b);  // [waves][max_b]
-  AtomSampling* sAS = reinterpret_cast<AtomSampling*>(sBR + kAlignWaves * a.max_b);  // [max_a]
-  float* sAa = reinterpret_cast<float*>(sAS + a.max_a);                    // [max_a]
-  float* sBa = sAa + a.max_a;                                              // [waves][max_b]
-
-  const int pair = a.order ? a.order[blockIdx.x] : blockIdx.x;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const bool bad = a.A.bad[pair] != 0 || a.B.bad[pair] != 0;
-  if (bad) {
-    for (int i = threadIdx.x; i < a.n_starts; i += blockDim.x) {
-      const size_t o = (size_t)pair * a.n_starts + i;
-      a.T[o] = __builtin_nanf("");
-      if (a.grad)
-        for (int c = 0; c < 7; ++c) a.grad[o * 7 + c] = __builtin_nanf("");
-    }
-    return;
+// A start's optimisation state, one pose component per lane (lanes past 6
+// repeat component 6): the pose is read across lanes where it is needed.
+struct LanePose {
+  float x, m = 0.f, v = 0.f;
+  float c1, c2;  // bias corrections of steps 64 k + 1 + lane, refilled every 64 steps
+  static __device__ __forceinline__ float lane_of(float f, int l) {
+    return __builtin_bit_cast(float,
+                              __builtin_amdgcn_readlane(__builtin_bit_cast(int, f), l));
   }
-  align_samples(a, pair, sSamp, sAF, sAS, sAR, sAa);
+  __device__ __forceinline__ float get(int c) const { return lane_of(x, c); }
+  // ascent step t (from 1) along the gradient g[7]
+  __device__ __forceinline__ void step(const float (&g)[7], int t, float lr, float b1, float b2,
+                                       float eps) {
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x & (kWave - 1);
+    float gl = g[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) gl = lane == c ? g[c] : gl;
+    const int i = (t - 1) % kWave;
+    if (i == 0) {
+      c1 = 1.f - powf(b1, (float)(t + lane));
+      c2 = 1.f - powf(b2, (float)(t + lane));
+    }
+    x = adam_component(x, m, v, gl, lane_of(c1, i), lane_of(c2, i), lr, b1, b2, eps);
+    const float inv = quat_inv_norm(get(0), get(1), get(2), get(3));
+    if (lane < 4) x *= inv;
+  }
+};
 
+// B's atoms moved by a pose, as the records the evaluation reads:
+// expanded-form records in A's frame, and 2 alpha_j (c''_j, 1).
+struct MovedAtoms {
+  AtomRec* rec;
+  float4* c;
+  float* a2;
+  // atoms lane, lane + 64, ... by the pose P; tx, ty, tz: B's origin (the
+  // rotation centre) in A's frame
+  __device__ __forceinline__ void move(const Atom* B, int nb, const float (&R)[9], float tx,
+                                       float ty, float tz) const {
+    for (int i = threadIdx.x & (kWave - 1); i < nb; i += kWave) {
+      const Atom at = B[i];
+      Atom moved = at;
+      moved.x = fmaf(R[0], at.x, fmaf(R[1], at.y, fmaf(R[2], at.z, tx)));
+      moved.y = fmaf(R[3], at.x, fmaf(R[4], at.y, fmaf(R[5], at.z, ty)));
+      moved.z = fmaf(R[6], at.x, fmaf(R[7], at.y, fmaf(R[8], at.z, tz)));
+      make_rec(moved, 0.f, 0.f, 0.f, rec[i], a2[i]);
+      // 2 alpha = 2 a2 ln 2
+      const float two_al = 2.0f * 0.693147180559945309f * at.a2;
+      c[i] = make_float4(two_al * moved.x, two_al * moved.y, two_al * moved.z, two_al);
+    }
+  }
+};
+
+// A lane's samples of slots t .. t + S - 1 (slot i holds sample lane + 64 i;
+// past the last sample: sample 0 with weight 0) against B's moved atoms.
+// term(s, w, f): the sample's weight and its seven integrands f = u, du/dt
+// (3), torque about B's origin (3).
+//
+// VALU issue bounds this loop: 13 FP32 instructions and one exponential per
+// atom and sample, the exponentials of U atoms grouped (trans_group).
+template <int S, int U, class Term>
+__device__ __forceinline__ void align_eval(const float4* sSamp, int n_samples, int t,
+                                           const MovedAtoms& B, int nb, float tx, float ty,
+                                           float tz, Term term) {
+  const int lane = threadIdx.x & (kWave - 1);
+  float rx[S], ry[S], rz[S], r2[S];
+  float P[S], S0[S], Sx[S], Sy[S], Sz[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const int k = lane + kWave * (t + s);
+    const float4 c = sSamp[k < n_samples ? k : 0];
+    rx[s] = c.x; ry[s] = c.y; rz[s] = c.z;
+    r2[s] = norm2(c.x, c.y, c.z);
+    P[s] = 1.f; S0[s] = 0.f; Sx[s] = 0.f; Sy[s] = 0.f; Sz[s] = 0.f;
+  }
+  const auto atoms = [&](int j, auto count) {
+    constexpr int V = decltype(count)::value;
+    float o[V * S];
+    float4 cj[V];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const AtomRec b = B.rec[j + u];
+      const float aj = B.a2[j + u];
+      cj[u] = B.c[j + u];
+#pragma unroll
+      for (int s = 0; s < S; ++s) o[u * S + s] = exponent_x(b, aj, rx[s], ry[s], rz[s], r2[s]);
+    }
+    exp2_group(o);
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        // S <- S (1 - o) + o P c  written as  S + o (c P - S): two fused
+        // operations per component, and P <- P - o P
+        const float oj = o[u * S + s];
+        S0[s] = fmaf(oj, fmaf(cj[u].w, P[s], -S0[s]), S0[s]);
+        Sx[s] = fmaf(oj, fmaf(cj[u].x, P[s], -Sx[s]), Sx[s]);
+        Sy[s] = fmaf(oj, fmaf(cj[u].y, P[s], -Sy[s]), Sy[s]);
+        Sz[s] = fmaf(oj, fmaf(cj[u].z, P[s], -Sz[s]), Sz[s]);
+        P[s] = fmaf(-oj, P[s], P[s]);
+      }
+  };
+  int j = 0;
+  for (; j + U <= nb; j += U) atoms(j, std::integral_constant<int, U>{});
+  if constexpr (U > 1)
+    for (; j < nb; ++j) atoms(j, std::integral_constant<int, 1>{});
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    // translation gradient of u at this point and the torque about B's origin
+    const float gx = fmaf(S0[s], rx[s], -Sx[s]);
+    const float gy = fmaf(S0[s], ry[s], -Sy[s]);
+    const float gz = fmaf(S0[s], rz[s], -Sz[s]);
+    const float cxr_x = Sy[s] * rz[s] - Sz[s] * ry[s];
+    const float cxr_y = Sz[s] * rx[s] - Sx[s] * rz[s];
+    const float cxr_z = Sx[s] * ry[s] - Sy[s] * rx[s];
+    const float txg_x = ty * gz - tz * gy;
+    const float txg_y = tz * gx - tx * gz;
+    const float txg_z = tx * gy - ty * gx;
+    const int k = lane + kWave * (t + s);
+    const float w = k < n_samples ? sSamp[k].w : 0.f;
+    const float f[7] = {1.f - P[s],      gx, gy, gz, cxr_x - txg_x, cxr_y - txg_y,
+                        cxr_z - txg_z};
+    term(s, w, f);
+  }
+}
+
+// T and its gradient over the pose, where asked for, from the seven weighted
+// sums of the integrands (FP64).
+__device__ __forceinline__ void align_value(const double (&sum)[7], double Za, double S,
+                                            int n_samples, const LanePose& ps, float inv_norm,
+                                            bool need_T, bool need_grad, float& T,
+                                            float (&g)[7]) {
+  const double scale = Za / (double)n_samples;
+  const double O = scale * sum[0];
+  const double D = S - O;
+  if (need_T) T = (float)(O / D);
+  if (!need_grad) return;
+  const double k = scale * S / (D * D);  // dT/dO * Z_A/n
+  const double gth[3] = {k * sum[4], k * sum[5], k * sum[6]};
+  // dT/dq = (2/|q|) [ -v.g ; w g - v x g ] with (w, v) = q/|q|
+  const double in = (double)inv_norm;
+  const double w = ps.get(0) * in, vx = ps.get(1) * in, vy = ps.get(2) * in, vz = ps.get(3) * in;
+  const double vdg = vx * gth[0] + vy * gth[1] + vz * gth[2];
+  const double vxg_x = vy * gth[2] - vz * gth[1];
+  const double vxg_y = vz * gth[0] - vx * gth[2];
+  const double vxg_z = vx * gth[1] - vy * gth[0];
+  g[0] = (float)(2.0 * in * (-vdg));
+  g[1] = (float)(2.0 * in * (w * gth[0] - vxg_x));
+  g[2] = (float)(2.0 * in * (w * gth[1] - vxg_y));
+  g[3] = (float)(2.0 * in * (w * gth[2] - vxg_z));
+  g[4] = (float)(k * sum[1]);
+  g[5] = (float)(k * sum[2]);
+  g[6] = (float)(k * sum[3]);
+}
+
+__device__ __forceinline__ void align_write(const AlignArgs& a, size_t o, const LanePose& ps,
+                                            float T, const float (&g)[7]) {
+  const int lane = threadIdx.x & (kWave - 1);
+  if (lane == 0) {
+    a.T[o] = T;
+    if (a.grad)
+#pragma unroll
+      for (int c = 0; c < 7; ++c) a.grad[o * 7 + c] = g[c];
+  }
+  if (a.n_steps > 0 && lane < 7) a.pose_out[o * 7 + lane] = ps.x;
+}
+
+// Whether the pair has invalid molecules; then starts [s0, s1) get NaN.
+__device__ __forceinline__ bool align_bad(const AlignArgs& a, int pair, int s0, int s1) {
+  if (a.A.bad[pair] == 0 && a.B.bad[pair] == 0) return false;
+  for (int i = s0 + (int)threadIdx.x; i < s1; i += blockDim.x) {
+    const size_t o = (size_t)pair * a.n_starts + i;
+    a.T[o] = __builtin_nanf("");
+    if (a.grad)
+      for (int c = 0; c < 7; ++c) a.grad[o * 7 + c] = __builtin_nanf("");
+  }
+  return true;
+}
+
+// LDS: the samples, then A's records while they are drawn; afterwards the
+// same memory holds B's moved atoms (one set per wave or one for the
+// workgroup) and, in the split kernel, the samples' integrands.  16-byte
+// arrays first, then 8-byte, then 4-byte: each stays aligned.
+__host__ __device__ inline size_t align_a_bytes(int max_a) {
+  return (size_t)max_a * (sizeof(AtomRec) + sizeof(Atom) + sizeof(AtomSampling) + sizeof(float));
+}
+__host__ __device__ inline size_t align_b_bytes(int sets, int max_b) {
+  return (size_t)sets * max_b * (sizeof(AtomRec) + sizeof(float4) + sizeof(float));
+}
+struct AlignStage {
+  Atom* AF;
+  AtomRec* AR;
+  AtomSampling* AS;
+  float* Aa;
+  __device__ AlignStage(void* mem, int max_a) {
+    AR = reinterpret_cast<AtomRec*>(mem);
+    AF = reinterpret_cast<Atom*>(AR + max_a);
+    AS = reinterpret_cast<AtomSampling*>(AF + max_a);
+    Aa = reinterpret_cast<float*>(AS + max_a);
+  }
+};
+__device__ __forceinline__ MovedAtoms moved_atoms(void* mem, int sets, int set, int max_b) {
+  AtomRec* rec = reinterpret_cast<AtomRec*>(mem);
+  float4* c = reinterpret_cast<float4*>(rec + (size_t)sets * max_b);
+  float* a2 = reinterpret_cast<float*>(c + (size_t)sets * max_b);
+  return MovedAtoms{rec + (size_t)set * max_b, c + (size_t)set * max_b,
+                    a2 + (size_t)set * max_b};
+}
+
+constexpr int kAS = 4;               // samples per lane evaluated together
+constexpr int kAlignMinWaves = 4;    // waves (starts in flight) per workgroup
+constexpr int kAlignMaxWaves = 8;
+
+// One workgroup per pair and group of starts_per_block starts; A's samples
+// are drawn once, then each wave optimises its starts in turn.  An evaluation
+// takes a lane's samples in order, so T and the gradient do not depend on how
+// the starts are spread over waves and workgroups.  Four samples per lane and
+// one atom at a time take 111 registers, four waves per SIMD, as many as the
+// samples' LDS allows: 10,000 pairs x 16 starts, 4 steps 17.2 -> 16.1 ms with
+// the exponentials grouped (two samples per lane at eight waves per SIMD
+// 17.9 ms: three LDS reads per two terms); 300 pairs x 16 starts, one
+// evaluation 321 -> 179 us with eight starts per workgroup (one workgroup per
+// pair and four waves left a third of the chip idle in its second round).
+__global__ __launch_bounds__(kAlignMaxWaves* kWave) __attribute__((amdgpu_waves_per_eu(4)))
+void k_align(AlignArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  float4* sSamp = reinterpret_cast<float4*>(smem);  // [n_samples]
+  void* rest = sSamp + a.n_samples;
+  const int pair = a.order ? a.order[blockIdx.x] : blockIdx.x;
+  const int s0 = blockIdx.y * a.starts_per_block;
+  const int s1 = min(a.n_starts, s0 + a.starts_per_block);
+  if (align_bad(a, pair, s0, s1)) return;
+  const AlignStage A(rest, a.max_a);
+  align_samples(a, pair, sSamp, A.AF, A.AS, A.AR, A.Aa);
+
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = threadIdx.x / kWave, waves = blockDim.x / kWave;
   const int b0 = a.offB[pair], nb = a.offB[pair + 1] - b0;
   const float4 cA = a.A.centre[pair];
   const double Za = a.A.Z[pair];
   const double S = (double)a.O_aa[pair] + (double)a.O_bb[pair];
-  AtomRec* wR = sBR + wave * a.max_b;
-  float* wa = sBa + wave * a.max_b;
-  float4* wC = sBC + wave * a.max_b;
+  const MovedAtoms B = moved_atoms(rest, waves, wave, a.max_b);
   const int per_lane = (a.n_samples + kWave - 1) / kWave;
-
-  for (int st = wave; st < a.n_starts; st += kAlignWaves) {
+  for (int st = s0 + wave; st < s1; st += waves) {
     const size_t o = (size_t)pair * a.n_starts + st;
-    float ps[7], am[7], av[7];
-#pragma unroll
-    for (int c = 0; c < 7; ++c) {
-      ps[c] = a.pose[o * 7 + c];
-      am[c] = 0.f;
-      av[c] = 0.f;
-    }
+    LanePose ps;
+    ps.x = a.pose[o * 7 + (lane < 7 ? lane : 6)];
     for (int it = 0;; ++it) {  // it = Adam steps taken
-      float R[9], inv_norm;
-      quat_rotation(ps[0], ps[1], ps[2], ps[3], R, inv_norm);
-      // B's origin in A's frame (the rotation centre)
-      const float tx = ps[4] - cA.x, ty = ps[5] - cA.y, tz = ps[6] - cA.z;
-      for (int i = lane; i < nb; i += kWave) {
-        const Atom at = a.B.atom[b0 + i];
-        Atom moved = at;
-        moved.x = fmaf(R[0], at.x, fmaf(R[1], at.y, fmaf(R[2], at.z, tx)));
-        moved.y = fmaf(R[3], at.x, fmaf(R[4], at.y, fmaf(R[5], at.z, ty)));
-        moved.z = fmaf(R[6], at.x, fmaf(R[7], at.y, fmaf(R[8], at.z, tz)));
-        make_rec(moved, 0.f, 0.f, 0.f, wR[i], wa[i]);
-        // 2 alpha_j (c''_j, 1), with 2 alpha = 2 a2 ln 2
-        const float two_al = 2.0f * 0.693147180559945309f * at.a2;
-        wC[i] = make_float4(two_al * moved.x, two_al * moved.y, two_al * moved.z, two_al);
+      float inv_norm;
+      const float tx = ps.get(4) - cA.x, ty = ps.get(5) - cA.y, tz = ps.get(6) - cA.z;
+      {
+        float R[9];
+        quat_rotation(ps.get(0), ps.get(1), ps.get(2), ps.get(3), R, inv_norm);
+        B.move(a.B.atom + b0, nb, R, tx, ty, tz);
       }
       wave_lds_sync();
-      float accO = 0.f, gtx = 0.f, gty = 0.f, gtz = 0.f, grx = 0.f, gry = 0.f, grz = 0.f;
-      for (int t = 0; t < per_lane; t += kAS) {
-        float rx[kAS], ry[kAS], rz[kAS], r2[kAS], w[kAS];
-        float P[kAS], S0[kAS], Sx[kAS], Sy[kAS], Sz[kAS];
+      float acc[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      for (int t = 0; t < per_lane; t += kAS)
+        align_eval<kAS, 1>(sSamp, a.n_samples, t, B, nb, tx, ty, tz,
+                        [&](int, float w, const float (&f)[7]) {
 #pragma unroll
-        for (int s = 0; s < kAS; ++s) {
-          const int k = lane + kWave * (t + s);
-          const bool ok = (t + s) < per_lane && k < a.n_samples;
-          const float4 c = sSamp[ok ? k : 0];
-          rx[s] = c.x; ry[s] = c.y; rz[s] = c.z;
-          w[s] = ok ? c.w : 0.f;
-          r2[s] = norm2(c.x, c.y, c.z);
-          P[s] = 1.f; S0[s] = 0.f; Sx[s] = 0.f; Sy[s] = 0.f; Sz[s] = 0.f;
-        }
-        // unrolled by two: no loop-carried register copies between atoms
-#pragma unroll 2
-        for (int j = 0; j < nb; ++j) {
-          const AtomRec b = wR[j];
-          const float aj = wa[j];
-          const float4 cj = wC[j];
-#pragma unroll
-          for (int s = 0; s < kAS; ++s) {
-            // S <- S (1 - o) + o P c  written as  S + o (c P - S): two fused
-            // operations per component, and P <- P - o P
-            const float oj =
-                __builtin_amdgcn_exp2f(-exponent_x(b, aj, rx[s], ry[s], rz[s], r2[s]));
-            S0[s] = fmaf(oj, fmaf(cj.w, P[s], -S0[s]), S0[s]);
-            Sx[s] = fmaf(oj, fmaf(cj.x, P[s], -Sx[s]), Sx[s]);
-            Sy[s] = fmaf(oj, fmaf(cj.y, P[s], -Sy[s]), Sy[s]);
-            Sz[s] = fmaf(oj, fmaf(cj.z, P[s], -Sz[s]), Sz[s]);
-            P[s] = fmaf(-oj, P[s], P[s]);
-          }
-        }
-#pragma unroll
-        for (int s = 0; s < kAS; ++s) {
-          // translation gradient of u at this point and the torque about B's origin
-          const float gx = fmaf(S0[s], rx[s], -Sx[s]);
-          const float gy = fmaf(S0[s], ry[s], -Sy[s]);
-          const float gz = fmaf(S0[s], rz[s], -Sz[s]);
-          const float cxr_x = Sy[s] * rz[s] - Sz[s] * ry[s];
-          const float cxr_y = Sz[s] * rx[s] - Sx[s] * rz[s];
-          const float cxr_z = Sx[s] * ry[s] - Sy[s] * rx[s];
-          const float txg_x = ty * gz - tz * gy;
-          const float txg_y = tz * gx - tx * gz;
-          const float txg_z = tx * gy - ty * gx;
-          accO = fmaf(w[s], 1.f - P[s], accO);
-          gtx = fmaf(w[s], gx, gtx);
-          gty = fmaf(w[s], gy, gty);
-          gtz = fmaf(w[s], gz, gtz);
-          grx = fmaf(w[s], cxr_x - txg_x, grx);
-          gry = fmaf(w[s], cxr_y - txg_y, gry);
-          grz = fmaf(w[s], cxr_z - txg_z, grz);
-        }
-      }
+                          for (int c = 0; c < 7; ++c) acc[c] = fmaf(w, f[c], acc[c]);
+                        });
       // butterfly sums: every lane holds the totals, so T and its gradient
-      // are wave-uniform and the Adam state can stay in registers
-      const double sO = wave_sum((double)accO);
-      const double s_tx = wave_sum((double)gtx), s_ty = wave_sum((double)gty),
-                   s_tz = wave_sum((double)gtz);
-      const double s_rx = wave_sum((double)grx), s_ry = wave_sum((double)gry),
-                   s_rz = wave_sum((double)grz);
-      const double scale = Za / (double)a.n_samples;
-      const double O = scale * sO;
-      const double D = S - O;
-      const float T = (float)(O / D);
+      // are wave-uniform
+      double sum[7];
+#pragma unroll
+      for (int c = 0; c < 7; ++c) sum[c] = wave_sum((double)acc[c]);
       const bool last = it >= a.n_steps;
-      float g[7];
-      if (a.grad || !last) {
-        const double k = scale * S / (D * D);  // dT/dO * Z_A/n
-        const double gth[3] = {k * s_rx, k * s_ry, k * s_rz};
-        // dT/dq = (2/|q|) [ -v.g ; w g - v x g ] with (w, v) = q/|q|
-        const double in = (double)inv_norm;
-        const double w = ps[0] * in, vx = ps[1] * in, vy = ps[2] * in, vz = ps[3] * in;
-        const double vdg = vx * gth[0] + vy * gth[1] + vz * gth[2];
-        const double vxg_x = vy * gth[2] - vz * gth[1];
-        const double vxg_y = vz * gth[0] - vx * gth[2];
-        const double vxg_z = vx * gth[1] - vy * gth[0];
-        g[0] = (float)(2.0 * in * (-vdg));
-        g[1] = (float)(2.0 * in * (w * gth[0] - vxg_x));
-        g[2] = (float)(2.0 * in * (w * gth[1] - vxg_y));
-        g[3] = (float)(2.0 * in * (w * gth[2] - vxg_z));
-        g[4] = (float)(k * s_tx);
-        g[5] = (float)(k * s_ty);
-        g[6] = (float)(k * s_tz);
-      }
+      float T, g[7];
+      align_value(sum, Za, S, a.n_samples, ps, inv_norm, last, a.grad || !last, T, g);
       wave_lds_sync();  // this pose's records are read before the next move
       if (last) {
-        if (lane == 0) {
-          a.T[o] = T;
-          if (a.grad)
-            for (int c = 0; c < 7; ++c) a.grad[o * 7 + c] = g[c];
-          if (a.n_steps > 0)
-            for (int c = 0; c < 7; ++c) a.pose_out[o * 7 + c] = ps[c];
-        }
+        align_write(a, o, ps, T, g);
         break;
       }
-      adam_pose_step(ps, am, av, g, it + 1, a.lr, 0.9f, 0.999f, 1e-8f);
+      ps.step(g, it + 1, a.lr, 0.9f, 0.999f, 1e-8f);
     }
+  }
+}
+
+// The same optimisation with one start per workgroup, its samples spread over
+// sixteen waves: for calls with too few starts to fill the chip.  The waves
+// write each sample's integrands to LDS, and a wave per sum adds them in the
+// order one wave would have taken them, so the sums have k_align's bits.
+// Latency bounds it: of about 10 us per step (2,048 samples, 30 atoms) 2.5 us
+// are the serial part of one wave (sums, gradient, Adam, moving the atoms).
+// 10 pairs x 16 starts, 60 steps: 12.5 -> 0.65 ms (one wave per start, four
+// starts in turn, before); eight waves of four samples per lane 0.72 ms.
+constexpr int kSplitWaves = 16;
+constexpr int kSplitS = 2;
+constexpr int kSplitSlots = kSplitWaves * kSplitS;  // slots of 64 samples per pass
+
+__global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ double sSum[7];
+  __shared__ float sT[3];  // B's origin in A's frame
+  float4* sSamp = reinterpret_cast<float4*>(smem);  // [n_samples]
+  void* rest = sSamp + a.n_samples;
+  const int pair = blockIdx.x, st = blockIdx.y;
+  if (align_bad(a, pair, st, st + 1)) return;
+  const AlignStage A(rest, a.max_a);
+  align_samples(a, pair, sSamp, A.AF, A.AS, A.AR, A.Aa);
+
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int b0 = a.offB[pair], nb = a.offB[pair + 1] - b0;
+  const float4 cA = a.A.centre[pair];
+  const double Za = a.A.Z[pair];
+  const double S = (double)a.O_aa[pair] + (double)a.O_bb[pair];
+  const MovedAtoms B = moved_atoms(rest, 1, 0, a.max_b);
+  const int per_lane = (a.n_samples + kWave - 1) / kWave;
+  // integrand c of slot i (of this pass), lane l: sF[(c slots + i) 64 + l]
+  const int slots = min(per_lane, kSplitSlots);
+  float* sF = reinterpret_cast<float*>((unsigned char*)rest + align_b_bytes(1, a.max_b));
+  const size_t o = (size_t)pair * a.n_starts + st;
+  LanePose ps;  // wave 0's
+  ps.x = a.pose[o * 7 + (lane < 7 ? lane : 6)];
+  for (int it = 0;; ++it) {
+    float inv_norm = 0.f;
+    if (wave == 0) {
+      float R[9];
+      quat_rotation(ps.get(0), ps.get(1), ps.get(2), ps.get(3), R, inv_norm);
+      const float tx = ps.get(4) - cA.x, ty = ps.get(5) - cA.y, tz = ps.get(6) - cA.z;
+      B.move(a.B.atom + b0, nb, R, tx, ty, tz);
+      if (lane == 0) {
+        sT[0] = tx;
+        sT[1] = ty;
+        sT[2] = tz;
+      }
+    }
+    __syncthreads();  // the moved atoms
+    float acc = 0.f;
+    for (int t0 = 0; t0 < per_lane; t0 += kSplitSlots) {
+      const int t = t0 + wave * kSplitS;
+      if (t < per_lane)
+        align_eval<kSplitS, 4>(sSamp, a.n_samples, t, B, nb, sT[0], sT[1], sT[2],
+                            [&](int s, float, const float (&f)[7]) {
+                              const int i = wave * kSplitS + s;
+                              if (i < slots)
+#pragma unroll
+                                for (int c = 0; c < 7; ++c)
+                                  sF[(c * slots + i) * kWave + lane] = f[c];
+                            });
+      __syncthreads();  // this pass's integrands
+      if (wave < 7) {
+        const int n = min(slots, per_lane - t0);
+        const float* F = sF + (size_t)wave * slots * kWave + lane;
+#pragma unroll 8
+        for (int i = 0; i < n; ++i) {
+          const int k = lane + kWave * (t0 + i);
+          acc = fmaf(k < a.n_samples ? sSamp[k].w : 0.f, F[i * kWave], acc);
+        }
+      }
+      if (t0 + kSplitSlots < per_lane) __syncthreads();  // read before the next pass writes
+    }
+    if (wave < 7) {
+      const double s = wave_sum((double)acc);
+      if (lane == 0) sSum[wave] = s;
+    }
+    __syncthreads();  // the sums (and every read of the moved atoms)
+    const bool last = it >= a.n_steps;
+    if (wave == 0) {
+      double sum[7];
+#pragma unroll
+      for (int c = 0; c < 7; ++c) sum[c] = sSum[c];
+      float T, g[7];
+      align_value(sum, Za, S, a.n_samples, ps, inv_norm, last, a.grad || !last, T, g);
+      if (last)
+        align_write(a, o, ps, T, g);
+      else
+        ps.step(g, it + 1, a.lr, 0.9f, 0.999f, 1e-8f);
+    }
+    if (last) break;
   }
 }
 
 // Self-overlap of each molecule from its own first n samples,
 // O_MM = Z_M / n sum_k w_M u_M (pose invariant); one workgroup per molecule.
-__global__ __launch_bounds__(256) void k_self_overlap(Prepared M, const int* __restrict__ off,
-                                                      int n_mols, int n_samples, uint2 key,
-                                                      float* __restrict__ out) {
+// All threads draw; the terms are then added by kSelfLanes lanes in a fixed
+// order (lane i takes samples i, i + kSelfLanes, ...).
+constexpr int kSelfThreads = 1024;
+constexpr int kSelfLanes = 256;
+constexpr int kSelfChunk = 2048;  // a multiple of kSelfLanes
+__global__ __launch_bounds__(kSelfThreads) void k_self_overlap(Prepared M,
+                                                               const int* __restrict__ off,
+                                                               int n_mols, int n_samples,
+                                                               uint2 key,
+                                                               float* __restrict__ out) {
+  __shared__ float2 sWU[kSelfChunk];  // weight and occupancy of a chunk's samples
   __shared__ Atom sF[SHAPE_MAX_ATOMS];
   __shared__ AtomSampling sS[SHAPE_MAX_ATOMS];
   __shared__ AtomRec sR[SHAPE_MAX_ATOMS];
   __shared__ float sA[SHAPE_MAX_ATOMS];
-  __shared__ double red[4];
+  __shared__ double red[kSelfLanes / kWave];
   const int mol = blockIdx.x;
   if (mol >= n_mols) return;
   if (M.bad[mol] != 0) {
@@ -277,19 +515,28 @@ __global__ __launch_bounds__(256) void k_self_overlap(Prepared M, const int* __r
   }
   __syncthreads();
   float acc = 0.f;
-  for (int k = threadIdx.x; k < n_samples; k += blockDim.x) {
-    float rx[1], ry[1], rz[1], r2[1], m[1] = {0.f}, u[1] = {0.f};
-    sample_point(sF, sS, na, M.id[mol], (uint64_t)k, key, rx[0], ry[0], rz[0]);
-    r2[0] = norm2(rx[0], ry[0], rz[0]);
-    eval_density_u_x<1>(sR, sA, na, rx, ry, rz, r2, m, u);
-    acc += bounded_weight(u[0], m[0]) * u[0];
+  for (int k0 = 0; k0 < n_samples; k0 += kSelfChunk) {
+    const int k1 = min(n_samples, k0 + kSelfChunk);
+    weigh_samples(sF, sS, sR, sA, na, M.id[mol], k0, k1, key,
+                  [&](int k, float, float, float, float w, float u) {
+                    sWU[k - k0] = make_float2(w, u);
+                  });
+    __syncthreads();
+    if (threadIdx.x < kSelfLanes)
+      for (int k = threadIdx.x; k < k1 - k0; k += kSelfLanes) {
+        const float2 t = sWU[k];
+        acc = fmaf(t.x, t.y, acc);
+      }
+    __syncthreads();
   }
-  const double s = wave_sum((double)acc);
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
+  if (threadIdx.x < kSelfLanes) {
+    const double s = wave_sum((double)acc);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     double t = 0.0;
-    for (int w = 0; w < (int)(blockDim.x / kWave); ++w) t += red[w];
+    for (int w = 0; w < kSelfLanes / kWave; ++w) t += red[w];
     out[mol] = (float)(M.Z[mol] * t / (double)n_samples);
   }
 }
@@ -311,10 +558,14 @@ __global__ void k_adam_pose(float* __restrict__ pose, const float* __restrict__ 
       vi[c] = v[i * 7 + c];
       g[c] = dT[i * 7 + c];
     }
-    adam_pose_step(x, mi, vi, g, t, lr, b1, b2, eps);
+    const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
+#pragma unroll
+    for (int c = 0; c < 7; ++c)
+      x[c] = adam_component(x[c], mi[c], vi[c], g[c], c1, c2, lr, b1, b2, eps);
+    const float inv = quat_inv_norm(x[0], x[1], x[2], x[3]);
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
-      pose[i * 7 + c] = x[c];
+      pose[i * 7 + c] = c < 4 ? x[c] * inv : x[c];
       m[i * 7 + c] = mi[c];
       v[i * 7 + c] = vi[c];
     }
@@ -343,22 +594,54 @@ __global__ void k_best_start(const float* __restrict__ T, int n_pairs, int n_sta
   best[p] = b;
 }
 
+// The layout with four waves (what a call must fit, whichever kernel runs it).
 size_t align_lds_bytes(int n_samples, int max_a, int max_b) {
-  return (size_t)n_samples * sizeof(float4) +
-         (size_t)max_a * (sizeof(AtomRec) + sizeof(Atom) + sizeof(float) + sizeof(AtomSampling)) +
-         (size_t)kAlignWaves * max_b * (sizeof(float4) + sizeof(AtomRec) + sizeof(float));
+  return (size_t)n_samples * sizeof(float4) + align_a_bytes(max_a) + align_b_bytes(kAlignMinWaves, max_b);
 }
 
-hipError_t launch_align(const AlignArgs& a, int n_pairs, hipStream_t st) {
-  hipLaunchKernelGGL(k_align, dim3((unsigned)n_pairs), dim3(kAlignThreads),
-                     align_lds_bytes(a.n_samples, a.max_a, a.max_b), st, a);
+static size_t align_lds(int n_samples, int max_a, int max_b, int sets, int split_slots) {
+  return (size_t)n_samples * sizeof(float4) +
+         std::max(align_a_bytes(max_a), align_b_bytes(sets, max_b) +
+                                            (size_t)split_slots * 7 * kWave * sizeof(float));
+}
+
+hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max_lds,
+                        hipStream_t st) {
+  AlignArgs a = args;
+  const int per_lane = (a.n_samples + kWave - 1) / kWave;
+  const int64_t starts = (int64_t)n_pairs * a.n_starts;
+  const size_t split_lds = align_lds(a.n_samples, a.max_a, a.max_b, 1,
+                                     std::min(per_lane, kSplitSlots));
+  // Few starts: sixteen waves each.  Every workgroup draws A's samples, about
+  // the work of one evaluation, so a single evaluation pays for it at fewer
+  // starts than an optimisation does.  2,048 samples, 15-45 atoms, 60 steps
+  // (split against four starts per workgroup): 10 pairs x 16 starts 0.65
+  // against 3.6 ms, 100 x 16 3.7 against 4.3 ms, 200 x 16 (30 steps) equal;
+  // one evaluation: 60 x 16 equal, 100 x 16 125 against 102 us.
+  const int64_t split_per_cu = a.n_steps > 0 ? 8 : 4;
+  if (starts <= split_per_cu * n_cu && a.n_starts <= 65535 && split_lds <= max_lds) {
+    hipLaunchKernelGGL(k_align_split, dim3((unsigned)n_pairs, (unsigned)a.n_starts),
+                       dim3(kSplitWaves * kWave), split_lds, st, a);
+    return hipGetLastError();
+  }
+  // Eight starts per workgroup share A's samples where that leaves two
+  // workgroups per compute unit, else four (the least a call is checked for).
+  // With many pairs a workgroup takes all of its pair's starts.
+  int waves = kAlignMaxWaves;
+  if (starts < (int64_t)2 * kAlignMaxWaves * n_cu || a.n_starts < kAlignMaxWaves ||
+      align_lds(a.n_samples, a.max_a, a.max_b, kAlignMaxWaves, 0) > max_lds)
+    waves = kAlignMinWaves;
+  a.starts_per_block = n_pairs >= 16 * n_cu ? a.n_starts
+                                            : std::max(waves, (a.n_starts + 65534) / 65535);
+  const unsigned groups = (unsigned)((a.n_starts + a.starts_per_block - 1) / a.starts_per_block);
+  hipLaunchKernelGGL(k_align, dim3((unsigned)n_pairs, groups), dim3(waves * kWave),
+                     align_lds(a.n_samples, a.max_a, a.max_b, waves, 0), st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_self_overlap(const Prepared& M, const int* off, int n_mols, int n_samples,
                                uint2 key, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_self_overlap, dim3((unsigned)n_mols), dim3(256), 0, st, M, off, n_mols,
-                     n_samples, key, out);
+  hipLaunchKernelGGL(k_self_overlap, dim3((unsigned)n_mols), dim3(kSelfThreads), 0, st, M, off, n_mols, n_samples, key, out);
   return hipGetLastError();
 }
 

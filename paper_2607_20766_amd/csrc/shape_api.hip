@@ -1048,7 +1048,7 @@ int align_launch(shape_ctx* c, const shape_mols* A, const shape_mols* B,
   a.lr = 0.f;
   a.pose_out = nullptr;
   a.order = wo.order;
-  HIP_TRY(c, shape::launch_align(a, A->n_mols, st), "alignment kernel");
+  HIP_TRY(c, shape::launch_align(a, A->n_mols, c->n_cu, c->lds_per_block, st), "alignment kernel");
   return SHAPE_OK;
 }
 
@@ -1157,7 +1157,7 @@ int shape_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t 
                                           wo.work, st),
               "launch order kernels");
     KernelTimer timer(c, st);
-    HIP_TRY(c, shape::launch_align(a, pairs, st), "alignment kernel");
+    HIP_TRY(c, shape::launch_align(a, pairs, c->n_cu, c->lds_per_block, st), "alignment kernel");
     timer.stop();
     if (best) HIP_TRY(c, shape::launch_best_start(T_final, pairs, n_starts, best, st), "best");
     return SHAPE_OK;

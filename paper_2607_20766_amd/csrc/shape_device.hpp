@@ -155,6 +155,23 @@ __device__ __forceinline__ int select_component(const AtomSampling* samp, int n,
   return j;
 }
 
+// The components of D words together.
+template <int D>
+__device__ __forceinline__ void select_components(const AtomSampling* samp, int n,
+                                                  const uint32_t (&word)[D], int (&j)[D]) {
+  const int last = n - 1;
+#pragma unroll
+  for (int d = 0; d < D; ++d) j[d] = 0;
+  if (last <= 0) return;
+  for (int step = 1 << (31 - __builtin_clz((unsigned)last)); step > 0; step >>= 1)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int c = j[d] + step;
+      const int idx = (c < last ? c : last) - 1;
+      if (c <= last && word[d] >= samp[idx].thr) j[d] = c;
+    }
+}
+
 // Guide table of a molecule's component choice, built once per molecule in
 // LDS: guide[g] = #{i < n-1 : thr_i <= g 2^24} for the top eight bits g of
 // a word.  Every threshold counted there lies at or below any word whose top
@@ -227,6 +244,35 @@ __device__ __forceinline__ void sample_point(const Atom* atoms, const AtomSampli
   rx = fmaf(normal_from_bits(x.y), sd, c.x);
   ry = fmaf(normal_from_bits(x.z), sd, c.y);
   rz = fmaf(normal_from_bits(x.w), sd, c.z);
+}
+
+// D sample points together (sample_point's, for sample numbers below 2^32):
+// the steps of all of them are interleaved, so their latencies overlap.
+template <int D>
+__device__ __forceinline__ void sample_points(const Atom* atoms, const AtomSampling* samp, int n,
+                                              uint32_t mol_id, const uint32_t (&k)[D], uint2 key,
+                                              float (&rx)[D], float (&ry)[D], float (&rz)[D]) {
+  uint32_t w0[D], wz[3 * D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const uint4 x = philox4x32_10(make_uint4(k[d], 0u, mol_id, 0u), key);
+    w0[d] = x.x;
+    wz[3 * d] = x.y;
+    wz[3 * d + 1] = x.z;
+    wz[3 * d + 2] = x.w;
+  }
+  int j[D];
+  select_components<D>(samp, n, w0, j);
+  float z[3 * D];
+  normals_from_bits<3 * D>(wz, z);
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const Atom c = atoms[j[d]];
+    const float sd = samp[j[d]].sd;
+    rx[d] = fmaf(z[3 * d], sd, c.x);
+    ry[d] = fmaf(z[3 * d + 1], sd, c.y);
+    rz[d] = fmaf(z[3 * d + 2], sd, c.z);
+  }
 }
 
 // Antithetic sample k (each draw paired with its reflection about its
@@ -440,9 +486,41 @@ __device__ __forceinline__ float bounded_weight(float u, float m) {
 // ---------------------------------------------------------------------------
 // Wave-level reductions (fixed butterfly order: deterministic).
 // ---------------------------------------------------------------------------
+// A butterfly over XOR partners 32, 16, 8, 4, 2, 1 on the vector ALU, without
+// LDS round trips: the halves and the rows of 16 are exchanged by gfx950's
+// permlane swaps; inside a row the partner of step d is reached by rotating
+// the row by d places, since by then the values repeat every 2 d lanes.
+// Every lane ends with the same bits (a sum of two does not depend on their
+// order).
+template <int Ctrl>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)b, Ctrl, 0xf, 0xf, true);
+  const long long hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), Ctrl, 0xf, 0xf, true);
+  return __longlong_as_double((hi << 32) | lo);
+}
+__device__ __forceinline__ double f64_of(unsigned lo, unsigned hi) {
+  return __longlong_as_double(((long long)hi << 32) | lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32),
+                                                     false, false);
+    v = f64_of(lo[0], hi[0]) + f64_of(lo[1], hi[1]);
+  }
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32),
+                                                     false, false);
+    v = f64_of(lo[0], hi[0]) + f64_of(lo[1], hi[1]);
+  }
+  v += dpp_f64<0x128>(v);  // row_ror:8
+  v += dpp_f64<0x124>(v);  // row_ror:4
+  v += dpp_f64<0x122>(v);  // row_ror:2
+  v += dpp_f64<0x121>(v);  // row_ror:1
   return v;
 }
 

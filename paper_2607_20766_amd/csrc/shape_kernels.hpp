@@ -84,6 +84,7 @@ struct AlignArgs {
   float lr;
   float* pose_out;    // the pose array again (written when n_steps > 0)
   const int* order;   // optional launch order: block b aligns pair order[b]
+  int starts_per_block = 0;  // starts a workgroup takes (set by launch_align)
 };
 
 // Dense layer C = epilogue(A B) with strided operands (see shape_gemm).
@@ -200,7 +201,9 @@ hipError_t launch_topk(const float* s, int n, int k, uint32_t* sel, uint32_t* hi
                        int* cnt_eq, int* out, hipStream_t st);
 
 size_t align_lds_bytes(int n_samples, int max_a, int max_b);
-hipError_t launch_align(const AlignArgs& a, int n_pairs, hipStream_t st);
+// max_lds: LDS bytes a workgroup may use
+hipError_t launch_align(const AlignArgs& a, int n_pairs, int n_cu, size_t max_lds,
+                        hipStream_t st);
 hipError_t launch_self_overlap(const Prepared& M, const int* off, int n_mols, int n_samples,
                                uint2 key, float* out, hipStream_t st);
 hipError_t launch_adam_pose(float* pose, const float* dT, float* m, float* v, int64_t n_poses,

@@ -161,6 +161,45 @@ def test_displaced_copy_recovered(eng):
     assert float(T.max()) > float(T0.max()) + 0.1
 
 
+@pytest.mark.parametrize("n_samples, na, nb", [(64, 1, 1), (100, 3, 5), (1000, 45, 33),
+                                               (2048, 30, 31), (2049, 64, 65), (4096, 256, 256)])
+def test_few_and_many_starts_same_bits(eng, n_samples, na, nb):
+    """One start per workgroup (few starts), four and eight starts per
+    workgroup (many): the same T, gradients, poses; a last slot of samples
+    that is partial, one or two passes over the samples, atom counts around
+    the wave's 64 lanes and the largest."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    gA, gB, _, _ = _gpu_sets(eng, molgen.molecule(21, na, na), molgen.molecule(22, nb, nb))
+    saa, sbb = eng.shape_self_overlap(gA, n_samples), eng.shape_self_overlap(gB, n_samples)
+    poses = torch.from_numpy(molgen.random_poses(23, 1, 16 * n_cu + 3)).to(eng.torch_device)
+    for starts in (3, 8 * n_cu + 1, 16 * n_cu + 3):
+        print(f"case: {n_samples} samples, {na} x {nb} atoms, {starts} starts", flush=True)
+        pose = poses[:, :starts].contiguous()
+        T, g = eng.shape_align_grad(gA, gB, pose, saa, sbb, n_samples)
+        moved = pose.clone()
+        Tf, _ = eng.shape_align(gA, gB, moved, n_samples=n_samples, n_steps=2)
+        got = [x[:, :3].cpu().numpy() for x in (T, g, moved, Tf)]
+        if starts == 3:
+            ref = got
+            assert all(np.all(np.isfinite(x)) for x in ref)
+        for k in range(4):
+            assert np.array_equal(got[k], ref[k]), (starts, k)
+
+
+@pytest.mark.parametrize("n_samples", [2, 255, 2047, 2049, 10000])
+def test_self_overlap_sample_counts(eng, n_samples):
+    """Self-overlaps over counts around a chunk of drawn samples, against the
+    single-pair estimator's O_aa on the same samples (both FP32 terms summed
+    in FP64: 1e-5, the parity bar)."""
+    ms = molgen.library(24, 3, 1, 60, workers=1)
+    M = eng.molecules(ms)
+    got = eng.shape_self_overlap(M, n_samples, seed=4).cpu().numpy()
+    for i in range(3):
+        one = eng.molecules(ms.mol(i), mol_id=[i])
+        ref = eng.shape_estimate(one, one, n_samples, n_samples, seed=4)["O_aa"]
+        assert abs(got[i] - ref) <= 1e-5 * abs(ref), (i, got[i], ref)
+
+
 def test_long_alignments_in_launch_order_same_bits(eng):
     """At least 4 pairs per compute unit are aligned largest pair first (the
     order comes from the atom counts); T, gradients, final poses and best
