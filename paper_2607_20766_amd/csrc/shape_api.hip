@@ -82,6 +82,7 @@ struct shape_ctx {
   bool timing = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
   int screen_variant = -1;        // -1: default tile shape
+  bool variant_set = false;       // by shape_screen_set_variant (not by the tuner)
   int sampling = SHAPE_SAMPLING_IID;
   bool capturing = false;         // a graph capture is open on capture_stream
   bool capture_failed = false;    // a call failed while capturing
@@ -776,7 +777,12 @@ int shape_screen(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
     int rc = screen_setup(c, query, lib, pairs, n_pairs, prm, st, out, &a);
     if (rc || a.n_pairs == 0) return rc;
     KernelTimer timer(c, st);
-    HIP_TRY(c, shape::launch_screen(a, screen_variant_of(c), st), "screen kernel");
+    // a variant set by the caller runs as set; the tuner's choice is for
+    // screens that take one wave per pair
+    const bool split = !c->variant_set && shape::screen_splits(a, c->n_cu);
+    HIP_TRY(c, split ? shape::launch_screen_split(a, st)
+                     : shape::launch_screen(a, screen_variant_of(c), st),
+            "screen kernel");
     timer.stop();
     return SHAPE_OK;
   } catch (...) {
@@ -895,6 +901,7 @@ int shape_screen_tune(shape_ctx* c, const shape_mols* query, const shape_mols* l
       auto it = g_tune.find(key);
       if (it != g_tune.end()) {  // chosen before: no timing
         c->screen_variant = it->second;
+        c->variant_set = false;
         if (ms)
           for (int v = 0; v < shape::kScreenVariants; ++v) ms[v] = -1.0f;
         if (best) *best = it->second;
@@ -938,6 +945,7 @@ int shape_screen_tune(shape_ctx* c, const shape_mols* query, const shape_mols* l
       for (int v = 0; v < shape::kScreenVariants; ++v) t[v] = 0.0f;
     }
     c->screen_variant = pick;
+    c->variant_set = false;
     if (ms)
       for (int v = 0; v < shape::kScreenVariants; ++v) ms[v] = t[v];
     if (best) *best = pick;
@@ -971,6 +979,7 @@ int shape_screen_set_variant(shape_ctx* c, int32_t variant) {
     return fail(c, SHAPE_E_RANGE, "variant %d outside [-1, %d)", variant,
                 shape::kScreenVariants);
   c->screen_variant = variant;
+  c->variant_set = variant >= 0;
   return SHAPE_OK;
 }
 

@@ -411,7 +411,8 @@ __device__ __forceinline__ double se_tanimoto(double n, double Za, double Zb, do
 // FP64 instruction; get(j) reads sum j in every lane.
 struct RoundSums {
   double s = 0.0;
-  __device__ __forceinline__ void add(const float (&fa)[3], const float (&fb)[3]) {
+  // the totals of one round, total j in lane j
+  static __device__ __forceinline__ float totals(const float (&fa)[3], const float (&fb)[3]) {
     const int lane = threadIdx.x & (kWave - 1);
     float v = 0.f;
 #pragma unroll
@@ -419,8 +420,9 @@ struct RoundSums {
       const float t = wave_sum_dpp(j < 3 ? fa[j] : fb[j - 3]);
       v = lane == j ? t : v;
     }
-    s += (double)v;
+    return v;
   }
+  __device__ __forceinline__ void add(float v) { s += (double)v; }
   __device__ __forceinline__ double get(int j) const { return readlane_f64(s, j); }
 };
 
@@ -693,7 +695,7 @@ void k_screen(ScreenArgs a) {
         B.term(t + s, w * (1.0f - qa[s]), w, ub);
       }
     }
-    S.add(A.f, B.f);
+    S.add(RoundSums::totals(A.f, B.f));
     n_side += rs;
     const ScreenArgs& r = screen_args_again();
     const bool stop = screen_stops(r, S, n_side, r.n_start ? (int64_t)r.n_start[p] : 0, kAnti,
@@ -702,6 +704,114 @@ void k_screen(ScreenArgs a) {
   }
   const ScreenArgs& r = screen_args_again();
   screen_write(r, p, S, n_side, kAnti, r.Q.Z[0], r.L.Z[m]);
+}
+
+// The same screen with several waves per pair, for calls with too few pairs to
+// fill the chip: two waves take two of a round's four slots each, of both
+// sides, and a workgroup of eight works on four rounds at a time.  The waves
+// write their slots' terms to LDS, one wave per round adds them in the order
+// a single wave would have, and the rounds' totals enter the running sums,
+// with the stop test after each, in turn: every output has k_screen's bits
+// (rounds drawn past the stop are dropped, 1.5 of about twenty).
+// Latency bounds such a screen (a pair's rounds are a chain): 501 molecules,
+// SE(T) <= 0.005, 358 -> 112 us; one 277 -> 74 us.  One slot per wave (two
+// LDS reads per term) 135 us, four slots 141 us, eight rounds at a time 144 us.
+constexpr int kSplitSlots = 4;  // rounds of 256 samples per side
+constexpr int kSplitS = 2;      // slots per wave
+constexpr int kSplitRounds = 4;
+constexpr int kSplitTerms = 5;  // side A: f1, f2; side B: f1, w, u
+constexpr int kSplitThreads = kSplitRounds * (kSplitSlots / kSplitS) * kWave;
+
+template <bool kAnti>
+__global__ __launch_bounds__(kSplitThreads) void k_screen_split(ScreenArgs a) {
+#pragma clang fp contract(off)
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int S = kSplitS, kRoundWaves = kSplitSlots / S;
+  __shared__ float sF[kSplitRounds][kSplitTerms][kSplitSlots][kWave];
+  __shared__ float sTot[kSplitRounds][8];
+  const ScreenLds lds(smem, a.max_q, a.max_b);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int g = wave / kRoundWaves, t = wave % kRoundWaves * S;  // this wave's round, first slot
+  const int p = a.order ? a.order[blockIdx.x] : xcd_chunk(blockIdx.x, gridDim.x);
+  if (p < 0 || p >= a.n_pairs) return;
+  const int m = a.pairs ? a.pairs[p] : p;
+  if (a.Q.bad[0] != 0 || m < 0 || m >= a.n_lib || a.L.bad[m] != 0) {
+    screen_write_nan(a, p);
+    return;
+  }
+  const int q0 = a.offQ[0], nq = a.offQ[1] - q0;
+  const int b0 = a.offL[m], nb = a.offL[m + 1] - b0;
+  lds.stage(a, m, q0, nq, b0, nb);
+  const uint32_t idb = a.L.id[m];
+  const double Za = a.Q.Z[0], Zb = a.L.Z[m];
+  const int rs = kSplitSlots * kWave;
+  const int64_t limit = a.mode == SHAPE_SCREEN_ADAPTIVE ? a.cap_pair / 2 : a.n_fixed;
+  const int64_t first_check = a.n_start ? (int64_t)a.n_start[p] : 0;
+  RoundSums sums;
+  int64_t n_side = 0;
+  for (bool stop = false; !stop;) {
+    const int64_t n0 = n_side + (int64_t)g * rs;
+    if (n0 < limit) {  // the last round is never past the samples asked for
+      {
+        float rx[S], ry[S], rz[S], r2[S], w[S], f2[S], q[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int i = t + s;
+          const int k = kAnti ? (int)n0 + 2 * lane + 2 * kWave * (i >> 1) + (i & 1)
+                              : (int)n0 + lane + kWave * i;
+          const float4 c = a.qs[k];
+          rx[s] = c.x; ry[s] = c.y; rz[s] = c.z; w[s] = c.w;
+          r2[s] = norm2(c.x, c.y, c.z);
+          f2[s] = a.qf2[k];
+          q[s] = 1.0f;
+        }
+        eval_union_x<S>(lds.BA, lds.aBA, nb, rx, ry, rz, r2, q);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          sF[g][0][t + s][lane] = w[s] * (1.0f - q[s]);
+          sF[g][1][t + s][lane] = f2[s];
+        }
+      }
+      {
+        float rx[S], ry[S], rz[S], r2[S], mb[S], qb[S], qa[S];
+        screen_draw<S, kAnti>(lds, nb, idb, (uint32_t)n0, t, kSplitSlots, a.key, rx, ry, rz);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          r2[s] = norm2(rx[s], ry[s], rz[s]);
+          mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
+        }
+        eval_density_x<S>(lds.BB, lds.aBB, nb, rx, ry, rz, r2, mb, qb);
+        eval_union_x<S>(lds.AB, lds.aAB, nq, rx, ry, rz, r2, qa);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const float ub = 1.0f - qb[s];
+          const float w = bounded_weight(ub, mb[s]);
+          sF[g][2][t + s][lane] = w * (1.0f - qa[s]);
+          sF[g][3][t + s][lane] = w;
+          sF[g][4][t + s][lane] = ub;
+        }
+      }
+    }
+    __syncthreads();  // the rounds' terms
+    if (wave < kSplitRounds) {
+      SideSums<kAnti> A, B;
+#pragma unroll
+      for (int i = 0; i < kSplitSlots; ++i) {
+        A.term(i, sF[wave][0][i][lane], sF[wave][1][i][lane], 1.0f);
+        B.term(i, sF[wave][2][i][lane], sF[wave][3][i][lane], sF[wave][4][i][lane]);
+      }
+      const float v = RoundSums::totals(A.f, B.f);
+      if (lane < 6) sTot[wave][lane] = v;
+    }
+    __syncthreads();  // the rounds' totals (and every read of their terms)
+    for (int r = 0; r < kSplitRounds && !stop; ++r) {
+      sums.add(sTot[r][lane < 6 ? lane : 5]);
+      n_side += rs;
+      stop = __builtin_amdgcn_readfirstlane(
+          screen_stops(a, sums, n_side, first_check, kAnti, Za, Zb));
+    }
+  }
+  if (wave == 0) screen_write(a, p, sums, n_side, kAnti, Za, Zb);
 }
 
 // ---------------------------------------------------------------------------
@@ -994,6 +1104,20 @@ static void launch_screen_t(const ScreenArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((k_screen<A, B, true>), grid, block, lds, st, a);
   else
     hipLaunchKernelGGL((k_screen<A, B, false>), grid, block, lds, st, a);
+}
+
+bool screen_splits(const ScreenArgs& a, int n_cu) {
+  return a.round_side == kSplitSlots * kWave && a.n_pairs <= kSplitPairsPerCu * n_cu;
+}
+
+hipError_t launch_screen_split(const ScreenArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)a.n_pairs), block(kSplitThreads);
+  const size_t lds = screen_lds_bytes(a.max_q, a.max_b);
+  if (a.anti)
+    hipLaunchKernelGGL((k_screen_split<true>), grid, block, lds, st, a);
+  else
+    hipLaunchKernelGGL((k_screen_split<false>), grid, block, lds, st, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_screen(const ScreenArgs& a, int variant, hipStream_t st) {

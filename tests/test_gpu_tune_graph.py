@@ -95,6 +95,42 @@ def test_round_sizes_every_variant(eng, data, round_per_pair, anti):
         eng.sampling(False)
 
 
+@pytest.mark.parametrize("anti", [False, True])
+@pytest.mark.parametrize("kw", [
+    dict(mode=SHAPE_SCREEN_ADAPTIVE, cap_per_pair=8192, tau=0.005),
+    dict(mode=SHAPE_SCREEN_ADAPTIVE, cap_per_pair=1536, tau=1e-9),   # cap inside a pass
+    dict(mode=SHAPE_SCREEN_ADAPTIVE, cap_per_pair=512, tau=0.5),     # one round
+    dict(mode=SHAPE_SCREEN_FIXED, n_per_side=256),
+    dict(mode=SHAPE_SCREEN_FIXED, n_per_side=1280),                  # five rounds
+])
+def test_few_pairs_same_bits_as_one_wave_per_pair(eng, kw, anti):
+    """A screen of few pairs (eight waves and four rounds at a time per pair)
+    gives the bits of one wave per pair, for pair lists with repeated and
+    invalid entries, seeded budgets, and 1 to 256 atoms."""
+    L = molgen.MolSet.concat([molgen.library(17, 20, 1, 12, workers=1),
+                              molgen.library(18, 6, 60, 70, workers=1),
+                              molgen.molecule(19, 0, 256)])
+    lib = eng.molecules(L)
+    Q = eng.molecules(molgen.molecule(20, 0, 33), mol_id=[QUERY_ID])
+    pairs = torch.tensor([26, 3, 3, -1, 20, 0, 27, 25] + list(range(20)), dtype=torch.int32,
+                         device=eng.torch_device)
+    n_start = torch.arange(pairs.numel(), dtype=torch.int32, device=pairs.device) * 300
+    print(f"case: few pairs, {kw}, anti {anti}", flush=True)
+    eng.sampling(anti)
+    try:
+        for ns in (None, n_start):
+            eng.screen_variant(5)
+            one = _np(eng.shape_screen(Q, lib, pairs=pairs, n_start=ns, seed=9, **kw))
+            eng.screen_variant(-1)
+            many = _np(eng.shape_screen(Q, lib, pairs=pairs, n_start=ns, seed=9, **kw))
+            _same(one, many)
+            bad = (pairs < 0) | (pairs >= lib.n_mols)
+            assert np.array_equal(np.isnan(many["T"]), bad.cpu().numpy())
+    finally:
+        eng.screen_variant(-1)
+        eng.sampling(False)
+
+
 def test_tuner_picks_a_variant(eng, data):
     Q, lib = data
     tune_cache_clear()
