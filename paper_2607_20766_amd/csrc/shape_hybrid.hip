@@ -14,6 +14,8 @@
 // and dT/dq follows from dtheta = 2 (w dv - dw v + v x dv) for q = (w, v).
 #include "shape_kernels.hpp"
 
+#include <type_traits>
+
 #include <math.h>
 
 namespace shape {
@@ -474,8 +476,17 @@ __global__ __launch_bounds__(64) void k_fo_align(FoAlignArgs a) {
 // per lane (lanes 0-6 of the row, with their moments) and read back by the
 // whole row, instead of all seven in every lane.
 // ---------------------------------------------------------------------------
+// VALU issue bounds it: of 952 instructions per wave and step (30 x 30 atoms)
+// 657 are terms; with the terms of four of B's atoms together and their
+// exponentials in one prioritised group (trans_group) 10,000 pairs x 8 starts
+// x 50 steps take 1.38 ms (1.45 ms four atoms unrolled without the group, 1.45
+// and 1.51 ms with two and one atoms per group).  More waves do not help: with
+// the constants tabulated per distinct width of B, a third of the LDS, six
+// waves per SIMD measured 1.43 ms (one more instruction per atom and row).
+constexpr int kFoTermAtoms = 4;
 template <int RA>
-__global__ __launch_bounds__(256) void k_fo_align_rows(FoAlignArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void k_fo_align_rows(FoAlignArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int RA16 = RA * 16;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -563,23 +574,40 @@ __global__ __launch_bounds__(256) void k_fo_align_rows(FoAlignArgs a) {
     float O[RA], W[RA], Px[RA], Py[RA], Pz[RA];
 #pragma unroll
     for (int r = 0; r < RA; ++r) O[r] = W[r] = Px[r] = Py[r] = Pz[r] = 0.f;
-#pragma unroll 4
-    for (int j = 0; j < nb; ++j) {
-      const float4 cj = mine[j];
+    // kFoTermAtoms of B's atoms at a time, their terms' exponentials grouped
+    const auto terms = [&](int j, auto count) {
+      constexpr int V = decltype(count)::value;
+      float4 cj[V];
+      float kk[V * RA], K[V * RA];
 #pragma unroll
-      for (int r = 0; r < RA; ++r) {
-        const float2 kp = trow[j * RA16 + 16 * r];
-        const float e = fmaf(-2.f * cx[r], cj.x,
-                             fmaf(-2.f * cy[r], cj.y, fmaf(-2.f * cz[r], cj.z, cj.w)));
-        const float K = __builtin_amdgcn_exp2f(fmaf(kp.x, e, kp.y));
-        O[r] += K;
-        const float fs = kp.x * K;
-        W[r] += fs;
-        Px[r] = fmaf(fs, cj.x, Px[r]);
-        Py[r] = fmaf(fs, cj.y, Py[r]);
-        Pz[r] = fmaf(fs, cj.z, Pz[r]);
+      for (int u = 0; u < V; ++u) {
+        cj[u] = mine[j + u];
+#pragma unroll
+        for (int r = 0; r < RA; ++r) {
+          const float2 kp = trow[(j + u) * RA16 + 16 * r];
+          const float e = fmaf(-2.f * cx[r], cj[u].x,
+                               fmaf(-2.f * cy[r], cj[u].y,
+                                    fmaf(-2.f * cz[r], cj[u].z, cj[u].w)));
+          kk[u * RA + r] = kp.x;
+          K[u * RA + r] = fmaf(kp.x, e, kp.y);
+        }
       }
-    }
+      trans_group<V * RA>([&](int i) { K[i] = __builtin_amdgcn_exp2f(K[i]); });
+#pragma unroll
+      for (int u = 0; u < V; ++u)
+#pragma unroll
+        for (int r = 0; r < RA; ++r) {
+          O[r] += K[u * RA + r];
+          const float fs = kk[u * RA + r] * K[u * RA + r];
+          W[r] += fs;
+          Px[r] = fmaf(fs, cj[u].x, Px[r]);
+          Py[r] = fmaf(fs, cj[u].y, Py[r]);
+          Pz[r] = fmaf(fs, cj[u].z, Pz[r]);
+        }
+    };
+    int j = 0;
+    for (; j + kFoTermAtoms <= nb; j += kFoTermAtoms) terms(j, std::integral_constant<int, kFoTermAtoms>{});
+    for (; j < nb; ++j) terms(j, std::integral_constant<int, 1>{});
     wave_lds_sync();  // this start's moved atoms are rewritten next step
     float Fx[RA], Fy[RA], Fz[RA];
 #pragma unroll
