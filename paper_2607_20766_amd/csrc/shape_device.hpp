@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "shape_normal_poly.hpp"
 
 namespace shape {
@@ -36,13 +38,18 @@ struct __align__(8) AtomSampling {
 // products are written as 32x32->64-bit multiplies so that each is one
 // v_mad_u64_u32 rather than a v_mul_hi_u32/v_mul_lo_u32 pair.
 // ---------------------------------------------------------------------------
+// The three-way XORs are one v_bitop3_b32 each (truth table 0x96).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * c.x;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c.z;
-    c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k.x, (uint32_t)p1,
-                   (uint32_t)(p0 >> 32) ^ c.w ^ k.y, (uint32_t)p0);
+    c = make_uint4(xor3((uint32_t)(p1 >> 32), c.y, k.x), (uint32_t)p1,
+                   xor3((uint32_t)(p0 >> 32), c.w, k.y), (uint32_t)p0);
     k.x += 0x9E3779B9u;
     k.y += 0xBB67AE85u;
   }
@@ -430,16 +437,78 @@ __device__ __forceinline__ void eval_atoms_x(const AtomRec* __restrict__ rec,
   }
 }
 
-// Union complement q = prod(1 - o_i) at S points (expanded form; the caller
-// initialises q to 1): one fused multiply-add per atom and point, u = 1 - q.
-template <int S>
-__device__ __forceinline__ void eval_union_x(const AtomRec* __restrict__ rec,
-                                             const float* __restrict__ a2, int n,
+// Two atoms' records in one 48-byte word, so that the inner loop needs one LDS
+// address.  A molecule of odd size ends with a phantom atom: e = 10^30 at
+// every point, o = 0 exactly, which changes no sum and no product.
+struct __align__(16) AtomRec2 {
+  AtomRec r[2];
+  float a2[2];
+  float pad[2];
+};
+__host__ __device__ constexpr int rec_pairs(int n) { return (n + 1) / 2; }
+
+// Atom i of n of a molecule in the frame of (rx, ry, rz); the last atom of an
+// odd molecule also writes the phantom.
+__device__ __forceinline__ void make_rec2(const Atom& a, float rx, float ry, float rz,
+                                          AtomRec2* rec, int i, int n) {
+  AtomRec2& w = rec[i >> 1];
+  make_rec(a, rx, ry, rz, w.r[i & 1], w.a2[i & 1]);
+  if (i == n - 1 && (n & 1)) {
+    w.r[1] = AtomRec{0.f, 0.f, 0.f, 1e30f};
+    w.a2[1] = 0.f;
+  }
+}
+
+// eval_atoms_x over such records: at least eight exponentials per group.
+template <int S, class Fold>
+__device__ __forceinline__ void eval_pairs_x(const AtomRec2* __restrict__ rec, int n,
                                              const float (&rx)[S], const float (&ry)[S],
                                              const float (&rz)[S], const float (&r2)[S],
-                                             float (&q)[S]) {
-  eval_atoms_x<S>(rec, a2, n, rx, ry, rz, r2,
+                                             Fold fold) {
+  constexpr int U = S >= 4 ? 1 : 4 / S;  // records per group
+  const auto group = [&](int i, auto count) {
+    constexpr int V = decltype(count)::value;
+    float o[2 * V * S];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const AtomRec2 w = rec[i + u];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          o[(2 * u + h) * S + s] = exponent_x(w.r[h], w.a2[h], rx[s], ry[s], rz[s], r2[s]);
+    }
+    exp2_group(o);
+#pragma unroll
+    for (int u = 0; u < 2 * V; ++u)
+#pragma unroll
+      for (int s = 0; s < S; ++s) fold(s, o[u * S + s]);
+  };
+  const int np = rec_pairs(n);
+  int i = 0;
+  for (; i + U <= np; i += U) group(i, std::integral_constant<int, U>{});
+  if constexpr (U > 1)
+    for (; i < np; ++i) group(i, std::integral_constant<int, 1>{});
+}
+
+// Union complement q = prod(1 - o_i) (the caller initialises q to 1, u = 1 - q),
+// and the first-order density m with it, over pair records.
+template <int S>
+__device__ __forceinline__ void eval_union_x2(const AtomRec2* rec, int n, const float (&rx)[S],
+                                              const float (&ry)[S], const float (&rz)[S],
+                                              const float (&r2)[S], float (&q)[S]) {
+  eval_pairs_x<S>(rec, n, rx, ry, rz, r2,
                   [&](int s, float o) { q[s] = fmaf(-q[s], o, q[s]); });
+}
+template <int S>
+__device__ __forceinline__ void eval_density_x2(const AtomRec2* rec, int n, const float (&rx)[S],
+                                                const float (&ry)[S], const float (&rz)[S],
+                                                const float (&r2)[S], float (&m)[S],
+                                                float (&q)[S]) {
+  eval_pairs_x<S>(rec, n, rx, ry, rz, r2, [&](int s, float o) {
+    m[s] += o;
+    q[s] = fmaf(-q[s], o, q[s]);
+  });
 }
 
 // First-order density m and union complement q at S points (expanded form).

@@ -491,31 +491,27 @@ __device__ __forceinline__ const ScreenArgs& screen_args_again() {
   return *(const ScreenArgs*)k;
 }
 
-// LDS of one pair (n = atoms):
-//   sBF   [max_b] Atom          library atoms in the library frame (sampling)
-//   sBB   [max_b] AtomRec + a2  library atoms, library frame (own density)
-//   sBA   [max_b] AtomRec + a2  library atoms, query frame (side A partner)
-//   sAB   [max_q] AtomRec + a2  query atoms, library frame (side B partner)
-//   sBS   [max_b] AtomSampling  the library atoms' sampling records
-//   guide [kGuideSize] uint8_t  the library molecule's component guide
-// 16-byte records first, then the 8-byte, the 4-byte and the 1-byte arrays,
-// so every array is aligned to its element size whatever the atom counts.
+// LDS of one pair (n = atoms, n' = rec_pairs(n)):
+//   BF    [max_b]  Atom          library atoms in the library frame (sampling)
+//   BB    [max_b'] AtomRec2      library atoms, library frame (own density)
+//   BA    [max_b'] AtomRec2      library atoms, query frame (side A partner)
+//   AB    [max_q'] AtomRec2      query atoms, library frame (side B partner)
+//   BS    [max_b]  AtomSampling  the library atoms' sampling records
+//   guide [kGuideSize] uint8_t   the library molecule's component guide
+// 16-byte records first, then the 8-byte and the 1-byte arrays, so every array
+// is aligned to its element size whatever the atom counts.
 struct ScreenLds {
   Atom* BF;
-  AtomRec *BB, *BA, *AB;
+  AtomRec2 *BB, *BA, *AB;
   AtomSampling* BS;
-  float *aBB, *aBA, *aAB;
   uint8_t* guide;
   __device__ ScreenLds(unsigned char* smem, int max_q, int max_b) {
     BF = reinterpret_cast<Atom*>(smem);
-    BB = reinterpret_cast<AtomRec*>(BF + max_b);
-    BA = BB + max_b;
-    AB = BA + max_b;
-    BS = reinterpret_cast<AtomSampling*>(AB + max_q);
-    aBB = reinterpret_cast<float*>(BS + max_b);
-    aBA = aBB + max_b;
-    aAB = aBA + max_b;
-    guide = reinterpret_cast<uint8_t*>(aAB + max_q);
+    BB = reinterpret_cast<AtomRec2*>(BF + max_b);
+    BA = BB + rec_pairs(max_b);
+    AB = BA + rec_pairs(max_b);
+    BS = reinterpret_cast<AtomSampling*>(AB + rec_pairs(max_q));
+    guide = reinterpret_cast<uint8_t*>(BS + max_b);
   }
   // the records of a pair, staged by the whole workgroup
   __device__ __forceinline__ void stage(const ScreenArgs& a, int m, int q0, int nq, int b0,
@@ -523,7 +519,7 @@ struct ScreenLds {
     const float4 cA = a.Q.centre[0];
     const float4 cB = a.L.centre[m];
     for (int i = threadIdx.x; i < nq; i += blockDim.x)
-      make_rec(a.Q.atom[q0 + i], cB.x, cB.y, cB.z, AB[i], aAB[i]);
+      make_rec2(a.Q.atom[q0 + i], cB.x, cB.y, cB.z, AB, i, nq);
     for (int i = threadIdx.x; i < nb; i += blockDim.x) {
       const Atom at = a.L.atom[b0 + i];
       Atom f = at;
@@ -532,8 +528,8 @@ struct ScreenLds {
       f.z = at.z - cB.z;
       BF[i] = f;
       BS[i] = a.L.samp[b0 + i];
-      make_rec(at, cB.x, cB.y, cB.z, BB[i], aBB[i]);
-      make_rec(at, cA.x, cA.y, cA.z, BA[i], aBA[i]);
+      make_rec2(at, cB.x, cB.y, cB.z, BB, i, nb);
+      make_rec2(at, cA.x, cA.y, cA.z, BA, i, nb);
     }
     __syncthreads();
     build_guide(BS, nb, guide, threadIdx.x, blockDim.x);
@@ -625,9 +621,11 @@ __device__ __forceinline__ void screen_draw(const ScreenLds& lds, int nb, uint32
 // together (trans_group); a density loop alone measured 21.6, 24.3 and 28.2
 // cycles per evaluation with eight, six and four waves.  100,000 molecules of
 // 10-50 atoms, 30-atom query, SE(T) <= 0.005: 8.07 ms with the exponentials
-// among the other instructions (76 registers), 7.15 ms with them grouped, 7.01
-// ms with the drawing steps of a lane's points grouped too; fixed 4,096 per
-// side, 7,003 molecules: 0.60 -> 0.53 ms.
+// among the other instructions (76 registers), 7.15 ms with them grouped, 7.07
+// ms with the drawing steps of a lane's points grouped too, 7.00 ms with two
+// atoms per LDS word, no remainder loop and three-way XORs (5.67e9 -> 5.52e9
+// instructions); fixed 4,096 per side, 7,003 molecules: 0.60 -> 0.52 ms.  Of
+// 4-cycle issue slots left by the exponentials, 1.62 of 2 hold an instruction.
 template <int kSA, int kSB, bool kAnti>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSA >= 8 ? 4 : 8)))
 void k_screen(ScreenArgs a) {
@@ -651,6 +649,7 @@ void k_screen(ScreenArgs a) {
   const uint32_t idb = a.L.id[m];
   const int rs = a.round_side;
   const int per_lane = rs / kWave;
+  const bool ragged = per_lane % kSA != 0 || per_lane % kSB != 0;
   RoundSums S;
   int64_t n_side = 0;
   for (;;) {
@@ -669,11 +668,11 @@ void k_screen(ScreenArgs a) {
         f2[s] = a.qf2[k];
         q[s] = 1.0f;
       }
-      eval_union_x<kSA>(lds.BA, lds.aBA, nb, rx, ry, rz, r2, q);
+      eval_union_x2<kSA>(lds.BA, nb, rx, ry, rz, r2, q);
 #pragma unroll
       for (int s = 0; s < kSA; ++s) {
-        const float valid = (t + s) < per_lane ? 1.0f : 0.0f;
-        A.term(t + s, w[s] * (1.0f - q[s]) * valid, f2[s], valid);
+        if (ragged && t + s >= per_lane) w[s] = f2[s] = 0.0f;  // a slot past the round's last
+        A.term(t + s, w[s] * (1.0f - q[s]), f2[s], 1.0f);
       }
     }
     // side B: library samples drawn here (library frame), partner = query
@@ -685,13 +684,13 @@ void k_screen(ScreenArgs a) {
         r2[s] = norm2(rx[s], ry[s], rz[s]);
         mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
       }
-      eval_density_x<kSB>(lds.BB, lds.aBB, nb, rx, ry, rz, r2, mb, qb);
-      eval_union_x<kSB>(lds.AB, lds.aAB, nq, rx, ry, rz, r2, qa);
+      eval_density_x2<kSB>(lds.BB, nb, rx, ry, rz, r2, mb, qb);
+      eval_union_x2<kSB>(lds.AB, nq, rx, ry, rz, r2, qa);
 #pragma unroll
       for (int s = 0; s < kSB; ++s) {
-        const float valid = (t + s) < per_lane ? 1.0f : 0.0f;
         const float ub = 1.0f - qb[s];
-        const float w = bounded_weight(ub, mb[s]) * valid;
+        float w = bounded_weight(ub, mb[s]);
+        if (ragged && t + s >= per_lane) w = 0.0f;
         B.term(t + s, w * (1.0f - qa[s]), w, ub);
       }
     }
@@ -765,7 +764,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_screen_split(ScreenArgs a) {
           f2[s] = a.qf2[k];
           q[s] = 1.0f;
         }
-        eval_union_x<S>(lds.BA, lds.aBA, nb, rx, ry, rz, r2, q);
+        eval_union_x2<S>(lds.BA, nb, rx, ry, rz, r2, q);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           sF[g][0][t + s][lane] = w[s] * (1.0f - q[s]);
@@ -780,8 +779,8 @@ __global__ __launch_bounds__(kSplitThreads) void k_screen_split(ScreenArgs a) {
           r2[s] = norm2(rx[s], ry[s], rz[s]);
           mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
         }
-        eval_density_x<S>(lds.BB, lds.aBB, nb, rx, ry, rz, r2, mb, qb);
-        eval_union_x<S>(lds.AB, lds.aAB, nq, rx, ry, rz, r2, qa);
+        eval_density_x2<S>(lds.BB, nb, rx, ry, rz, r2, mb, qb);
+        eval_union_x2<S>(lds.AB, nq, rx, ry, rz, r2, qa);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           const float ub = 1.0f - qb[s];
@@ -1091,9 +1090,9 @@ hipError_t launch_work_order(const OrderArgs& o, int* order, int* work, hipStrea
 }
 
 size_t screen_lds_bytes(int max_q, int max_b) {
-  return (size_t)max_b * (sizeof(Atom) + 2 * (sizeof(AtomRec) + sizeof(float)) +
-                          sizeof(AtomSampling)) +
-         (size_t)max_q * (sizeof(AtomRec) + sizeof(float)) + kGuideSize * sizeof(uint8_t);
+  return (size_t)max_b * (sizeof(Atom) + sizeof(AtomSampling)) +
+         (size_t)(2 * rec_pairs(max_b) + rec_pairs(max_q)) * sizeof(AtomRec2) +
+         kGuideSize * sizeof(uint8_t);
 }
 
 template <int A, int B>
