@@ -49,7 +49,10 @@ __device__ __forceinline__ void weigh_samples(const Atom* AF, const AtomSampling
       m[d] = 0.f;
       u[d] = 0.f;
     }
-    sample_points<D>(AF, AS, na, id, k, key, rx, ry, rz);
+    int j[D];
+    float z[3 * D];
+    draws<D>(AS, na, id, k, key, j, z);
+    draw_points<D>(AF, AS, j, z, 1.0f, rx, ry, rz);
 #pragma unroll
     for (int d = 0; d < D; ++d) r2[d] = norm2(rx[d], ry[d], rz[d]);
     eval_density_u_x<D>(AR, Aa, na, rx, ry, rz, r2, m, u);

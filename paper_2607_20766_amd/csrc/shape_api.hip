@@ -31,7 +31,7 @@ struct Buffer {
 enum Slot {
   S_Q_ATOM, S_Q_SAMP, S_Q_Z, S_Q_ID, S_Q_BAD, S_Q_CENTRE,
   S_L_ATOM, S_L_SAMP, S_L_Z, S_L_ID, S_L_BAD, S_L_CENTRE,
-  S_PARTIALS, S_RESULT, S_QS, S_QF2,
+  S_PARTIALS, S_QS, S_QF2,
   S_SELF_A, S_SELF_B,
   S_MSE, S_TOPK_SEL, S_TOPK_HIST, S_TOPK_GT, S_TOPK_EQ, S_COLSUM, S_TUNE, S_MLP_PACK, S_FEAT_MOM, S_GEMM_PART,
   S_GRID_BOX, S_GRID_TAB, S_GRID_PART, S_PEAK, S_MLP_D, S_MLP_STEP, S_ORDER,
@@ -88,6 +88,8 @@ struct shape_ctx {
   bool capture_failed = false;    // a call failed while capturing
   hipStream_t capture_stream = nullptr;
   void* noalloc = nullptr;        // device address of this GPU's copy of `scratch`
+  shape::EstOut* est_out = nullptr;      // pinned host memory an estimate is written to
+  shape::EstOut* est_out_dev = nullptr;  // its device address
 };
 
 struct shape_graph {
@@ -102,13 +104,13 @@ struct shape_graph {
 // creation), held until the process ends.  Host code never passes the array's
 // name to a kernel: in host code it is only a stand-in symbol.  Layout: the
 // prepared records of the two one-molecule sets (at most SHAPE_MAX_ATOMS atoms
-// each), the per-block partial sums of est_blocks(SHAPE_NOALLOC_MAX_SAMPLES)
-// blocks per side, and the device copy of the result.
+// each) and the per-block partial sums of est_blocks(SHAPE_NOALLOC_MAX_SAMPLES)
+// blocks per side.
 // ---------------------------------------------------------------------------
 namespace {
 
 struct NoallocLayout {
-  size_t atom[2], samp[2], Z, id, bad, centre, partials, result, total;
+  size_t atom[2], samp[2], Z, id, bad, centre, partials, total;
   int max_blocks;
   NoallocLayout() {
     size_t o = 0;
@@ -127,7 +129,6 @@ struct NoallocLayout {
     centre = take(2 * sizeof(float4));
     max_blocks = shape::est_blocks(SHAPE_NOALLOC_MAX_SAMPLES);
     partials = take((size_t)2 * max_blocks * shape::kEstSums * sizeof(double));
-    result = take(sizeof(shape_result));
     total = o;
   }
 };
@@ -230,22 +231,14 @@ int check_mols(shape_ctx* c, const shape_mols* m, const char* name, bool single)
   return SHAPE_OK;
 }
 
-// Prepare a molecule set into the query (q = true) or library slots.
-// subset (device int32 [n_subset], optional): prepare only these molecules
-// (records at their usual places; the rest of the slots stay as they were),
-// for calls that read no other molecule.  Such a partial preparation is
-// never kept for reuse.
-int prepare(shape_ctx* c, const shape_mols* m, bool q, hipStream_t st, shape::Prepared* P,
-            const int32_t* subset = nullptr, int32_t n_subset = 0) {
+shape::MolsDev mols_dev(const shape_mols* m) {
+  return shape::MolsDev{m->n_mols, m->max_atoms, m->n_atoms, m->atom_offset, m->xyz, m->alpha,
+                        m->mol_id};
+}
+
+// The query (q = true) or library slots, large enough for a set's records.
+int prepared_slots(shape_ctx* c, const shape_mols* m, bool q, shape::Prepared* P) {
   const int base = q ? S_Q_ATOM : S_L_ATOM;
-  PrepKey& key = c->prepared[q ? 0 : 1];
-  int* set_flag = c->flag + (q ? 1 : 2);
-  if (c->prep_cache && key.same(m)) {
-    *P = key.P;
-    HIP_TRY(c, shape::launch_flag_or(c->flag, set_flag, st), "flag kernel");
-    return SHAPE_OK;
-  }
-  key.valid = false;
   void* p[6];
   int rc;
   const size_t na = (size_t)m->n_atoms, nm = (size_t)m->n_mols;
@@ -261,6 +254,26 @@ int prepare(shape_ctx* c, const shape_mols* m, bool q, hipStream_t st, shape::Pr
   P->id = (uint32_t*)p[3];
   P->bad = (int*)p[4];
   P->centre = (float4*)p[5];
+  return SHAPE_OK;
+}
+
+// Prepare a molecule set into the query (q = true) or library slots.
+// subset (device int32 [n_subset], optional): prepare only these molecules
+// (records at their usual places; the rest of the slots stay as they were),
+// for calls that read no other molecule.  Such a partial preparation is
+// never kept for reuse.
+int prepare(shape_ctx* c, const shape_mols* m, bool q, hipStream_t st, shape::Prepared* P,
+            const int32_t* subset = nullptr, int32_t n_subset = 0) {
+  PrepKey& key = c->prepared[q ? 0 : 1];
+  int* set_flag = c->flag + (q ? 1 : 2);
+  if (c->prep_cache && key.same(m)) {
+    *P = key.P;
+    HIP_TRY(c, shape::launch_flag_or(c->flag, set_flag, st), "flag kernel");
+    return SHAPE_OK;
+  }
+  key.valid = false;
+  int rc;
+  if ((rc = prepared_slots(c, m, q, P))) return rc;
   shape::MolsDev in{m->n_mols, m->max_atoms, m->n_atoms, m->atom_offset, m->xyz, m->alpha,
                     m->mol_id};
   if (subset) {
@@ -546,7 +559,12 @@ int shape_create(shape_ctx** out, int device) {
   // this device's copy of the allocation-free entry point's scratch (the
   // device is current here; every GPU holds the array at its own address)
   if (e == hipSuccess) e = hipGetSymbolAddress(&c->noalloc, HIP_SYMBOL(scratch));
+  if (e == hipSuccess)
+    e = hipHostMalloc((void**)&c->est_out, sizeof(shape::EstOut), hipHostMallocMapped);
+  if (e == hipSuccess)
+    e = hipHostGetDevicePointer((void**)&c->est_out_dev, c->est_out, 0);
   if (e != hipSuccess) {
+    if (c->est_out) (void)hipHostFree(c->est_out);
     if (c->flag) (void)hipFree(c->flag);
     delete c;
     return fail(nullptr, SHAPE_E_HIP, "context set-up: %s", hipGetErrorString(e));
@@ -573,6 +591,7 @@ void shape_destroy(shape_ctx* c) {
     (void)hipEventDestroy(e.first);
     (void)hipEventDestroy(e.second);
   }
+  if (c->est_out) (void)hipHostFree(c->est_out);
   if (c->flag) (void)hipFree(c->flag);
   delete c;
 }
@@ -620,6 +639,28 @@ int estimate_check(shape_ctx* c, const shape_mols* A, const shape_mols* B, int64
   return SHAPE_OK;
 }
 
+// The kernels of one estimate on prepared sets.  The last one writes the
+// result, and which molecules are invalid, to the context's pinned host
+// buffer, so the call waits for the stream once and copies nothing.
+int estimate_run(shape_ctx* c, const shape::Prepared& PA, const shape::Prepared& PB,
+                 const shape_mols* A, const shape_mols* B, int64_t n_a, int64_t n_b,
+                 uint64_t seed, double* partials, int nblk, hipStream_t st, shape_result* out) {
+  const int anti = c->sampling == SHAPE_SAMPLING_ANTITHETIC ? 1 : 0;
+  KernelTimer timer(c, st);
+  HIP_TRY(c, shape::launch_estimate(PA, PB, A->atom_offset, B->atom_offset, n_a, n_b,
+                                    key_of(seed), anti, partials, nblk, c->est_out_dev, st),
+          "estimate kernels");
+  timer.stop();
+  HIP_TRY(c, hipStreamSynchronize(st), "hipStreamSynchronize");
+  const shape::EstOut& r = *c->est_out;
+  if (r.bad[0] || r.bad[1]) {
+    HIP_TRY(c, shape::launch_fill_int(c->flag, 1, 0, st), "flag reset");
+    return fail(c, SHAPE_E_DATA, "invalid molecule data in %s", r.bad[0] ? "A" : "B");
+  }
+  *out = r.r;
+  return SHAPE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -636,34 +677,24 @@ int shape_estimate(shape_ctx* c, const shape_mols* A, const shape_mols* B, int64
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)stream;
     shape::Prepared PA, PB;
-    if ((rc = prepare(c, A, true, st, &PA))) return rc;
-    if ((rc = prepare(c, B, false, st, &PB))) return rc;
+    if (c->prep_cache) {
+      if ((rc = prepare(c, A, true, st, &PA))) return rc;
+      if ((rc = prepare(c, B, false, st, &PB))) return rc;
+    } else {
+      c->prepared[0].valid = c->prepared[1].valid = false;
+      if ((rc = prepared_slots(c, A, true, &PA))) return rc;
+      if ((rc = prepared_slots(c, B, false, &PB))) return rc;
+    }
     const int64_t units = (n_a > n_b ? n_a : n_b) / (anti ? 2 : 1);
     const int nblk = shape::est_blocks(units);
-    void *partials, *res;
+    void* partials;
     if ((rc = ensure(c, S_PARTIALS, (size_t)2 * nblk * shape::kEstSums * sizeof(double),
                      &partials)))
       return rc;
-    if ((rc = ensure(c, S_RESULT, sizeof(shape_result), &res))) return rc;
-    // invalid inputs are reported before the sampling kernels read them
-    int bad[2] = {0, 0};
-    HIP_TRY(c, hipMemcpyAsync(&bad[0], PA.bad, sizeof(int), hipMemcpyDeviceToHost, st), "copy");
-    HIP_TRY(c, hipMemcpyAsync(&bad[1], PB.bad, sizeof(int), hipMemcpyDeviceToHost, st), "copy");
-    HIP_TRY(c, hipStreamSynchronize(st), "hipStreamSynchronize");
-    if (bad[0] || bad[1]) {
-      HIP_TRY(c, shape::launch_fill_int(c->flag, 1, 0, st), "flag reset");
-      return fail(c, SHAPE_E_DATA, "invalid molecule data in %s", bad[0] ? "A" : "B");
-    }
-    KernelTimer timer(c, st);
-    HIP_TRY(c, shape::launch_estimate(PA, PB, A->atom_offset, B->atom_offset, n_a, n_b,
-                                      key_of(seed), anti, (double*)partials, nblk,
-                                      (shape_result*)res, st),
-            "estimate kernels");
-    timer.stop();
-    HIP_TRY(c, hipMemcpyAsync(out, res, sizeof(shape_result), hipMemcpyDeviceToHost, st),
-            "result copy");
-    HIP_TRY(c, hipStreamSynchronize(st), "hipStreamSynchronize");
-    return SHAPE_OK;
+    if (!c->prep_cache)
+      HIP_TRY(c, shape::launch_prepare_pair(mols_dev(A), PA, mols_dev(B), PB, c->flag, st),
+              "prepare kernel");
+    return estimate_run(c, PA, PB, A, B, n_a, n_b, seed, (double*)partials, nblk, st, out);
   } catch (...) {
     return fail(c, SHAPE_E_HIP, "internal error");
   }
@@ -691,7 +722,6 @@ int shape_estimate_noalloc(shape_ctx* c, const shape_mols* A, const shape_mols* 
     hipStream_t st = (hipStream_t)stream;
     char* base = (char*)c->noalloc;  // this GPU's copy, never the symbol's name
     shape::Prepared P[2];
-    const shape_mols* M[2] = {A, B};
     for (int s = 0; s < 2; ++s) {
       P[s].atom = (shape::Atom*)(base + L.atom[s]);
       P[s].samp = (shape::AtomSampling*)(base + L.samp[s]);
@@ -699,33 +729,16 @@ int shape_estimate_noalloc(shape_ctx* c, const shape_mols* A, const shape_mols* 
       P[s].id = (uint32_t*)(base + L.id) + s;
       P[s].bad = (int*)(base + L.bad) + s;
       P[s].centre = (float4*)(base + L.centre) + s;
-      const shape::MolsDev in{M[s]->n_mols,     M[s]->max_atoms, M[s]->n_atoms,
-                              M[s]->atom_offset, M[s]->xyz,       M[s]->alpha,
-                              M[s]->mol_id};
-      // every record the kernels read below is written here (the one
-      // molecule's Z, id, flag, centre and its atoms): nothing has to start
-      // at zero
-      HIP_TRY(c, shape::launch_prepare(in, P[s], c->flag, nullptr, st), "prepare kernel");
     }
+    // every record the kernels read below is written here (the one
+    // molecule's Z, id, flag, centre and its atoms): nothing has to start
+    // at zero
+    HIP_TRY(c, shape::launch_prepare_pair(mols_dev(A), P[0], mols_dev(B), P[1], c->flag, st),
+            "prepare kernel");
     const int64_t units = (n_a > n_b ? n_a : n_b) / (anti ? 2 : 1);
     const int nblk = shape::est_blocks(units);  // <= L.max_blocks by the range check
-    int bad[2] = {0, 0};
-    HIP_TRY(c, hipMemcpyAsync(bad, base + L.bad, sizeof bad, hipMemcpyDeviceToHost, st),
-            "copy");
-    HIP_TRY(c, hipStreamSynchronize(st), "hipStreamSynchronize");
-    if (bad[0] || bad[1]) {
-      HIP_TRY(c, shape::launch_fill_int(c->flag, 1, 0, st), "flag reset");
-      return fail(c, SHAPE_E_DATA, "invalid molecule data in %s", bad[0] ? "A" : "B");
-    }
-    shape_result* res = (shape_result*)(base + L.result);
-    HIP_TRY(c, shape::launch_estimate(P[0], P[1], A->atom_offset, B->atom_offset, n_a, n_b,
-                                      key_of(seed), anti, (double*)(base + L.partials), nblk,
-                                      res, st),
-            "estimate kernels");
-    HIP_TRY(c, hipMemcpyAsync(out, res, sizeof(shape_result), hipMemcpyDeviceToHost, st),
-            "result copy");
-    HIP_TRY(c, hipStreamSynchronize(st), "hipStreamSynchronize");
-    return SHAPE_OK;
+    return estimate_run(c, P[0], P[1], A, B, n_a, n_b, seed, (double*)(base + L.partials), nblk,
+                        st, out);
   } catch (...) {
     return fail(c, SHAPE_E_HIP, "internal error");
   }
@@ -1185,11 +1198,6 @@ int fo_pairs_check(shape_ctx* c, const shape_mols* A, const shape_mols* B) {
     return fail(c, SHAPE_E_RANGE, "A->n_mols = %d must be 1 or B->n_mols = %d", A->n_mols,
                 B->n_mols);
   return SHAPE_OK;
-}
-
-shape::MolsDev mols_dev(const shape_mols* m) {
-  return shape::MolsDev{m->n_mols, m->max_atoms, m->n_atoms, m->atom_offset, m->xyz, m->alpha,
-                        m->mol_id};
 }
 
 int shape_fo_starts(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t n_random,

@@ -83,6 +83,10 @@ __device__ __forceinline__ void exp2_group(float (&e)[N]) {
   trans_group<N>([&](int i) { e[i] = __builtin_amdgcn_exp2f(-e[i]); });
 }
 
+// Atoms taken together by the evaluators below, so that a group holds eight
+// exponentials (and one loop step) whatever the number of points per lane.
+constexpr int exp_atoms(int S) { return S >= 8 ? 1 : 8 / S; }
+
 // Standard normal from the top 24 bits b of a Philox word: u = (b + 1/2) 2^-24,
 // z = Phi^-1(u) = sqrt(2) erfinv(x), x = 2u - 1 = b 2^-23 + (2^-24 - 1), which
 // one FP32 fma forms exactly, so the tails are resolved to the last bit.
@@ -253,32 +257,39 @@ __device__ __forceinline__ void sample_point(const Atom* atoms, const AtomSampli
   rz = fmaf(normal_from_bits(x.w), sd, c.z);
 }
 
-// D sample points together (sample_point's, for sample numbers below 2^32):
-// the steps of all of them are interleaved, so their latencies overlap.
+// D draws together (Philox blocks below 2^32): components and normals, the
+// steps of all of them interleaved so that their latencies overlap.
 template <int D>
-__device__ __forceinline__ void sample_points(const Atom* atoms, const AtomSampling* samp, int n,
-                                              uint32_t mol_id, const uint32_t (&k)[D], uint2 key,
-                                              float (&rx)[D], float (&ry)[D], float (&rz)[D]) {
+__device__ __forceinline__ void draws(const AtomSampling* samp, int n, uint32_t mol_id,
+                                      const uint32_t (&blk)[D], uint2 key, int (&j)[D],
+                                      float (&z)[3 * D]) {
   uint32_t w0[D], wz[3 * D];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    const uint4 x = philox4x32_10(make_uint4(k[d], 0u, mol_id, 0u), key);
+    const uint4 x = philox4x32_10(make_uint4(blk[d], 0u, mol_id, 0u), key);
     w0[d] = x.x;
     wz[3 * d] = x.y;
     wz[3 * d + 1] = x.z;
     wz[3 * d + 2] = x.w;
   }
-  int j[D];
   select_components<D>(samp, n, w0, j);
-  float z[3 * D];
   normals_from_bits<3 * D>(wz, z);
+}
+
+// The draws' points (sample_point's), or their reflections about the
+// components' centres (sign = -1).
+template <int D>
+__device__ __forceinline__ void draw_points(const Atom* atoms, const AtomSampling* samp,
+                                            const int (&j)[D], const float (&z)[3 * D],
+                                            float sign, float (&rx)[D], float (&ry)[D],
+                                            float (&rz)[D]) {
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     const Atom c = atoms[j[d]];
     const float sd = samp[j[d]].sd;
-    rx[d] = fmaf(z[3 * d], sd, c.x);
-    ry[d] = fmaf(z[3 * d + 1], sd, c.y);
-    rz[d] = fmaf(z[3 * d + 2], sd, c.z);
+    rx[d] = fmaf(sign * z[3 * d], sd, c.x);
+    ry[d] = fmaf(sign * z[3 * d + 1], sd, c.y);
+    rz[d] = fmaf(sign * z[3 * d + 2], sd, c.z);
   }
 }
 
@@ -320,45 +331,40 @@ __device__ __forceinline__ void sample_pair(const Atom* atoms, const AtomSamplin
   bz = fmaf(-zz, sd, c.z);
 }
 
-__device__ __forceinline__ float occupancy(const Atom& a, float rx, float ry, float rz) {
-  const float dx = rx - a.x, dy = ry - a.y, dz = rz - a.z;
-  const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-  return __builtin_amdgcn_exp2f(-a.a2 * d2);
-}
-
-// Union complement q = prod (1 - o_i) of a molecule at S points (the caller
-// initialises q to 1); u = 1 - q.  One fused multiply-add per atom and point.
-template <int S>
-__device__ __forceinline__ void eval_union(const Atom* __restrict__ atoms, int n,
-                                           const float (&rx)[S], const float (&ry)[S],
-                                           const float (&rz)[S], float (&q)[S]) {
-#pragma unroll 2
-  for (int i = 0; i < n; ++i) {
-    const Atom a = atoms[i];
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const float o = occupancy(a, rx[s], ry[s], rz[s]);
-      q[s] = fmaf(-q[s], o, q[s]);
-    }
-  }
-}
-
-// First-order density m = sum o_i and union complement q at S points.
+// First-order density m = sum o_i and union complement q = prod (1 - o_i) of a
+// molecule at S points (the caller initialises m to 0 and q to 1; u = 1 - q),
+// from the differences r - c_i.
 template <int S>
 __device__ __forceinline__ void eval_density(const Atom* __restrict__ atoms, int n,
                                              const float (&rx)[S], const float (&ry)[S],
                                              const float (&rz)[S], float (&m)[S],
                                              float (&q)[S]) {
-#pragma unroll 2
-  for (int i = 0; i < n; ++i) {
-    const Atom a = atoms[i];
+  constexpr int U = exp_atoms(S);
+  const auto group = [&](int i, auto count) {
+    constexpr int V = decltype(count)::value;
+    float o[V * S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const float o = occupancy(a, rx[s], ry[s], rz[s]);
-      m[s] += o;
-      q[s] = fmaf(-q[s], o, q[s]);
+    for (int u = 0; u < V; ++u) {
+      const Atom a = atoms[i + u];
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const float dx = rx[s] - a.x, dy = ry[s] - a.y, dz = rz[s] - a.z;
+        o[u * S + s] = a.a2 * fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+      }
     }
-  }
+    exp2_group(o);
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        m[s] += o[u * S + s];
+        q[s] = fmaf(-q[s], o[u * S + s], q[s]);
+      }
+  };
+  int i = 0;
+  for (; i + U <= n; i += U) group(i, std::integral_constant<int, U>{});
+  if constexpr (U > 1)
+    for (; i < n; ++i) group(i, std::integral_constant<int, 1>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -393,10 +399,6 @@ __device__ __forceinline__ float exponent_x(const AtomRec& b, float a2, float rx
   e = fmaf(b.by, ry, e);
   return fmaf(b.bz, rz, e);
 }
-
-// Atoms taken together by the evaluators below, so that a group holds eight
-// exponentials (and one loop step) whatever the number of points per lane.
-constexpr int exp_atoms(int S) { return S >= 8 ? 1 : 8 / S; }
 
 // Occupancies of n atoms at S points, folded in atom order:
 // fold(s, o) is called for atom 0, 1, ... of each point s.

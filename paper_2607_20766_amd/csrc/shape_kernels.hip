@@ -35,17 +35,13 @@ __global__ void k_alpha_from_radius(const float* __restrict__ R, int64_t n, doub
 constexpr int kPrepWaves = 4;
 constexpr int kPrepChunks = SHAPE_MAX_ATOMS / kWave;
 
-__global__ __launch_bounds__(256) void k_prepare(MolsDev in, Prepared out, int* __restrict__ flag,
-                                                 int* __restrict__ set_flag,
-                                                 const int* __restrict__ which, int n_which) {
+__device__ __forceinline__ void prepare_molecule(const MolsDev& in, const Prepared& out, int m,
+                                                 int* __restrict__ flag,
+                                                 int* __restrict__ set_flag) {
   // FP64 without contraction: Z and the thresholds are the values the plain
   // expressions define, bit for bit.
 #pragma clang fp contract(off)
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int idx = blockIdx.x * kPrepWaves + w;
-  if (idx >= n_which) return;
-  const int m = which ? which[idx] : idx;  // a listed index may repeat
-  if (m < 0 || m >= in.n_mols) return;     // or lie outside: the screen flags it
+  const int lane = threadIdx.x & (kWave - 1);
   const int a0 = in.off[m], a1 = in.off[m + 1];
   const int n = a1 - a0;
   const bool range_bad = !(a0 >= 0 && (int64_t)a1 <= in.n_atoms && n >= 1 && n <= in.max_atoms);
@@ -132,6 +128,25 @@ __global__ __launch_bounds__(256) void k_prepare(MolsDev in, Prepared out, int* 
   }
 }
 
+__global__ __launch_bounds__(256) void k_prepare(MolsDev in, Prepared out, int* __restrict__ flag,
+                                                 int* __restrict__ set_flag,
+                                                 const int* __restrict__ which, int n_which) {
+  const int idx = blockIdx.x * kPrepWaves + threadIdx.x / kWave;
+  if (idx >= n_which) return;
+  const int m = which ? which[idx] : idx;  // a listed index may repeat
+  if (m < 0 || m >= in.n_mols) return;     // or lie outside: the screen flags it
+  prepare_molecule(in, out, m, flag, set_flag);
+}
+
+// Both one-molecule sets of a pair in one launch, a wave each.
+__global__ __launch_bounds__(2 * kWave) void k_prepare_pair(MolsDev inA, Prepared A, MolsDev inB,
+                                                            Prepared B, int* __restrict__ flag) {
+  if (threadIdx.x < kWave)
+    prepare_molecule(inA, A, 0, flag, nullptr);
+  else
+    prepare_molecule(inB, B, 0, flag, nullptr);
+}
+
 // Re-raises the invalid-data flag for a molecule set reused from an earlier
 // preparation that found invalid molecules.
 __global__ void k_flag_or(int* __restrict__ flag, const int* __restrict__ set_flag) {
@@ -172,12 +187,21 @@ __device__ void block_sum(double (&v)[K], double* lds /* [4][K] */) {
 // one side (samples from P, partner Q):
 //   f1 = w_P u_Q, f2 = w_P u_P, f3 = w_P, f4 = m_Q, f5 = m_P
 // sums: f1, f1^2, f2, f2^2, f3, f3^2, f4, f4^2, f5, f5^2, f1 f2.
-// blockIdx.y = side (0: P = A, 1: P = B).
+// blockIdx.y = side (0: P = A, 1: P = B).  A lane takes S independent terms
+// (samples, or antithetic pairs by their means) at a time and `turns` times S
+// in all, in FP32; the block's lanes are added in FP64.  Invalid molecules
+// (bad flags) are not read: the blocks write nothing.
+//
+// Few samples are bound by latency: one term per lane over four blocks of
+// waves per 1,024 samples instead of eight in turn (4,096 samples per side,
+// 20 x 24 atoms: 30 -> 9 us).  Many are bound by VALU issue (7 instructions,
+// an exponential and 2 to 3 more per atom): four terms at a time with their
+// exponentials grouped (trans_group; 10^6 x 0.8 10^6 samples, 30 x 45 atoms:
+// 73 -> 49 us).
 // ---------------------------------------------------------------------------
-constexpr int kEstSPT = 8;
-
+template <int S, bool kAnti>
 __global__ __launch_bounds__(256) void k_est_partials(Prepared A, Prepared B, int64_t n_a,
-                                                      int64_t n_b, uint2 key, int anti,
+                                                      int64_t n_b, uint2 key, int turns,
                                                       double* __restrict__ partials,
                                                       int nblk, const int* __restrict__ offA,
                                                       const int* __restrict__ offB) {
@@ -185,13 +209,14 @@ __global__ __launch_bounds__(256) void k_est_partials(Prepared A, Prepared B, in
   __shared__ Atom sQ[SHAPE_MAX_ATOMS];
   __shared__ AtomSampling sS[SHAPE_MAX_ATOMS];
   __shared__ double red[4 * kEstSums];
+  if (A.bad[0] != 0 || B.bad[0] != 0) return;
   const int side = blockIdx.y;
   const Prepared& P = side ? B : A;
   const Prepared& Q = side ? A : B;
   const int* offP = side ? offB : offA;
   const int* offQ = side ? offA : offB;
   const int64_t n = side ? n_b : n_a;
-  const int64_t units = anti ? n / 2 : n;  // independent terms: samples or pairs
+  const int64_t units = kAnti ? n / 2 : n;  // independent terms: samples or pairs
   const int p0 = offP[0], np = offP[1] - offP[0];
   const int q0 = offQ[0], nq = offQ[1] - offQ[0];
   const uint32_t idp = P.id[0];
@@ -204,35 +229,50 @@ __global__ __launch_bounds__(256) void k_est_partials(Prepared A, Prepared B, in
   float acc[kEstSums];
 #pragma unroll
   for (int j = 0; j < kEstSums; ++j) acc[j] = 0.0f;
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * kEstSPT;
-  for (int s = 0; s < kEstSPT; ++s) {
-    const int64_t u = base + (int64_t)s * blockDim.x + threadIdx.x;
-    if (u >= units) break;
-    // the unit's term: the sample itself, or the mean over an antithetic pair
-    float f[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-    const int members = anti ? 2 : 1;
-    for (int mbr = 0; mbr < members; ++mbr) {
-      float rx[1], ry[1], rz[1];
-      if (anti)
-        sample_point_anti(sP, sS, np, idp, (uint64_t)(2 * u + mbr), key, rx[0], ry[0], rz[0]);
-      else
-        sample_point(sP, sS, np, idp, (uint64_t)u, key, rx[0], ry[0], rz[0]);
-      float mp[1] = {0.0f}, qp[1] = {1.0f}, mq[1] = {0.0f}, qq[1] = {1.0f};
-      eval_density<1>(sP, np, rx, ry, rz, mp, qp);
-      eval_density<1>(sQ, nq, rx, ry, rz, mq, qq);
-      const float uP = 1.0f - qp[0], uQ = 1.0f - qq[0];
-      const float w = bounded_weight(uP, mp[0]);
-      f[0] += w * uQ; f[1] += w * uP; f[2] += w; f[3] += mq[0]; f[4] += mp[0];
-    }
-    if (anti)
+  const int64_t base = (int64_t)blockIdx.x * turns * S * blockDim.x + threadIdx.x;
+  for (int turn = 0; turn < turns; ++turn) {
+    const int64_t first = base + (int64_t)turn * S * blockDim.x;
+    if (first >= units) break;
+    uint32_t u[S];  // terms lie below 2^32 (at most 2^31 samples)
 #pragma unroll
-      for (int j = 0; j < 5; ++j) f[j] *= 0.5f;
-    acc[0] += f[0]; acc[1] += f[0] * f[0];
-    acc[2] += f[1]; acc[3] += f[1] * f[1];
-    acc[4] += f[2]; acc[5] += f[2] * f[2];
-    acc[6] += f[3]; acc[7] += f[3] * f[3];
-    acc[8] += f[4]; acc[9] += f[4] * f[4];
-    acc[10] += f[0] * f[1];
+    for (int s = 0; s < S; ++s) {
+      const int64_t t = first + (int64_t)s * blockDim.x;
+      u[s] = (uint32_t)(t < units ? t : first);
+    }
+    int j[S];
+    float z[3 * S], f[S][5];
+    draws<S>(sS, np, idp, u, key, j, z);
+#pragma unroll
+    for (int mbr = 0; mbr < (kAnti ? 2 : 1); ++mbr) {
+      float rx[S], ry[S], rz[S], mp[S], qp[S], mq[S], qq[S];
+      draw_points<S>(sP, sS, j, z, mbr ? -1.0f : 1.0f, rx, ry, rz);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        mp[s] = mq[s] = 0.0f;
+        qp[s] = qq[s] = 1.0f;
+      }
+      eval_density<S>(sP, np, rx, ry, rz, mp, qp);
+      eval_density<S>(sQ, nq, rx, ry, rz, mq, qq);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const float uP = 1.0f - qp[s], uQ = 1.0f - qq[s];
+        const float w = bounded_weight(uP, mp[s]);
+        const float g[5] = {w * uQ, w * uP, w, mq[s], mp[s]};
+#pragma unroll
+        for (int c = 0; c < 5; ++c) f[s][c] = mbr ? 0.5f * (f[s][c] + g[c]) : g[c];
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if (first + (int64_t)s * blockDim.x < units) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          acc[2 * c] += f[s][c];
+          acc[2 * c + 1] += f[s][c] * f[s][c];
+        }
+        acc[10] += f[s][0] * f[s][1];
+      }
+    }
   }
   double v[kEstSums];
 #pragma unroll
@@ -245,73 +285,90 @@ __global__ __launch_bounds__(256) void k_est_partials(Prepared A, Prepared B, in
   }
 }
 
-// Mean, sample variance (n-1) and covariance from running sums.
-struct Moments {
-  double n, s, ss;
-  __device__ double mean() const { return s / n; }
-  __device__ double var() const {
-    const double v = (ss - s * s / n) / (n - 1.0);
-    return v > 0.0 ? v : 0.0;
+// The blocks' sums added in a fixed order, and the result from them: thread
+// 32 part + q < 22 adds quantity q of blocks part, part + 32, ..., then thread
+// q adds the parts.  Lane 5 side + channel of the first wave forms that
+// channel's mean and standard error (ten divisions and roots side by side
+// instead of in turn).  A chain of FP64 latencies: 11 -> 4 us (16 blocks).
+constexpr int kEstParts = 32;
+__global__ __launch_bounds__(kEstParts * 32) void k_est_finalize(
+    const double* __restrict__ partials, int nblk, Prepared A, Prepared B, int64_t n_a,
+    int64_t n_b, int anti, EstOut* __restrict__ out) {
+  __shared__ double part[kEstParts][2 * kEstSums];
+  __shared__ double tot[2 * kEstSums];
+  __shared__ double mean[10], se[10], cov[2];
+  const int badA = A.bad[0], badB = B.bad[0];
+  if (badA != 0 || badB != 0) {
+    if (threadIdx.x == 0) {
+      out->bad[0] = badA;
+      out->bad[1] = badB;
+    }
+    return;
   }
-};
-
-__global__ __launch_bounds__(256) void k_est_finalize(const double* __restrict__ partials,
-                                                      int nblk, Prepared A, Prepared B,
-                                                      int64_t n_a, int64_t n_b, int anti,
-                                                      shape_result* __restrict__ out) {
-  __shared__ double red[4 * 2 * kEstSums];
-  double v[2 * kEstSums];
-#pragma unroll
-  for (int j = 0; j < 2 * kEstSums; ++j) v[j] = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
-#pragma unroll
-    for (int side = 0; side < 2; ++side)
-#pragma unroll
-      for (int j = 0; j < kEstSums; ++j)
-        v[side * kEstSums + j] += partials[((size_t)side * nblk + b) * kEstSums + j];
+  const int q = threadIdx.x % 32, pt = threadIdx.x / 32;
+  if (q < 2 * kEstSums) {
+    const double* src = partials + (size_t)(q / kEstSums) * nblk * kEstSums + q % kEstSums;
+    double v = 0.0;
+#pragma unroll 8
+    for (int b = pt; b < nblk; b += kEstParts) v += src[(size_t)b * kEstSums];
+    part[pt][q] = v;
   }
-  block_sum<2 * kEstSums>(v, red);
-  if (threadIdx.x != 0) return;
-  const double Za = A.Z[0], Zb = B.Z[0];
+  __syncthreads();
+  if (threadIdx.x < 2 * kEstSums) {
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < kEstParts; ++k) v += part[k][threadIdx.x];
+    tot[threadIdx.x] = v;
+  }
+  __syncthreads();
   // independent terms per side: samples, or antithetic pair means
-  const double na = (double)(anti ? n_a / 2 : n_a), nb = (double)(anti ? n_b / 2 : n_b);
-  const double* a = v;
-  const double* b = v + kEstSums;
-  auto mom = [](double n, const double* s, int j) { return Moments{n, s[2 * j], s[2 * j + 1]}; };
-  const Moments a1 = mom(na, a, 0), a2 = mom(na, a, 1), a3 = mom(na, a, 2), a4 = mom(na, a, 3),
-                a5 = mom(na, a, 4);
-  const Moments b1 = mom(nb, b, 0), b2 = mom(nb, b, 1), b3 = mom(nb, b, 2), b4 = mom(nb, b, 3),
-                b5 = mom(nb, b, 4);
-  const double cov_a = (a[10] - a[0] * a[2] / na) / (na - 1.0);
-  const double cov_b = (b[10] - b[0] * b[2] / nb) / (nb - 1.0);
+  const int l = threadIdx.x;
+  if (l < 12) {
+    const int side = l < 10 ? l / 5 : l - 10;
+    const double n = (double)(anti ? (side ? n_b : n_a) / 2 : (side ? n_b : n_a));
+    const double* s = tot + side * kEstSums;
+    if (l < 10) {
+      const double Z = side ? B.Z[0] : A.Z[0];
+      const double sum = s[2 * (l % 5)], sq = s[2 * (l % 5) + 1];
+      const double var = (sq - sum * sum / n) / (n - 1.0);
+      mean[l] = Z * (sum / n);
+      se[l] = Z * sqrt((var > 0.0 ? var : 0.0) / n);
+    } else {
+      const double Z = side ? B.Z[0] : A.Z[0];
+      cov[side] = 0.5 * Z * Z * ((s[10] - s[0] * s[2] / n) / (n - 1.0)) / n;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   shape_result r;
-  r.O_ab_from_a = Za * a1.mean();
-  r.O_ab_from_b = Zb * b1.mean();
-  const double se_xa = Za * sqrt(a1.var() / na), se_xb = Zb * sqrt(b1.var() / nb);
+  r.O_ab_from_a = mean[0];
+  r.O_ab_from_b = mean[5];
   r.O_ab = 0.5 * (r.O_ab_from_a + r.O_ab_from_b);
-  r.se_O_ab = 0.5 * sqrt(se_xa * se_xa + se_xb * se_xb);
-  r.O_aa = Za * a2.mean();
-  r.O_bb = Zb * b2.mean();
-  r.se_O_aa = Za * sqrt(a2.var() / na);
-  r.se_O_bb = Zb * sqrt(b2.var() / nb);
-  r.V_a = Za * a3.mean();
-  r.V_b = Zb * b3.mean();
-  r.se_V_a = Za * sqrt(a3.var() / na);
-  r.se_V_b = Zb * sqrt(b3.var() / nb);
-  r.Ofo_ab_is = 0.5 * (Za * a4.mean() + Zb * b4.mean());
-  r.Ofo_aa_is = Za * a5.mean();
-  r.Ofo_bb_is = Zb * b5.mean();
+  r.se_O_ab = 0.5 * sqrt(se[0] * se[0] + se[5] * se[5]);
+  r.O_aa = mean[1];
+  r.O_bb = mean[6];
+  r.se_O_aa = se[1];
+  r.se_O_bb = se[6];
+  r.V_a = mean[2];
+  r.V_b = mean[7];
+  r.se_V_a = se[2];
+  r.se_V_b = se[7];
+  r.Ofo_ab_is = 0.5 * (mean[3] + mean[8]);
+  r.Ofo_aa_is = mean[4];
+  r.Ofo_bb_is = mean[9];
   const double S = r.O_aa + r.O_bb, D = S - r.O_ab;
   r.T = r.O_ab / D;
-  r.se_T = fabs(S / (D * D)) * r.se_O_ab;
-  const double g_ab = S / (D * D), g_s = -r.O_ab / (D * D);
+  const double iD2 = 1.0 / (D * D);
+  const double g_ab = S * iD2, g_s = -r.O_ab * iD2;
+  r.se_T = fabs(g_ab) * r.se_O_ab;
   const double var_s = r.se_O_aa * r.se_O_aa + r.se_O_bb * r.se_O_bb;
-  const double cov = 0.5 * Za * Za * cov_a / na + 0.5 * Zb * Zb * cov_b / nb;
-  const double vt = g_ab * g_ab * r.se_O_ab * r.se_O_ab + g_s * g_s * var_s + 2.0 * g_ab * g_s * cov;
+  const double vt = g_ab * g_ab * r.se_O_ab * r.se_O_ab + g_s * g_s * var_s +
+                    2.0 * g_ab * g_s * (cov[0] + cov[1]);
   r.se_T_full = sqrt(vt > 0.0 ? vt : 0.0);
   r.n_a = n_a;
   r.n_b = n_b;
-  *out = r;
+  out->bad[0] = out->bad[1] = 0;
+  out->r = r;
 }
 
 // ---------------------------------------------------------------------------
@@ -890,19 +947,54 @@ hipError_t launch_fill_int(int* p, int n, int v, hipStream_t st) {
   return hipGetLastError();
 }
 
+hipError_t launch_prepare_pair(const MolsDev& inA, const Prepared& A, const MolsDev& inB,
+                               const Prepared& B, int* flag, hipStream_t st) {
+  hipLaunchKernelGGL(k_prepare_pair, dim3(1), dim3(2 * kWave), 0, st, inA, A, inB, B, flag);
+  return hipGetLastError();
+}
+
+// Terms per lane of the single-pair kernel: one while that still leaves at
+// most four workgroups per compute unit and side, then four, then eight in
+// two turns (which bounds the partial sums at 2,048 terms per block).
+struct EstShape {
+  int s, turns;
+  int per_block() const { return 256 * s * turns; }
+};
+static EstShape est_shape(int64_t n_units) {
+  if (n_units <= 256 * 1024) return {1, 1};
+  if (n_units <= 1024 * 1024) return {4, 1};
+  return {4, 2};
+}
+
 int est_blocks(int64_t n_units) {
-  return (int)((n_units + 256 * kEstSPT - 1) / (256 * kEstSPT));
+  const int per = est_shape(n_units).per_block();
+  return (int)((n_units + per - 1) / per);
+}
+
+template <int S>
+static void launch_est_partials(const Prepared& A, const Prepared& B, const int* offA,
+                                const int* offB, int64_t n_a, int64_t n_b, uint2 key, int anti,
+                                int turns, double* partials, int nblk, hipStream_t st) {
+  if (anti)
+    hipLaunchKernelGGL((k_est_partials<S, true>), dim3(nblk, 2), dim3(256), 0, st, A, B, n_a, n_b,
+                       key, turns, partials, nblk, offA, offB);
+  else
+    hipLaunchKernelGGL((k_est_partials<S, false>), dim3(nblk, 2), dim3(256), 0, st, A, B, n_a,
+                       n_b, key, turns, partials, nblk, offA, offB);
 }
 
 hipError_t launch_estimate(const Prepared& A, const Prepared& B, const int* offA,
                            const int* offB, int64_t n_a, int64_t n_b, uint2 key, int anti,
-                           double* partials, int nblk, shape_result* out_dev, hipStream_t st) {
-  hipLaunchKernelGGL(k_est_partials, dim3(nblk, 2), dim3(256), 0, st, A, B, n_a, n_b, key, anti,
-                     partials, nblk, offA, offB);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_est_finalize, dim3(1), dim3(256), 0, st, partials, nblk, A, B, n_a, n_b,
-                     anti, out_dev);
+                           double* partials, int nblk, EstOut* out, hipStream_t st) {
+  const EstShape e = est_shape((n_a > n_b ? n_a : n_b) / (anti ? 2 : 1));
+  if (e.s == 1)
+    launch_est_partials<1>(A, B, offA, offB, n_a, n_b, key, anti, e.turns, partials, nblk, st);
+  else
+    launch_est_partials<4>(A, B, offA, offB, n_a, n_b, key, anti, e.turns, partials, nblk, st);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(k_est_finalize, dim3(1), dim3(kEstParts * 32), 0, st, partials, nblk, A, B, n_a, n_b,
+                     anti, out);
   return hipGetLastError();
 }
 

@@ -218,10 +218,19 @@ hipError_t launch_prepare(const MolsDev& in, const Prepared& out, int* flag, int
                           hipStream_t st, const int* which = nullptr, int n_which = 0);
 hipError_t launch_flag_or(int* flag, const int* set_flag, hipStream_t st);
 hipError_t launch_fill_int(int* p, int n, int v, hipStream_t st);
+// Both one-molecule sets of a pair in one launch.
+hipError_t launch_prepare_pair(const MolsDev& inA, const Prepared& A, const MolsDev& inB,
+                               const Prepared& B, int* flag, hipStream_t st);
+// What a single-pair estimate leaves for the host: which molecules are invalid
+// (then no result), and the result.
+struct EstOut {
+  shape_result r;
+  int bad[2];
+};
 int est_blocks(int64_t n_units);
 hipError_t launch_estimate(const Prepared& A, const Prepared& B, const int* offA,
                            const int* offB, int64_t n_a, int64_t n_b, uint2 key, int anti,
-                           double* partials, int nblk, shape_result* out_dev, hipStream_t st);
+                           double* partials, int nblk, EstOut* out, hipStream_t st);
 hipError_t launch_query_cache(const Prepared& Q, const int* offQ, int64_t n, uint2 key, int anti,
                               float4* qs, float* qf2, hipStream_t st);
 // sampling steps of one prepared molecule (thresholds, Philox words,

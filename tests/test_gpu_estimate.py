@@ -69,6 +69,27 @@ def test_edge_cases(eng, n_a, n_b, na, nb, seed):
     _check(g, r, se_tol=1e-4 if min(n_a, n_b) > 2 else 1e-3)
 
 
+@pytest.mark.parametrize("n_a,n_b,anti", [
+    (262144, 257, False), (262145, 255, False),      # one term per lane up to 262,144
+    (1048576, 1023, False), (1049601, 2047, False),  # four terms per lane, one and two turns
+    (524290, 2050, True), (2097154, 1026, True),     # the same in antithetic pairs
+])
+def test_terms_per_lane(eng, n_a, n_b, anti):
+    """Sample counts on both sides of each change of the launch shape, and
+    partial blocks, against the oracle at the parity bar."""
+    a, b = molgen.molecule(79, 0, 5), molgen.molecule(79, 1, 3)
+    print(f"case: n_a={n_a} n_b={n_b} anti {anti}", flush=True)
+    eng.sampling(anti)
+    try:
+        g = eng.shape_estimate(eng.molecules(a, mol_id=[11]), eng.molecules(b, mol_id=[12]),
+                               n_a, n_b, seed=6)
+    finally:
+        eng.sampling(False)
+    r = O.estimate(oracle_mol(O, a), oracle_mol(O, b), n_a, n_b, seed=6, id_a=11, id_b=12,
+                   antithetic=anti)
+    _check(g, r)
+
+
 def test_self_pair_is_exactly_one(eng):
     a, _ = cases.config0()
     A = eng.molecules(a, mol_id=[5])
