@@ -1210,12 +1210,8 @@ int shape_fo_starts(shape_ctx* c, const shape_mols* A, const shape_mols* B, int3
     if (n_random < 0 || n_random > 1024) return fail(c, SHAPE_E_RANGE, "n_random outside [0, 1024]");
     if (!pose) return fail(c, SHAPE_E_INVAL, "pose is NULL");
     if ((rc = set_device(c))) return rc;
-    hipStream_t st = (hipStream_t)stream;
-    shape::Prepared PA, PB;
-    if ((rc = prepare(c, A, true, st, &PA))) return rc;
-    if ((rc = prepare(c, B, false, st, &PB))) return rc;
-    HIP_TRY(c, shape::launch_fo_starts(mols_dev(A), mols_dev(B), PA.bad, PB.bad, n_random,
-                                       key_of(seed), pose, st),
+    HIP_TRY(c, shape::launch_fo_starts(mols_dev(A), mols_dev(B), n_random, key_of(seed), c->flag,
+                                       pose, (hipStream_t)stream),
             "alignment starts kernel");
     return SHAPE_OK;
   } catch (...) {
@@ -1245,9 +1241,6 @@ int shape_fo_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32
     if (shape::fo_align_pair_major(A->max_atoms, B->max_atoms, n_starts) &&
         (rc = work_order_slot(c, B->n_mols, kOrderFoAlignPerCu, &wo)))
       return rc;
-    shape::Prepared PA, PB;
-    if ((rc = prepare(c, A, true, st, &PA))) return rc;
-    if ((rc = prepare(c, B, false, st, &PB))) return rc;
     if (wo.order) {
       // per step and start: one pass over B's atoms (A's atoms sit on the
       // lanes) and the rotation, sums and Adam step, worth about 4 atoms
@@ -1262,8 +1255,8 @@ int shape_fo_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32
       HIP_TRY(c, shape::launch_work_order(o, wo.order, wo.work, st), "launch order kernels");
     }
     KernelTimer timer(c, st);
-    HIP_TRY(c, shape::launch_fo_align(mols_dev(A), mols_dev(B), PA.bad, PB.bad, n_starts,
-                                      n_steps, lr, pose, T, grad, st, wo.order),
+    HIP_TRY(c, shape::launch_fo_align(mols_dev(A), mols_dev(B), n_starts, n_steps, lr, c->flag,
+                                      pose, T, grad, st, wo.order),
             "first-order alignment kernel");
     timer.stop();
     return SHAPE_OK;

@@ -21,7 +21,7 @@
 namespace shape {
 
 // ---------------------------------------------------------------------------
-// Starts: one thread per pair, FP64.
+// Starts, FP64.
 // ---------------------------------------------------------------------------
 
 // Symmetric 3x3 eigen-decomposition by cyclic Jacobi rotations: eigenvalues
@@ -29,9 +29,19 @@ namespace shape {
 __device__ void jacobi3(double a[3][3], double V[9]) {
   double U[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
   for (int sweep = 0; sweep < 60; ++sweep) {
+    // every remaining rotation is below 10^-30 (apart from exactly degenerate
+    // axes, which go on): no component of U changes at FP64.  Rounding leaves
+    // off-diagonals of 10^-16 of the rotated terms, so waiting for them to
+    // vanish took about twenty sweeps instead of six.
+    if (fabs(a[0][1]) <= 1e-30 * fabs(a[1][1] - a[0][0]) &&
+        fabs(a[0][2]) <= 1e-30 * fabs(a[2][2] - a[0][0]) &&
+        fabs(a[1][2]) <= 1e-30 * fabs(a[2][2] - a[1][1]))
+      break;
     const double off = fabs(a[0][1]) + fabs(a[0][2]) + fabs(a[1][2]);
     if (off < 1e-300) break;
+#pragma unroll
     for (int p = 0; p < 2; ++p)
+#pragma unroll
       for (int q = p + 1; q < 3; ++q) {
         if (a[p][q] == 0.0) continue;
         const double theta = (a[q][q] - a[p][p]) / (2.0 * a[p][q]);
@@ -54,50 +64,67 @@ __device__ void jacobi3(double a[3][3], double V[9]) {
         }
       }
   }
-  int idx[3] = {0, 1, 2};
+  // columns by descending eigenvalue (registers only: no indexed arrays)
+  double ev[3] = {a[0][0], a[1][1], a[2][2]};
+#pragma unroll
   for (int i = 0; i < 3; ++i)
-    for (int j = i + 1; j < 3; ++j)
-      if (a[idx[j]][idx[j]] > a[idx[i]][idx[i]]) {
-        const int t = idx[i];
-        idx[i] = idx[j];
-        idx[j] = t;
+#pragma unroll
+    for (int j = i + 1; j < 3; ++j) {
+      const bool swap = ev[j] > ev[i];
+      const double e = ev[i];
+      ev[i] = swap ? ev[j] : e;
+      ev[j] = swap ? e : ev[j];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const double u = U[r][i];
+        U[r][i] = swap ? U[r][j] : u;
+        U[r][j] = swap ? u : U[r][j];
       }
+    }
+#pragma unroll
   for (int c = 0; c < 3; ++c)
-    for (int r = 0; r < 3; ++r) V[3 * r + c] = U[r][idx[c]];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) V[3 * r + c] = U[r][c];
 }
 
 // Mixture mean and principal axes of one molecule (weights v_i / Z,
-// v_i = (pi/alpha_i)^(3/2)); axes as columns of U, descending variance, the
-// largest-magnitude component of the first two positive, U right-handed.
-__device__ void principal_frame(const float* xyz, const float* alpha, int n, double mu[3],
+// v_i = (pi/alpha_i)^(3/2), given as t = pi/alpha_i and its root); axes as
+// columns of U, descending variance, the largest-magnitude component of the
+// first two positive, U right-handed.
+__device__ void principal_frame(const float* xyz, const double2* t_root, int n, double mu[3],
                                 double U[9]) {
   double Z = 0.0, m0 = 0.0, m1 = 0.0, m2 = 0.0;
   for (int i = 0; i < n; ++i) {
-    const double t = M_PI / (double)alpha[i];
-    const double v = t * sqrt(t);
-    Z += v;
-    m0 += v * (double)xyz[3 * i];
-    m1 += v * (double)xyz[3 * i + 1];
-    m2 += v * (double)xyz[3 * i + 2];
+    const double2 t = t_root[i];
+    const double v = t.x * t.y;
+    Z = fma(t.x, t.y, Z);
+    m0 = fma(v, (double)xyz[3 * i], m0);
+    m1 = fma(v, (double)xyz[3 * i + 1], m1);
+    m2 = fma(v, (double)xyz[3 * i + 2], m2);
   }
   mu[0] = m0 / Z;
   mu[1] = m1 / Z;
   mu[2] = m2 / Z;
   double C[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
   for (int i = 0; i < n; ++i) {
-    const double t = M_PI / (double)alpha[i];
-    const double w = t * sqrt(t) / Z;
+    const double2 t = t_root[i];
+    const double w = t.x * t.y / Z;
     const double x[3] = {(double)xyz[3 * i] - mu[0], (double)xyz[3 * i + 1] - mu[1],
                          (double)xyz[3 * i + 2] - mu[2]};
+#pragma unroll
     for (int r = 0; r < 3; ++r)
+#pragma unroll
       for (int c = 0; c < 3; ++c) C[r][c] += w * x[r] * x[c];
   }
   jacobi3(C, U);
+#pragma unroll
   for (int c = 0; c < 2; ++c) {
-    int big = 0;
+    double big = U[c];
+#pragma unroll
     for (int r = 1; r < 3; ++r)
-      if (fabs(U[3 * r + c]) > fabs(U[3 * big + c])) big = r;
-    if (U[3 * big + c] < 0)
+      if (fabs(U[3 * r + c]) > fabs(big)) big = U[3 * r + c];
+    if (big < 0)
+#pragma unroll
       for (int r = 0; r < 3; ++r) U[3 * r + c] = -U[3 * r + c];
   }
   U[2] = U[3] * U[7] - U[6] * U[4];
@@ -133,33 +160,100 @@ __device__ void quat_of_rot(const double R[9], double q[4]) {
   q[0] = sg * w; q[1] = sg * x; q[2] = sg * y; q[3] = sg * z;
 }
 
-__global__ void k_fo_starts(MolsDev A, MolsDev B, const int* __restrict__ badA,
-                            const int* __restrict__ badB, int n_random, uint2 key,
-                            float* __restrict__ pose) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= B.n_mols) return;
+// Whether a molecule is valid, as in the preparation: offsets in range, 1 to
+// max_atoms atoms (here), and every alpha > 0 and every value finite.
+__device__ __forceinline__ bool fo_range_ok(const MolsDev& M, int a0, int a1) {
+  return a0 >= 0 && (int64_t)a1 <= M.n_atoms && a1 - a0 >= 1 && a1 - a0 <= M.max_atoms;
+}
+__device__ __forceinline__ bool fo_atom_ok(const float4& c) {
+  return c.w > 0.0f && isfinite(c.w) && isfinite(c.x) && isfinite(c.y) && isfinite(c.z);
+}
+__device__ __forceinline__ float4 fo_atom(const MolsDev& M, int i) {
+  return make_float4(M.xyz[3 * (int64_t)i], M.xyz[3 * (int64_t)i + 1], M.xyz[3 * (int64_t)i + 2],
+                     M.alpha[i]);
+}
+
+// Eight lanes per pair: even lanes take A's frame, odd lanes B's (the four
+// lanes of a molecule share its weights' roots and divisions through LDS and
+// then form the same sums in atom order), and each lane takes every eighth
+// start.  A chain of FP64 latencies (sums, Jacobi, quaternions) whatever the
+// number of pairs: 10,000 pairs 154 -> 28 us (one lane per pair took two
+// frames and seven starts in turn, with arrays in scratch memory).
+constexpr int kStartLanes = 8;
+constexpr int kStartPairs = kWave / kStartLanes;
+__host__ __device__ inline size_t fo_starts_lds_bytes(int max_atoms) {
+  return (size_t)2 * kStartPairs * max_atoms * (sizeof(double2) + 3 * sizeof(float));
+}
+
+__global__ __launch_bounds__(kWave) void k_fo_starts(MolsDev A, MolsDev B, int n_random, uint2 key,
+                                                     int* __restrict__ flag,
+                                                     float* __restrict__ pose) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x, l = lane % kStartLanes, half = l & 1;
+  const int max_n = A.max_atoms > B.max_atoms ? A.max_atoms : B.max_atoms;
+  const int set = 2 * (lane / kStartLanes) + half;
+  double2* t_root = reinterpret_cast<double2*>(smem) + (size_t)set * max_n;
+  float* xyz = reinterpret_cast<float*>(reinterpret_cast<double2*>(smem) +
+                                        (size_t)2 * kStartPairs * max_n) +
+               (size_t)set * 3 * max_n;
+  const int p = blockIdx.x * kStartPairs + lane / kStartLanes;
+  const bool live = p < B.n_mols;
+  int n = 0;
+  bool bad = false;
+  if (live) {
+    const MolsDev& M = half ? B : A;
+    const int m = half ? p : (A.n_mols == 1 ? 0 : p);
+    const int a0 = M.off[m], a1 = M.off[m + 1];
+    bad = !fo_range_ok(M, a0, a1);
+    n = bad ? 0 : a1 - a0;
+    for (int i = l >> 1; i < n; i += kStartLanes / 2) {
+      const float4 c = fo_atom(M, a0 + i);
+      if (!fo_atom_ok(c)) bad = true;
+      const double t = M_PI / (double)c.w;
+      t_root[i] = make_double2(t, sqrt(t));
+      xyz[3 * i] = c.x;
+      xyz[3 * i + 1] = c.y;
+      xyz[3 * i + 2] = c.z;
+    }
+  }
+  const uint64_t mine = 0xFFull << (lane & ~(kStartLanes - 1));
+  bad = (__ballot(bad) & mine) != 0;
+  wave_lds_sync();
+  double mu[3] = {0, 0, 0}, U[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
+  if (live && !bad) principal_frame(xyz, t_root, n, mu, U);
+  double muA[3], UA[9], muB[3], UB[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    UA[k] = __shfl(U[k], lane & ~1, kWave);
+    UB[k] = __shfl(U[k], lane | 1, kWave);
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    muA[k] = __shfl(mu[k], lane & ~1, kWave);
+    muB[k] = __shfl(mu[k], lane | 1, kWave);
+  }
+  if (!live) return;
   const int n_starts = 5 + n_random;
   float* out = pose + (size_t)p * n_starts * 7;
-  const int ma = A.n_mols == 1 ? 0 : p;
-  if (badA[ma] != 0 || badB[p] != 0) {
-    for (int c = 0; c < n_starts * 7; ++c) out[c] = __builtin_nanf("");
+  if (bad) {
+    for (int c = l; c < n_starts * 7; c += kStartLanes) out[c] = __builtin_nanf("");
+    if (l == 0) atomicOr(flag, 1);
     return;
   }
-  const int a0 = A.off[ma], na = A.off[ma + 1] - a0;
-  const int b0 = B.off[p], nb = B.off[p + 1] - b0;
-  out[0] = 1.f;
-  for (int c = 1; c < 7; ++c) out[c] = 0.f;
-  double muA[3], UA[9], muB[3], UB[9];
-  principal_frame(A.xyz + 3 * (size_t)a0, A.alpha + a0, na, muA, UA);
-  principal_frame(B.xyz + 3 * (size_t)b0, B.alpha + b0, nb, muB, UB);
-  const double Ds[4][3] = {{1, 1, 1}, {1, -1, -1}, {-1, 1, -1}, {-1, -1, 1}};
-  for (int s = 0; s < 4 + n_random; ++s) {
+  if (l < 7) out[l] = l == 0 ? 1.f : 0.f;
+  for (int s = l; s < 4 + n_random; s += kStartLanes) {
     double R[9];
     if (s < 4) {
+      // the proper sign matrices diag(1, 1, 1), (1, -1, -1), (-1, 1, -1), (-1, -1, 1)
+      const double D[3] = {s < 2 ? 1.0 : -1.0, s == 0 || s == 2 ? 1.0 : -1.0,
+                           s == 0 || s == 3 ? 1.0 : -1.0};
+#pragma unroll
       for (int r = 0; r < 3; ++r)
+#pragma unroll
         for (int c = 0; c < 3; ++c) {
           double acc = 0.0;
-          for (int k = 0; k < 3; ++k) acc += UA[3 * r + k] * Ds[s][k] * UB[3 * c + k];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) acc += UA[3 * r + k] * D[k] * UB[3 * c + k];
           R[3 * r + c] = acc;
         }
     } else {
@@ -199,8 +293,7 @@ __host__ __device__ inline int fo_rows_stride(int max_b) {
 
 struct FoAlignArgs {
   MolsDev A, B;
-  const int* badA;  // invalid-molecule flags of the prepared sets
-  const int* badB;
+  int* flag;        // raised on invalid data
   int n_starts, n_steps;
   float lr;
   float* pose;  // [pairs][starts][7], read and written
@@ -208,6 +301,28 @@ struct FoAlignArgs {
   float* grad;  // [pairs][starts][7] at the final pose, or nullptr
   const int* order;  // optional launch order of the row layout: block x takes pair order[x]
 };
+
+// Both molecules into LDS (x, y, z, alpha) by the threads tid of n; whether
+// the pair is valid, the same in every thread (any: an OR over the group,
+// after which the staged atoms are visible to it if it is a barrier).
+template <class Any>
+__device__ __forceinline__ bool fo_stage(const FoAlignArgs& a, bool ok, float4* sA, int a0, int na,
+                                         float4* sB, int b0, int nb, int tid, int n, Any any) {
+  bool bad = !ok;  // then the counts are not trusted and nothing is read
+  if (ok) {
+    for (int i = tid; i < na; i += n) {
+      const float4 c = fo_atom(a.A, a0 + i);
+      if (!fo_atom_ok(c)) bad = true;
+      sA[i] = c;
+    }
+    for (int j = tid; j < nb; j += n) {
+      const float4 c = fo_atom(a.B, b0 + j);
+      if (!fo_atom_ok(c)) bad = true;
+      sB[j] = c;
+    }
+  }
+  return !any(bad);
+}
 
 // One pass over the N_A x N_B atom pairs spread over the lanes (the row of
 // flat index p stepped incrementally, as in the cross-overlap kernel):
@@ -344,25 +459,21 @@ __global__ __launch_bounds__(64) void k_fo_align(FoAlignArgs a) {
   const int item = blockIdx.x;  // pair * n_starts + start
   const int pair = item / a.n_starts;
   const int ma = a.A.n_mols == 1 ? 0 : pair;
-  if (a.badA[ma] != 0 || a.badB[pair] != 0) {
+  const int a0 = a.A.off[ma], a1 = a.A.off[ma + 1], na = a1 - a0;
+  const int b0 = a.B.off[pair], b_end = a.B.off[pair + 1], nb = b_end - b0;
+  float4* sA = reinterpret_cast<float4*>(smem);  // [max_a] x, y, z, alpha
+  float4* sB = sA + a.A.max_atoms;               // [max_b] B as given
+  float4* sM = sB + a.B.max_atoms;               // [max_b] B moved
+  const bool ok = fo_range_ok(a.A, a0, a1) && fo_range_ok(a.B, b0, b_end);
+  if (!fo_stage(a, ok, sA, a0, na, sB, b0, nb, lane, kWave, [](bool b) { return __any(b); })) {
     if (lane == 0) {
       a.T[item] = __builtin_nanf("");
       if (a.grad)
         for (int c = 0; c < 7; ++c) a.grad[(size_t)item * 7 + c] = __builtin_nanf("");
+      atomicOr(a.flag, 1);
     }
     return;
   }
-  const int a0 = a.A.off[ma], na = a.A.off[ma + 1] - a0;
-  const int b0 = a.B.off[pair], nb = a.B.off[pair + 1] - b0;
-  float4* sA = reinterpret_cast<float4*>(smem);  // [max_a] x, y, z, alpha
-  float4* sB = sA + a.A.max_atoms;               // [max_b] B as given
-  float4* sM = sB + a.B.max_atoms;               // [max_b] B moved
-  for (int i = lane; i < na; i += kWave)
-    sA[i] = make_float4(a.A.xyz[3 * (a0 + i)], a.A.xyz[3 * (a0 + i) + 1],
-                        a.A.xyz[3 * (a0 + i) + 2], a.A.alpha[a0 + i]);
-  for (int j = lane; j < nb; j += kWave)
-    sB[j] = make_float4(a.B.xyz[3 * (b0 + j)], a.B.xyz[3 * (b0 + j) + 1],
-                        a.B.xyz[3 * (b0 + j) + 2], a.B.alpha[b0 + j]);
   wave_lds_sync();
   const float S = fo_self(sA, na) + fo_self(sB, nb);  // O_AA + O_BB
   FoTermConsts tc;
@@ -497,29 +608,25 @@ void k_fo_align_rows(FoAlignArgs a) {
   const int s = live ? s_raw : a.n_starts - 1;  // spare rows repeat the last start
   const size_t item = (size_t)pair * a.n_starts + s;
   const int ma = a.A.n_mols == 1 ? 0 : pair;
-  if (a.badA[ma] != 0 || a.badB[pair] != 0) {
-    if (live && l16 == 0) {
-      a.T[item] = __builtin_nanf("");
-      if (a.grad)
-        for (int c = 0; c < 7; ++c) a.grad[item * 7 + c] = __builtin_nanf("");
-    }
-    return;
-  }
-  const int a0 = a.A.off[ma], na = a.A.off[ma + 1] - a0;
-  const int b0 = a.B.off[pair], nb = a.B.off[pair + 1] - b0;
+  const int a0 = a.A.off[ma], a1 = a.A.off[ma + 1], na = a1 - a0;
+  const int b0 = a.B.off[pair], b_end = a.B.off[pair + 1], nb = b_end - b0;
   const int stride = fo_rows_stride(a.B.max_atoms);
   const int n_rows = (int)(blockDim.x / 16);
   float4* sA = reinterpret_cast<float4*>(smem);  // [max_a] x, y, z, alpha
   float4* sB = sA + a.A.max_atoms;               // [max_b] B as given
   float4* sM = sB + a.B.max_atoms;               // [rows][stride] B moved, per start
   float2* tab = reinterpret_cast<float2*>(sM + (size_t)n_rows * stride);  // [max_b][RA16]
-  for (int i = tid; i < na; i += blockDim.x)
-    sA[i] = make_float4(a.A.xyz[3 * (a0 + i)], a.A.xyz[3 * (a0 + i) + 1],
-                        a.A.xyz[3 * (a0 + i) + 2], a.A.alpha[a0 + i]);
-  for (int j = tid; j < nb; j += blockDim.x)
-    sB[j] = make_float4(a.B.xyz[3 * (b0 + j)], a.B.xyz[3 * (b0 + j) + 1],
-                        a.B.xyz[3 * (b0 + j) + 2], a.B.alpha[b0 + j]);
-  __syncthreads();
+  const bool ok = fo_range_ok(a.A, a0, a1) && fo_range_ok(a.B, b0, b_end);
+  if (!fo_stage(a, ok, sA, a0, na, sB, b0, nb, tid, blockDim.x,
+                [](bool b) { return __syncthreads_or(b) != 0; })) {
+    if (live && l16 == 0) {
+      a.T[item] = __builtin_nanf("");
+      if (a.grad)
+        for (int c = 0; c < 7; ++c) a.grad[item * 7 + c] = __builtin_nanf("");
+      atomicOr(a.flag, 1);
+    }
+    return;
+  }
   for (int e = tid; e < nb * RA16; e += blockDim.x) {
     const int j = e / RA16, i = e % RA16;
     float kk = 0.f, pre = 0.f, f2, lq = -INFINITY;
@@ -770,11 +877,11 @@ __global__ __launch_bounds__(64) void k_apply_pose(MolsDev M, const float* __res
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, const int* badA,
-                            const int* badB, int n_random, uint2 key, float* pose,
-                            hipStream_t st) {
-  hipLaunchKernelGGL(k_fo_starts, dim3((B.n_mols + 63) / 64), dim3(64), 0, st, A, B, badA, badB,
-                     n_random, key, pose);
+hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, int n_random, uint2 key,
+                            int* flag, float* pose, hipStream_t st) {
+  const int max_atoms = A.max_atoms > B.max_atoms ? A.max_atoms : B.max_atoms;
+  hipLaunchKernelGGL(k_fo_starts, dim3((B.n_mols + kStartPairs - 1) / kStartPairs), dim3(kWave),
+                     fo_starts_lds_bytes(max_atoms), st, A, B, n_random, key, flag, pose);
   return hipGetLastError();
 }
 
@@ -811,10 +918,10 @@ static void launch_fo_rows_t(const FoAlignArgs& a, size_t lds, hipStream_t st) {
                      dim3(rows / 4 * kWave), lds, st, a);
 }
 
-hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, const int* badA, const int* badB,
-                           int n_starts, int n_steps, float lr, float* pose, float* T,
-                           float* grad, hipStream_t st, const int* order) {
-  FoAlignArgs a{A, B, badA, badB, n_starts, n_steps, lr, pose, T, grad, nullptr};
+hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, int n_starts, int n_steps,
+                           float lr, int* flag, float* pose, float* T, float* grad,
+                           hipStream_t st, const int* order) {
+  FoAlignArgs a{A, B, flag, n_starts, n_steps, lr, pose, T, grad, nullptr};
   const size_t lds = fo_rows_lds_bytes(A.max_atoms, B.max_atoms, n_starts);
   if (lds > 0) {
     a.order = order;

@@ -161,15 +161,14 @@ hipError_t launch_grid_box(const float* xa, int na, const float* xb, int nb, dou
 hipError_t launch_grid(const float* xa, const float* aa, int na, const float* xb,
                        const float* ab, int nb, const GridDims& g, double* tables, double* part,
                        double* out, hipStream_t st);
-// hybrid pipeline (first-order alignment)
-hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, const int* badA,
-                            const int* badB, int n_random, uint2 key, float* pose,
-                            hipStream_t st);
+// hybrid pipeline (first-order alignment); the caller's arrays are read
+// directly, invalid molecules give NaN and raise *flag
+hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, int n_random, uint2 key,
+                            int* flag, float* pose, hipStream_t st);
 size_t fo_align_lds_bytes(int max_a, int max_b);
-hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, const int* badA, const int* badB,
-                           int n_starts, int n_steps, float lr, float* pose, float* T,
-                           float* grad, hipStream_t st,
-                           const int* order = nullptr);
+hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, int n_starts, int n_steps,
+                           float lr, int* flag, float* pose, float* T, float* grad,
+                           hipStream_t st, const int* order = nullptr);
 // whether launch_fo_align runs one workgroup per pair (the row layout)
 bool fo_align_pair_major(int max_a, int max_b, int n_starts);
 hipError_t launch_best_pose(const float* T, const float* pose, int n_pairs, int n_starts,

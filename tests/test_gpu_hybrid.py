@@ -72,6 +72,33 @@ def test_starts_match_oracle(eng, pairs):
             assert np.abs(st[p, s, 4:] - ref[s, 4:]).max() <= 1e-4, (p, s)
 
 
+@pytest.mark.parametrize("n_pairs, n_random, atoms", [(1, 0, (4, 9)), (7, 4, (5, 40)),
+                                                      (9, 5, (30, 70)), (17, 13, (200, 256))])
+def test_starts_over_lane_groups(eng, n_pairs, n_random, atoms):
+    """Eight lanes per pair: pair counts around a wave's eight, more and fewer
+    starts than lanes, the largest molecules, one invalid molecule."""
+    A = molgen.library(51, n_pairs, *atoms, workers=1)
+    B = molgen.library(52, n_pairs, *atoms, workers=1)
+    dA, dB = eng.molecules(A), eng.molecules(B)
+    bad = n_pairs - 1 if n_pairs > 1 else -1
+    if bad >= 0:
+        dB.alpha[int(B.offsets[bad])] = -1.0
+    print(f"case: {n_pairs} pairs, {n_random} random starts, {atoms} atoms", flush=True)
+    st = eng.shape_fo_starts(dA, dB, n_random=n_random, seed=9).cpu().numpy()
+    assert st.shape == (n_pairs, 5 + n_random, 7)
+    for p in range(n_pairs):
+        if p == bad:
+            assert np.all(np.isnan(st[p]))
+            with pytest.raises(ShapeError):
+                eng.shape_check_data()
+            continue
+        ref = O.fo_starts(oracle_mol(O, A.mol(p)), oracle_mol(O, B.mol(p)), pair_id=p,
+                          n_random=n_random, seed=9)
+        for s in range(5 + n_random):
+            assert np.abs(_rot(st[p, s, :4]) - _rot(ref[s, :4])).max() <= 1e-5, (p, s)
+            assert np.abs(st[p, s, 4:] - ref[s, 4:]).max() <= 1e-4, (p, s)
+
+
 def test_shared_query_broadcasts(eng, pairs):
     """A single A molecule serves every pair, as the same molecule repeated."""
     _, B = pairs
