@@ -792,9 +792,9 @@ int shape_screen(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
     KernelTimer timer(c, st);
     // a variant set by the caller runs as set; the tuner's choice is for
     // screens that take one wave per pair
-    const bool split = !c->variant_set && shape::screen_splits(a, c->n_cu);
-    HIP_TRY(c, split ? shape::launch_screen_split(a, st)
-                     : shape::launch_screen(a, screen_variant_of(c), st),
+    const int variant = screen_variant_of(c);
+    HIP_TRY(c, c->variant_set ? shape::launch_screen(a, variant, st)
+                              : shape::launch_screen_auto(a, variant, c->n_cu, st),
             "screen kernel");
     timer.stop();
     return SHAPE_OK;

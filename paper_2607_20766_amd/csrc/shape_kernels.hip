@@ -421,10 +421,13 @@ __global__ __launch_bounds__(256) void k_query_cache(Prepared Qp, const int* __r
 }
 
 // ---------------------------------------------------------------------------
-// Screening kernel: one single-wave workgroup per (query, library) pair, so
-// the pair index comes from blockIdx and is uniform by construction (no
-// cross-lane broadcast); the hardware dispatcher balances pairs of uneven
-// size.  Pairs are renumbered so that each XCD screens tiles of consecutive
+// Screening kernel: one workgroup per (query, library) pair, so the pair index
+// comes from blockIdx and is uniform by construction (no cross-lane
+// broadcast); the hardware dispatcher balances pairs of uneven size.  The
+// workgroup is a single wave, or kRounds waves that each take one of kRounds
+// consecutive rounds and then add the rounds' totals, with the stop test after
+// each, in turn (screen_rounds: where single waves would leave the chip short
+// of waves; the same bits).  Pairs are renumbered so that each XCD screens tiles of consecutive
 // library molecules (xcd_chunk).  Per round, `round_side` samples on each side:
 //   side A (query samples, from the cache): f1 = w_A u_B, f2 = w_A u_A
 //   side B (library samples, drawn here):   f1 = w_B u_A, f2 = w_B u_B
@@ -536,6 +539,11 @@ __device__ __forceinline__ void screen_write_nan(const ScreenArgs& a, int p) {
     if (a.O_bb) a.O_bb[p] = nanv;
     if (a.n_used) a.n_used[p] = 0;
   }
+}
+
+// Samples per side after which a pair stops at the latest.
+__device__ __forceinline__ int screen_limit(const ScreenArgs& a) {
+  return (int)(a.mode == SHAPE_SCREEN_ADAPTIVE ? a.cap_pair / 2 : a.n_fixed);
 }
 
 // The kernel's arguments, read again from the kernel-argument segment: what
@@ -681,17 +689,21 @@ __device__ __forceinline__ void screen_draw(const ScreenLds& lds, int nb, uint32
 // among the other instructions (76 registers), 7.15 ms with them grouped, 7.07
 // ms with the drawing steps of a lane's points grouped too, 7.00 ms with two
 // atoms per LDS word, no remainder loop and three-way XORs (5.67e9 -> 5.52e9
-// instructions); fixed 4,096 per side, 7,003 molecules: 0.60 -> 0.52 ms.  Of
+// instructions); fixed 4,096 per side, 7,003 molecules: 0.60 -> 0.52 ms, and
+// 0.49 ms with four rounds of a pair at a time (screen_rounds).  Of
 // 4-cycle issue slots left by the exponentials, 1.62 of 2 hold an instruction.
-template <int kSA, int kSB, bool kAnti>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSA >= 8 ? 4 : 8)))
+template <int kSA, int kSB, bool kAnti, int kRounds>
+__global__ __launch_bounds__(kRounds * kWave)
+__attribute__((amdgpu_waves_per_eu(kSA >= 8 ? 4 : 8)))
 void k_screen(ScreenArgs a) {
   // No implicit multiply-add contraction: the fused operations are written
   // out, so every tile variant rounds identically.
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ float sTot[2][kRounds][8];  // the rounds' totals (two sets: one barrier per pass)
   const ScreenLds lds(smem, a.max_q, a.max_b);
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = kRounds == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   // grid = n_pairs; a launch order, when given, is a permutation of the pairs
   const int p = a.order ? a.order[blockIdx.x] : xcd_chunk(blockIdx.x, gridDim.x);
   if (p < 0 || p >= a.n_pairs) return;
@@ -709,53 +721,72 @@ void k_screen(ScreenArgs a) {
   const bool ragged = per_lane % kSA != 0 || per_lane % kSB != 0;
   RoundSums S;
   int64_t n_side = 0;
+  int buf = 0;
   for (;;) {
     SideSums<kAnti> A, B;
-    // side A: query samples from the cache (query frame), partner = library
-    for (int t = 0; t < per_lane; t += kSA) {
-      float rx[kSA], ry[kSA], rz[kSA], r2[kSA], w[kSA], f2[kSA], q[kSA];
+    const int n0 = (int)n_side + wave * rs;  // this wave's round, if the pair has it
+    if (kRounds == 1 || n0 < screen_limit(screen_args_again())) {
+      // side A: query samples from the cache (query frame), partner = library
+      for (int t = 0; t < per_lane; t += kSA) {
+        float rx[kSA], ry[kSA], rz[kSA], r2[kSA], w[kSA], f2[kSA], q[kSA];
 #pragma unroll
-      for (int s = 0; s < kSA; ++s) {
-        const int i = (t + s) < per_lane ? t + s : t;
-        const int k = kAnti ? (int)n_side + 2 * lane + 2 * kWave * (i >> 1) + (i & 1)
-                            : (int)n_side + lane + kWave * i;
-        const float4 c = a.qs[k];
-        rx[s] = c.x; ry[s] = c.y; rz[s] = c.z; w[s] = c.w;
-        r2[s] = norm2(c.x, c.y, c.z);
-        f2[s] = a.qf2[k];
-        q[s] = 1.0f;
+        for (int s = 0; s < kSA; ++s) {
+          const int i = (t + s) < per_lane ? t + s : t;
+          const int k = kAnti ? n0 + 2 * lane + 2 * kWave * (i >> 1) + (i & 1)
+                              : n0 + lane + kWave * i;
+          const float4 c = a.qs[k];
+          rx[s] = c.x; ry[s] = c.y; rz[s] = c.z; w[s] = c.w;
+          r2[s] = norm2(c.x, c.y, c.z);
+          f2[s] = a.qf2[k];
+          q[s] = 1.0f;
+        }
+        eval_union_x2<kSA>(lds.BA, nb, rx, ry, rz, r2, q);
+#pragma unroll
+        for (int s = 0; s < kSA; ++s) {
+          if (ragged && t + s >= per_lane) w[s] = f2[s] = 0.0f;  // a slot past the round's last
+          A.term(t + s, w[s] * (1.0f - q[s]), f2[s], 1.0f);
+        }
       }
-      eval_union_x2<kSA>(lds.BA, nb, rx, ry, rz, r2, q);
+      // side B: library samples drawn here (library frame), partner = query
+      for (int t = 0; t < per_lane; t += kSB) {
+        float rx[kSB], ry[kSB], rz[kSB], r2[kSB], mb[kSB], qb[kSB], qa[kSB];
+        screen_draw<kSB, kAnti>(lds, nb, idb, (uint32_t)n0, t, per_lane, a.key, rx, ry, rz);
 #pragma unroll
-      for (int s = 0; s < kSA; ++s) {
-        if (ragged && t + s >= per_lane) w[s] = f2[s] = 0.0f;  // a slot past the round's last
-        A.term(t + s, w[s] * (1.0f - q[s]), f2[s], 1.0f);
+        for (int s = 0; s < kSB; ++s) {
+          r2[s] = norm2(rx[s], ry[s], rz[s]);
+          mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
+        }
+        eval_density_x2<kSB>(lds.BB, nb, rx, ry, rz, r2, mb, qb);
+        eval_union_x2<kSB>(lds.AB, nq, rx, ry, rz, r2, qa);
+#pragma unroll
+        for (int s = 0; s < kSB; ++s) {
+          const float ub = 1.0f - qb[s];
+          float w = bounded_weight(ub, mb[s]);
+          if (ragged && t + s >= per_lane) w = 0.0f;
+          B.term(t + s, w * (1.0f - qa[s]), w, ub);
+        }
       }
     }
-    // side B: library samples drawn here (library frame), partner = query
-    for (int t = 0; t < per_lane; t += kSB) {
-      float rx[kSB], ry[kSB], rz[kSB], r2[kSB], mb[kSB], qb[kSB], qa[kSB];
-      screen_draw<kSB, kAnti>(lds, nb, idb, (uint32_t)n_side, t, per_lane, a.key, rx, ry, rz);
-#pragma unroll
-      for (int s = 0; s < kSB; ++s) {
-        r2[s] = norm2(rx[s], ry[s], rz[s]);
-        mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
-      }
-      eval_density_x2<kSB>(lds.BB, nb, rx, ry, rz, r2, mb, qb);
-      eval_union_x2<kSB>(lds.AB, nq, rx, ry, rz, r2, qa);
-#pragma unroll
-      for (int s = 0; s < kSB; ++s) {
-        const float ub = 1.0f - qb[s];
-        float w = bounded_weight(ub, mb[s]);
-        if (ragged && t + s >= per_lane) w = 0.0f;
-        B.term(t + s, w * (1.0f - qa[s]), w, ub);
-      }
-    }
-    S.add(RoundSums::totals(A.f, B.f));
-    n_side += rs;
+    const float v = RoundSums::totals(A.f, B.f);
     const ScreenArgs& r = screen_args_again();
-    const bool stop = screen_stops(r, S, n_side, r.n_start ? (int64_t)r.n_start[p] : 0, kAnti,
-                                   r.Q.Z[0], r.L.Z[m]);
+    bool stop = false;
+    if constexpr (kRounds == 1) {
+      S.add(v);
+      n_side += rs;
+      stop = screen_stops(r, S, n_side, r.n_start ? (int64_t)r.n_start[p] : 0, kAnti, r.Q.Z[0],
+                          r.L.Z[m]);
+    } else {
+      if (lane < 6) sTot[buf][wave][lane] = v;
+      __syncthreads();
+      for (int k = 0; k < kRounds && !stop; ++k) {
+        S.add(sTot[buf][k][lane < 6 ? lane : 5]);
+        n_side += rs;
+        stop = __builtin_amdgcn_readfirstlane(
+            screen_stops(r, S, n_side, r.n_start ? (int64_t)r.n_start[p] : 0, kAnti, r.Q.Z[0],
+                         r.L.Z[m]));
+      }
+      buf ^= 1;
+    }
     if (__builtin_amdgcn_readfirstlane(stop)) break;
   }
   const ScreenArgs& r = screen_args_again();
@@ -801,7 +832,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_screen_split(ScreenArgs a) {
   const uint32_t idb = a.L.id[m];
   const double Za = a.Q.Z[0], Zb = a.L.Z[m];
   const int rs = kSplitSlots * kWave;
-  const int64_t limit = a.mode == SHAPE_SCREEN_ADAPTIVE ? a.cap_pair / 2 : a.n_fixed;
+  const int limit = screen_limit(a);
   const int64_t first_check = a.n_start ? (int64_t)a.n_start[p] : 0;
   RoundSums sums;
   int64_t n_side = 0;
@@ -1187,21 +1218,17 @@ size_t screen_lds_bytes(int max_q, int max_b) {
          kGuideSize * sizeof(uint8_t);
 }
 
-template <int A, int B>
+template <int A, int B, int R = 1>
 static void launch_screen_t(const ScreenArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)a.n_pairs), block(kWave);
+  const dim3 grid((unsigned)a.n_pairs), block(R * kWave);
   const size_t lds = screen_lds_bytes(a.max_q, a.max_b);
   if (a.anti)
-    hipLaunchKernelGGL((k_screen<A, B, true>), grid, block, lds, st, a);
+    hipLaunchKernelGGL((k_screen<A, B, true, R>), grid, block, lds, st, a);
   else
-    hipLaunchKernelGGL((k_screen<A, B, false>), grid, block, lds, st, a);
+    hipLaunchKernelGGL((k_screen<A, B, false, R>), grid, block, lds, st, a);
 }
 
-bool screen_splits(const ScreenArgs& a, int n_cu) {
-  return a.round_side == kSplitSlots * kWave && a.n_pairs <= kSplitPairsPerCu * n_cu;
-}
-
-hipError_t launch_screen_split(const ScreenArgs& a, hipStream_t st) {
+static hipError_t launch_screen_split(const ScreenArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)a.n_pairs), block(kSplitThreads);
   const size_t lds = screen_lds_bytes(a.max_q, a.max_b);
   if (a.anti)
@@ -1222,6 +1249,45 @@ hipError_t launch_screen(const ScreenArgs& a, int variant, hipStream_t st) {
     case 6: launch_screen_t<8, 4>(a, st); break;
     case 7: launch_screen_t<2, 4>(a, st); break;
     default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// Rounds of a pair that its workgroup works on at a time, a wave each
+// (k_screen's kRounds), for screens that one wave per pair leaves short of
+// waves.  Rounds drawn past an adaptive pair's stop are dropped, (R - 1)/2 on
+// average, so R falls as a round grows.  One : two : four rounds, ms:
+//   few pairs          5,000 molecules of 10-50 atoms, adaptive 0.58 : 0.51 :
+//                      0.49; 8,000 0.78 : 0.71 : 0.72; 11,000 1.00 : 0.92 : 0.96;
+//                      13,000 1.09 : 1.07 : 1.14; 16,000 1.29 : 1.30 : 1.37
+//   LDS per pair       20,000 of 50-100 atoms (17 pairs' records in a compute
+//                      unit's LDS) 3.04 : 2.63 : 2.78; 60,000 of 30-70 (25) 6.59
+//                      : 6.53 : 6.90; of 30-60 (28) 6.49 : 6.52 : 6.88; 20,000
+//                      of 100-150 (11) fixed 3.09 : 2.59 : 2.32, of 200-256 (6)
+//                      6.98 : 5.03 : 3.99
+//   long rounds        8,000 pairs, 1,024 samples per side and round 0.81 :
+//                      0.77 : 0.88
+static int screen_rounds(const ScreenArgs& a, int n_cu) {
+  constexpr int kLdsPerCu = 160 * 1024;
+  const bool adaptive = a.mode == SHAPE_SCREEN_ADAPTIVE;
+  const int64_t n_rounds = (adaptive ? a.cap_pair / 2 : a.n_fixed) / a.round_side;
+  const int64_t resident = kLdsPerCu / (int64_t)screen_lds_bytes(a.max_q, a.max_b);
+  int R = 1;
+  if (a.n_pairs <= kTwoRoundPairsPerCu * n_cu || resident <= 25) R = 2;
+  if (a.n_pairs <= kFourRoundPairsPerCu * n_cu || resident <= 11) R = 4;
+  if (adaptive && a.n_pairs > kSplitPairsPerCu * n_cu)
+    while (R > 1 && R * a.round_side > 1024) R /= 2;
+  while (R > n_rounds) R /= 2;
+  return R;
+}
+
+hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStream_t st) {
+  if (a.round_side == kSplitSlots * kWave && a.n_pairs <= kSplitPairsPerCu * n_cu)
+    return launch_screen_split(a, st);
+  switch (screen_rounds(a, n_cu)) {
+    case 4: launch_screen_t<4, 4, 4>(a, st); break;
+    case 2: launch_screen_t<4, 4, 2>(a, st); break;
+    default: return launch_screen(a, variant, st);
   }
   return hipGetLastError();
 }

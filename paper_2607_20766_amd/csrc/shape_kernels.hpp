@@ -241,15 +241,18 @@ size_t screen_lds_bytes(int max_q, int max_b);
 constexpr int kScreenVariants = 8;
 extern const int kScreenVariantShape[kScreenVariants][2];  // {kSA, kSB}
 hipError_t launch_screen(const ScreenArgs& a, int variant, hipStream_t st);
-// Whether a screen is better run with eight waves per pair (the same bits):
-// rounds of 256 samples per side and at most 28 pairs per compute unit, which
-// one wave per pair fills with fewer than eight waves per SIMD.  Against one
-// wave per pair: 4,000 molecules 0.46 : 0.61 ms adaptive and 0.35 : 0.44 ms
-// fixed (4,096 per side), 7,000 fixed 0.55 : 0.57, 8,000 adaptive 0.82 : 0.80,
-// 16,000 1.57 : 1.31.
-constexpr int kSplitPairsPerCu = 28;
-bool screen_splits(const ScreenArgs& a, int n_cu);
-hipError_t launch_screen_split(const ScreenArgs& a, hipStream_t st);
+// The screen kernel that suits the call (all give the same bits): eight waves
+// per pair up to kSplitPairsPerCu pairs per compute unit (rounds of 256 samples
+// per side), where a pair's chain of rounds bounds the call (256 molecules 0.10
+// ms against 0.12 with four rounds at a time, 1,000 0.190 : 0.185); then four
+// rounds and two rounds of a pair at a time (screen_rounds), which fill the chip
+// up to kFourRoundPairsPerCu (28 pairs per compute unit are fewer than eight
+// waves per SIMD) and kTwoRoundPairsPerCu; else one wave per pair in the tile
+// shape `variant`.
+constexpr int kSplitPairsPerCu = 3;
+constexpr int kFourRoundPairsPerCu = 28;
+constexpr int kTwoRoundPairsPerCu = 50;
+hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStream_t st);
 // Launch order of a grid with one workgroup per pair (blocks along x):
 // largest estimated work first.  The work of pair p is
 // wA N_A + wB N_B + w0 atoms' worth, times the rounds of its seeded budget

@@ -131,6 +131,48 @@ def test_few_pairs_same_bits_as_one_wave_per_pair(eng, kw, anti):
         eng.sampling(False)
 
 
+@pytest.mark.parametrize("anti", [False, True])
+@pytest.mark.parametrize("pairs_per_cu,atoms,kw", [
+    # four rounds at a time
+    (4, 40, dict(mode=SHAPE_SCREEN_ADAPTIVE, cap_per_pair=4608, tau=0.02)),  # cap inside a pass
+    (4, 40, dict(mode=SHAPE_SCREEN_ADAPTIVE, round_per_pair=256, cap_per_pair=2560, tau=0.02)),
+    (4, 40, dict(mode=SHAPE_SCREEN_FIXED, n_per_side=640)),        # five rounds of 128 or 64
+    (60, 200, dict(mode=SHAPE_SCREEN_FIXED, n_per_side=1280)),     # by LDS per pair
+    # two rounds at a time: by the number of pairs, of samples per round, of rounds, by LDS
+    (40, 40, dict(mode=SHAPE_SCREEN_ADAPTIVE, cap_per_pair=2560, tau=0.02)),
+    (4, 40, dict(mode=SHAPE_SCREEN_ADAPTIVE, round_per_pair=1024, cap_per_pair=5120, tau=0.02)),
+    (4, 40, dict(mode=SHAPE_SCREEN_FIXED, n_per_side=384)),
+    (60, 90, dict(mode=SHAPE_SCREEN_ADAPTIVE, cap_per_pair=1536, tau=0.02)),
+    (4, 40, dict(mode=SHAPE_SCREEN_ADAPTIVE, round_per_pair=512, cap_per_pair=512, tau=0.02)),
+])
+def test_rounds_at_a_time_same_bits(eng, pairs_per_cu, atoms, kw, anti):
+    """Screens whose workgroups work on two or four rounds of a pair at a time
+    give the bits of one wave per pair, also with invalid pairs and seeded
+    budgets."""
+    L = molgen.MolSet.concat([molgen.library(27, 40, 1, 30, workers=1),
+                              molgen.library(28, 6, atoms - 8, atoms, workers=1)])
+    lib = eng.molecules(L)
+    Q = eng.molecules(molgen.molecule(29, 0, 33), mol_id=[QUERY_ID])
+    dev = eng.torch_device
+    n = pairs_per_cu * torch.cuda.get_device_properties(dev).multi_processor_count
+    pairs = (torch.arange(n, dtype=torch.int32, device=dev) * 7) % (lib.n_mols + 1)
+    n_start = (torch.arange(n, dtype=torch.int32, device=dev) * 37) % 3000
+    print(f"case: rounds at a time, {pairs_per_cu}/CU {atoms} {kw}, anti {anti}", flush=True)
+    eng.sampling(anti)
+    try:
+        for ns in (None, n_start):
+            eng.screen_variant(5)
+            one = _np(eng.shape_screen(Q, lib, pairs=pairs, n_start=ns, seed=9, **kw))
+            eng.screen_variant(-1)
+            many = _np(eng.shape_screen(Q, lib, pairs=pairs, n_start=ns, seed=9, **kw))
+            _same(one, many)
+            bad = pairs >= lib.n_mols
+            assert np.array_equal(np.isnan(many["T"]), bad.cpu().numpy())
+    finally:
+        eng.screen_variant(-1)
+        eng.sampling(False)
+
+
 def test_tuner_picks_a_variant(eng, data):
     Q, lib = data
     tune_cache_clear()
