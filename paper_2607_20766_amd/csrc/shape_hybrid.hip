@@ -29,13 +29,15 @@ namespace shape {
 __device__ void jacobi3(double a[3][3], double V[9]) {
   double U[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
   for (int sweep = 0; sweep < 60; ++sweep) {
-    // every remaining rotation is below 10^-30 (apart from exactly degenerate
-    // axes, which go on): no component of U changes at FP64.  Rounding leaves
-    // off-diagonals of 10^-16 of the rotated terms, so waiting for them to
-    // vanish took about twenty sweeps instead of six.
-    if (fabs(a[0][1]) <= 1e-30 * fabs(a[1][1] - a[0][0]) &&
-        fabs(a[0][2]) <= 1e-30 * fabs(a[2][2] - a[0][0]) &&
-        fabs(a[1][2]) <= 1e-30 * fabs(a[2][2] - a[1][1]))
+    // every remaining rotation is below 10^-30 and no two eigenvalues are so
+    // close that it could change their order: no component of U changes at
+    // FP64.  Rounding leaves off-diagonals of 10^-16 of the rotated terms, so
+    // waiting for them to vanish took about twenty sweeps instead of six.
+    const double d01 = fabs(a[1][1] - a[0][0]), d02 = fabs(a[2][2] - a[0][0]),
+                 d12 = fabs(a[2][2] - a[1][1]);
+    if (fmin(fmin(d01, d02), d12) > 1e-10 * (fabs(a[0][0]) + fabs(a[1][1]) + fabs(a[2][2])) &&
+        fabs(a[0][1]) <= 1e-30 * d01 && fabs(a[0][2]) <= 1e-30 * d02 &&
+        fabs(a[1][2]) <= 1e-30 * d12)
       break;
     const double off = fabs(a[0][1]) + fabs(a[0][2]) + fabs(a[1][2]);
     if (off < 1e-300) break;
