@@ -1256,7 +1256,7 @@ int shape_fo_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32
     }
     KernelTimer timer(c, st);
     HIP_TRY(c, shape::launch_fo_align(mols_dev(A), mols_dev(B), n_starts, n_steps, lr, c->flag,
-                                      pose, T, grad, st, wo.order),
+                                      pose, T, grad, st, wo.order, c->n_cu),
             "first-order alignment kernel");
     timer.stop();
     return SHAPE_OK;

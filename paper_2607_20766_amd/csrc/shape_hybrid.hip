@@ -280,8 +280,8 @@ __global__ __launch_bounds__(kWave) void k_fo_starts(MolsDev A, MolsDev B, int n
 }
 
 // ---------------------------------------------------------------------------
-// First-order alignment: one wave per (pair, start); Adam runs inside the
-// kernel, the pose and its moments stay in registers (wave-uniform).
+// First-order alignment: Adam runs inside the kernel, poses and moments stay in
+// registers.
 // ---------------------------------------------------------------------------
 // Row layout: at most kFoRowsStarts starts (rows of 16 lanes) per
 // workgroup; moved-atom arrays of the rows at a stride of s float4 with
@@ -326,82 +326,59 @@ __device__ __forceinline__ bool fo_stage(const FoAlignArgs& a, bool ok, float4* 
   return !any(bad);
 }
 
-// One pass over the N_A x N_B atom pairs spread over the lanes (the row of
-// flat index p stepped incrementally, as in the cross-overlap kernel):
-// O, dO/dt and the torque about B's origin, summed over the wave.  Per term,
-// the pose-independent factors come from the widths alone: with
-// rs = 1/sqrt(a_i + a_j), (pi/(a_i+a_j))^(3/2) = pi^(3/2) rs^3 and
-// k_ij = a_i a_j rs^2.  A lane's first kFoCache terms keep them in registers
-// for the whole optimisation (fo_term_consts, filled once per wave); later
-// terms derive them on the spot from one rsqrt.  The torque is accumulated
-// as sum c''_j x f and shifted by -t x sum f once at the end.
-constexpr int kFoCache = 16;
-
-struct FoTermConsts {
-  float kk[kFoCache];   // -log2(e) k_ij
-  float pre[kFoCache];  // pi^(3/2) (a_i + a_j)^(-3/2)
-  float f2[kFoCache];   // 2 k_ij
-};
-
-__device__ __forceinline__ void fo_consts(float ai, float aj, float& kk, float& pre, float& f2) {
-  const float rs = __builtin_amdgcn_rsqf(ai + aj);
+// (pi/(a_i+a_j))^(3/2) = pi^(3/2) rs^3 and k_ij = a_i a_j rs^2 of a pair of
+// widths, from rs = 1/sqrt(a_i + a_j): kk = -log2(e) k_ij, pre = the
+// prefactor, f2 = 2 k_ij.
+__device__ __forceinline__ void fo_consts_rs(float ai, float aj, float rs, float& kk, float& pre,
+                                             float& f2) {
   const float ir = rs * rs;
   const float k = ai * aj * ir;
   kk = -1.44269504088896f * k;
   pre = 5.56832799683170785f * ir * rs;
   f2 = 2.f * k;
 }
-
-__device__ __forceinline__ void fo_term_consts(const float4* sA, int na, const float4* sB,
-                                               int nb, FoTermConsts& c) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int di = kWave / nb, dj = kWave % nb;
-  int i = lane / nb, j = lane % nb;
-#pragma unroll
-  for (int t = 0; t < kFoCache; ++t) {
-    c.kk[t] = 0.f;
-    c.pre[t] = 0.f;
-    c.f2[t] = 0.f;
-    if (i < na) {
-      fo_consts(sA[i].w, sB[j].w, c.kk[t], c.pre[t], c.f2[t]);
-      i += di;
-      j += dj;
-      if (j >= nb) {
-        j -= nb;
-        ++i;
-      }
-    }
-  }
+__device__ __forceinline__ void fo_consts(float ai, float aj, float& kk, float& pre, float& f2) {
+  fo_consts_rs(ai, aj, __builtin_amdgcn_rsqf(ai + aj), kk, pre, f2);
 }
 
 struct FoAcc {
   float O = 0.f, gx = 0.f, gy = 0.f, gz = 0.f, rx = 0.f, ry = 0.f, rz = 0.f;
-  __device__ __forceinline__ void add(const float4& ci, const float4& cj, float kk, float pre,
+  // the term pre exp of c''_j at distance d from c_i: O, dO/dc''_j, torque
+  __device__ __forceinline__ void add(const float3& d, const float4& cj, float e, float pre,
                                       float f2) {
-    const float dx = ci.x - cj.x, dy = ci.y - cj.y, dz = ci.z - cj.z;
-    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    const float K = pre * __builtin_amdgcn_exp2f(kk * d2);
-    O += K;
-    const float f = f2 * K;
-    const float fx = f * dx, fy = f * dy, fz = f * dz;  // dO/dc''_j from this term
-    gx += fx; gy += fy; gz += fz;
+    O = fmaf(pre, e, O);
+    const float f = f2 * (pre * e);
+    const float fx = f * d.x, fy = f * d.y, fz = f * d.z;
+    gx = fmaf(f, d.x, gx); gy = fmaf(f, d.y, gy); gz = fmaf(f, d.z, gz);
     rx = fmaf(cj.y, fz, fmaf(-cj.z, fy, rx));
     ry = fmaf(cj.z, fx, fmaf(-cj.x, fz, ry));
     rz = fmaf(cj.x, fy, fmaf(-cj.y, fx, rz));
   }
 };
 
-__device__ __forceinline__ void fo_pass(const float4* sA, int na, const float4* sM, int nb,
-                                        float tx, float ty, float tz, const FoTermConsts& c,
-                                        float (&r)[7]) {
+// One pass over the N_A x N_B atom pairs spread over the lanes (pair p = lane
+// + 64 t is lane's term t; its row i and column j are stepped incrementally),
+// for S poses of B at once: per pose the lane's part of O, dO/dt and the torque
+// sum c''_j x f, its terms added in turn.  The pose-independent factors of a
+// pair come from its widths (one rsqrt) and serve all S poses.  U terms go
+// together; the last few are masked (prefactor 0: their terms add exactly 0).
+template <int S, int U>
+__device__ __forceinline__ void fo_pass(const float4* sA, int na, const float4* sM, int stride,
+                                        int nb, FoAcc (&acc)[S]) {
   const int lane = threadIdx.x & (kWave - 1);
   const int di = kWave / nb, dj = kWave % nb;
+  const int n = na * nb, terms = (n + kWave - 1) / kWave, whole = n / kWave / U * U;
   int i = lane / nb, j = lane % nb;
-  FoAcc acc;
+  const auto group = [&](int t, auto masked) {
+    float4 ci[U], cj[U][S];
+    float rs[U], kk[U], pre[U], f2[U], e[U * S];
+    float3 d[U][S];
 #pragma unroll
-  for (int t = 0; t < kFoCache; ++t) {
-    if (i < na) {
-      acc.add(sA[i], sM[j], c.kk[t], c.pre[t], c.f2[t]);
+    for (int u = 0; u < U; ++u) {
+      ci[u] = sA[decltype(masked)::value ? min(i, na - 1) : i];
+#pragma unroll
+      for (int s = 0; s < S; ++s) cj[u][s] = sM[s * stride + j];
+      rs[u] = ci[u].w + cj[u][0].w;
       i += di;
       j += dj;
       if (j >= nb) {
@@ -409,25 +386,29 @@ __device__ __forceinline__ void fo_pass(const float4* sA, int na, const float4* 
         ++i;
       }
     }
-  }
-  for (; i < na;) {
-    const float4 ci = sA[i], cj = sM[j];
-    float kk, pre, f2;
-    fo_consts(ci.w, cj.w, kk, pre, f2);
-    acc.add(ci, cj, kk, pre, f2);
-    i += di;
-    j += dj;
-    if (j >= nb) {
-      j -= nb;
-      ++i;
+    trans_group<U>([&](int u) { rs[u] = __builtin_amdgcn_rsqf(rs[u]); });
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      fo_consts_rs(ci[u].w, cj[u][0].w, rs[u], kk[u], pre[u], f2[u]);
+      if constexpr (decltype(masked)::value)
+        if (lane + kWave * (t + u) >= n) pre[u] = 0.f;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const float dx = ci[u].x - cj[u][s].x, dy = ci[u].y - cj[u][s].y,
+                    dz = ci[u].z - cj[u][s].z;
+        d[u][s] = make_float3(dx, dy, dz);
+        e[u * S + s] = kk[u] * fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+      }
     }
-  }
-  r[0] = wave_sum_dpp(acc.O);
-  r[1] = wave_sum_dpp(acc.gx); r[2] = wave_sum_dpp(acc.gy); r[3] = wave_sum_dpp(acc.gz);
-  // torque about B's origin: sum (c''_j - t) x f = sum c''_j x f - t x sum f
-  r[4] = wave_sum_dpp(acc.rx) - (ty * r[3] - tz * r[2]);
-  r[5] = wave_sum_dpp(acc.ry) - (tz * r[1] - tx * r[3]);
-  r[6] = wave_sum_dpp(acc.rz) - (tx * r[2] - ty * r[1]);
+    trans_group<U * S>([&](int x) { e[x] = __builtin_amdgcn_exp2f(e[x]); });
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < S; ++s) acc[s].add(d[u][s], cj[u][s], e[u * S + s], pre[u], f2[u]);
+  };
+  int t = 0;
+  for (; t < whole; t += U) group(t, std::false_type{});
+  for (; t < terms; t += U) group(t, std::true_type{});
 }
 
 // sum_ij K_ij of a molecule with itself (pose invariant), over all lanes.
@@ -455,37 +436,52 @@ __device__ __forceinline__ float fo_self(const float4* s, int n) {
   return wave_sum_dpp(acc);
 }
 
-__global__ __launch_bounds__(64) void k_fo_align(FoAlignArgs a) {
+// One wave per pair and S of its starts, for molecules that the row layout below
+// does not take.  VALU issue bounds it: per atom pair and pose 22 instructions and
+// an exponential, shared by the poses 8 (widths), a reciprocal root, 8 (indices)
+// and A's LDS read.  8,000 pairs of 75 x 50-100 atoms, 8 starts, 50 steps: 16.1 ms
+// with one start per wave, a lane's first terms' factors kept in registers and one
+// term at a time; 15.4 ms with the transcendentals of two terms grouped, 13.4 ms
+// with two starts and 12.3 ms with four; 100 pairs 0.79 -> 0.62 ms.  All lanes walk the atom pairs for the
+// S poses together (fo_pass); the steps between two passes are taken by S rows of
+// 64/S lanes, each for its own start: every lane of a row holds its pose, and
+// Adam's component c with its moments sits in lane c of the row.
+template <int S, int U>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+void k_fo_align(FoAlignArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x;
-  const int item = blockIdx.x;  // pair * n_starts + start
-  const int pair = item / a.n_starts;
+  constexpr int kRow = kWave / S;
+  const int lane = threadIdx.x, lr = lane % kRow, row = lane / kRow;
+  const int groups = (a.n_starts + S - 1) / S;
+  const int pair = blockIdx.x / groups;
+  const int s_raw = (int)(blockIdx.x % groups) * S + row;
+  const bool live = s_raw < a.n_starts;
+  // spare rows repeat the last start
+  const size_t item = (size_t)pair * a.n_starts + (live ? s_raw : a.n_starts - 1);
   const int ma = a.A.n_mols == 1 ? 0 : pair;
   const int a0 = a.A.off[ma], a1 = a.A.off[ma + 1], na = a1 - a0;
   const int b0 = a.B.off[pair], b_end = a.B.off[pair + 1], nb = b_end - b0;
+  const int stride = a.B.max_atoms;
   float4* sA = reinterpret_cast<float4*>(smem);  // [max_a] x, y, z, alpha
   float4* sB = sA + a.A.max_atoms;               // [max_b] B as given
-  float4* sM = sB + a.B.max_atoms;               // [max_b] B moved
+  float4* sM = sB + stride;                      // [S][max_b] B moved
   const bool ok = fo_range_ok(a.A, a0, a1) && fo_range_ok(a.B, b0, b_end);
   if (!fo_stage(a, ok, sA, a0, na, sB, b0, nb, lane, kWave, [](bool b) { return __any(b); })) {
-    if (lane == 0) {
+    if (live && lr == 0) {
       a.T[item] = __builtin_nanf("");
       if (a.grad)
-        for (int c = 0; c < 7; ++c) a.grad[(size_t)item * 7 + c] = __builtin_nanf("");
+        for (int c = 0; c < 7; ++c) a.grad[item * 7 + c] = __builtin_nanf("");
       atomicOr(a.flag, 1);
     }
     return;
   }
   wave_lds_sync();
-  const float S = fo_self(sA, na) + fo_self(sB, nb);  // O_AA + O_BB
-  FoTermConsts tc;
-  fo_term_consts(sA, na, sB, nb, tc);
-  // pose x (wave-uniform); lane c < 7 holds component c of the Adam state
+  const float S0 = fo_self(sA, na) + fo_self(sB, nb);  // O_AA + O_BB
   float x[7];
-  float* ps = a.pose + (size_t)item * 7;
+  float* ps = a.pose + item * 7;
 #pragma unroll
   for (int c = 0; c < 7; ++c) x[c] = ps[c];
-  const int mine = lane < 7 ? lane : 6;
+  const int mine = lr < 7 ? lr : 6;
   float m_l = 0.f, v_l = 0.f;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   float b1t = 1.f, b2t = 1.f;  // b1^t, b2^t as running products
@@ -500,20 +496,34 @@ __global__ __launch_bounds__(64) void k_fo_align(FoAlignArgs a) {
                 R4 = 1.f - 2.f * (qx * qx + qz * qz), R5 = 2.f * (qy * qz - qw * qx),
                 R6 = 2.f * (qx * qz - qw * qy), R7 = 2.f * (qy * qz + qw * qx),
                 R8 = 1.f - 2.f * (qx * qx + qy * qy);
-    for (int j = lane; j < nb; j += kWave) {
+    for (int j = lr; j < nb; j += kRow) {
       const float4 c = sB[j];
-      sM[j] = make_float4(fmaf(R0, c.x, fmaf(R1, c.y, fmaf(R2, c.z, x[4]))),
-                          fmaf(R3, c.x, fmaf(R4, c.y, fmaf(R5, c.z, x[5]))),
-                          fmaf(R6, c.x, fmaf(R7, c.y, fmaf(R8, c.z, x[6]))), c.w);
+      sM[row * stride + j] =
+          make_float4(fmaf(R0, c.x, fmaf(R1, c.y, fmaf(R2, c.z, x[4]))),
+                      fmaf(R3, c.x, fmaf(R4, c.y, fmaf(R5, c.z, x[5]))),
+                      fmaf(R6, c.x, fmaf(R7, c.y, fmaf(R8, c.z, x[6]))), c.w);
     }
     wave_lds_sync();
-    float r[7];
-    fo_pass(sA, na, sM, nb, x[4], x[5], x[6], tc, r);
+    FoAcc acc[S];
+    fo_pass<S, U>(sA, na, sM, stride, nb, acc);
     wave_lds_sync();  // sM is rewritten next step
-    const float D = S - r[0];
-    T = r[0] / D;
+    float r[7];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const float w[7] = {wave_sum_dpp(acc[s].O),  wave_sum_dpp(acc[s].gx),
+                          wave_sum_dpp(acc[s].gy), wave_sum_dpp(acc[s].gz),
+                          wave_sum_dpp(acc[s].rx), wave_sum_dpp(acc[s].ry),
+                          wave_sum_dpp(acc[s].rz)};
+#pragma unroll
+      for (int c = 0; c < 7; ++c) r[c] = s == 0 || row == s ? w[c] : r[c];
+    }
+    // torque about B's origin: sum (c''_j - t) x f = sum c''_j x f - t x sum f
+    r[4] -= x[5] * r[3] - x[6] * r[2];
+    r[5] -= x[6] * r[1] - x[4] * r[3];
+    r[6] -= x[4] * r[2] - x[5] * r[1];
+    const float D = S0 - r[0];
     const float iD = __builtin_amdgcn_rcpf(D);
-    const float dTdO = S * iD * iD;
+    const float dTdO = S0 * iD * iD;
     const float gth[3] = {dTdO * r[4], dTdO * r[5], dTdO * r[6]};
     // dT/dq = (2/|q|) [ -v.g ; w g - v x g ]
     const float vdg = qx * gth[0] + qy * gth[1] + qz * gth[2];
@@ -524,10 +534,13 @@ __global__ __launch_bounds__(64) void k_fo_align(FoAlignArgs a) {
     g[4] = dTdO * r[1];
     g[5] = dTdO * r[2];
     g[6] = dTdO * r[3];
-    if (it == a.n_steps) break;
+    if (it == a.n_steps) {
+      T = r[0] / D;  // only the final pose's T is returned
+      break;
+    }
     // Adam on -T (bias-corrected moments, betas 0.9 / 0.999), q renormalised;
     // reciprocals by the hardware (a step of length ~lr tolerates 1 ulp).
-    // Lane c < 7 updates component c; the new pose is gathered by readlane.
+    // Lane c < 7 of the row updates component c; the row reads the new pose.
     b1t *= b1;
     b2t *= b2;
     const float ic1 = __builtin_amdgcn_rcpf(1.f - b1t), ic2 = __builtin_amdgcn_rcpf(1.f - b2t);
@@ -544,21 +557,20 @@ __global__ __launch_bounds__(64) void k_fo_align(FoAlignArgs a) {
     const float xn_l = x_l - a.lr * (m_l * ic1) * __builtin_amdgcn_rcpf(den);
     float xn[7];
 #pragma unroll
-    for (int c = 0; c < 7; ++c)
-      xn[c] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, xn_l), c));
+    for (int c = 0; c < 7; ++c) xn[c] = __shfl(xn_l, lane - lr + c, kWave);
     const float inv = rsqrtf(xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3]);
 #pragma unroll
     for (int c = 0; c < 4; ++c) x[c] = xn[c] * inv;
 #pragma unroll
     for (int c = 4; c < 7; ++c) x[c] = xn[c];
   }
-  if (lane == 0) {
+  if (live && lr == 0) {
 #pragma unroll
     for (int c = 0; c < 7; ++c) ps[c] = x[c];
     a.T[item] = T;
     if (a.grad)
 #pragma unroll
-      for (int c = 0; c < 7; ++c) a.grad[(size_t)item * 7 + c] = g[c];
+      for (int c = 0; c < 7; ++c) a.grad[item * 7 + c] = g[c];
   }
 }
 
@@ -764,7 +776,7 @@ void k_fo_align_rows(FoAlignArgs a) {
       T = r7[0] / D;  // only the final pose's T is returned
       break;
     }
-    // Adam on -T, the one-start-per-wave kernel's arithmetic: lane l16 < 7
+    // Adam on -T, k_fo_align's arithmetic: lane l16 < 7
     // of the row updates component l16, then the row reads the seven new
     // components back from those lanes
     b1t *= b1;
@@ -887,14 +899,16 @@ hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, int n_random, ui
   return hipGetLastError();
 }
 
-size_t fo_align_lds_bytes(int max_a, int max_b) {
-  return (size_t)(max_a + 2 * max_b) * sizeof(float4);
+// For s starts per wave.
+static size_t fo_align_lds_bytes(int max_a, int max_b, int s) {
+  return (size_t)(max_a + (1 + s) * max_b) * sizeof(float4);
 }
+size_t fo_align_lds_bytes(int max_a, int max_b) { return fo_align_lds_bytes(max_a, max_b, 2); }
 
 // Row-layout launch shape: rows (starts) per workgroup and its LDS bytes, or
 // 0 when the row kernel does not apply (A over 64 atoms, LDS beyond
 // kFoRowsLdsMax, or more start blocks than a grid's y extent) and the
-// one-start-per-wave kernel runs instead.
+// k_fo_align runs instead.
 static int fo_rows_per_block(int n_starts) {
   return n_starts >= kFoRowsStarts ? kFoRowsStarts : ((n_starts + 3) / 4) * 4;
 }
@@ -920,9 +934,16 @@ static void launch_fo_rows_t(const FoAlignArgs& a, size_t lds, hipStream_t st) {
                      dim3(rows / 4 * kWave), lds, st, a);
 }
 
+template <int S, int U>
+static void launch_fo_align_t(const FoAlignArgs& a, hipStream_t st) {
+  const int64_t blocks = (int64_t)a.B.n_mols * ((a.n_starts + S - 1) / S);
+  hipLaunchKernelGGL((k_fo_align<S, U>), dim3((unsigned)blocks), dim3(kWave),
+                     fo_align_lds_bytes(a.A.max_atoms, a.B.max_atoms, S), st, a);
+}
+
 hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, int n_starts, int n_steps,
                            float lr, int* flag, float* pose, float* T, float* grad,
-                           hipStream_t st, const int* order) {
+                           hipStream_t st, const int* order, int n_cu) {
   FoAlignArgs a{A, B, flag, n_starts, n_steps, lr, pose, T, grad, nullptr};
   const size_t lds = fo_rows_lds_bytes(A.max_atoms, B.max_atoms, n_starts);
   if (lds > 0) {
@@ -935,9 +956,19 @@ hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, int n_starts, int
     }
     return hipGetLastError();
   }
+  // Four starts per wave once two would give every SIMD more than one wave,
+  // while sixteen waves' LDS fit a compute unit (B up to about 100 atoms); two
+  // once one would give three.  20 steps, 75 x 50-100 atoms, 8 starts, one : two
+  // : four, ms: 384 pairs 0.47 : 0.48 : 0.65, 512 0.58 : 0.48 : 0.65, 768 0.80 :
+  // 0.69 : 0.78, 1,024 1.04 : 0.86 : 0.79, 6,000 5.1 : 4.2 : 3.9; 4,000 of 256 x
+  // 200-256 atoms 37.9 : 31.9 : 34.6.
   const int64_t items = (int64_t)B.n_mols * n_starts;
-  hipLaunchKernelGGL(k_fo_align, dim3((unsigned)items), dim3(kWave),
-                     fo_align_lds_bytes(A.max_atoms, B.max_atoms), st, a);
+  if (items > 24 * n_cu && fo_align_lds_bytes(A.max_atoms, B.max_atoms, 4) <= 10 * 1024)
+    launch_fo_align_t<4, 2>(a, st);
+  else if (items > 12 * n_cu)
+    launch_fo_align_t<2, 4>(a, st);
+  else
+    launch_fo_align_t<1, 4>(a, st);
   return hipGetLastError();
 }
 

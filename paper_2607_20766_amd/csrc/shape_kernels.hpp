@@ -168,7 +168,7 @@ hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, int n_random, ui
 size_t fo_align_lds_bytes(int max_a, int max_b);
 hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, int n_starts, int n_steps,
                            float lr, int* flag, float* pose, float* T, float* grad,
-                           hipStream_t st, const int* order = nullptr);
+                           hipStream_t st, const int* order, int n_cu);
 // whether launch_fo_align runs one workgroup per pair (the row layout)
 bool fo_align_pair_major(int max_a, int max_b, int n_starts);
 hipError_t launch_best_pose(const float* T, const float* pose, int n_pairs, int n_starts,

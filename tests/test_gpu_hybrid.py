@@ -99,6 +99,35 @@ def test_starts_over_lane_groups(eng, n_pairs, n_random, atoms):
             assert np.abs(st[p, s, 4:] - ref[s, 4:]).max() <= 1e-4, (p, s)
 
 
+@pytest.mark.parametrize("max_b, n_starts", [(3, 1), (20, 5), (70, 8), (130, 6)])
+def test_starts_per_wave_same_bits(eng, max_b, n_starts):
+    """Alignments of a query too large for the row layout take one, two or four
+    starts per wave by the number of starts: the same bits for a pair in a call
+    of a few pairs, of a thousand and of several, and NaN for an invalid one."""
+    q = eng.molecules(molgen.molecule(61, 0, 75))
+    B = molgen.MolSet.concat([molgen.library(62, 9, 1, 3, workers=1),
+                              molgen.library(63, 10, max(1, max_b - 5), max_b, workers=1)])
+    n_cu = torch.cuda.get_device_properties(eng.torch_device).multi_processor_count
+    counts = [19, 18 * n_cu // n_starts, 30 * n_cu // n_starts]
+    print(f"case: B up to {max_b} atoms, {n_starts} starts, pairs {counts}", flush=True)
+    out = []
+    for n in counts:
+        lib = eng.molecules(molgen.MolSet.concat([B] * ((n + 18) // 19)))
+        lib.alpha[int(lib.offsets[18])] = -1.0
+        pose = eng.shape_fo_starts(q, lib, n_random=3, seed=5)[:, :n_starts].contiguous()
+        pose[:19] = torch.arange(7, device=pose.device) * 0.1 + 0.3
+        pose[:19] += torch.arange(19 * n_starts, device=pose.device).view(19, n_starts, 1) * 0.01
+        T, g = eng.shape_fo_align(q, lib, pose, n_steps=3, need_grad=True)
+        with pytest.raises(ShapeError):
+            eng.shape_check_data()
+        out.append((T[:19].cpu(), g[:19].cpu(), pose[:18].cpu()))
+    for T, g, pose in out:
+        assert torch.isnan(T[18]).all() and torch.isnan(g[18]).all()
+        assert torch.isfinite(T[:18]).all()
+        assert torch.equal(T[:18], out[0][0][:18]) and torch.equal(g[:18], out[0][1][:18])
+        assert torch.equal(pose, out[0][2])
+
+
 def test_shared_query_broadcasts(eng, pairs):
     """A single A molecule serves every pair, as the same molecule repeated."""
     _, B = pairs
