@@ -301,7 +301,7 @@ __global__ void k_features_eigen(int n_mols, const float* __restrict__ mom,
 // last atom hold a phantom atom 10^18 A away whose terms are exactly zero.
 // The terms of four library atoms per lane go together, their reciprocal roots
 // and their exponentials each as one prioritised group (trans_group): 300,000
-// pairs, 30-atom query, 163 -> 145 us.
+// pairs, 30-atom query, 163 -> 150 us (k_fo_cross_rows, below, 138 us).
 // A pair is only ~15 terms per lane, so the wave hides the memory latency
 // itself: the headers (molecule index, atom range) of 64 pairs are read at
 // once, one per lane, and the next pair's atoms are loaded while the current
@@ -320,6 +320,9 @@ __global__ void k_features_eigen(int n_mols, const float* __restrict__ mom,
 // the FP64 closed form.  Library widths use the hardware reciprocal and
 // log2 (once per atom and pair).
 constexpr int kFoWaves = 4;
+constexpr int kFoChunks = SHAPE_MAX_ATOMS / kWave;  // library atoms per lane, at most
+constexpr int kFoPairs = 4;  // per wave: a row of 16 lanes each
+constexpr int kFoAhead = 4;  // sixteens of a pair's atoms that are loaded ahead
 
 __device__ __forceinline__ bool atom_ok(float al, float x, float y, float z) {
   return al > 0.0f && isfinite(al) && isfinite(x) && isfinite(y) && isfinite(z);
@@ -329,7 +332,6 @@ __device__ __forceinline__ bool atom_ok(float al, float x, float y, float z) {
 // with invalid data (offsets out of range, alpha <= 0, non-finite values)
 // gives NaN and raises the data-error flag; a pair index outside the
 // library gives NaN.
-constexpr int kFoChunks = SHAPE_MAX_ATOMS / kWave;  // library atoms per lane, at most
 
 // Phantom atoms 10^18 A from every real atom, the query's at +10^18 and the
 // library's at -10^18 on each axis (so two phantoms are 2 10^18 apart too),
@@ -509,6 +511,224 @@ __global__ __launch_bounds__(kWave * kFoWaves) void k_fo_cross(
       const float sum = 9.64909578231936f * wave_sum_dpp(acc);  // (pi log2(e))^(3/2)
       if (lane == 0) out[p] = sum;
       wave_lds_sync();  // every read of this pair's atoms before the next pair's writes
+    }
+  }
+}
+
+// The same overlaps with four pairs per wave, a row of 16 lanes each: a lane of
+// the row takes query atoms l16 + 16 r and every library atom, so an atom read
+// from LDS serves two query atoms and the query is padded to 16, not to the
+// layout above's 16, 32 or 64 slots.  The kernel above is bound by LDS reads (24
+// bytes per lane and term: 48 of its 55 cycles per wave and term at 75 x 50-100
+// atoms); this one by VALU issue (300,000 pairs of 75 x 50-100 atoms 1,016 ->
+// 655 us, of 45 x 15-45 230 -> 190, of 30 x 10-50 150 -> 139).
+// The sums are the same: acc[x] holds, per lane, the partial that lane 16 x + l16
+// of the layout above holds (NI slots, 64/NI phases), the rows are summed in the
+// same tree and added in the same order, and padding adds exact zeros, so the
+// results have the same bits.  A wave's pairs are taken in order of size, so that
+// the four together are alike.  V library atoms go together.
+template <int NI, int V>
+__global__ __launch_bounds__(kWave) void k_fo_cross_rows(MolsDev Q, MolsDev L,
+                                                    const int* __restrict__ pairs, int n_pairs,
+                                                    int per_wave, int stride,
+                                                    int* __restrict__ flag,
+                                                    float* __restrict__ out) {
+  constexpr int kPhases = kWave / NI;
+  constexpr int kRows = NI == 16 ? 1 : 2;  // query atoms per lane and pass
+  static_assert(V % kPhases == 0, "a group holds whole phases");
+  // library records of four pairs, [4][stride]: (c, |c|^2), then (b, 1.5 log2 b);
+  // the query's records (-2 c, |c|^2) and (b, b^1.5), [max_q]
+  extern __shared__ float4 fo_lds[];
+  float4* sC = fo_lds;
+  float4* sQ = sC + kFoPairs * stride;
+  float2* sW = reinterpret_cast<float2*>(sQ + Q.max_atoms);
+  float2* sQw = sW + kFoPairs * stride;
+  const int lane = threadIdx.x, l16 = lane & 15, row = lane >> 4;
+  const int p_begin = (int)min((int64_t)n_pairs, (int64_t)blockIdx.x * per_wave);
+  const int p_end = (int)min((int64_t)n_pairs, (int64_t)p_begin + per_wave);
+  const int q0 = Q.off[0], q1 = Q.off[1], nq = q1 - q0;
+  bool q_bad = !(q0 >= 0 && (int64_t)q1 <= Q.n_atoms && nq >= 1 && nq <= Q.max_atoms);
+  float cx = 0.0f, cy = 0.0f, cz = 0.0f;  // the query's centroid
+  if (!q_bad) {
+    for (int i = lane; i < nq; i += kWave) {
+      cx += Q.xyz[3 * (q0 + i)];
+      cy += Q.xyz[3 * (q0 + i) + 1];
+      cz += Q.xyz[3 * (q0 + i) + 2];
+    }
+    const float inv = 1.0f / (float)nq;
+    cx = wave_sum_dpp(cx) * inv;
+    cy = wave_sum_dpp(cy) * inv;
+    cz = wave_sum_dpp(cz) * inv;
+    for (int i = lane; i < nq; i += kWave) {
+      const float al = Q.alpha[q0 + i];
+      const float x = Q.xyz[3 * (q0 + i)], y = Q.xyz[3 * (q0 + i) + 1],
+                  z = Q.xyz[3 * (q0 + i) + 2];
+      if (!atom_ok(al, x, y, z)) q_bad = true;
+      const float dx = x - cx, dy = y - cy, dz = z - cz;
+      const float b = 1.0f / (1.44269504088896f * al);
+      sQ[i] = make_float4(-2.0f * dx, -2.0f * dy, -2.0f * dz, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
+      sQw[i] = make_float2(b, b * sqrtf(b));
+    }
+  }
+  if (__any(q_bad)) {  // the same in every wave
+    for (int p = p_begin + lane; p < p_end; p += kWave) out[p] = __builtin_nanf("");
+    if (blockIdx.x == 0 && lane == 0) atomicOr(flag, 1);
+    return;
+  }
+  wave_lds_sync();
+  for (int sub = p_begin; sub < p_end; sub += kWave) {
+    const int cnt = min(kWave, p_end - sub);
+    // headers of up to 64 pairs, one per lane, in order of descending size:
+    // bit 0 the atom range is valid, bit 1 the molecule index lies in the
+    // library, the pair's place in the run from bit 2 on
+    int hb0 = 0, hnb = -1, hfl = 0;
+    if (lane < cnt) {
+      const int m = pairs ? pairs[sub + lane] : sub + lane;
+      hnb = 0;
+      if (m >= 0 && m < L.n_mols) {
+        hb0 = L.off[m];
+        const int b1 = L.off[m + 1], nb = b1 - hb0;
+        const bool ok = hb0 >= 0 && (int64_t)b1 <= L.n_atoms && nb >= 1 && nb <= L.max_atoms;
+        hnb = ok ? nb : 0;
+        hfl = 2 | (ok ? 1 : 0);
+      }
+      hfl |= lane << 2;
+    }
+    int rank = 0;
+    for (int k = 0; k < cnt; ++k) {
+      const int other = __builtin_amdgcn_readlane(hnb, k);
+      rank += other > hnb || (other == hnb && k < lane) ? 1 : 0;
+    }
+    if (lane >= cnt) rank = lane;  // a permutation of the 64 lanes
+    hb0 = __builtin_amdgcn_ds_permute(4 * rank, hb0);
+    hnb = __builtin_amdgcn_ds_permute(4 * rank, hnb);
+    hfl = __builtin_amdgcn_ds_permute(4 * rank, hfl);
+    // the first kFoAhead * 16 atoms (x, y, z, alpha) of four pairs into registers,
+    // a row of 16 lanes per pair; the loads stay in flight until they are used
+    float4 nxt[kFoAhead];
+    int b0 = 0, nb = 0;
+    const auto atom = [&](int j) {
+      const size_t x = (size_t)b0 + j;
+      return make_float4(L.xyz[3 * x], L.xyz[3 * x + 1], L.xyz[3 * x + 2], L.alpha[x]);
+    };
+    const auto load = [&](int k) {
+      b0 = __shfl(hb0, k + row, kWave);
+      nb = __shfl(hnb, k + row, kWave);
+#pragma unroll
+      for (int c = 0; c < kFoAhead; ++c)
+        if (l16 + 16 * c < nb) nxt[c] = atom(l16 + 16 * c);
+    };
+    load(0);
+    for (int k = 0; k < cnt; k += kFoPairs) {
+      const int top = __builtin_amdgcn_readlane(hnb, k);  // the largest of the four
+      const int n_j = (top + V - 1) / V * V;
+      bool a_bad = false;
+      const auto stage = [&](int j, const float4& at) {
+        float4 c = fo_phantom_lib();
+        float2 w = make_float2(1.0f, 0.0f);
+        if (j < nb) {
+          if (!atom_ok(at.w, at.x, at.y, at.z)) a_bad = true;
+          const float dx = at.x - cx, dy = at.y - cy, dz = at.z - cz;
+          const float b = __builtin_amdgcn_rcpf(1.44269504088896f * at.w);
+          c = make_float4(dx, dy, dz, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
+          w = make_float2(b, 1.5f * __builtin_amdgcn_logf(b));
+        }
+        if (j < n_j) {
+          sC[row * stride + j] = c;
+          sW[row * stride + j] = w;
+        }
+      };
+#pragma unroll
+      for (int c = 0; c < kFoAhead; ++c)
+        if (16 * c < n_j) stage(l16 + 16 * c, nxt[c]);
+      for (int j0 = 16 * kFoAhead; j0 < n_j; j0 += 16) {
+        const int j = j0 + l16;
+        stage(j, j < nb ? atom(j) : make_float4(0.0f, 0.0f, 0.0f, 1.0f));
+      }
+      const uint32_t bad = (uint32_t)(__ballot(a_bad) >> (16 * row)) & 0xFFFFu;
+      const int fl = __shfl(hfl, k + row, kWave);
+      if (k + kFoPairs < cnt) load(k + kFoPairs);  // arrive during these pairs' terms
+      wave_lds_sync();
+      const float4* rC = sC + row * stride;
+      const float2* rW = sW + row * stride;
+      // sums of the four rows of the summation order
+      float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      const auto pass = [&](int i0, auto rows, auto first) {
+        constexpr int R = decltype(rows)::value, kFirst = decltype(first)::value;
+        float4 ci[R];
+        float2 wi[R];
+        float accb[kPhases * R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int i = i0 + 16 * r + l16;
+          const bool real = i < nq;
+          ci[r] = real ? sQ[i] : fo_phantom_query();
+          wi[r] = real ? sQw[i] : make_float2(1.0f, 1.0f);
+        }
+#pragma unroll
+        for (int x = 0; x < kPhases * R; ++x) accb[x] = 0.0f;
+        for (int j = 0; j < n_j; j += V) {
+          float rs[V * R], e[V * R], d2[V * R];
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            const float4 cj = rC[j + v];
+            const float2 wj = rW[j + v];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              const int x = v * R + r;
+              d2[x] = fmaf(ci[r].x, cj.x, fmaf(ci[r].y, cj.y, fmaf(ci[r].z, cj.z, ci[r].w + cj.w)));
+              rs[x] = wi[r].x + wj.x;
+              e[x] = wj.y;
+            }
+          }
+          trans_group<V * R>([&](int x) { rs[x] = __builtin_amdgcn_rsqf(rs[x]); });  // k^(1/2)
+#pragma unroll
+          for (int x = 0; x < V * R; ++x) {
+            const float kk = rs[x] * rs[x];
+            e[x] = fmaf(-kk, d2[x], e[x]);
+            rs[x] *= kk;
+          }
+          trans_group<V * R>([&](int x) { e[x] = __builtin_amdgcn_exp2f(e[x]); });
+#pragma unroll
+          for (int x = 0; x < V * R; ++x) {
+            float& s = accb[x / R % kPhases * R + x % R];
+            s = fmaf(rs[x], e[x], s);
+          }
+        }
+#pragma unroll
+        for (int x = 0; x < kPhases * R; ++x)
+          acc[kFirst + x] = fmaf(accb[x], wi[x % R].y, acc[kFirst + x]);
+      };
+      using std::integral_constant;
+      if constexpr (NI < 64) {
+        pass(0, integral_constant<int, kRows>{}, integral_constant<int, 0>{});
+      } else {
+        for (int i0 = 0; i0 < nq; i0 += kWave) {
+          if (i0 + 16 < nq)
+            pass(i0, integral_constant<int, 2>{}, integral_constant<int, 0>{});
+          else
+            pass(i0, integral_constant<int, 1>{}, integral_constant<int, 0>{});
+          if (i0 + 48 < nq)
+            pass(i0 + 32, integral_constant<int, 2>{}, integral_constant<int, 2>{});
+          else if (i0 + 32 < nq)
+            pass(i0 + 32, integral_constant<int, 1>{}, integral_constant<int, 2>{});
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {  // row x of the summation order, in lane 15
+        acc[x] = dpp_step<0x111, 0xf>(acc[x]);
+        acc[x] = dpp_step<0x112, 0xf>(acc[x]);
+        acc[x] = dpp_step<0x114, 0xf>(acc[x]);
+        acc[x] = dpp_step<0x118, 0xf>(acc[x]);
+      }
+      const float sum = 9.64909578231936f * ((acc[3] + acc[2]) + (acc[1] + acc[0]));
+      if (l16 == 15 && k + row < cnt) {
+        const bool ok = (fl & 1) && !bad;
+        out[sub + (fl >> 2)] = ok ? sum : __builtin_nanf("");
+        // invalid data is flagged; an index outside the library only gives NaN
+        if (!ok && (fl & 2)) atomicOr(flag, 1);
+      }
+      wave_lds_sync();  // every read of these pairs' atoms before the next ones' writes
     }
   }
 }
@@ -2055,9 +2275,51 @@ static hipError_t launch_fo_cross_t(const MolsDev& Q, const MolsDev& L, const in
   return hipGetLastError();
 }
 
+constexpr int kFoCrossV = 4;
+static int fo_cross_stride(int max_b) { return (max_b + kFoCrossV - 1) / kFoCrossV * kFoCrossV; }
+static size_t fo_cross_lds_bytes(int max_q, int max_b) {
+  return (size_t)(kFoPairs * fo_cross_stride(max_b) + max_q) * (sizeof(float4) + sizeof(float2));
+}
+
+template <int NI>
+static hipError_t launch_fo_cross_rows_t(const MolsDev& Q, const MolsDev& L, const int* pairs,
+                                   int n_pairs, int n_cu, int* flag, float* out,
+                                   hipStream_t st) {
+  // 64 waves per compute unit (about 20 are resident), each with a run of pairs
+  // that is sorted by size (300,000 pairs, 30 x 10-50 atoms: 143 us with 32, 135
+  // with 64, 137 with 128; 75 x 50-100: 689, 635, 625)
+  const int64_t waves_wanted = (int64_t)n_cu * 64;
+  int per_wave = (int)((n_pairs + waves_wanted - 1) / waves_wanted);
+  per_wave = (per_wave + kFoPairs - 1) / kFoPairs * kFoPairs;
+  const dim3 grid((unsigned)(((int64_t)n_pairs + per_wave - 1) / per_wave));
+  hipLaunchKernelGGL((k_fo_cross_rows<NI, kFoCrossV>), grid, dim3(kWave),
+                     fo_cross_lds_bytes(Q.max_atoms, L.max_atoms), st, Q, L, pairs, n_pairs,
+                     per_wave, fo_cross_stride(L.max_atoms), flag, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_fo_cross(const MolsDev& Q, const MolsDev& L, const int* pairs, int n_pairs,
                            int n_cu, int* flag, float* out, hipStream_t st) {
   if (n_pairs <= 0) return hipSuccess;
+  if (n_cu <= 0) n_cu = 256;
+  // Four pairs per wave while twelve waves' LDS fit a compute unit (about 100
+  // library atoms): with fewer query slots by a fifth or more once there are two
+  // such waves per SIMD, else once the runs are long enough to be sorted by size.
+  // One : four pairs, us: 75 x 50-100 atoms, 4,000 pairs 25 : 25, 8,000 40 : 29,
+  // 300,000 1,020 : 655; 45 x 10-50, 16,000 22 : 22, 200,000 146 : 119; 64 x 50-100,
+  // 30,000 69 : 75, 300,000 537 : 502; 30 x 10-50, 100,000 52 : 51, 200,000 92 :
+  // 84; 100 x 1-256, 60,000 452 : 659.
+  const int slots = Q.max_atoms <= 16 ? 16 : (Q.max_atoms <= 32 ? 32 : (Q.max_atoms + 63) / 64 * 64);
+  const int rows = (Q.max_atoms + 15) / 16 * 16;
+  const int min_per_cu = 5 * rows <= 4 * slots ? 32 : 512;
+  if (n_pairs >= min_per_cu * n_cu &&
+      fo_cross_lds_bytes(Q.max_atoms, L.max_atoms) <= 12800) {
+    if (Q.max_atoms <= 16)
+      return launch_fo_cross_rows_t<16>(Q, L, pairs, n_pairs, n_cu, flag, out, st);
+    if (Q.max_atoms <= 32)
+      return launch_fo_cross_rows_t<32>(Q, L, pairs, n_pairs, n_cu, flag, out, st);
+    return launch_fo_cross_rows_t<64>(Q, L, pairs, n_pairs, n_cu, flag, out, st);
+  }
   // query slots: 16 (4 phases) up to 16 query atoms, 32 (2 phases) up to 32,
   // 64 beyond (blocks of 64); one chunk of library atoms per lane up to 64
   const bool one = L.max_atoms <= kWave;

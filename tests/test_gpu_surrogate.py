@@ -242,6 +242,35 @@ def test_fo_overlap_every_lane_layout(eng, q_atoms):
     assert np.array_equal(g_sub, g_all[pairs.cpu().numpy()])
 
 
+@pytest.mark.parametrize("q_atoms", [1, 16, 17, 32, 33, 49, 64, 65, 81, 100])
+def test_fo_overlap_four_pairs_per_wave(eng, q_atoms):
+    """Calls of many pairs (four per wave) give the bits of a call of few, for
+    query atoms around the rows of 16, library molecules of 1 to 90 atoms,
+    invalid molecules and indices, listed pairs and a whole library."""
+    q = molgen.molecule(82, q_atoms, q_atoms)
+    n_cu = torch.cuda.get_device_properties(eng.torch_device).multi_processor_count
+    L = molgen.MolSet.concat([molgen.molecule(83, i, n) for i, n in
+                              enumerate((1, 2, 15, 16, 17, 31, 33, 50, 63, 64, 65, 81, 90))])
+    Q = eng.molecules(q)
+    lib = eng.molecules(L)
+    lib.alpha[int(lib.offsets[3])] = -1.0
+    print(f"case: four pairs per wave, query {q_atoms} atoms", flush=True)
+    few = eng.shape_fo_overlap(Q, lib).cpu().numpy()
+    assert np.array_equal(np.isnan(few), np.arange(L.n_mols) == 3)
+    n = 512 * n_cu + 3
+    pairs = (torch.arange(n, dtype=torch.int32, device="cuda") * 11) % 29 - 1
+    idx = pairs.cpu().numpy()
+    want = np.where((idx >= 0) & (idx < L.n_mols), few[np.clip(idx, 0, L.n_mols - 1)], np.nan)
+    got = eng.shape_fo_overlap(Q, lib, pairs=pairs).cpu().numpy()
+    assert np.array_equal(got, want.astype(np.float32), equal_nan=True)
+    whole = eng.molecules(molgen.MolSet.concat([L] * (n // L.n_mols + 1)))
+    whole.alpha[whole.offsets[3:-1:L.n_mols].long()] = -1.0
+    got = eng.shape_fo_overlap(Q, whole).cpu().numpy()
+    assert np.array_equal(got, np.tile(few, n // L.n_mols + 1), equal_nan=True)
+    with pytest.raises(ShapeError):
+        eng.shape_check_data()
+
+
 def test_triage_gain(eng):
     """Surrogate-seeded screening spends far fewer IS samples than plain
     confidence-bounded IS over the whole library, keeps the top 1 %, and
