@@ -1825,8 +1825,8 @@ int shape_topk(shape_ctx* c, const float* score, int32_t n, int32_t k, void* str
   if (rc) return rc;
   void *sel, *hist, *gt, *eq;
   const int nb = shape::topk_blocks(n);
-  if ((rc = ensure(c, S_TOPK_SEL, 4 * sizeof(uint32_t), &sel))) return rc;
-  if ((rc = ensure(c, S_TOPK_HIST, 256 * sizeof(uint32_t), &hist))) return rc;
+  if ((rc = ensure(c, S_TOPK_SEL, shape::kTopkSel * sizeof(uint32_t), &sel))) return rc;
+  if ((rc = ensure(c, S_TOPK_HIST, shape::topk_hist_ints() * sizeof(uint32_t), &hist))) return rc;
   if ((rc = ensure(c, S_TOPK_GT, (size_t)nb * sizeof(int), &gt))) return rc;
   if ((rc = ensure(c, S_TOPK_EQ, (size_t)nb * sizeof(int), &eq))) return rc;
   KernelTimer timer(c, (hipStream_t)stream);

@@ -195,6 +195,9 @@ hipError_t launch_mse(const float* y, const float* t, const float* w, int B, int
                       double* partial, float* loss, hipStream_t st);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, int* step,
                        float lr, float b1, float b2, float eps, hipStream_t st);
+// scratch of launch_topk: sel [kTopkSel], hist [topk_hist_ints()], counts [topk_blocks(n)]
+constexpr int kTopkSel = 16;
+int topk_hist_ints();
 int topk_blocks(int n);
 hipError_t launch_topk(const float* s, int n, int k, uint32_t* sel, uint32_t* hist, int* cnt_gt,
                        int* cnt_eq, int* out, hipStream_t st);

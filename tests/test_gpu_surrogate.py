@@ -197,6 +197,25 @@ def test_topk_degenerate_scores(eng):
         assert np.array_equal(got, want), (s.size, k)
 
 
+@pytest.mark.parametrize("n", [1, 255, 257, 1023, 1024, 1025, 65537, 262145])
+def test_topk_digits_and_blocks(eng, n):
+    """Top-k around the block sizes, for scores that differ in every digit of
+    their keys (11, 11 and 10 bits), in the last one only, and in the first
+    one only, of both signs."""
+    rng = np.random.default_rng(n)
+    bits = {"all": rng.integers(0, 1 << 32, n, dtype=np.uint32),
+            "low": np.uint32(0x3E800000) + rng.integers(0, 1 << 10, n, dtype=np.uint32),
+            "high": rng.integers(0, 1 << 11, n, dtype=np.uint32) << np.uint32(21)}
+    for kind, b in bits.items():
+        s = b.view(np.float32)
+        key = np.where(np.isnan(s), -np.inf, s) + np.float32(0.0)
+        # NaN ranks below -inf, and -0 below +0
+        rank = np.lexsort((np.arange(n), np.signbit(s), -key, np.isnan(s)))
+        for k in sorted({1, (n + 2) // 3, n}):
+            got = eng.shape_topk(torch.from_numpy(s.copy()).cuda(), k).cpu().numpy()
+            assert np.array_equal(got, np.sort(rank[:k])), (n, kind, k)
+
+
 @pytest.mark.parametrize("shift", [(0.0, 0.0, 0.0), (120.0, -75.0, 40.0)])
 def test_fo_overlap_matches_oracle(eng, shift):
     """First-order cross overlaps (Eq. fo) against the oracle's closed form
