@@ -481,25 +481,28 @@ __global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a)
 }
 
 // Self-overlap of each molecule from its own first n samples,
-// O_MM = Z_M / n sum_k w_M u_M (pose invariant); one workgroup per molecule.
+// O_MM = Z_M / n sum_k w_M u_M (pose invariant); one workgroup per molecule of
+// the first set, then of the second.
 // All threads draw; the terms are then added by kSelfLanes lanes in a fixed
 // order (lane i takes samples i, i + kSelfLanes, ...).
 constexpr int kSelfThreads = 1024;
 constexpr int kSelfLanes = 256;
 constexpr int kSelfChunk = 2048;  // a multiple of kSelfLanes
-__global__ __launch_bounds__(kSelfThreads) void k_self_overlap(Prepared M,
-                                                               const int* __restrict__ off,
-                                                               int n_mols, int n_samples,
-                                                               uint2 key,
-                                                               float* __restrict__ out) {
+__global__ __launch_bounds__(kSelfThreads) void k_self_overlap(SelfSet first, SelfSet second,
+                                                               int n_samples, uint2 key) {
   __shared__ float2 sWU[kSelfChunk];  // weight and occupancy of a chunk's samples
   __shared__ Atom sF[SHAPE_MAX_ATOMS];
   __shared__ AtomSampling sS[SHAPE_MAX_ATOMS];
   __shared__ AtomRec sR[SHAPE_MAX_ATOMS];
   __shared__ float sA[SHAPE_MAX_ATOMS];
   __shared__ double red[kSelfLanes / kWave];
-  const int mol = blockIdx.x;
-  if (mol >= n_mols) return;
+  const bool in_first = (int)blockIdx.x < first.n;
+  const SelfSet& set = in_first ? first : second;
+  const int mol = in_first ? blockIdx.x : blockIdx.x - first.n;
+  if (mol >= set.n) return;
+  const Prepared& M = set.M;
+  const int* __restrict__ off = set.off;
+  float* __restrict__ out = set.out;
   if (M.bad[mol] != 0) {
     if (threadIdx.x == 0) out[mol] = __builtin_nanf("");
     return;
@@ -642,9 +645,10 @@ hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max
   return hipGetLastError();
 }
 
-hipError_t launch_self_overlap(const Prepared& M, const int* off, int n_mols, int n_samples,
-                               uint2 key, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_self_overlap, dim3((unsigned)n_mols), dim3(kSelfThreads), 0, st, M, off, n_mols, n_samples, key, out);
+hipError_t launch_self_overlap(const SelfSet& a, const SelfSet& b, int n_samples, uint2 key,
+                               hipStream_t st) {
+  hipLaunchKernelGGL(k_self_overlap, dim3((unsigned)(a.n + (int64_t)b.n)), dim3(kSelfThreads), 0,
+                     st, a, b, n_samples, key);
   return hipGetLastError();
 }
 

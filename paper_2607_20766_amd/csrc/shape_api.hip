@@ -298,6 +298,32 @@ int prepare(shape_ctx* c, const shape_mols* m, bool q, hipStream_t st, shape::Pr
   return SHAPE_OK;
 }
 
+// Both sets of a call, A in the query slots and B (or its listed subset) in the
+// library slots, with the first step of the launch order o when given (into
+// work): one launch unless preparations are kept for reuse.
+int prepare_sets(shape_ctx* c, const shape_mols* A, const shape_mols* B, hipStream_t st,
+                 shape::Prepared* PA, shape::Prepared* PB, const int32_t* subset = nullptr,
+                 int32_t n_subset = 0, const shape::OrderArgs* o = nullptr, int* work = nullptr) {
+  int rc;
+  shape::PrepSet a{mols_dev(A), {}, nullptr, 0}, b{mols_dev(B), {}, nullptr, 0};
+  if (c->prep_cache) {
+    if ((rc = prepare(c, A, true, st, PA))) return rc;
+    if ((rc = prepare(c, B, false, st, PB, subset, n_subset))) return rc;
+    if (!o) return SHAPE_OK;
+  } else {
+    c->prepared[0].valid = c->prepared[1].valid = false;
+    if ((rc = prepared_slots(c, A, true, PA))) return rc;
+    if ((rc = prepared_slots(c, B, false, PB))) return rc;
+    a.out = *PA;
+    a.n = A->n_mols;
+    b.out = *PB;
+    b.which = subset;
+    b.n = subset ? n_subset : B->n_mols;
+  }
+  HIP_TRY(c, shape::launch_prepare_sets(a, b, c->flag, o, work, st), "prepare kernel");
+  return SHAPE_OK;
+}
+
 // Calls that synchronise cannot be recorded into a graph.
 int refuse_in_capture(shape_ctx* c, const char* what) {
   return fail(c, SHAPE_E_UNSUPPORTED, "%s synchronises and cannot run during graph capture",
@@ -433,14 +459,6 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
     return SHAPE_OK;
   }
   if ((rc = set_device(c))) return rc;
-  shape::Prepared PQ, PL;
-  if ((rc = prepare(c, query, true, st, &PQ))) return rc;
-  // a screen of a small subset of a large library prepares only that subset
-  // (unless the whole set is already prepared for reuse)
-  const bool subset = pairs && (int64_t)n_pairs * 4 < lib->n_mols &&
-                      !(c->prep_cache && c->prepared[1].same(lib));
-  if ((rc = prepare(c, lib, false, st, &PL, subset ? pairs : nullptr, subset ? n_pairs : 0)))
-    return rc;
   const int64_t n_cache = prm->mode == SHAPE_SCREEN_FIXED ? n_fixed : cap / 2;
   void *qs, *qf2;
   if ((rc = ensure(c, S_QS, (size_t)n_cache * sizeof(float4), &qs))) return rc;
@@ -449,11 +467,39 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   // the order; the last workgroups then finish closer together)
   WorkOrder wo;
   if ((rc = work_order_slot(c, n_pairs, kOrderScreenPerCu, &wo))) return rc;
+  // per pair of samples: N_B evaluations at the query's sample, N_B + N_A
+  // at the library's, and Philox, inverse normals, component choice and
+  // weights, worth about 24 evaluations; times the rounds of a seeded budget
+  shape::OrderArgs o{};
+  o.n = n_pairs;
+  o.per_xcd = 1;
+  o.pairs = pairs;
+  o.offA = query->atom_offset;
+  o.nA_mols = 1;
+  o.max_a = query->max_atoms;
+  o.a_single = 1;
+  o.offB = lib->atom_offset;
+  o.nB_mols = lib->n_mols;
+  o.max_b = lib->max_atoms;
+  o.wA = 1;
+  o.wB = 2;
+  o.w0 = 24;
+  o.n_start = prm->mode == SHAPE_SCREEN_ADAPTIVE ? prm->n_start : nullptr;
+  o.round_pair = 2 * (int64_t)round_side;
+  o.cap = cap;
+  const shape::OrderArgs* order = wo.order ? &o : nullptr;
+  shape::Prepared PQ, PL;
+  // a screen of a small subset of a large library prepares only that subset
+  // (unless the whole set is already prepared for reuse)
+  const bool subset = pairs && (int64_t)n_pairs * 4 < lib->n_mols &&
+                      !(c->prep_cache && c->prepared[1].same(lib));
+  if ((rc = prepare_sets(c, query, lib, st, &PQ, &PL, subset ? pairs : nullptr,
+                         subset ? n_pairs : 0, order, wo.work)))
+    return rc;
   const uint2 key = key_of(prm->seed);
   HIP_TRY(c, shape::launch_query_cache(PQ, query->atom_offset, n_cache, key, anti ? 1 : 0,
-                                       (float4*)qs,
-                                       (float*)qf2, st),
-          "query cache kernel");
+                                       (float4*)qs, (float*)qf2, order, wo.order, wo.work, st),
+          "query cache and launch order kernels");
   a->Q = PQ;
   a->offQ = query->atom_offset;
   a->max_q = query->max_atoms;
@@ -471,7 +517,7 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   a->cap_pair = cap;
   a->tau = prm->tau;
   a->key = key;
-  a->n_start = prm->mode == SHAPE_SCREEN_ADAPTIVE ? prm->n_start : nullptr;
+  a->n_start = o.n_start;
   a->anti = anti ? 1 : 0;
   a->T = out->T;
   a->se_T = out->se_T;
@@ -479,31 +525,7 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   a->O_aa = out->O_aa;
   a->O_bb = out->O_bb;
   a->n_used = out->n_used;
-  a->order = nullptr;
-  if (wo.order) {
-    // per pair of samples: N_B evaluations at the query's sample, N_B + N_A
-    // at the library's, and Philox, inverse normals, component choice and
-    // weights, worth about 24 evaluations; times the rounds of a seeded budget
-    shape::OrderArgs o{};
-    o.n = n_pairs;
-    o.per_xcd = 1;
-    o.pairs = pairs;
-    o.offA = query->atom_offset;
-    o.nA_mols = 1;
-    o.max_a = query->max_atoms;
-    o.a_single = 1;
-    o.offB = lib->atom_offset;
-    o.nB_mols = lib->n_mols;
-    o.max_b = lib->max_atoms;
-    o.wA = 1;
-    o.wB = 2;
-    o.w0 = 24;
-    o.n_start = a->n_start;
-    o.round_pair = 2 * (int64_t)round_side;
-    o.cap = cap;
-    HIP_TRY(c, shape::launch_work_order(o, wo.order, wo.work, st), "launch order kernels");
-    a->order = wo.order;
-  }
+  a->order = wo.order;
   return SHAPE_OK;
 }
 
@@ -1012,8 +1034,8 @@ int shape_self_overlap(shape_ctx* c, const shape_mols* M, int32_t n_samples, uin
     hipStream_t st = (hipStream_t)stream;
     shape::Prepared P;
     if ((rc = prepare(c, M, false, st, &P))) return rc;
-    HIP_TRY(c, shape::launch_self_overlap(P, M->atom_offset, M->n_mols, n_samples, key_of(seed),
-                                          O_self, st),
+    HIP_TRY(c, shape::launch_self_overlap({P, M->atom_offset, M->n_mols, O_self}, {}, n_samples,
+                                          key_of(seed), st),
             "self-overlap kernel");
     return SHAPE_OK;
   } catch (...) {
@@ -1092,8 +1114,7 @@ int shape_align_grad(shape_ctx* c, const shape_mols* A, const shape_mols* B, int
     WorkOrder wo;
     if ((rc = work_order_slot(c, A->n_mols, kOrderAlignPerCu, &wo))) return rc;
     shape::Prepared PA, PB;
-    if ((rc = prepare(c, A, true, st, &PA))) return rc;
-    if ((rc = prepare(c, B, false, st, &PB))) return rc;
+    if ((rc = prepare_sets(c, A, B, st, &PA, &PB))) return rc;
     KernelTimer timer(c, st);
     rc = align_launch(c, A, B, PA, PB, n_starts, pose, O_aa, O_bb, n_samples, seed, st, T,
                       dT_dpose, wo);
@@ -1142,16 +1163,11 @@ int shape_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t 
     if ((rc = ensure(c, S_SELF_B, (size_t)pairs * sizeof(float), &sbb))) return rc;
     WorkOrder wo;
     if ((rc = work_order_slot(c, pairs, kOrderAlignPerCu, &wo))) return rc;
-    // self-overlaps use the library slots; prepare both sets afterwards
-    if ((rc = prepare(c, A, false, st, &PB))) return rc;
-    HIP_TRY(c, shape::launch_self_overlap(PB, A->atom_offset, pairs, n_samples, key_of(seed),
-                                          (float*)saa, st),
+    if ((rc = prepare_sets(c, A, B, st, &PA, &PB))) return rc;
+    HIP_TRY(c, shape::launch_self_overlap({PA, A->atom_offset, pairs, (float*)saa},
+                                          {PB, B->atom_offset, pairs, (float*)sbb}, n_samples,
+                                          key_of(seed), st),
             "self-overlap kernel");
-    if ((rc = prepare(c, B, false, st, &PB))) return rc;
-    HIP_TRY(c, shape::launch_self_overlap(PB, B->atom_offset, pairs, n_samples, key_of(seed),
-                                          (float*)sbb, st),
-            "self-overlap kernel");
-    if ((rc = prepare(c, A, true, st, &PA))) return rc;
     // the whole optimisation in one launch: A's samples are drawn once per
     // pair, each start's Adam state stays in registers (the same steps as
     // shape_align_grad followed by shape_adam_pose, n_steps times)
@@ -1322,8 +1338,7 @@ int shape_grid_integrals(shape_ctx* c, const shape_mols* A, const shape_mols* B,
     hipStream_t st = (hipStream_t)stream;
     // invalid molecules are reported before the grid reads them
     shape::Prepared PA, PB;
-    if ((rc = prepare(c, A, true, st, &PA))) return rc;
-    if ((rc = prepare(c, B, false, st, &PB))) return rc;
+    if ((rc = prepare_sets(c, A, B, st, &PA, &PB))) return rc;
     int bad[2] = {0, 0}, offA[2] = {0, 0}, offB[2] = {0, 0};
     HIP_TRY(c, hipMemcpyAsync(&bad[0], PA.bad, sizeof(int), hipMemcpyDeviceToHost, st), "copy");
     HIP_TRY(c, hipMemcpyAsync(&bad[1], PB.bad, sizeof(int), hipMemcpyDeviceToHost, st), "copy");

@@ -206,8 +206,14 @@ size_t align_lds_bytes(int n_samples, int max_a, int max_b);
 // max_lds: LDS bytes a workgroup may use
 hipError_t launch_align(const AlignArgs& a, int n_pairs, int n_cu, size_t max_lds,
                         hipStream_t st);
-hipError_t launch_self_overlap(const Prepared& M, const int* off, int n_mols, int n_samples,
-                               uint2 key, float* out, hipStream_t st);
+struct SelfSet {
+  Prepared M;
+  const int* off;
+  int n;  // molecules
+  float* out;
+};
+hipError_t launch_self_overlap(const SelfSet& a, const SelfSet& b, int n_samples, uint2 key,
+                               hipStream_t st);
 hipError_t launch_adam_pose(float* pose, const float* dT, float* m, float* v, int64_t n_poses,
                             int* step, float lr, float b1, float b2, float eps, hipStream_t st);
 hipError_t launch_best_start(const float* T, int n_pairs, int n_starts, int* best,
@@ -233,8 +239,6 @@ int est_blocks(int64_t n_units);
 hipError_t launch_estimate(const Prepared& A, const Prepared& B, const int* offA,
                            const int* offB, int64_t n_a, int64_t n_b, uint2 key, int anti,
                            double* partials, int nblk, EstOut* out, hipStream_t st);
-hipError_t launch_query_cache(const Prepared& Q, const int* offQ, int64_t n, uint2 key, int anti,
-                              float4* qs, float* qf2, hipStream_t st);
 // sampling steps of one prepared molecule (thresholds, Philox words,
 // components, points); n samples from counter k0
 hipError_t launch_sample_points(const Prepared& P, const int* off, int mol, int max_atoms,
@@ -278,6 +282,22 @@ struct OrderArgs {
 // 16-byte aligned
 int work_order_ints();
 hipError_t launch_work_order(const OrderArgs& o, int* order, int* work, hipStream_t st);
+
+// A molecule set to prepare: all n = n_mols molecules, or the n listed ones.
+struct PrepSet {
+  MolsDev in;
+  Prepared out;
+  const int* which;
+  int n;
+};
+// Prepares both sets (n may be 0), and with o takes the first of the launch
+// order's three steps into work.
+hipError_t launch_prepare_sets(const PrepSet& a, const PrepSet& b, int* flag, const OrderArgs* o,
+                               int* work, hipStream_t st);
+// The query's sample cache, and with o the order's other two steps.
+hipError_t launch_query_cache(const Prepared& Q, const int* offQ, int64_t n, uint2 key, int anti,
+                              float4* qs, float* qf2, const OrderArgs* o, int* order, int* work,
+                              hipStream_t st);
 
 // issue-rate microbenchmarks (measurement support): which = 0 FP32 FMA,
 // 1 v_exp_f32, 2 v_mad_u64_u32, 3 LDS 16-byte reads, 4 FP32 FMA with SGPR
