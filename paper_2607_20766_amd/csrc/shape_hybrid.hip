@@ -304,6 +304,22 @@ struct FoAlignArgs {
   const int* order;  // optional launch order of the row layout: block x takes pair order[x]
 };
 
+// v of lane c of this lane's row of 16.
+__device__ __forceinline__ float row_lane(float v, int c) {
+  const int b = __builtin_bit_cast(int, v);
+  int r = 0;
+  switch (c) {  // a constant at every use
+    case 0: r = __builtin_amdgcn_mov_dpp(b, 0x150, 0xf, 0xf, true); break;
+    case 1: r = __builtin_amdgcn_mov_dpp(b, 0x151, 0xf, 0xf, true); break;
+    case 2: r = __builtin_amdgcn_mov_dpp(b, 0x152, 0xf, 0xf, true); break;
+    case 3: r = __builtin_amdgcn_mov_dpp(b, 0x153, 0xf, 0xf, true); break;
+    case 4: r = __builtin_amdgcn_mov_dpp(b, 0x154, 0xf, 0xf, true); break;
+    case 5: r = __builtin_amdgcn_mov_dpp(b, 0x155, 0xf, 0xf, true); break;
+    default: r = __builtin_amdgcn_mov_dpp(b, 0x156, 0xf, 0xf, true); break;  // row_newbcast:6
+  }
+  return __builtin_bit_cast(float, r);
+}
+
 // Both molecules into LDS (x, y, z, alpha) by the threads tid of n; whether
 // the pair is valid, the same in every thread (any: an OR over the group,
 // after which the staged atoms are visible to it if it is a barrier).
@@ -601,14 +617,24 @@ void k_fo_align(FoAlignArgs a) {
 // per lane (lanes 0-6 of the row, with their moments) and read back by the
 // whole row, instead of all seven in every lane.
 // ---------------------------------------------------------------------------
-// VALU issue bounds it: of 952 instructions per wave and step (30 x 30 atoms)
-// 657 are terms; with the terms of four of B's atoms together and their
-// exponentials in one prioritised group (trans_group) 10,000 pairs x 8 starts
-// x 50 steps take 1.38 ms (1.45 ms four atoms unrolled without the group, 1.45
-// and 1.51 ms with two and one atoms per group).  More waves do not help: with
-// the constants tabulated per distinct width of B, a third of the LDS, six
-// waves per SIMD measured 1.43 ms (one more instruction per atom and row).
-constexpr int kFoTermAtoms = 4;
+// VALU issue bounds it, at two thirds of its LDS bandwidth (a moved atom and RA
+// constants per RA terms): of 952 instructions per wave and step (30 x 30 atoms)
+// 657 are terms.  The terms of a few of B's atoms go together, their exponentials
+// in one prioritised group (trans_group), while the next ones' data are read
+// from LDS: 10,000 pairs x 8 starts x 50 steps (2 rows) 1.45 ms with four atoms
+// unrolled, 1.41 with the group, 1.35 with the data read ahead.  Atoms per group
+// and rows of A: as many as the registers of four waves per SIMD hold twice (2
+// rows: two atoms 1.42 ms, three 1.35, four 1.35; 4 rows, 4,000 pairs of 64 x
+// 20-64 atoms: one 2.23, two 2.16, four spilled 2.82; none read ahead 2.36).
+// More waves do not help: with the constants tabulated per distinct width of B, a
+// third of the LDS, six waves per SIMD measured 3 % more.
+constexpr int fo_term_atoms(int ra) { return ra == 1 ? 6 : (ra == 4 ? 2 : 3); }
+template <int N, int RA>
+struct FoTermGroup {
+  static constexpr int V = N;
+  float4 cj[V];        // moved atoms
+  float2 kp[V * RA];   // their constants with the lane's atoms of A
+};
 template <int RA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void k_fo_align_rows(FoAlignArgs a) {
@@ -664,14 +690,14 @@ void k_fo_align_rows(FoAlignArgs a) {
   }
   float4* mine = sM + (size_t)(wave * 4 + row) * stride;
   const float2* trow = tab + l16;
-  // the pose in every lane of the row; Adam's moments of component
-  // cA = min(l16, 6) in lane l16 (lanes past 6 repeat component 6)
+  // the pose in every lane of the row; its component cA = min(l16, 6) and
+  // Adam's moments of it in lane l16 (lanes past 6 repeat component 6)
   float x[7];
   float* ps = a.pose + item * 7;
 #pragma unroll
   for (int c = 0; c < 7; ++c) x[c] = ps[c];
   const int cA = l16 < 7 ? l16 : 6;
-  float mA = 0.f, vA = 0.f;
+  float xA = ps[cA], mA = 0.f, vA = 0.f;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   float b1t = 1.f, b2t = 1.f;
   float T = 0.f, g[7];
@@ -695,40 +721,62 @@ void k_fo_align_rows(FoAlignArgs a) {
     float O[RA], W[RA], Px[RA], Py[RA], Pz[RA];
 #pragma unroll
     for (int r = 0; r < RA; ++r) O[r] = W[r] = Px[r] = Py[r] = Pz[r] = 0.f;
-    // kFoTermAtoms of B's atoms at a time, their terms' exponentials grouped
-    const auto terms = [&](int j, auto count) {
-      constexpr int V = decltype(count)::value;
-      float4 cj[V];
-      float kk[V * RA], K[V * RA];
+    // a few of B's atoms at a time, the next ones read from LDS meanwhile
+    const auto load = [&](int j, auto& g) {
 #pragma unroll
-      for (int u = 0; u < V; ++u) {
-        cj[u] = mine[j + u];
+      for (int u = 0; u < g.V; ++u) {
+        g.cj[u] = mine[j + u];
+#pragma unroll
+        for (int r = 0; r < RA; ++r) g.kp[u * RA + r] = trow[(j + u) * RA16 + 16 * r];
+      }
+    };
+    const auto terms = [&](const auto& g) {
+      constexpr int V = std::remove_reference_t<decltype(g)>::V;
+      float K[V * RA];
+#pragma unroll
+      for (int u = 0; u < V; ++u)
 #pragma unroll
         for (int r = 0; r < RA; ++r) {
-          const float2 kp = trow[(j + u) * RA16 + 16 * r];
-          const float e = fmaf(-2.f * cx[r], cj[u].x,
-                               fmaf(-2.f * cy[r], cj[u].y,
-                                    fmaf(-2.f * cz[r], cj[u].z, cj[u].w)));
-          kk[u * RA + r] = kp.x;
-          K[u * RA + r] = fmaf(kp.x, e, kp.y);
+          const float e = fmaf(-2.f * cx[r], g.cj[u].x,
+                               fmaf(-2.f * cy[r], g.cj[u].y,
+                                    fmaf(-2.f * cz[r], g.cj[u].z, g.cj[u].w)));
+          K[u * RA + r] = fmaf(g.kp[u * RA + r].x, e, g.kp[u * RA + r].y);
         }
-      }
       trans_group<V * RA>([&](int i) { K[i] = __builtin_amdgcn_exp2f(K[i]); });
 #pragma unroll
       for (int u = 0; u < V; ++u)
 #pragma unroll
         for (int r = 0; r < RA; ++r) {
           O[r] += K[u * RA + r];
-          const float fs = kk[u * RA + r] * K[u * RA + r];
+          const float fs = g.kp[u * RA + r].x * K[u * RA + r];
           W[r] += fs;
-          Px[r] = fmaf(fs, cj[u].x, Px[r]);
-          Py[r] = fmaf(fs, cj[u].y, Py[r]);
-          Pz[r] = fmaf(fs, cj[u].z, Pz[r]);
+          Px[r] = fmaf(fs, g.cj[u].x, Px[r]);
+          Py[r] = fmaf(fs, g.cj[u].y, Py[r]);
+          Pz[r] = fmaf(fs, g.cj[u].z, Pz[r]);
         }
     };
+    constexpr int V = fo_term_atoms(RA);
     int j = 0;
-    for (; j + kFoTermAtoms <= nb; j += kFoTermAtoms) terms(j, std::integral_constant<int, kFoTermAtoms>{});
-    for (; j < nb; ++j) terms(j, std::integral_constant<int, 1>{});
+    const int whole = nb / V * V;
+    if (whole > 0) {
+      FoTermGroup<V, RA> g0, g1;
+      load(0, g0);
+      for (; j + 2 * V <= whole; j += 2 * V) {
+        load(j + V, g1);
+        terms(g0);
+        load(min(j + 2 * V, whole - V), g0);  // the last time read again, unused
+        terms(g1);
+      }
+      if (j < whole) {
+        terms(g0);
+        j = whole;
+      }
+    }
+    for (; j < nb; ++j) {
+      FoTermGroup<1, RA> g;
+      load(j, g);
+      terms(g);
+    }
     wave_lds_sync();  // this start's moved atoms are rewritten next step
     float Fx[RA], Fy[RA], Fz[RA];
 #pragma unroll
@@ -782,14 +830,9 @@ void k_fo_align_rows(FoAlignArgs a) {
     b1t *= b1;
     b2t *= b2;
     const float ic1 = __builtin_amdgcn_rcpf(1.f - b1t), ic2 = __builtin_amdgcn_rcpf(1.f - b2t);
-    float gA = g[0], xA = x[0];
+    float gA = g[0];
 #pragma unroll
-    for (int c = 1; c < 7; ++c) {
-      if (cA == c) {
-        gA = g[c];
-        xA = x[c];
-      }
-    }
+    for (int c = 1; c < 7; ++c) gA = cA == c ? g[c] : gA;
     {
       const float gc = -gA;
       mA = fmaf(b1, mA, (1.f - b1) * gc);
@@ -799,12 +842,13 @@ void k_fo_align_rows(FoAlignArgs a) {
     }
     float xn[7];
 #pragma unroll
-    for (int c = 0; c < 7; ++c) xn[c] = __shfl(xA, (lane & ~15) + c, kWave);
+    for (int c = 0; c < 7; ++c) xn[c] = row_lane(xA, c);
     const float inv = rsqrtf(xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3]);
 #pragma unroll
     for (int c = 0; c < 4; ++c) x[c] = xn[c] * inv;
 #pragma unroll
     for (int c = 4; c < 7; ++c) x[c] = xn[c];
+    xA = cA < 4 ? xA * inv : xA;
   }
   if (live && l16 == 0) {
 #pragma unroll
