@@ -622,13 +622,14 @@ void k_fo_align(FoAlignArgs a) {
 // 657 are terms.  The terms of a few of B's atoms go together, their exponentials
 // in one prioritised group (trans_group), while the next ones' data are read
 // from LDS: 10,000 pairs x 8 starts x 50 steps (2 rows) 1.45 ms with four atoms
-// unrolled, 1.41 with the group, 1.35 with the data read ahead.  Atoms per group
-// and rows of A: as many as the registers of four waves per SIMD hold twice (2
-// rows: two atoms 1.42 ms, three 1.35, four 1.35; 4 rows, 4,000 pairs of 64 x
-// 20-64 atoms: one 2.23, two 2.16, four spilled 2.82; none read ahead 2.36).
-// More waves do not help: with the constants tabulated per distinct width of B, a
-// third of the LDS, six waves per SIMD measured 3 % more.
-constexpr int fo_term_atoms(int ra) { return ra == 1 ? 6 : (ra == 4 ? 2 : 3); }
+// unrolled, 1.41 with the group, 1.35 with the data read ahead.  Atoms per group:
+// as many as the registers of four waves per SIMD hold twice (2 rows: two atoms
+// 1.42 ms, three 1.35, four 1.35; 4 rows, 4,000 pairs of 64 x 20-64 atoms: one
+// 2.23, two 2.16, four spilled 2.82, none read ahead 2.36; 1 row, 8,000 of 16 x
+// 10-50: two 0.77, three 0.71, six 0.73, none read ahead 0.77).  More waves do
+// not help: with the constants tabulated per distinct width of B, a third of the
+// LDS, six waves per SIMD measured 3 % more.
+constexpr int fo_term_atoms(int ra) { return ra == 4 ? 2 : 3; }
 template <int N, int RA>
 struct FoTermGroup {
   static constexpr int V = N;
