@@ -461,19 +461,21 @@ __device__ __forceinline__ void make_rec2(const Atom& a, float rx, float ry, flo
   }
 }
 
-// eval_atoms_x over such records: at least eight exponentials per group.
-template <int S, class Fold>
+// eval_atoms_x over such records: at least eight exponentials per group.  kAhead
+// reads the next group's records before this one's terms, for kernels with too
+// few waves to cover the LDS latency and registers to spare.
+template <int S, bool kAhead, class Fold>
 __device__ __forceinline__ void eval_pairs_x(const AtomRec2* __restrict__ rec, int n,
                                              const float (&rx)[S], const float (&ry)[S],
                                              const float (&rz)[S], const float (&r2)[S],
                                              Fold fold) {
   constexpr int U = S >= 4 ? 1 : 4 / S;  // records per group
-  const auto group = [&](int i, auto count) {
+  const auto group = [&](auto count, auto get) {
     constexpr int V = decltype(count)::value;
     float o[2 * V * S];
 #pragma unroll
     for (int u = 0; u < V; ++u) {
-      const AtomRec2 w = rec[i + u];
+      const AtomRec2 w = get(u);
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -486,28 +488,52 @@ __device__ __forceinline__ void eval_pairs_x(const AtomRec2* __restrict__ rec, i
 #pragma unroll
       for (int s = 0; s < S; ++s) fold(s, o[u * S + s]);
   };
+  using Whole = std::integral_constant<int, U>;
   const int np = rec_pairs(n);
   int i = 0;
-  for (; i + U <= np; i += U) group(i, std::integral_constant<int, U>{});
+  if constexpr (kAhead) {
+    const int whole = np / U * U;
+    if (whole > 0) {
+      AtomRec2 w0[U], w1[U];
+      const auto read = [&](int j, AtomRec2 (&w)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = rec[j + u];
+      };
+      const auto first = [&](int u) { return w0[u]; };
+      const auto second = [&](int u) { return w1[u]; };
+      read(0, w0);
+      for (; i + 2 * U <= whole; i += 2 * U) {
+        read(i + U, w1);
+        group(Whole{}, first);
+        read(min(i + 2 * U, whole - U), w0);  // the last time read again, unused
+        group(Whole{}, second);
+      }
+      if (i < whole) group(Whole{}, first);
+      i = whole;
+    }
+  } else {
+    for (; i + U <= np; i += U) group(Whole{}, [&](int u) { return rec[i + u]; });
+  }
   if constexpr (U > 1)
-    for (; i < np; ++i) group(i, std::integral_constant<int, 1>{});
+    for (; i < np; ++i)
+      group(std::integral_constant<int, 1>{}, [&](int u) { return rec[i + u]; });
 }
 
 // Union complement q = prod(1 - o_i) (the caller initialises q to 1, u = 1 - q),
 // and the first-order density m with it, over pair records.
-template <int S>
+template <int S, bool kAhead = false>
 __device__ __forceinline__ void eval_union_x2(const AtomRec2* rec, int n, const float (&rx)[S],
                                               const float (&ry)[S], const float (&rz)[S],
                                               const float (&r2)[S], float (&q)[S]) {
-  eval_pairs_x<S>(rec, n, rx, ry, rz, r2,
+  eval_pairs_x<S, kAhead>(rec, n, rx, ry, rz, r2,
                   [&](int s, float o) { q[s] = fmaf(-q[s], o, q[s]); });
 }
-template <int S>
+template <int S, bool kAhead = false>
 __device__ __forceinline__ void eval_density_x2(const AtomRec2* rec, int n, const float (&rx)[S],
                                                 const float (&ry)[S], const float (&rz)[S],
                                                 const float (&r2)[S], float (&m)[S],
                                                 float (&q)[S]) {
-  eval_pairs_x<S>(rec, n, rx, ry, rz, r2, [&](int s, float o) {
+  eval_pairs_x<S, kAhead>(rec, n, rx, ry, rz, r2, [&](int s, float o) {
     m[s] += o;
     q[s] = fmaf(-q[s], o, q[s]);
   });

@@ -802,6 +802,8 @@ void k_screen(ScreenArgs a) {
 // Latency bounds such a screen (a pair's rounds are a chain): 501 molecules,
 // SE(T) <= 0.005, 358 -> 112 us; one 277 -> 74 us.  One slot per wave (two
 // LDS reads per term) 135 us, four slots 141 us, eight rounds at a time 144 us.
+// With a few waves per SIMD the next records are read ahead: 110 -> 105 us (one
+// molecule, 16,384 samples per side 129 -> 121).
 constexpr int kSplitSlots = 4;  // rounds of 256 samples per side
 constexpr int kSplitS = 2;      // slots per wave
 constexpr int kSplitRounds = 4;
@@ -851,7 +853,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_screen_split(ScreenArgs a) {
           f2[s] = a.qf2[k];
           q[s] = 1.0f;
         }
-        eval_union_x2<S>(lds.BA, nb, rx, ry, rz, r2, q);
+        eval_union_x2<S, true>(lds.BA, nb, rx, ry, rz, r2, q);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           sF[g][0][t + s][lane] = w[s] * (1.0f - q[s]);
@@ -866,8 +868,8 @@ __global__ __launch_bounds__(kSplitThreads) void k_screen_split(ScreenArgs a) {
           r2[s] = norm2(rx[s], ry[s], rz[s]);
           mb[s] = 0.0f; qb[s] = 1.0f; qa[s] = 1.0f;
         }
-        eval_density_x2<S>(lds.BB, nb, rx, ry, rz, r2, mb, qb);
-        eval_union_x2<S>(lds.AB, nq, rx, ry, rz, r2, qa);
+        eval_density_x2<S, true>(lds.BB, nb, rx, ry, rz, r2, mb, qb);
+        eval_union_x2<S, true>(lds.AB, nq, rx, ry, rz, r2, qa);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           const float ub = 1.0f - qb[s];
