@@ -145,10 +145,11 @@ int shape_estimate(shape_ctx* ctx, const shape_mols* A, const shape_mols* B,
  * device memory (code that must not call hipMalloc: tight serving loops,
  * harnesses that forbid allocation).  Same arguments, checks, kernels and
  * results (bit for bit) as shape_estimate, but the call allocates nothing:
- * the prepared molecule records, the per-block partial sums and the device
- * copy of the result live in a fixed array of the library's device code
- * (about 1.5 MiB, one copy per GPU, held until the process ends), and the
- * context's own scratch is neither used nor grown.  Limits: n_a and n_b at
+ * the prepared molecule records and the per-block partial sums live in a fixed
+ * array of the library's device code (about 1.5 MiB, one copy per GPU, held
+ * until the process ends), the result in a pinned host buffer that the context
+ * has had since its creation, and the context's own scratch is neither used nor
+ * grown.  Limits: n_a and n_b at
  * most SHAPE_NOALLOC_MAX_SAMPLES, and A->n_atoms, B->n_atoms at most
  * SHAPE_MAX_ATOMS (else SHAPE_E_RANGE).  Every call on one GPU, from any
  * context, shares that GPU's array: calls that overlap in time on one GPU
