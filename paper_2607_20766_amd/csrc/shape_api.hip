@@ -1491,7 +1491,7 @@ int shape_mlp_infer(shape_ctx* c, const float* f_q, const float* f_lib, const in
     if ((rc = ensure(c, S_MLP_PACK, shape::mlp_pack_bytes(), &packed))) return rc;
     KernelTimer timer(c, (hipStream_t)stream);
     HIP_TRY(c, shape::launch_mlp_infer(f_q, f_lib, qidx, idx, n, fo_cross, mean, inv_std, params,
-                                       packed, out, (hipStream_t)stream),
+                                       packed, out, (hipStream_t)stream, c->n_cu),
             "surrogate inference kernel");
     timer.stop();
     return SHAPE_OK;
@@ -1520,7 +1520,7 @@ int shape_mlp_forward(shape_ctx* c, const float* f_q, const float* f_lib, const 
     float* const h[3] = {h1, h2, h3};
     KernelTimer timer(c, (hipStream_t)stream);
     HIP_TRY(c, shape::launch_mlp_infer(f_q, f_lib, qidx, idx, n, fo_cross, mean, inv_std, params,
-                                       packed, out, (hipStream_t)stream, x, h),
+                                       packed, out, (hipStream_t)stream, c->n_cu, x, h),
             "surrogate forward kernel");
     timer.stop();
     return SHAPE_OK;

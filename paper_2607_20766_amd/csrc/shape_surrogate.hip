@@ -2488,14 +2488,19 @@ size_t mlp_pack_bytes() { return (size_t)kMlpPackElems * sizeof(short); }
 
 // Pairs per workgroup of the fused network kernel: 64 for the training
 // forward (a minibatch of a few thousand rows then spreads over twice the
-// workgroups: 0.66 against 0.68 s for the training run), 128 for inference
-// over large sets (half the weight reads; the two measured equal there).
-static int mlp_rows(bool training) { return training ? 64 : 128; }
+// workgroups: 0.66 against 0.68 s for the training run) and for inference over
+// up to 400 rows per compute unit, whose last workgroups of 128 would run on a
+// half-empty chip (64 : 128 rows, us: 40,000 rows 22 : 25, 80,000 32 : 37, 100,000
+// 39 : 43); 128 beyond (half the weight reads: 130,000 45 : 44, 500,000 149 : 147,
+// 10^6 288 : 278).
+static int mlp_rows(int n, bool training, int n_cu) {
+  return training || n <= 400 * n_cu ? 64 : 128;
+}
 
 hipError_t launch_mlp_infer(const float* fq, const float* flib, const int* qidx, const int* idx,
                             int n, const float* fo_cross, const float* mean,
                             const float* inv_std, const float* params, void* packed,
-                            float* out, hipStream_t st, float* x_out,
+                            float* out, hipStream_t st, int n_cu, float* x_out,
                             float* const* h_out) {
   hipLaunchKernelGGL(k_mlp_pack, dim3((kMlpPackElems + 255) / 256), dim3(256), 0, st, params,
                      (short*)packed);
@@ -2522,12 +2527,10 @@ hipError_t launch_mlp_infer(const float* fq, const float* flib, const int* qidx,
   a.out = out;
   a.x_out = x_out;
   for (int l = 0; l < 3; ++l) a.h_out[l] = h_out ? h_out[l] : nullptr;
-  const int rows = mlp_rows(x_out != nullptr);
+  const int rows = mlp_rows(n, x_out != nullptr, n_cu);
   const dim3 grid((unsigned)((n + rows - 1) / rows));
-  if (x_out && rows == 64)
+  if (x_out)
     hipLaunchKernelGGL((k_mlp_infer<64, true>), grid, dim3(256), 0, st, a);
-  else if (x_out)
-    hipLaunchKernelGGL((k_mlp_infer<128, true>), grid, dim3(256), 0, st, a);
   else if (rows == 64)
     hipLaunchKernelGGL((k_mlp_infer<64, false>), grid, dim3(256), 0, st, a);
   else

@@ -343,6 +343,23 @@ def test_triage_gain(eng):
     assert np.all((se <= 0.005 * (1 + 1e-6)) | (n_used == 65536))
 
 
+def test_fused_inference_workgroup_rows(eng):
+    """Inference over few rows (64 per workgroup) and many (128) gives the same
+    bits row by row."""
+    rng = np.random.default_rng(3)
+    n = 400 * torch.cuda.get_device_properties(eng.torch_device).multi_processor_count + 65
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda()
+    fq, fl = d(rng.normal(size=(1, 24))), d(rng.normal(size=(n, 24)))
+    mean, inv_std = d(rng.normal(size=96)), d(rng.uniform(0.5, 2.0, 96))
+    params, fo = d(init_params(7)), d(rng.uniform(1, 40, n))
+    print(f"case: inference of {n} rows in one call and in parts", flush=True)
+    whole = eng.shape_mlp_infer(fq, fl, mean, inv_std, params, n=n, fo_cross=fo)
+    for lo, hi in ((0, 1), (0, n - 65), (n - 1000, n)):
+        part = eng.shape_mlp_infer(fq, fl[lo:hi].contiguous(), mean, inv_std, params, n=hi - lo,
+                                   fo_cross=fo[lo:hi].contiguous())
+        assert torch.equal(part, whole[lo:hi]), (lo, hi)
+
+
 @pytest.mark.parametrize("n,with_fo,with_idx", [(1000, True, False), (300, False, True),
                                                 (128, True, True), (1, False, False)])
 def test_fused_inference_matches_layers(eng, n, with_fo, with_idx):
