@@ -90,6 +90,7 @@ struct shape_ctx {
   void* noalloc = nullptr;        // device address of this GPU's copy of `scratch`
   shape::EstOut* est_out = nullptr;      // pinned host memory an estimate is written to
   shape::EstOut* est_out_dev = nullptr;  // its device address
+  int* short_order = nullptr;            // launch order of short alignment grids
 };
 
 struct shape_graph {
@@ -300,10 +301,12 @@ int prepare(shape_ctx* c, const shape_mols* m, bool q, hipStream_t st, shape::Pr
 
 // Both sets of a call, A in the query slots and B (or its listed subset) in the
 // library slots, with the first step of the launch order o when given (into
-// work): one launch unless preparations are kept for reuse.
+// work), or all of it (into order, without work): one launch unless preparations
+// are kept for reuse.
 int prepare_sets(shape_ctx* c, const shape_mols* A, const shape_mols* B, hipStream_t st,
                  shape::Prepared* PA, shape::Prepared* PB, const int32_t* subset = nullptr,
-                 int32_t n_subset = 0, const shape::OrderArgs* o = nullptr, int* work = nullptr) {
+                 int32_t n_subset = 0, const shape::OrderArgs* o = nullptr, int* work = nullptr,
+                 int* order = nullptr) {
   int rc;
   shape::PrepSet a{mols_dev(A), {}, nullptr, 0}, b{mols_dev(B), {}, nullptr, 0};
   if (c->prep_cache) {
@@ -320,7 +323,7 @@ int prepare_sets(shape_ctx* c, const shape_mols* A, const shape_mols* B, hipStre
     b.which = subset;
     b.n = subset ? n_subset : B->n_mols;
   }
-  HIP_TRY(c, shape::launch_prepare_sets(a, b, c->flag, o, work, st), "prepare kernel");
+  HIP_TRY(c, shape::launch_prepare_sets(a, b, c->flag, o, work, order, st), "prepare kernel");
   return SHAPE_OK;
 }
 
@@ -411,6 +414,28 @@ shape::OrderArgs align_order_args(const shape_mols* A, const shape_mols* B, int 
   o.wB = 2 * S;
   o.w0 = 24 + 4 * S;
   return o;
+}
+
+// Prepares an alignment's two sets and its launch order: three launches of their
+// own for long grids, beside the preparation for short ones.  These hold up to
+// four pairs per compute unit, all resident at once, so that the order only
+// decides which pairs share a compute unit: the largest start on different ones.
+// One evaluation, 16 starts, 2,048 samples: 300 pairs of 15-45 atoms 177 -> 150 us,
+// 270 of 50-100 363 -> 293 (163 and 307 with the order in three launches).
+int align_prepare(shape_ctx* c, const shape_mols* A, const shape_mols* B, int n_starts,
+                  int n_steps, hipStream_t st, shape::Prepared* PA, shape::Prepared* PB,
+                  const int** order) {
+  int rc;
+  WorkOrder wo;
+  if ((rc = work_order_slot(c, A->n_mols, kOrderAlignPerCu, &wo))) return rc;
+  const shape::OrderArgs o = align_order_args(A, B, n_starts, n_steps);
+  *order = wo.order ? wo.order : c->short_order;
+  if ((rc = prepare_sets(c, A, B, st, PA, PB, nullptr, 0, wo.order ? nullptr : &o, nullptr,
+                         c->short_order)))
+    return rc;
+  if (wo.order)
+    HIP_TRY(c, shape::launch_work_order(o, wo.order, wo.work, st), "launch order kernels");
+  return SHAPE_OK;
 }
 
 // Validation, molecule preparation and the query-side sample cache of a
@@ -585,6 +610,9 @@ int shape_create(shape_ctx** out, int device) {
     e = hipHostMalloc((void**)&c->est_out, sizeof(shape::EstOut), hipHostMallocMapped);
   if (e == hipSuccess)
     e = hipHostGetDevicePointer((void**)&c->est_out_dev, c->est_out, 0);
+  // not grown on demand: a captured call needs no earlier one of its kind
+  if (e == hipSuccess)
+    e = hipMalloc(&c->short_order, (size_t)kOrderAlignPerCu * c->n_cu * sizeof(int));
   if (e != hipSuccess) {
     if (c->est_out) (void)hipHostFree(c->est_out);
     if (c->flag) (void)hipFree(c->flag);
@@ -614,6 +642,7 @@ void shape_destroy(shape_ctx* c) {
     (void)hipEventDestroy(e.second);
   }
   if (c->est_out) (void)hipHostFree(c->est_out);
+  if (c->short_order) (void)hipFree(c->short_order);
   if (c->flag) (void)hipFree(c->flag);
   delete c;
 }
@@ -1068,11 +1097,7 @@ int align_launch(shape_ctx* c, const shape_mols* A, const shape_mols* B,
                  const shape::Prepared& PA, const shape::Prepared& PB, int32_t n_starts,
                  const float* pose, const float* O_aa, const float* O_bb, int32_t n_samples,
                  uint64_t seed, hipStream_t st, float* T, float* grad,
-                 const WorkOrder& wo) {
-  if (wo.order)
-    HIP_TRY(c, shape::launch_work_order(align_order_args(A, B, n_starts, 0), wo.order, wo.work,
-                                        st),
-            "launch order kernels");
+                 const int* order) {
   shape::AlignArgs a;
   a.A = PA;
   a.offA = A->atom_offset;
@@ -1091,7 +1116,7 @@ int align_launch(shape_ctx* c, const shape_mols* A, const shape_mols* B,
   a.n_steps = 0;
   a.lr = 0.f;
   a.pose_out = nullptr;
-  a.order = wo.order;
+  a.order = order;
   HIP_TRY(c, shape::launch_align(a, A->n_mols, c->n_cu, c->lds_per_block, st), "alignment kernel");
   return SHAPE_OK;
 }
@@ -1111,13 +1136,12 @@ int shape_align_grad(shape_ctx* c, const shape_mols* A, const shape_mols* B, int
     if (!pose || !O_aa || !O_bb || !T) return fail(c, SHAPE_E_INVAL, "NULL array");
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)stream;
-    WorkOrder wo;
-    if ((rc = work_order_slot(c, A->n_mols, kOrderAlignPerCu, &wo))) return rc;
+    const int* order;
     shape::Prepared PA, PB;
-    if ((rc = prepare_sets(c, A, B, st, &PA, &PB))) return rc;
+    if ((rc = align_prepare(c, A, B, n_starts, 0, st, &PA, &PB, &order))) return rc;
     KernelTimer timer(c, st);
     rc = align_launch(c, A, B, PA, PB, n_starts, pose, O_aa, O_bb, n_samples, seed, st, T,
-                      dT_dpose, wo);
+                      dT_dpose, order);
     timer.stop();
     return rc;
   } catch (...) {
@@ -1161,9 +1185,8 @@ int shape_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t 
     void *saa, *sbb;
     if ((rc = ensure(c, S_SELF_A, (size_t)pairs * sizeof(float), &saa))) return rc;
     if ((rc = ensure(c, S_SELF_B, (size_t)pairs * sizeof(float), &sbb))) return rc;
-    WorkOrder wo;
-    if ((rc = work_order_slot(c, pairs, kOrderAlignPerCu, &wo))) return rc;
-    if ((rc = prepare_sets(c, A, B, st, &PA, &PB))) return rc;
+    const int* order;
+    if ((rc = align_prepare(c, A, B, n_starts, n_steps, st, &PA, &PB, &order))) return rc;
     HIP_TRY(c, shape::launch_self_overlap({PA, A->atom_offset, pairs, (float*)saa},
                                           {PB, B->atom_offset, pairs, (float*)sbb}, n_samples,
                                           key_of(seed), st),
@@ -1189,11 +1212,7 @@ int shape_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t 
     a.n_steps = n_steps;
     a.lr = lr;
     a.pose_out = pose;
-    a.order = wo.order;
-    if (wo.order)
-      HIP_TRY(c, shape::launch_work_order(align_order_args(A, B, n_starts, n_steps), wo.order,
-                                          wo.work, st),
-              "launch order kernels");
+    a.order = order;
     KernelTimer timer(c, st);
     HIP_TRY(c, shape::launch_align(a, pairs, c->n_cu, c->lds_per_block, st), "alignment kernel");
     timer.stop();

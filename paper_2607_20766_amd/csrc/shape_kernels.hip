@@ -1109,8 +1109,7 @@ __device__ __forceinline__ void order_share(int n, int& begin, int& end) {
 // hist[k][b]: pairs of block b's share with key k (bucket-major, so that
 // the scan reads each bucket's counts as 16 consecutive 16-byte words)
 template <int N>
-__device__ __forceinline__ void order_hist(const OrderArgs& o, int* __restrict__ hist) {
-  __shared__ int h[kOrderBuckets];
+__device__ __forceinline__ void order_hist(const OrderArgs& o, int* __restrict__ hist, int* h) {
   for (int k = threadIdx.x; k < kOrderBuckets; k += N) h[k] = 0;
   __syncthreads();
   int begin, end;
@@ -1122,7 +1121,28 @@ __device__ __forceinline__ void order_hist(const OrderArgs& o, int* __restrict__
 }
 __global__ __launch_bounds__(kOrderThreads) void k_order_hist(OrderArgs o,
                                                               int* __restrict__ hist) {
-  order_hist<kOrderThreads>(o, hist);
+  __shared__ int h[kOrderBuckets];
+  order_hist<kOrderThreads>(o, hist, h);
+}
+
+// The whole order of a short grid (per_xcd = 0) by one block of kOrderKeys
+// threads, key k at thread k; h [kOrderKeys] in LDS.
+__device__ __forceinline__ void order_short(const OrderArgs& o, int* __restrict__ order, int* h) {
+  const int t = threadIdx.x;
+  h[t] = 0;
+  __syncthreads();
+  for (int p = t; p < o.n; p += kOrderKeys) atomicAdd(&h[order_key(o, p)], 1);
+  __syncthreads();
+  const int mine = h[t];
+  for (int d = 1; d < kOrderKeys; d <<= 1) {  // h[t] = pairs with keys >= t
+    const int add = t + d < kOrderKeys ? h[t + d] : 0;
+    __syncthreads();
+    h[t] += add;
+    __syncthreads();
+  }
+  h[t] -= mine;
+  __syncthreads();
+  for (int p = t; p < o.n; p += kOrderKeys) order[atomicAdd(&h[order_key(o, p)], 1)] = p;
 }
 
 // One thread per key k: replaces hist[k][b] by the number of pairs with key k
@@ -1224,14 +1244,22 @@ hipError_t launch_work_order(const OrderArgs& o, int* order, int* work, hipStrea
 // gradients of 16 starts 180 -> 171).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_prepare_sets(PrepSet a, PrepSet b, int* __restrict__ flag,
-                                                      OrderArgs o, int* __restrict__ hist) {
+                                                      OrderArgs o, int* __restrict__ hist,
+                                                      int* __restrict__ order) {
+  __shared__ int h[kOrderBuckets];
   int blk = blockIdx.x;
   if (hist) {  // the order's blocks come first
     if (blk < kOrderBlocks) {
-      order_hist<256>(o, hist);
+      order_hist<256>(o, hist, h);
       return;
     }
     blk -= kOrderBlocks;
+  } else if (order) {
+    if (blk == 0) {
+      order_short(o, order, h);
+      return;
+    }
+    --blk;
   }
   const int blocks_a = (a.n + kPrepWaves - 1) / kPrepWaves;
   const bool first = blk < blocks_a;
@@ -1256,12 +1284,13 @@ __global__ __launch_bounds__(256) void k_query_cache(Prepared Qp, const int* __r
 }
 
 hipError_t launch_prepare_sets(const PrepSet& a, const PrepSet& b, int* flag, const OrderArgs* o,
-                               int* work, hipStream_t st) {
+                               int* work, int* order, hipStream_t st) {
   const int64_t blocks = ((int64_t)a.n + kPrepWaves - 1) / kPrepWaves +
-                         ((int64_t)b.n + kPrepWaves - 1) / kPrepWaves + (o ? kOrderBlocks : 0);
+                         ((int64_t)b.n + kPrepWaves - 1) / kPrepWaves +
+                         (!o ? 0 : (work ? kOrderBlocks : 1));
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(k_prepare_sets, dim3((unsigned)blocks), dim3(256), 0, st, a, b, flag,
-                     o ? *o : OrderArgs{}, o ? work : nullptr);
+                     o ? *o : OrderArgs{}, o ? work : nullptr, o ? order : nullptr);
   return hipGetLastError();
 }
 

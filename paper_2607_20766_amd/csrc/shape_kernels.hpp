@@ -291,9 +291,10 @@ struct PrepSet {
   int n;
 };
 // Prepares both sets (n may be 0), and with o takes the first of the launch
-// order's three steps into work.
+// order's three steps into work, or without work the whole order of a short grid
+// (per_xcd = 0) into order.
 hipError_t launch_prepare_sets(const PrepSet& a, const PrepSet& b, int* flag, const OrderArgs* o,
-                               int* work, hipStream_t st);
+                               int* work, int* order, hipStream_t st);
 // The query's sample cache, and with o the order's other two steps.
 hipError_t launch_query_cache(const Prepared& Q, const int* offQ, int64_t n, uint2 key, int anti,
                               float4* qs, float* qf2, const OrderArgs* o, int* order, int* work,

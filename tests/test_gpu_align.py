@@ -8,7 +8,7 @@ import torch
 
 import oracle as O
 from paper_2607_20766_amd import molgen
-from paper_2607_20766_amd.engine import Engine, LAMBDA_P27, ShapeAlignFn
+from paper_2607_20766_amd.engine import Engine, LAMBDA_P27, ShapeAlignFn, ShapeError
 from tests.gpu_common import oracle_mol, rel_err, require_gpu
 
 pytestmark = pytest.mark.gpu
@@ -184,6 +184,39 @@ def test_few_and_many_starts_same_bits(eng, n_samples, na, nb):
             assert all(np.all(np.isfinite(x)) for x in ref)
         for k in range(4):
             assert np.array_equal(got[k], ref[k]), (starts, k)
+
+
+@pytest.mark.parametrize("n_pairs", [1, 2, 255, 257, 1023])
+def test_short_grids_in_launch_order(eng, n_pairs):
+    """Alignments of few pairs run the largest first: each pair's T, gradient and
+    final pose are the bits it has in the reversed call, also beside an invalid
+    pair, and without the preparations of an earlier call."""
+    rng = np.random.default_rng(n_pairs)
+    base = molgen.library(31, 40, 1, 40, workers=1)
+    starts, ns = 9, 128
+    a, b = rng.integers(0, 40, n_pairs), rng.integers(0, 40, n_pairs)
+    poses = molgen.random_poses(32, n_pairs, starts).astype(np.float32)
+    print(f"case: {n_pairs} pairs in launch order", flush=True)
+    out = []
+    for perm in (np.arange(n_pairs), np.arange(n_pairs)[::-1]):
+        A = eng.molecules(molgen.MolSet.concat([base.mol(i) for i in a[perm]]), mol_id=a[perm])
+        B = eng.molecules(molgen.MolSet.concat([base.mol(i) for i in b[perm]]), mol_id=b[perm])
+        bad = n_pairs // 2 if n_pairs > 1 else -1
+        if bad >= 0:
+            B.alpha[int(B.offsets[int(np.where(perm == bad)[0][0])])] = -1.0
+        saa, sbb = eng.shape_self_overlap(A, ns), eng.shape_self_overlap(B, ns)
+        pose = torch.from_numpy(poses[perm].copy()).to(eng.torch_device)
+        T, g = eng.shape_align_grad(A, B, pose, saa, sbb, ns)
+        Tf, _ = eng.shape_align(A, B, pose, n_samples=ns, n_steps=2)
+        got = [x.cpu().numpy()[np.argsort(perm)] for x in (T, g, Tf, pose)]
+        if bad >= 0:
+            assert all(np.isnan(x[bad]).all() for x in got[:3])
+            with pytest.raises(ShapeError):
+                eng.shape_check_data()
+        keep = np.arange(n_pairs) != bad
+        assert all(np.isfinite(x[keep]).all() for x in got)
+        out.append([x[keep] for x in got])
+    assert all(np.array_equal(x, y) for x, y in zip(*out))
 
 
 @pytest.mark.parametrize("n_samples", [2, 255, 2047, 2049, 10000])
