@@ -90,7 +90,7 @@ struct shape_ctx {
   void* noalloc = nullptr;        // device address of this GPU's copy of `scratch`
   shape::EstOut* est_out = nullptr;      // pinned host memory an estimate is written to
   shape::EstOut* est_out_dev = nullptr;  // its device address
-  int* short_order = nullptr;            // launch order of short alignment grids
+  int* short_order = nullptr;            // launch order of short grids
 };
 
 struct shape_graph {
@@ -364,14 +364,18 @@ struct ProfRange {
 };
 
 // Grids of one workgroup per pair are launched in the order
-// shape::launch_work_order computes (largest estimated work first; a few
-// microseconds) when they hold at least this many pairs per compute unit:
-// fewer run in a few waves of workgroups, where the order hardly changes
-// when the last ones finish.  Screens run up to eight 64-lane workgroups per
-// SIMD, alignments four 256-lane workgroups per compute unit.
+// shape::launch_work_order computes (largest estimated work first; three small
+// steps) when they hold at least this many pairs per compute unit.  Shorter grids
+// are ordered by one block (order_short): their workgroups are resident at once or
+// nearly so, and the order decides which of them share a compute unit.
 constexpr int kOrderScreenPerCu = 16;
 constexpr int kOrderAlignPerCu = 4;
 constexpr int kOrderFoAlignPerCu = 16;
+// Shorter grids are ordered by one block (of the preparation launch, if there is
+// one) into a buffer of the context's.
+constexpr int kOrderShortPerCu = 16;
+static_assert(kOrderShortPerCu >= kOrderScreenPerCu && kOrderShortPerCu >= kOrderAlignPerCu &&
+              kOrderShortPerCu >= kOrderFoAlignPerCu, "short_order holds every short grid");
 // Features: the order groups molecules of one size into a wave (it matters
 // at any size, but its three launches cost a few microseconds).
 constexpr int kOrderFeaturesPerCu = 512;
@@ -513,13 +517,25 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   o.round_pair = 2 * (int64_t)round_side;
   o.cap = cap;
   const shape::OrderArgs* order = wo.order ? &o : nullptr;
+  // Short grids: from the preparation launch, one order over all blocks, every
+  // second turn over the compute units backwards, so that a large pair and a
+  // small one share one: adaptive 300 molecules 102 -> 86 us, 501 102 : 103, 1,000
+  // 169 -> 154, 2,000 273 -> 238, 4,000 418 -> 396; fixed, 4,096 per side, 501 74 ->
+  // 65, 1,000 122 -> 102, 4,000 330 -> 304 (without the turns 2,000 243, 1,000
+  // fixed 106).
+  int* short_order = nullptr;
+  if (!wo.order && n_pairs > c->n_cu) {
+    short_order = c->short_order;
+    o.per_xcd = 0;
+    o.snake = c->n_cu;
+  }
   shape::Prepared PQ, PL;
   // a screen of a small subset of a large library prepares only that subset
   // (unless the whole set is already prepared for reuse)
   const bool subset = pairs && (int64_t)n_pairs * 4 < lib->n_mols &&
                       !(c->prep_cache && c->prepared[1].same(lib));
   if ((rc = prepare_sets(c, query, lib, st, &PQ, &PL, subset ? pairs : nullptr,
-                         subset ? n_pairs : 0, order, wo.work)))
+                         subset ? n_pairs : 0, short_order ? &o : order, wo.work, short_order)))
     return rc;
   const uint2 key = key_of(prm->seed);
   HIP_TRY(c, shape::launch_query_cache(PQ, query->atom_offset, n_cache, key, anti ? 1 : 0,
@@ -550,7 +566,7 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   a->O_aa = out->O_aa;
   a->O_bb = out->O_bb;
   a->n_used = out->n_used;
-  a->order = wo.order;
+  a->order = wo.order ? wo.order : short_order;
   return SHAPE_OK;
 }
 
@@ -612,7 +628,7 @@ int shape_create(shape_ctx** out, int device) {
     e = hipHostGetDevicePointer((void**)&c->est_out_dev, c->est_out, 0);
   // not grown on demand: a captured call needs no earlier one of its kind
   if (e == hipSuccess)
-    e = hipMalloc(&c->short_order, (size_t)kOrderAlignPerCu * c->n_cu * sizeof(int));
+    e = hipMalloc(&c->short_order, (size_t)kOrderShortPerCu * c->n_cu * sizeof(int));
   if (e != hipSuccess) {
     if (c->est_out) (void)hipHostFree(c->est_out);
     if (c->flag) (void)hipFree(c->flag);
@@ -1273,25 +1289,36 @@ int shape_fo_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)stream;
     WorkOrder wo;
-    if (shape::fo_align_pair_major(A->max_atoms, B->max_atoms, n_starts) &&
-        (rc = work_order_slot(c, B->n_mols, kOrderFoAlignPerCu, &wo)))
-      return rc;
-    if (wo.order) {
+    const bool rows = shape::fo_align_pair_major(A->max_atoms, B->max_atoms, n_starts);
+    if (rows && (rc = work_order_slot(c, B->n_mols, kOrderFoAlignPerCu, &wo))) return rc;
+    const int* order = wo.order;
+    // Short grids: a launch of one block (4 us), worth it from about a thousand
+    // atoms and steps per start on: 50 steps, 8 starts, 30 x 10-50 atoms, 1,000
+    // pairs 234 -> 213 us, 2,000 445 -> 355, 4,000 686 -> 573; 25 steps of 12 x
+    // 4-20 53 -> 56.
+    if (rows && (wo.order ||
+                 (B->n_mols > c->n_cu && (int64_t)n_steps * B->max_atoms >= 1000))) {
       // per step and start: one pass over B's atoms (A's atoms sit on the
       // lanes) and the rotation, sums and Adam step, worth about 4 atoms
       shape::OrderArgs o{};
       o.n = B->n_mols;
-      o.per_xcd = 1;
+      o.per_xcd = wo.order ? 1 : 0;
       o.offB = B->atom_offset;
       o.nB_mols = B->n_mols;
       o.max_b = B->max_atoms;
       o.wB = 1;
       o.w0 = 4;
-      HIP_TRY(c, shape::launch_work_order(o, wo.order, wo.work, st), "launch order kernels");
+      if (wo.order) {
+        HIP_TRY(c, shape::launch_work_order(o, wo.order, wo.work, st), "launch order kernels");
+      } else {
+        order = c->short_order;
+        HIP_TRY(c, shape::launch_prepare_sets({}, {}, c->flag, &o, nullptr, c->short_order, st),
+                "launch order kernel");
+      }
     }
     KernelTimer timer(c, st);
     HIP_TRY(c, shape::launch_fo_align(mols_dev(A), mols_dev(B), n_starts, n_steps, lr, c->flag,
-                                      pose, T, grad, st, wo.order, c->n_cu),
+                                      pose, T, grad, st, order, c->n_cu),
             "first-order alignment kernel");
     timer.stop();
     return SHAPE_OK;

@@ -1142,7 +1142,14 @@ __device__ __forceinline__ void order_short(const OrderArgs& o, int* __restrict_
   }
   h[t] -= mine;
   __syncthreads();
-  for (int p = t; p < o.n; p += kOrderKeys) order[atomicAdd(&h[order_key(o, p)], 1)] = p;
+  for (int p = t; p < o.n; p += kOrderKeys) {
+    int r = atomicAdd(&h[order_key(o, p)], 1);
+    if (o.snake > 0 && (r / o.snake & 1)) {  // odd turns over the compute units backwards
+      const int first = r / o.snake * o.snake;
+      r = first + min(o.snake, o.n - first) - 1 - (r - first);
+    }
+    order[r] = p;
+  }
 }
 
 // One thread per key k: replaces hist[k][b] by the number of pairs with key k

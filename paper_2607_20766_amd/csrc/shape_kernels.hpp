@@ -277,6 +277,7 @@ struct OrderArgs {
   uint32_t wA, wB, w0;
   const int* n_start;   // optional per-pair sample budgets
   int64_t round_pair, cap;
+  int snake;            // short grids: every second run of this many blocks ascending
 };
 // order: int [n] (a permutation of [0, n)); work: work_order_ints() ints,
 // 16-byte aligned

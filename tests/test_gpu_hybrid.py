@@ -128,6 +128,27 @@ def test_starts_per_wave_same_bits(eng, max_b, n_starts):
         assert torch.equal(pose, out[0][2])
 
 
+@pytest.mark.parametrize("n", [257, 1025, 4095])
+def test_short_alignments_in_launch_order(eng, n):
+    """First-order alignments of more pairs than compute units, up to sixteen times
+    as many, run the largest first: each pair has the bits of a call too short
+    for an order."""
+    base = molgen.library(64, 50, 1, 40, workers=1)
+    q = eng.molecules(molgen.molecule(65, 0, 20))
+    order = [(7 * i) % 50 for i in range(n)]
+    lib = eng.molecules(molgen.MolSet.concat([base.mol(i) for i in order]))
+    few = eng.molecules(base)
+    first = torch.arange(35, dtype=torch.float32, device=eng.torch_device).view(1, 5, 7) * 0.05 + 0.2
+    print(f"case: {n} alignments in launch order", flush=True)
+    pose = first.expand(n, 5, 7).contiguous()
+    T, _ = eng.shape_fo_align(q, lib, pose, n_steps=30)
+    pose_few = first.expand(50, 5, 7).contiguous()
+    T_few, _ = eng.shape_fo_align(q, few, pose_few, n_steps=30)
+    idx = torch.tensor(order, device=eng.torch_device)
+    assert torch.isfinite(T_few).all()
+    assert torch.equal(T, T_few[idx]) and torch.equal(pose, pose_few[idx])
+
+
 def test_shared_query_broadcasts(eng, pairs):
     """A single A molecule serves every pair, as the same molecule repeated."""
     _, B = pairs

@@ -173,6 +173,28 @@ def test_rounds_at_a_time_same_bits(eng, pairs_per_cu, atoms, kw, anti):
         eng.sampling(False)
 
 
+@pytest.mark.parametrize("n", [257, 511, 513, 769, 4095])
+def test_short_screens_in_launch_order(eng, n):
+    """Screens of more pairs than compute units, up to sixteen times as many, run
+    in an order of their own: every pair has the bits of calls too short for one,
+    with repeated and invalid pairs and seeded budgets."""
+    L = molgen.library(33, 60, 1, 40, workers=1)
+    lib, Q = eng.molecules(L), eng.molecules(molgen.molecule(34, 0, 20), mol_id=[QUERY_ID])
+    dev = eng.torch_device
+    pairs = (torch.arange(n, dtype=torch.int32, device=dev) * 17) % (lib.n_mols + 2) - 1
+    n_start = (torch.arange(n, dtype=torch.int32, device=dev) * 37) % 3000
+    kw = dict(mode=SHAPE_SCREEN_ADAPTIVE, tau=0.02, cap_per_pair=4096, seed=9)
+    print(f"case: short screen in launch order, {n} pairs", flush=True)
+    for ns in (None, n_start):
+        whole = _np(eng.shape_screen(Q, lib, pairs=pairs, n_start=ns, **kw))
+        parts = [_np(eng.shape_screen(Q, lib, pairs=pairs[i:i + 200].contiguous(),
+                                      n_start=None if ns is None else ns[i:i + 200].contiguous(),
+                                      **kw)) for i in range(0, n, 200)]
+        _same(whole, {k: np.concatenate([x[k] for x in parts]) for k in whole})
+        bad = ((pairs < 0) | (pairs >= lib.n_mols)).cpu().numpy()
+        assert np.array_equal(np.isnan(whole["T"]), bad)
+
+
 def test_tuner_picks_a_variant(eng, data):
     Q, lib = data
     tune_cache_clear()
