@@ -14,6 +14,7 @@
 //                                             origin, t' = B's origin)
 // and dT/dq follows from dtheta = 2 (w dv - dw v + v x dv) for q = (w, v).
 #include "shape_kernels.hpp"
+#include "shape_launch.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -313,9 +314,7 @@ __device__ __forceinline__ MovedAtoms moved_atoms(void* mem, int sets, int set, 
                     a2 + (size_t)set * max_b};
 }
 
-constexpr int kAS = 4;               // samples per lane evaluated together
-constexpr int kAlignMinWaves = 4;    // waves (starts in flight) per workgroup
-constexpr int kAlignMaxWaves = 8;
+constexpr int kAS = 4;  // samples per lane evaluated together
 
 // One workgroup per pair and group of starts_per_block starts; A's samples
 // are drawn once, then each wave optimises its starts in turn.  An evaluation
@@ -482,23 +481,25 @@ __global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a)
 
 // Self-overlap of each molecule from its own first n samples,
 // O_MM = Z_M / n sum_k w_M u_M (pose invariant); one workgroup per molecule of
-// the first set, then of the second.
+// the first set, then of the second (from: the launch's first of them).
 // All threads draw; the terms are then added by kSelfLanes lanes in a fixed
 // order (lane i takes samples i, i + kSelfLanes, ...).
 constexpr int kSelfThreads = 1024;
 constexpr int kSelfLanes = 256;
 constexpr int kSelfChunk = 2048;  // a multiple of kSelfLanes
 __global__ __launch_bounds__(kSelfThreads) void k_self_overlap(SelfSet first, SelfSet second,
-                                                               int n_samples, uint2 key) {
+                                                               int64_t from, int n_samples,
+                                                               uint2 key) {
   __shared__ float2 sWU[kSelfChunk];  // weight and occupancy of a chunk's samples
   __shared__ Atom sF[SHAPE_MAX_ATOMS];
   __shared__ AtomSampling sS[SHAPE_MAX_ATOMS];
   __shared__ AtomRec sR[SHAPE_MAX_ATOMS];
   __shared__ float sA[SHAPE_MAX_ATOMS];
   __shared__ double red[kSelfLanes / kWave];
-  const bool in_first = (int)blockIdx.x < first.n;
+  const int64_t item = from + blockIdx.x;
+  const bool in_first = item < first.n;
   const SelfSet& set = in_first ? first : second;
-  const int mol = in_first ? blockIdx.x : blockIdx.x - first.n;
+  const int mol = (int)(in_first ? item : item - first.n);
   if (mol >= set.n) return;
   const Prepared& M = set.M;
   const int* __restrict__ off = set.off;
@@ -630,13 +631,10 @@ hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max
                        dim3(kSplitWaves * kWave), split_lds, st, a);
     return hipGetLastError();
   }
-  // Eight starts per workgroup share A's samples where that leaves two
-  // workgroups per compute unit, else four (the least a call is checked for).
   // With many pairs a workgroup takes all of its pair's starts.
-  int waves = kAlignMaxWaves;
-  if (starts < (int64_t)2 * kAlignMaxWaves * n_cu || a.n_starts < kAlignMaxWaves ||
-      align_lds(a.n_samples, a.max_a, a.max_b, kAlignMaxWaves, 0) > max_lds)
-    waves = kAlignMinWaves;
+  const int waves = align_waves(
+      n_pairs, a.n_starts, align_lds(a.n_samples, a.max_a, a.max_b, kAlignMaxWaves, 0) <= max_lds,
+      n_cu);
   a.starts_per_block = n_pairs >= 16 * n_cu ? a.n_starts
                                             : std::max(waves, (a.n_starts + 65534) / 65535);
   const unsigned groups = (unsigned)((a.n_starts + a.starts_per_block - 1) / a.starts_per_block);
@@ -647,9 +645,14 @@ hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max
 
 hipError_t launch_self_overlap(const SelfSet& a, const SelfSet& b, int n_samples, uint2 key,
                                hipStream_t st) {
-  hipLaunchKernelGGL(k_self_overlap, dim3((unsigned)(a.n + (int64_t)b.n)), dim3(kSelfThreads), 0,
-                     st, a, b, n_samples, key);
-  return hipGetLastError();
+  const int64_t n = a.n + (int64_t)b.n, most = max_workgroups(kSelfThreads);
+  for (int64_t from = 0; from < n; from += most) {
+    hipLaunchKernelGGL(k_self_overlap, dim3((unsigned)std::min(most, n - from)),
+                       dim3(kSelfThreads), 0, st, a, b, from, n_samples, key);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_adam_pose(float* pose, const float* dT, float* m, float* v, int64_t n_poses,

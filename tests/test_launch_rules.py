@@ -1,0 +1,54 @@
+"""The launch rules that depend on sizes alone (csrc/shape_launch.hpp), built
+for the host and checked at sizes no test would launch: a launch holds fewer
+than 2^32 work-items along x, or the driver refuses it."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2607_20766_amd", "csrc")
+SHIM = """
+#include "shape_launch.hpp"
+using namespace shape;
+extern "C" {
+int64_t r_max_workgroups(int threads) { return max_workgroups(threads); }
+int r_align_waves(int64_t pairs, int starts, int fit, int n_cu) {
+  return align_waves(pairs, starts, fit, n_cu);
+}
+}
+"""
+LIMIT = 1 << 32
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = d / "rules.cpp", d / "rules.so"
+    src.write_text(SHIM)
+    subprocess.run([gxx, "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    str(src), "-o", str(lib)], check=True)
+    L = ctypes.CDLL(str(lib))
+    L.r_max_workgroups.restype = ctypes.c_int64
+    L.r_align_waves.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    return L
+
+
+@pytest.mark.parametrize("threads", [64, 128, 256, 512, 1024])
+def test_a_launch_stays_below_the_work_item_limit(rules, threads):
+    n = rules.r_max_workgroups(threads)
+    assert n * threads < LIMIT <= (n + 1) * threads
+
+
+@pytest.mark.parametrize("pairs", [1, 255, 256, 4096, (1 << 23) - 1, 1 << 23, (1 << 24) - 1])
+@pytest.mark.parametrize("starts", [1, 7, 8, 16, 1000])
+def test_alignment_workgroups_fit_a_launch(rules, pairs, starts):
+    """Up to 2^24 - 1 pairs, as with four waves per workgroup throughout."""
+    waves = rules.r_align_waves(pairs, starts, 1, 256)
+    assert waves in (4, 8) and pairs * waves * 64 < LIMIT
+    assert rules.r_align_waves(pairs, starts, 0, 256) == 4
