@@ -6,6 +6,7 @@
 //   AtomSampling   8 B  (1/sqrt(2 alpha), threshold)  only for sampling
 //   Z             FP64 per molecule, stream id per molecule, invalid flag.
 #include "shape_kernels.hpp"
+#include "shape_launch.hpp"
 
 #include <math.h>
 
@@ -1296,6 +1297,12 @@ hipError_t launch_prepare_sets(const PrepSet& a, const PrepSet& b, int* flag, co
                          ((int64_t)b.n + kPrepWaves - 1) / kPrepWaves +
                          (!o ? 0 : (work ? kOrderBlocks : 1));
   if (blocks == 0) return hipSuccess;
+  if (blocks > max_workgroups(256) && a.n > 0) {  // too many for one launch: set by set
+    const PrepSet none{};
+    const hipError_t e = launch_prepare_sets(a, none, flag, o, work, order, st);
+    return e != hipSuccess ? e
+                           : launch_prepare_sets(none, b, flag, nullptr, nullptr, nullptr, st);
+  }
   hipLaunchKernelGGL(k_prepare_sets, dim3((unsigned)blocks), dim3(256), 0, st, a, b, flag,
                      o ? *o : OrderArgs{}, o ? work : nullptr, o ? order : nullptr);
   return hipGetLastError();
@@ -1352,38 +1359,13 @@ hipError_t launch_screen(const ScreenArgs& a, int variant, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Rounds of a pair that its workgroup works on at a time, a wave each
-// (k_screen's kRounds), for screens that one wave per pair leaves short of
-// waves.  Rounds drawn past an adaptive pair's stop are dropped, (R - 1)/2 on
-// average, so R falls as a round grows.  One : two : four rounds, ms:
-//   few pairs          5,000 molecules of 10-50 atoms, adaptive 0.58 : 0.51 :
-//                      0.49; 8,000 0.78 : 0.71 : 0.72; 11,000 1.00 : 0.92 : 0.96;
-//                      13,000 1.09 : 1.07 : 1.14; 16,000 1.29 : 1.30 : 1.37
-//   LDS per pair       20,000 of 50-100 atoms (17 pairs' records in a compute
-//                      unit's LDS) 3.04 : 2.63 : 2.78; 60,000 of 30-70 (25) 6.59
-//                      : 6.53 : 6.90; of 30-60 (28) 6.49 : 6.52 : 6.88; 20,000
-//                      of 100-150 (11) fixed 3.09 : 2.59 : 2.32, of 200-256 (6)
-//                      6.98 : 5.03 : 3.99
-//   long rounds        8,000 pairs, 1,024 samples per side and round 0.81 :
-//                      0.77 : 0.88
-static int screen_rounds(const ScreenArgs& a, int n_cu) {
-  constexpr int kLdsPerCu = 160 * 1024;
-  const bool adaptive = a.mode == SHAPE_SCREEN_ADAPTIVE;
-  const int64_t n_rounds = (adaptive ? a.cap_pair / 2 : a.n_fixed) / a.round_side;
-  const int64_t resident = kLdsPerCu / (int64_t)screen_lds_bytes(a.max_q, a.max_b);
-  int R = 1;
-  if (a.n_pairs <= kTwoRoundPairsPerCu * n_cu || resident <= 25) R = 2;
-  if (a.n_pairs <= kFourRoundPairsPerCu * n_cu || resident <= 11) R = 4;
-  if (adaptive && a.n_pairs > kSplitPairsPerCu * n_cu)
-    while (R > 1 && R * a.round_side > 1024) R /= 2;
-  while (R > n_rounds) R /= 2;
-  return R;
-}
-
 hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStream_t st) {
   if (a.round_side == kSplitSlots * kWave && a.n_pairs <= kSplitPairsPerCu * n_cu)
     return launch_screen_split(a, st);
-  switch (screen_rounds(a, n_cu)) {
+  const bool adaptive = a.mode == SHAPE_SCREEN_ADAPTIVE;
+  const int64_t n_rounds = (adaptive ? a.cap_pair / 2 : a.n_fixed) / a.round_side;
+  switch (screen_rounds(adaptive, a.n_pairs, n_rounds, a.round_side,
+                        (int64_t)screen_lds_bytes(a.max_q, a.max_b), n_cu)) {
     case 4: launch_screen_t<4, 4, 4>(a, st); break;
     case 2: launch_screen_t<4, 4, 2>(a, st); break;
     default: return launch_screen(a, variant, st);

@@ -251,14 +251,9 @@ hipError_t launch_screen(const ScreenArgs& a, int variant, hipStream_t st);
 // The screen kernel that suits the call (all give the same bits): eight waves
 // per pair up to kSplitPairsPerCu pairs per compute unit (rounds of 256 samples
 // per side), where a pair's chain of rounds bounds the call (256 molecules 0.10
-// ms against 0.12 with four rounds at a time, 1,000 0.190 : 0.185); then four
-// rounds and two rounds of a pair at a time (screen_rounds), which fill the chip
-// up to kFourRoundPairsPerCu (28 pairs per compute unit are fewer than eight
-// waves per SIMD) and kTwoRoundPairsPerCu; else one wave per pair in the tile
+// ms against 0.12 with four rounds at a time, 1,000 0.190 : 0.185); then several
+// rounds of a pair at a time (screen_rounds); else one wave per pair in the tile
 // shape `variant`.
-constexpr int kSplitPairsPerCu = 3;
-constexpr int kFourRoundPairsPerCu = 28;
-constexpr int kTwoRoundPairsPerCu = 50;
 hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStream_t st);
 // Launch order of a grid with one workgroup per pair (blocks along x):
 // largest estimated work first.  The work of pair p is

@@ -3,6 +3,7 @@ workgroups holds: the same values as a small call of the same molecules."""
 import pytest
 import torch
 
+from paper_2607_20766_amd import molgen
 from paper_2607_20766_amd.engine import Engine, Molecules
 from tests.gpu_common import require_gpu
 
@@ -54,3 +55,21 @@ def test_alignment_of_over_two_million_pairs(eng):
     assert torch.isfinite(T_ref).all()
     _repeats(T, T_ref)
     _repeats(pose, small)
+
+
+def test_screen_of_over_sixteen_million_pairs_of_a_large_molecule_library(eng):
+    """A library whose largest molecule (200 atoms) asks for several waves per
+    pair; the list holds 2^24 + 9 pairs."""
+    n = (1 << 24) + 9
+    print(f"case: screen of {n} listed pairs", flush=True)
+    q = eng.molecules(molgen.molecule(91, 0, 3), mol_id=[7])
+    L = eng.molecules(molgen.MolSet.concat(
+        [molgen.molecule(91, 1, 200)] + [molgen.molecule(91, i, 2) for i in range(2, PERIOD)]))
+    ref = eng.shape_screen(q, L, n_per_side=320, seed=5)
+    # the large molecule once, then the small ones in turn
+    pairs = 1 + torch.arange(n, device=eng.torch_device, dtype=torch.int32) % (PERIOD - 2)
+    pairs[-1] = 0
+    out = {k: torch.empty(n, device=eng.torch_device) for k in ("T", "se_T")}
+    eng.shape_screen(q, L, n_per_side=320, seed=5, pairs=pairs, out=out)
+    for k, v in out.items():
+        assert torch.equal(v, ref[k][pairs.long()])

@@ -18,6 +18,9 @@ int64_t r_max_workgroups(int threads) { return max_workgroups(threads); }
 int r_align_waves(int64_t pairs, int starts, int fit, int n_cu) {
   return align_waves(pairs, starts, fit, n_cu);
 }
+int r_screen_rounds(int adaptive, int64_t pairs, int64_t rounds, int side, int64_t lds, int n_cu) {
+  return screen_rounds(adaptive, pairs, rounds, side, lds, n_cu);
+}
 }
 """
 LIMIT = 1 << 32
@@ -36,6 +39,8 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(str(lib))
     L.r_max_workgroups.restype = ctypes.c_int64
     L.r_align_waves.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    L.r_screen_rounds.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int,
+                                  ctypes.c_int64, ctypes.c_int]
     return L
 
 
@@ -52,3 +57,15 @@ def test_alignment_workgroups_fit_a_launch(rules, pairs, starts):
     waves = rules.r_align_waves(pairs, starts, 1, 256)
     assert waves in (4, 8) and pairs * waves * 64 < LIMIT
     assert rules.r_align_waves(pairs, starts, 0, 256) == 4
+
+
+@pytest.mark.parametrize("pairs", [1, 7168, 12800, 12801, (1 << 24) - 1, 1 << 24, (1 << 25) - 1,
+                                   1 << 25, (1 << 26) - 1])
+@pytest.mark.parametrize("lds", [2000, 6400, 8000, 16000, 24000])  # bytes per pair
+@pytest.mark.parametrize("adaptive,side,rounds", [(0, 256, 16), (0, 64, 1), (1, 256, 128),
+                                                  (1, 4096, 8), (1, 64, 2)])
+def test_screen_workgroups_fit_a_launch(rules, pairs, lds, adaptive, side, rounds):
+    """Up to 2^26 - 1 pairs, as with one wave per pair throughout, however
+    much LDS a pair takes."""
+    R = rules.r_screen_rounds(adaptive, pairs, rounds, side, lds, 256)
+    assert R in (1, 2, 4) and R <= rounds and pairs * R * 64 < LIMIT
