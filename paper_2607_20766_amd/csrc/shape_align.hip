@@ -395,11 +395,14 @@ void k_align(AlignArgs a) {
 constexpr int kSplitWaves = 16;
 constexpr int kSplitS = 2;
 constexpr int kSplitSlots = kSplitWaves * kSplitS;  // slots of 64 samples per pass
+struct SplitShared {
+  double sum[7];  // the integrands' weighted sums
+  float t[3];     // B's origin in A's frame
+};
 
 __global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double sSum[7];
-  __shared__ float sT[3];  // B's origin in A's frame
+  __shared__ SplitShared sh;
   float4* sSamp = reinterpret_cast<float4*>(smem);  // [n_samples]
   void* rest = sSamp + a.n_samples;
   const int pair = blockIdx.x, st = blockIdx.y;
@@ -428,9 +431,9 @@ __global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a)
       const float tx = ps.get(4) - cA.x, ty = ps.get(5) - cA.y, tz = ps.get(6) - cA.z;
       B.move(a.B.atom + b0, nb, R, tx, ty, tz);
       if (lane == 0) {
-        sT[0] = tx;
-        sT[1] = ty;
-        sT[2] = tz;
+        sh.t[0] = tx;
+        sh.t[1] = ty;
+        sh.t[2] = tz;
       }
     }
     __syncthreads();  // the moved atoms
@@ -438,7 +441,7 @@ __global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a)
     for (int t0 = 0; t0 < per_lane; t0 += kSplitSlots) {
       const int t = t0 + wave * kSplitS;
       if (t < per_lane)
-        align_eval<kSplitS, 4>(sSamp, a.n_samples, t, B, nb, sT[0], sT[1], sT[2],
+        align_eval<kSplitS, 4>(sSamp, a.n_samples, t, B, nb, sh.t[0], sh.t[1], sh.t[2],
                             [&](int s, float, const float (&f)[7]) {
                               const int i = wave * kSplitS + s;
                               if (i < slots)
@@ -460,14 +463,14 @@ __global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a)
     }
     if (wave < 7) {
       const double s = wave_sum((double)acc);
-      if (lane == 0) sSum[wave] = s;
+      if (lane == 0) sh.sum[wave] = s;
     }
     __syncthreads();  // the sums (and every read of the moved atoms)
     const bool last = it >= a.n_steps;
     if (wave == 0) {
       double sum[7];
 #pragma unroll
-      for (int c = 0; c < 7; ++c) sum[c] = sSum[c];
+      for (int c = 0; c < 7; ++c) sum[c] = sh.sum[c];
       float T, g[7];
       align_value(sum, Za, S, a.n_samples, ps, inv_norm, last, a.grad || !last, T, g);
       if (last)
@@ -626,7 +629,8 @@ hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max
   // against 3.6 ms, 100 x 16 3.7 against 4.3 ms, 200 x 16 (30 steps) equal;
   // one evaluation: 60 x 16 equal, 100 x 16 125 against 102 us.
   const int64_t split_per_cu = a.n_steps > 0 ? 8 : 4;
-  if (starts <= split_per_cu * n_cu && a.n_starts <= 65535 && split_lds <= max_lds) {
+  if (starts <= split_per_cu * n_cu && a.n_starts <= 65535 &&
+      align_split_fits(split_lds, sizeof(SplitShared), max_lds)) {
     hipLaunchKernelGGL(k_align_split, dim3((unsigned)n_pairs, (unsigned)a.n_starts),
                        dim3(kSplitWaves * kWave), split_lds, st, a);
     return hipGetLastError();

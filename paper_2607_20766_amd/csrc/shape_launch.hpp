@@ -2,6 +2,7 @@
 // they can be checked at sizes no test would launch.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -24,6 +25,12 @@ inline int align_waves(int64_t n_pairs, int n_starts, bool eight_fit, int n_cu) 
                      n_starts >= kAlignMaxWaves && eight_fit &&
                      n_pairs <= max_workgroups(kAlignMaxWaves * 64);
   return eight ? kAlignMaxWaves : kAlignMinWaves;
+}
+
+// Whether a workgroup's dynamic LDS and its kernel's own (rounded up to 16 bytes,
+// the dynamic part's alignment) are within what the device allows.
+inline bool align_split_fits(size_t dynamic, size_t own, size_t max_lds) {
+  return dynamic + (own + 15) / 16 * 16 <= max_lds;
 }
 
 // Rounds of a pair that its workgroup works on at a time, a wave each, in screens

@@ -18,6 +18,9 @@ int64_t r_max_workgroups(int threads) { return max_workgroups(threads); }
 int r_align_waves(int64_t pairs, int starts, int fit, int n_cu) {
   return align_waves(pairs, starts, fit, n_cu);
 }
+int r_align_split_fits(int64_t dynamic, int64_t own, int64_t max_lds) {
+  return align_split_fits(dynamic, own, max_lds);
+}
 int r_screen_rounds(int adaptive, int64_t pairs, int64_t rounds, int side, int64_t lds, int n_cu) {
   return screen_rounds(adaptive, pairs, rounds, side, lds, n_cu);
 }
@@ -39,6 +42,7 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(str(lib))
     L.r_max_workgroups.restype = ctypes.c_int64
     L.r_align_waves.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    L.r_align_split_fits.argtypes = [ctypes.c_int64] * 3
     L.r_screen_rounds.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int,
                                   ctypes.c_int64, ctypes.c_int]
     return L
@@ -69,3 +73,10 @@ def test_screen_workgroups_fit_a_launch(rules, pairs, lds, adaptive, side, round
     much LDS a pair takes."""
     R = rules.r_screen_rounds(adaptive, pairs, rounds, side, lds, 256)
     assert R in (1, 2, 4) and R <= rounds and pairs * R * 64 < LIMIT
+
+
+def test_a_kernels_own_lds_counts_towards_the_limit(rules):
+    most = 160 * 1024
+    assert rules.r_align_split_fits(most - 80, 72, most)
+    assert not rules.r_align_split_fits(most - 64, 72, most)
+    assert not rules.r_align_split_fits(most, 72, most)
