@@ -615,24 +615,30 @@ static size_t align_lds(int n_samples, int max_a, int max_b, int sets, int split
                                             (size_t)split_slots * 7 * kWave * sizeof(float));
 }
 
+// Whether an alignment of few starts runs k_align_split: sixteen waves a start.
+// Every workgroup draws A's samples, about the work of one evaluation, so a single
+// evaluation pays for it at fewer starts than an optimisation does.  2,048 samples,
+// 15-45 atoms, 60 steps (split against four starts per workgroup): 10 pairs x 16
+// starts 0.65 against 3.6 ms, 100 x 16 3.7 against 4.3 ms, 200 x 16 (30 steps)
+// equal; one evaluation: 60 x 16 equal, 100 x 16 125 against 102 us.
+static size_t split_lds_bytes(int n_samples, int max_a, int max_b) {
+  const int per_lane = (n_samples + kWave - 1) / kWave;
+  return align_lds(n_samples, max_a, max_b, 1, std::min(per_lane, kSplitSlots));
+}
+bool align_splits(int n_pairs, int n_starts, int n_steps, int n_samples, int max_a, int max_b,
+                  int n_cu, size_t max_lds) {
+  const int64_t per_cu = n_steps > 0 ? 8 : 4;
+  return (int64_t)n_pairs * n_starts <= per_cu * n_cu && n_starts <= 65535 &&
+         align_split_fits(split_lds_bytes(n_samples, max_a, max_b), sizeof(SplitShared), max_lds);
+}
+
 hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max_lds,
                         hipStream_t st) {
   AlignArgs a = args;
-  const int per_lane = (a.n_samples + kWave - 1) / kWave;
-  const int64_t starts = (int64_t)n_pairs * a.n_starts;
-  const size_t split_lds = align_lds(a.n_samples, a.max_a, a.max_b, 1,
-                                     std::min(per_lane, kSplitSlots));
-  // Few starts: sixteen waves each.  Every workgroup draws A's samples, about
-  // the work of one evaluation, so a single evaluation pays for it at fewer
-  // starts than an optimisation does.  2,048 samples, 15-45 atoms, 60 steps
-  // (split against four starts per workgroup): 10 pairs x 16 starts 0.65
-  // against 3.6 ms, 100 x 16 3.7 against 4.3 ms, 200 x 16 (30 steps) equal;
-  // one evaluation: 60 x 16 equal, 100 x 16 125 against 102 us.
-  const int64_t split_per_cu = a.n_steps > 0 ? 8 : 4;
-  if (starts <= split_per_cu * n_cu && a.n_starts <= 65535 &&
-      align_split_fits(split_lds, sizeof(SplitShared), max_lds)) {
+  if (align_splits(n_pairs, a.n_starts, a.n_steps, a.n_samples, a.max_a, a.max_b, n_cu, max_lds)) {
     hipLaunchKernelGGL(k_align_split, dim3((unsigned)n_pairs, (unsigned)a.n_starts),
-                       dim3(kSplitWaves * kWave), split_lds, st, a);
+                       dim3(kSplitWaves * kWave), split_lds_bytes(a.n_samples, a.max_a, a.max_b),
+                       st, a);
     return hipGetLastError();
   }
   // With many pairs a workgroup takes all of its pair's starts.

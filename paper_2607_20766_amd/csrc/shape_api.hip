@@ -426,10 +426,16 @@ shape::OrderArgs align_order_args(const shape_mols* A, const shape_mols* B, int 
 // decides which pairs share a compute unit: the largest start on different ones.
 // One evaluation, 16 starts, 2,048 samples: 300 pairs of 15-45 atoms 177 -> 150 us,
 // 270 of 50-100 363 -> 293 (163 and 307 with the order in three launches).
+// Calls that run every start by itself take no order.
 int align_prepare(shape_ctx* c, const shape_mols* A, const shape_mols* B, int n_starts,
-                  int n_steps, hipStream_t st, shape::Prepared* PA, shape::Prepared* PB,
-                  const int** order) {
+                  int n_steps, int n_samples, hipStream_t st, shape::Prepared* PA,
+                  shape::Prepared* PB, const int** order) {
   int rc;
+  if (shape::align_splits(A->n_mols, n_starts, n_steps, n_samples, A->max_atoms, B->max_atoms,
+                          c->n_cu, c->lds_per_block)) {
+    *order = nullptr;
+    return prepare_sets(c, A, B, st, PA, PB);
+  }
   WorkOrder wo;
   if ((rc = work_order_slot(c, A->n_mols, kOrderAlignPerCu, &wo))) return rc;
   const shape::OrderArgs o = align_order_args(A, B, n_starts, n_steps);
@@ -1154,7 +1160,7 @@ int shape_align_grad(shape_ctx* c, const shape_mols* A, const shape_mols* B, int
     hipStream_t st = (hipStream_t)stream;
     const int* order;
     shape::Prepared PA, PB;
-    if ((rc = align_prepare(c, A, B, n_starts, 0, st, &PA, &PB, &order))) return rc;
+    if ((rc = align_prepare(c, A, B, n_starts, 0, n_samples, st, &PA, &PB, &order))) return rc;
     KernelTimer timer(c, st);
     rc = align_launch(c, A, B, PA, PB, n_starts, pose, O_aa, O_bb, n_samples, seed, st, T,
                       dT_dpose, order);
@@ -1202,7 +1208,7 @@ int shape_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t 
     if ((rc = ensure(c, S_SELF_A, (size_t)pairs * sizeof(float), &saa))) return rc;
     if ((rc = ensure(c, S_SELF_B, (size_t)pairs * sizeof(float), &sbb))) return rc;
     const int* order;
-    if ((rc = align_prepare(c, A, B, n_starts, n_steps, st, &PA, &PB, &order))) return rc;
+    if ((rc = align_prepare(c, A, B, n_starts, n_steps, n_samples, st, &PA, &PB, &order))) return rc;
     HIP_TRY(c, shape::launch_self_overlap({PA, A->atom_offset, pairs, (float*)saa},
                                           {PB, B->atom_offset, pairs, (float*)sbb}, n_samples,
                                           key_of(seed), st),

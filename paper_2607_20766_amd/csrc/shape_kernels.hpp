@@ -203,7 +203,10 @@ hipError_t launch_topk(const float* s, int n, int k, uint32_t* sel, uint32_t* hi
                        int* cnt_eq, int* out, hipStream_t st);
 
 size_t align_lds_bytes(int n_samples, int max_a, int max_b);
-// max_lds: LDS bytes a workgroup may use
+// max_lds: LDS bytes a workgroup may use.  A call that align_splits runs every
+// start by itself and reads no launch order.
+bool align_splits(int n_pairs, int n_starts, int n_steps, int n_samples, int max_a, int max_b,
+                  int n_cu, size_t max_lds);
 hipError_t launch_align(const AlignArgs& a, int n_pairs, int n_cu, size_t max_lds,
                         hipStream_t st);
 struct SelfSet {
