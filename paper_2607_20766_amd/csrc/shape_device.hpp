@@ -440,8 +440,9 @@ __device__ __forceinline__ void eval_atoms_x(const AtomRec* __restrict__ rec,
 }
 
 // Two atoms' records in one 48-byte word, so that the inner loop needs one LDS
-// address.  A molecule of odd size ends with a phantom atom: e = 10^30 at
-// every point, o = 0 exactly, which changes no sum and no product.
+// address.  A molecule of odd size ends with a phantom atom: e = |r|^2 + 10^30,
+// so o = 0 exactly at every point, also where |r|^2 overflows (a width of 0 would
+// make that NaN), which changes no sum and no product.
 struct __align__(16) AtomRec2 {
   AtomRec r[2];
   float a2[2];
@@ -457,7 +458,7 @@ __device__ __forceinline__ void make_rec2(const Atom& a, float rx, float ry, flo
   make_rec(a, rx, ry, rz, w.r[i & 1], w.a2[i & 1]);
   if (i == n - 1 && (n & 1)) {
     w.r[1] = AtomRec{0.f, 0.f, 0.f, 1e30f};
-    w.a2[1] = 0.f;
+    w.a2[1] = 1.f;
   }
 }
 

@@ -351,3 +351,24 @@ def test_long_screen_order_edge_cases():
     bad[::2] = L.n_mols
     out = _to_np(e.shape_screen(Q, lib, pairs=bad, **kw))
     assert np.all(np.isnan(out["T"])) and np.all(out["n_used"] == 0)
+
+
+@pytest.mark.parametrize("variant", [-1, 0, 1, 3, 6])
+def test_points_whose_squared_norm_overflows(eng, variant):
+    """A query so wide (alpha 2e-38, sd 5e18) that |r|^2 of some of its samples
+    is beyond FP32: every occupancy is 0 there, for libraries of odd and of
+    even molecules."""
+    print(f"case: overflowing squared norms, variant {variant}", flush=True)
+    Q = eng.molecules(molgen.molecule(12, 0, 1), mol_id=[QUERY_ID])
+    Q.alpha.fill_(2e-38)
+    lib = eng.molecules(molgen.MolSet.concat([molgen.molecule(12, n, n)
+                                              for n in (1, 2, 3, 4, 9)]))
+    eng.screen_variant(variant)
+    try:
+        g = _to_np(eng.shape_screen(Q, lib, n_per_side=4096, seed=7))
+    finally:
+        eng.screen_variant(-1)
+    for k in ("T", "se_T", "O_ab", "O_bb"):
+        assert np.all(np.isfinite(g[k])), (k, g[k])
+    # O_AA is about 10^56 times O_AB
+    assert np.all(np.abs(g["T"]) < 1e-30) and np.all(g["O_ab"] >= 0)
