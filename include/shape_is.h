@@ -766,9 +766,9 @@ int shape_range_push(const char* name);
 int shape_range_pop(void);
 
 /* Kernel timing (measurement support, not part of the method).  While
- * enabled, every call records a pair of HIP events on its stream around its
- * dominant kernel (the screening kernel of shape_screen, the sample kernel of
- * shape_estimate).  shape_timing_read synchronises those events and returns
+ * enabled, every call but shape_estimate_noalloc records a pair of HIP events
+ * on its stream around its dominant kernel (the screening kernel of
+ * shape_screen, the sample kernel of shape_estimate).  shape_timing_read synchronises those events and returns
  * the summed kernel time in milliseconds and the number of launches since the
  * last reset (host pointers; either may be NULL); reset != 0 clears them.
  * Errors: SHAPE_E_INVAL, SHAPE_E_HIP. */

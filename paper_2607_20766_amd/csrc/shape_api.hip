@@ -340,8 +340,8 @@ struct KernelTimer {
   shape_ctx* c;
   hipStream_t st;
   hipEvent_t a = nullptr, b = nullptr;
-  KernelTimer(shape_ctx* c_, hipStream_t st_) : c(c_), st(st_) {
-    if (!c->timing || c->capturing) return;
+  KernelTimer(shape_ctx* c_, hipStream_t st_, bool on = true) : c(c_), st(st_) {
+    if (!on || !c->timing || c->capturing) return;
     if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess ||
         hipEventRecord(a, st) != hipSuccess) {
       a = b = nullptr;
@@ -714,12 +714,14 @@ int estimate_check(shape_ctx* c, const shape_mols* A, const shape_mols* B, int64
 
 // The kernels of one estimate on prepared sets.  The last one writes the
 // result, and which molecules are invalid, to the context's pinned host
-// buffer, so the call waits for the stream once and copies nothing.
+// buffer, so the call waits for the stream once and copies nothing.  Without
+// timed no events are made (the entry point that allocates nothing).
 int estimate_run(shape_ctx* c, const shape::Prepared& PA, const shape::Prepared& PB,
                  const shape_mols* A, const shape_mols* B, int64_t n_a, int64_t n_b,
-                 uint64_t seed, double* partials, int nblk, hipStream_t st, shape_result* out) {
+                 uint64_t seed, double* partials, int nblk, bool timed, hipStream_t st,
+                 shape_result* out) {
   const int anti = c->sampling == SHAPE_SAMPLING_ANTITHETIC ? 1 : 0;
-  KernelTimer timer(c, st);
+  KernelTimer timer(c, st, timed);
   HIP_TRY(c, shape::launch_estimate(PA, PB, A->atom_offset, B->atom_offset, n_a, n_b,
                                     key_of(seed), anti, partials, nblk, c->est_out_dev, st),
           "estimate kernels");
@@ -767,7 +769,7 @@ int shape_estimate(shape_ctx* c, const shape_mols* A, const shape_mols* B, int64
     if (!c->prep_cache)
       HIP_TRY(c, shape::launch_prepare_pair(mols_dev(A), PA, mols_dev(B), PB, c->flag, st),
               "prepare kernel");
-    return estimate_run(c, PA, PB, A, B, n_a, n_b, seed, (double*)partials, nblk, st, out);
+    return estimate_run(c, PA, PB, A, B, n_a, n_b, seed, (double*)partials, nblk, true, st, out);
   } catch (...) {
     return fail(c, SHAPE_E_HIP, "internal error");
   }
@@ -811,7 +813,7 @@ int shape_estimate_noalloc(shape_ctx* c, const shape_mols* A, const shape_mols* 
     const int64_t units = (n_a > n_b ? n_a : n_b) / (anti ? 2 : 1);
     const int nblk = shape::est_blocks(units);  // <= L.max_blocks by the range check
     return estimate_run(c, P[0], P[1], A, B, n_a, n_b, seed, (double*)(base + L.partials), nblk,
-                        st, out);
+                        false, st, out);
   } catch (...) {
     return fail(c, SHAPE_E_HIP, "internal error");
   }

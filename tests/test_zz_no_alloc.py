@@ -73,3 +73,18 @@ def test_noalloc_rejects_sizes_beyond_its_limit():
     # the entry point still works after the rejected calls
     got = eng.shape_estimate_noalloc(A, A, 2048, 2048)
     assert got["T"] == 1.0
+
+
+def test_noalloc_makes_no_timing_events():
+    require_gpu()
+    print("noalloc: with kernel timing on", flush=True)
+    eng = Engine(0)
+    A = eng.molecules(molgen.molecule(0, 0, 20), mol_id=[0])
+    eng.shape_timing_enable()
+    try:
+        eng.shape_estimate_noalloc(A, A, 2048, 2048)
+        assert eng.shape_timing_read()[1] == 0
+        eng.shape_estimate(A, A, 2048, 2048)
+        assert eng.shape_timing_read()[1] == 1
+    finally:
+        eng.shape_timing_enable(False)
