@@ -304,7 +304,10 @@ int shape_prepare_cache(shape_ctx* ctx, int enable);
  * with the same bits.
  * shape_screen_set_variant selects a variant by index, for every later screen
  * of the context (-1 = default: the library chooses);
- * shape_screen_get_variant returns the current one (-1 if ctx is NULL).
+ * shape_screen_get_variant returns the current one (-1 if ctx is NULL);
+ * shape_screen_copy_variant makes ctx choose its kernels as `from` does, whether
+ * the library, the tuner or a caller chose from's variant (SHAPE_E_INVAL if
+ * either is NULL).
  *
  * Tuning cache: each choice is remembered process-wide under the kind of
  * screen — the device's architecture name and compute-unit count, mode,
@@ -327,6 +330,7 @@ int shape_screen_tune(shape_ctx* ctx, const shape_mols* query, const shape_mols*
                       const shape_screen_params* params, void* stream, float* ms,
                       int32_t* best);
 int shape_screen_set_variant(shape_ctx* ctx, int32_t variant);
+int shape_screen_copy_variant(shape_ctx* ctx, const shape_ctx* from);
 int32_t shape_screen_get_variant(const shape_ctx* ctx);
 int shape_tune_cache_file(const char* path);
 int shape_tune_cache_clear(void);

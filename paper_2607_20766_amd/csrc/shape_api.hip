@@ -1071,6 +1071,14 @@ int shape_screen_set_variant(shape_ctx* c, int32_t variant) {
   return SHAPE_OK;
 }
 
+int shape_screen_copy_variant(shape_ctx* c, const shape_ctx* from) {
+  if (!c) return SHAPE_E_INVAL;
+  if (!from) return fail(c, SHAPE_E_INVAL, "from is NULL");
+  c->screen_variant = from->screen_variant;
+  c->variant_set = from->variant_set;
+  return SHAPE_OK;
+}
+
 int32_t shape_screen_get_variant(const shape_ctx* c) { return c ? c->screen_variant : -1; }
 
 int shape_self_overlap(shape_ctx* c, const shape_mols* M, int32_t n_samples, uint64_t seed,

@@ -153,6 +153,7 @@ def load_library():
         L.shape_get_sampling.argtypes = [vp]
         L.shape_get_sampling.restype = i32
         L.shape_screen_set_variant.argtypes = [vp, i32]
+        L.shape_screen_copy_variant.argtypes = [vp, vp]
         L.shape_screen_get_variant.argtypes = [vp]
         L.shape_screen_get_variant.restype = i32
         L.shape_graph_begin.argtypes = [vp, vp]
@@ -522,6 +523,11 @@ class Engine:
         if variant is not None:
             self._check(L.shape_screen_set_variant(self._ctx, int(variant)))
         return int(L.shape_screen_get_variant(self._ctx))
+
+    def screen_variant_of(self, other: "Engine"):
+        """Choose screening kernels as `other` does: its tile variant, whether
+        the library, the tuner or a caller chose it."""
+        self._check(load_library().shape_screen_copy_variant(self._ctx, other._ctx))
 
     # -- graphs ----------------------------------------------------------------
     def capture(self, fn, stream=None, warmup: bool = True) -> "Graph":

@@ -210,7 +210,7 @@ class Triage:
         helpers = [Engine(self.eng.device) for _ in range(max(n_streams, 1) - 1)]
         engs = [self.eng] + helpers
         for e in helpers:
-            e.screen_variant(self.eng.screen_variant())
+            e.screen_variant_of(self.eng)
             e.sampling(self.eng.sampling())
         streams = [torch.cuda.Stream(device=dev) for _ in engs]
         cur = torch.cuda.current_stream(dev)

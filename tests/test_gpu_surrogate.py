@@ -716,3 +716,53 @@ def test_training_resumes_from_checkpoint(eng, tmp_path):
     bad["params"] = bad["params"][:-1]
     with pytest.raises(ValueError):
         b.load_state_dict(bad)
+
+
+def test_labels_many_helpers_take_the_engines_kernels(eng, monkeypatch):
+    """After tuning, the helper contexts of labels_many screen a few hundred
+    molecules with several waves per pair, as the engine does: the tuner's
+    choice is not the caller's.  One wave per pair takes over three times as
+    long (0.36 against 0.10 ms for 500 molecules)."""
+    from paper_2607_20766_amd import surrogate
+    print("case: labels_many after tuning, kernel times of the helpers", flush=True)
+    helpers = []
+
+    class Timed(Engine):
+        def __init__(self, *a):
+            super().__init__(*a)
+            self.shape_timing_enable()
+            self.ms = None
+            helpers.append(self)
+
+        def close(self):
+            if self.ms is None:
+                self.ms = self.shape_timing_read()
+            super().close()
+
+    L = molgen.library(61, 500, 10, 50, workers=1)
+    lib = eng.molecules(L)
+    q = eng.molecules(molgen.molecule(61, 600, 30), mol_id=[77])
+    tr = Triage(eng, seed=1)
+    kw = dict(mode=SHAPE_SCREEN_ADAPTIVE, round_per_pair=tr.round_per_pair,
+              cap_per_pair=tr.cap_per_pair, tau=tr.tau, seed=0)
+    eng.shape_timing_enable()
+    try:
+        ms = {}
+        for variant in (-1, 3):  # several waves per pair, one wave per pair
+            eng.screen_variant(variant)
+            for _ in range(2):
+                eng.shape_timing_read()
+                eng.shape_screen(q, lib, **kw)
+            ms[variant] = eng.shape_timing_read()[0]
+        eng.screen_variant(-1)
+        eng.shape_screen_tune(q, lib, **kw)
+        monkeypatch.setattr(surrogate, "Engine", Timed)
+        for _ in range(2):  # the second time warm
+            tr.labels_many([q, q], lib, n_streams=2)
+    finally:
+        eng.shape_timing_enable(False)
+        eng.screen_variant(-1)
+    assert ms[3] > 2.0 * ms[-1], ms
+    total, n = helpers[-1].ms
+    # beside the engine's own screen; one wave per pair would take ms[3] or more
+    assert n == 1 and total < 0.75 * ms[3], (total, ms)
