@@ -34,13 +34,12 @@ __device__ __forceinline__ void quat_rotation(float qw, float qx, float qy, floa
 }
 
 // A molecule's samples k0 .. k1 - 1 and their weights, drawn by the whole
-// workgroup two per thread at a time: put(k, x, y, z, w, u) for each of them.
-// The molecule's records are in its own frame.
-template <class Put>
+// workgroup D per thread at a time: put(k, x, y, z, w, u) for each of them, a
+// thread's in ascending order.  The molecule's records are in its own frame.
+template <int D, class Put>
 __device__ __forceinline__ void weigh_samples(const Atom* AF, const AtomSampling* AS,
                                               const AtomRec* AR, const float* Aa, int na,
                                               uint32_t id, int k0, int k1, uint2 key, Put put) {
-  constexpr int D = 2;
   for (int i = k0 + threadIdx.x; i < k1; i += D * blockDim.x) {
     uint32_t k[D];
     float rx[D], ry[D], rz[D], r2[D], m[D], u[D];
@@ -80,10 +79,10 @@ __device__ void align_samples(const AlignArgs& a, int pair, float4* sSamp, Atom*
     make_rec(at, cA.x, cA.y, cA.z, sAR[i], sAa[i]);
   }
   __syncthreads();
-  weigh_samples(sAF, sAS, sAR, sAa, na, a.A.id[pair], 0, a.n_samples, a.key,
-                [&](int k, float x, float y, float z, float w, float) {
-                  sSamp[k] = make_float4(x, y, z, w);
-                });
+  weigh_samples<2>(sAF, sAS, sAR, sAa, na, a.A.id[pair], 0, a.n_samples, a.key,
+                   [&](int k, float x, float y, float z, float w, float) {
+                     sSamp[k] = make_float4(x, y, z, w);
+                   });
   __syncthreads();
 }
 
@@ -485,15 +484,22 @@ __global__ __launch_bounds__(kSplitWaves* kWave) void k_align_split(AlignArgs a)
 // Self-overlap of each molecule from its own first n samples,
 // O_MM = Z_M / n sum_k w_M u_M (pose invariant); one workgroup per molecule of
 // the first set, then of the second (from: the launch's first of them).
-// All threads draw; the terms are then added by kSelfLanes lanes in a fixed
-// order (lane i takes samples i, i + kSelfLanes, ...).
+// The terms are added by kSelfLanes lanes in a fixed order: lane i takes samples
+// i, i + kSelfLanes, ...  A workgroup of kSelfLanes threads draws D samples per
+// thread and adds them at once; one of kSelfThreads, for few molecules, draws
+// them four times as fast into LDS and adds them from there.  VALU issue bounds
+// long calls, latency short ones.  256 : 1,024 threads, us, 10-50 atoms: 2,048
+// samples, 512 molecules 36 : 25, 1,500 50 : 45, 3,000 72 : 75, 20,000 350 : 393;
+// 512 samples, 512 molecules 19 : 19, 1,500 21 : 32, 20,000 118 : 275.
 constexpr int kSelfThreads = 1024;
 constexpr int kSelfLanes = 256;
 constexpr int kSelfChunk = 2048;  // a multiple of kSelfLanes
-__global__ __launch_bounds__(kSelfThreads) void k_self_overlap(SelfSet first, SelfSet second,
-                                                               int64_t from, int n_samples,
-                                                               uint2 key) {
-  __shared__ float2 sWU[kSelfChunk];  // weight and occupancy of a chunk's samples
+template <int kThreads, int D>
+__global__ __launch_bounds__(kThreads) void k_self_overlap(SelfSet first, SelfSet second,
+                                                           int64_t from, int n_samples,
+                                                           uint2 key) {
+  constexpr bool kStaged = kThreads != kSelfLanes;
+  __shared__ float2 sWU[kStaged ? kSelfChunk : 1];  // weight and occupancy of a chunk's samples
   __shared__ Atom sF[SHAPE_MAX_ATOMS];
   __shared__ AtomSampling sS[SHAPE_MAX_ATOMS];
   __shared__ AtomRec sR[SHAPE_MAX_ATOMS];
@@ -525,19 +531,24 @@ __global__ __launch_bounds__(kSelfThreads) void k_self_overlap(SelfSet first, Se
   }
   __syncthreads();
   float acc = 0.f;
-  for (int k0 = 0; k0 < n_samples; k0 += kSelfChunk) {
-    const int k1 = min(n_samples, k0 + kSelfChunk);
-    weigh_samples(sF, sS, sR, sA, na, M.id[mol], k0, k1, key,
-                  [&](int k, float, float, float, float w, float u) {
-                    sWU[k - k0] = make_float2(w, u);
-                  });
-    __syncthreads();
-    if (threadIdx.x < kSelfLanes)
-      for (int k = threadIdx.x; k < k1 - k0; k += kSelfLanes) {
-        const float2 t = sWU[k];
-        acc = fmaf(t.x, t.y, acc);
-      }
-    __syncthreads();
+  if constexpr (!kStaged) {
+    weigh_samples<D>(sF, sS, sR, sA, na, M.id[mol], 0, n_samples, key,
+                     [&](int, float, float, float, float w, float u) { acc = fmaf(w, u, acc); });
+  } else {
+    for (int k0 = 0; k0 < n_samples; k0 += kSelfChunk) {
+      const int k1 = min(n_samples, k0 + kSelfChunk);
+      weigh_samples<D>(sF, sS, sR, sA, na, M.id[mol], k0, k1, key,
+                       [&](int k, float, float, float, float w, float u) {
+                         sWU[k - k0] = make_float2(w, u);
+                       });
+      __syncthreads();
+      if (threadIdx.x < kSelfLanes)
+        for (int k = threadIdx.x; k < k1 - k0; k += kSelfLanes) {
+          const float2 t = sWU[k];
+          acc = fmaf(t.x, t.y, acc);
+        }
+      __syncthreads();
+    }
   }
   if (threadIdx.x < kSelfLanes) {
     const double s = wave_sum((double)acc);
@@ -653,16 +664,30 @@ hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max
   return hipGetLastError();
 }
 
-hipError_t launch_self_overlap(const SelfSet& a, const SelfSet& b, int n_samples, uint2 key,
-                               hipStream_t st) {
-  const int64_t n = a.n + (int64_t)b.n, most = max_workgroups(kSelfThreads);
+template <int kThreads, int D>
+static hipError_t launch_self_overlap_t(const SelfSet& a, const SelfSet& b, int n_samples,
+                                        uint2 key, hipStream_t st) {
+  const int64_t n = a.n + (int64_t)b.n, most = max_workgroups(kThreads);
   for (int64_t from = 0; from < n; from += most) {
-    hipLaunchKernelGGL(k_self_overlap, dim3((unsigned)std::min(most, n - from)),
-                       dim3(kSelfThreads), 0, st, a, b, from, n_samples, key);
+    hipLaunchKernelGGL((k_self_overlap<kThreads, D>), dim3((unsigned)std::min(most, n - from)),
+                       dim3(kThreads), 0, st, a, b, from, n_samples, key);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_self_overlap(const SelfSet& a, const SelfSet& b, int n_samples, uint2 key,
+                               int n_cu, hipStream_t st) {
+  // 1,024 threads while their workgroups, two per compute unit, all start within a
+  // few turns; with one sample per thread the smaller ones win earlier
+  const int64_t n = a.n + (int64_t)b.n;
+  if (n_samples > kSelfThreads && n <= (int64_t)8 * n_cu)
+    return launch_self_overlap_t<kSelfThreads, 2>(a, b, n_samples, key, st);
+  if (n_samples > kSelfLanes && n <= (int64_t)4 * n_cu)
+    return launch_self_overlap_t<kSelfThreads, 1>(a, b, n_samples, key, st);
+  if (n_samples > kSelfLanes) return launch_self_overlap_t<kSelfLanes, 2>(a, b, n_samples, key, st);
+  return launch_self_overlap_t<kSelfLanes, 1>(a, b, n_samples, key, st);
 }
 
 hipError_t launch_adam_pose(float* pose, const float* dT, float* m, float* v, int64_t n_poses,

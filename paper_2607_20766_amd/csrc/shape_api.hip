@@ -1096,7 +1096,7 @@ int shape_self_overlap(shape_ctx* c, const shape_mols* M, int32_t n_samples, uin
     shape::Prepared P;
     if ((rc = prepare(c, M, false, st, &P))) return rc;
     HIP_TRY(c, shape::launch_self_overlap({P, M->atom_offset, M->n_mols, O_self}, {}, n_samples,
-                                          key_of(seed), st),
+                                          key_of(seed), c->n_cu, st),
             "self-overlap kernel");
     return SHAPE_OK;
   } catch (...) {
@@ -1221,7 +1221,7 @@ int shape_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t 
     if ((rc = align_prepare(c, A, B, n_starts, n_steps, n_samples, st, &PA, &PB, &order))) return rc;
     HIP_TRY(c, shape::launch_self_overlap({PA, A->atom_offset, pairs, (float*)saa},
                                           {PB, B->atom_offset, pairs, (float*)sbb}, n_samples,
-                                          key_of(seed), st),
+                                          key_of(seed), c->n_cu, st),
             "self-overlap kernel");
     // the whole optimisation in one launch: A's samples are drawn once per
     // pair, each start's Adam state stays in registers (the same steps as

@@ -216,7 +216,7 @@ struct SelfSet {
   float* out;
 };
 hipError_t launch_self_overlap(const SelfSet& a, const SelfSet& b, int n_samples, uint2 key,
-                               hipStream_t st);
+                               int n_cu, hipStream_t st);
 hipError_t launch_adam_pose(float* pose, const float* dT, float* m, float* v, int64_t n_poses,
                             int* step, float lr, float b1, float b2, float eps, hipStream_t st);
 hipError_t launch_best_start(const float* T, int n_pairs, int n_starts, int* best,

@@ -266,3 +266,20 @@ def test_long_alignments_in_launch_order_same_bits(eng):
         got = np.concatenate([p[k] for p in parts])
         assert np.array_equal(full.cpu().numpy(), got), k
     assert np.all(np.isfinite(T.cpu().numpy()))
+
+
+@pytest.mark.parametrize("n_samples", [2, 255, 256, 257, 512, 1023, 1024, 1025, 2049])
+def test_self_overlap_of_few_and_many_molecules_same_bits(eng, n_samples):
+    """A workgroup's threads and samples per thread go by the sample count and
+    by how many molecules a call holds; a molecule's value does not."""
+    print(f"case: self-overlap of few and many molecules, {n_samples} samples", flush=True)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    L = molgen.MolSet.concat([molgen.molecule(19, n, n) for n in (1, 2, 64, 65, 30)])
+    ids = np.arange(5, dtype=np.uint32)
+    few = eng.shape_self_overlap(eng.molecules(L, mol_id=ids), n_samples, seed=9)
+    assert torch.isfinite(few).all()
+    for n in (4 * n_cu + 1, 8 * n_cu + 1):
+        i = np.arange(n) % 5
+        many = eng.shape_self_overlap(eng.molecules(L.subset(i), mol_id=ids[i]), n_samples,
+                                      seed=9)
+        assert torch.equal(many, few[torch.from_numpy(i).to(few.device)])

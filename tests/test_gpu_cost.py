@@ -1,0 +1,49 @@
+"""Calls with less to do take accordingly less time: launch shapes chosen for
+large calls must not be forced on small ones.  Ratios of times on one box, with
+room for noise; what a wrong shape costs is stated at each test."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2607_20766_amd import molgen
+from paper_2607_20766_amd.engine import SHAPE_SCREEN_ADAPTIVE, Engine
+from tests.gpu_common import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def eng():
+    require_gpu()
+    return Engine(0)
+
+
+@pytest.fixture(scope="module")
+def base():
+    return molgen.library(93, 400, 10, 50, workers=4)
+
+
+def _library(eng, base, n):
+    return eng.molecules(base.subset(np.arange(n) % base.n_mols))
+
+
+def _ms(f, repeat=5):
+    f()
+    torch.cuda.synchronize()
+    best = 1e9
+    for _ in range(repeat):
+        t = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return 1e3 * best
+
+
+def test_self_overlap_of_few_samples(eng, base):
+    """1/32 of the samples; in workgroups of 1,024 threads 0.68 of the time."""
+    M = _library(eng, base, 100_000)
+    few, many = (_ms(lambda: eng.shape_self_overlap(M, n, seed=1)) for n in (64, 2048))
+    print(f"case: 100,000 self-overlaps, 64 samples {few:.3f} ms, 2,048 {many:.3f}", flush=True)
+    assert few < 0.4 * many
