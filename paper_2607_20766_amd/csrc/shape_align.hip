@@ -79,10 +79,14 @@ __device__ void align_samples(const AlignArgs& a, int pair, float4* sSamp, Atom*
     make_rec(at, cA.x, cA.y, cA.z, sAR[i], sAa[i]);
   }
   __syncthreads();
-  weigh_samples<2>(sAF, sAS, sAR, sAa, na, a.A.id[pair], 0, a.n_samples, a.key,
-                   [&](int k, float x, float y, float z, float w, float) {
-                     sSamp[k] = make_float4(x, y, z, w);
-                   });
+  const auto put = [&](int k, float x, float y, float z, float w, float) {
+    sSamp[k] = make_float4(x, y, z, w);
+  };
+  // two per thread would draw the last sample in place of those past the end
+  if (a.n_samples > (int)blockDim.x)
+    weigh_samples<2>(sAF, sAS, sAR, sAa, na, a.A.id[pair], 0, a.n_samples, a.key, put);
+  else
+    weigh_samples<1>(sAF, sAS, sAR, sAa, na, a.A.id[pair], 0, a.n_samples, a.key, put);
   __syncthreads();
 }
 
@@ -626,20 +630,17 @@ static size_t align_lds(int n_samples, int max_a, int max_b, int sets, int split
                                             (size_t)split_slots * 7 * kWave * sizeof(float));
 }
 
-// Whether an alignment of few starts runs k_align_split: sixteen waves a start.
-// Every workgroup draws A's samples, about the work of one evaluation, so a single
-// evaluation pays for it at fewer starts than an optimisation does.  2,048 samples,
-// 15-45 atoms, 60 steps (split against four starts per workgroup): 10 pairs x 16
-// starts 0.65 against 3.6 ms, 100 x 16 3.7 against 4.3 ms, 200 x 16 (30 steps)
-// equal; one evaluation: 60 x 16 equal, 100 x 16 125 against 102 us.
 static size_t split_lds_bytes(int n_samples, int max_a, int max_b) {
   const int per_lane = (n_samples + kWave - 1) / kWave;
   return align_lds(n_samples, max_a, max_b, 1, std::min(per_lane, kSplitSlots));
 }
 bool align_splits(int n_pairs, int n_starts, int n_steps, int n_samples, int max_a, int max_b,
                   int n_cu, size_t max_lds) {
-  const int64_t per_cu = n_steps > 0 ? 8 : 4;
-  return (int64_t)n_pairs * n_starts <= per_cu * n_cu && n_starts <= 65535 &&
+  const int per_lane = (n_samples + kWave - 1) / kWave;
+  const int busy = std::min(kSplitWaves, (per_lane + kSplitS - 1) / kSplitS);
+  const int resident = (int)(max_lds / align_lds(n_samples, max_a, max_b, kAlignMinWaves, 0)) *
+                       std::min(n_starts, kAlignMinWaves);
+  return align_splits_starts(n_pairs, n_starts, n_steps, busy, resident, n_cu) &&
          align_split_fits(split_lds_bytes(n_samples, max_a, max_b), sizeof(SplitShared), max_lds);
 }
 
@@ -652,12 +653,10 @@ hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max
                        st, a);
     return hipGetLastError();
   }
-  // With many pairs a workgroup takes all of its pair's starts.
   const int waves = align_waves(
       n_pairs, a.n_starts, align_lds(a.n_samples, a.max_a, a.max_b, kAlignMaxWaves, 0) <= max_lds,
-      n_cu);
-  a.starts_per_block = n_pairs >= 16 * n_cu ? a.n_starts
-                                            : std::max(waves, (a.n_starts + 65534) / 65535);
+      3 * align_lds(a.n_samples, a.max_a, a.max_b, kAlignMinWaves, 0) > max_lds, n_cu);
+  a.starts_per_block = align_starts_per_block(n_pairs, a.n_starts, waves, n_cu);
   const unsigned groups = (unsigned)((a.n_starts + a.starts_per_block - 1) / a.starts_per_block);
   hipLaunchKernelGGL(k_align, dim3((unsigned)n_pairs, groups), dim3(waves * kWave),
                      align_lds(a.n_samples, a.max_a, a.max_b, waves, 0), st, a);

@@ -14,17 +14,59 @@ namespace shape {
 constexpr int64_t kMaxWorkItems = ((int64_t)1 << 32) - 1;
 inline int64_t max_workgroups(int threads) { return kMaxWorkItems / threads; }
 
-// Waves (starts in flight) of an alignment's workgroup, one workgroup per pair
-// and group of starts: eight share the samples of A where that leaves two
-// workgroups per compute unit and their LDS fits (eight_fit), else four, the least
-// a call is checked for.
+// Alignments (k_align, k_align_split): how starts are spread over waves and
+// workgroups.  Every shape gives the same bits.
+//
+// Whether every start runs by itself in a workgroup of sixteen waves.  Of these
+// `busy` have samples (two slots of 64 each), and every workgroup draws A's samples,
+// about the work of one evaluation: the fewer are busy, and the fewer evaluations
+// there are, the fewer starts it takes for one wave per start to be as fast.  15-45
+// atoms, split : four waves of a start each, us:
+//   8 steps     256 samples (two busy), 400 starts 110 : 97, 800 184 : 99, 2,000 369 :
+//               104; 512 (four) 800 194 : 165, 2,000 380 : 177; 1,000 (eight) 1,600 391
+//               : 328; 2,048 (sixteen) 160 280 : 520, 2,000 720 : 610
+//   none        256 samples, 550 starts 33 : 27; 512, 550 34 : 29; 1,000, 1,000 54 : 48;
+//               2,048, 1,000 equal
+// resident: waves of k_align with a start that a compute unit's LDS holds (the samples
+// take 16 bytes each).  With one per SIMD or less every wave waits for its own chain
+// alone, however many starts there are: 5,000 pairs x 1 start, 8 steps of 4,096 samples
+// 3.4 : 8.0 ms, of 2,048 1.8 : 2.2; 2,000 x 2 of 4,096 2.6 : 3.5 (x 4, 500 pairs 1.3 : 1.2).
+inline bool align_splits_starts(int64_t n_pairs, int n_starts, int n_steps, int busy,
+                                int resident, int n_cu) {
+  if (n_starts > 65535 || n_pairs > max_workgroups(1024)) return false;
+  if (resident <= (n_steps > 0 ? 4 : 2)) return true;
+  // starts per compute unit, times four
+  const int64_t most = n_steps > 0 ? std::min(28, 2 * (busy + 1)) : std::min(16, busy + 4);
+  return 4 * n_pairs * n_starts <= most * n_cu;
+}
+
+// Waves (starts in flight) of a workgroup: eight share the samples of A where that
+// leaves two workgroups per compute unit and their LDS fits (eight_fit), else four, the
+// least a call is checked for.  Four also where there are pairs enough and the last
+// eight starts would fill half of the waves or less (eight : four, one evaluation of
+// 3,000 pairs, 256 samples: 9 starts 158 : 131 us, 20 256 : 228; 16 201 : 203), unless
+// LDS holds only two workgroups (crowded; 1,000 pairs x 9 of 4,096 569 : 655).
 constexpr int kAlignMinWaves = 4;
 constexpr int kAlignMaxWaves = 8;
-inline int align_waves(int64_t n_pairs, int n_starts, bool eight_fit, int n_cu) {
+inline int align_waves(int64_t n_pairs, int n_starts, bool eight_fit, bool crowded, int n_cu) {
+  const int last = n_starts % kAlignMaxWaves;
+  const bool full = last == 0 || last > kAlignMinWaves;
   const bool eight = n_pairs * n_starts >= (int64_t)2 * kAlignMaxWaves * n_cu &&
-                     n_starts >= kAlignMaxWaves && eight_fit &&
+                     n_starts >= kAlignMaxWaves &&
+                     (full || crowded || n_pairs < (int64_t)3 * n_cu) && eight_fit &&
                      n_pairs <= max_workgroups(kAlignMaxWaves * 64);
   return eight ? kAlignMaxWaves : kAlignMinWaves;
+}
+
+// Starts that a workgroup takes: with many pairs all of its pair's, so that A's samples
+// are drawn once (3,000 pairs x 16 starts, one evaluation of 256 samples: 201 us with
+// eight, 186 with all); with few as many as it has waves, so that there are more
+// workgroups (300 x 16: 34 : 40), or eight (1,000 x 9: four 53, eight 50, all 47; 4 steps
+// 187 : 187 : 194).
+inline int align_starts_per_block(int64_t n_pairs, int n_starts, int waves, int n_cu) {
+  if (n_pairs >= (int64_t)8 * n_cu) return n_starts;
+  const int some = n_pairs >= (int64_t)3 * n_cu ? kAlignMaxWaves : waves;
+  return std::max(some, (n_starts + 65534) / 65535);
 }
 
 // Whether a workgroup's dynamic LDS and its kernel's own (rounded up to 16 bytes,

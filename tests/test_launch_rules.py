@@ -15,8 +15,15 @@ SHIM = """
 using namespace shape;
 extern "C" {
 int64_t r_max_workgroups(int threads) { return max_workgroups(threads); }
-int r_align_waves(int64_t pairs, int starts, int fit, int n_cu) {
-  return align_waves(pairs, starts, fit, n_cu);
+int r_align_waves(int64_t pairs, int starts, int fit, int crowded, int n_cu) {
+  return align_waves(pairs, starts, fit, crowded, n_cu);
+}
+int r_align_splits_starts(int64_t pairs, int starts, int steps, int busy, int resident,
+                          int n_cu) {
+  return align_splits_starts(pairs, starts, steps, busy, resident, n_cu);
+}
+int r_align_starts_per_block(int64_t pairs, int starts, int waves, int n_cu) {
+  return align_starts_per_block(pairs, starts, waves, n_cu);
 }
 int r_align_split_fits(int64_t dynamic, int64_t own, int64_t max_lds) {
   return align_split_fits(dynamic, own, max_lds);
@@ -41,7 +48,9 @@ def rules(tmp_path_factory):
                     str(src), "-o", str(lib)], check=True)
     L = ctypes.CDLL(str(lib))
     L.r_max_workgroups.restype = ctypes.c_int64
-    L.r_align_waves.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    L.r_align_waves.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
+    L.r_align_splits_starts.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 5
+    L.r_align_starts_per_block.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     L.r_align_split_fits.argtypes = [ctypes.c_int64] * 3
     L.r_screen_rounds.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int,
                                   ctypes.c_int64, ctypes.c_int]
@@ -58,9 +67,10 @@ def test_a_launch_stays_below_the_work_item_limit(rules, threads):
 @pytest.mark.parametrize("starts", [1, 7, 8, 16, 1000])
 def test_alignment_workgroups_fit_a_launch(rules, pairs, starts):
     """Up to 2^24 - 1 pairs, as with four waves per workgroup throughout."""
-    waves = rules.r_align_waves(pairs, starts, 1, 256)
-    assert waves in (4, 8) and pairs * waves * 64 < LIMIT
-    assert rules.r_align_waves(pairs, starts, 0, 256) == 4
+    for crowded in (0, 1):
+        waves = rules.r_align_waves(pairs, starts, 1, crowded, 256)
+        assert waves in (4, 8) and pairs * waves * 64 < LIMIT
+        assert rules.r_align_waves(pairs, starts, 0, crowded, 256) == 4
 
 
 @pytest.mark.parametrize("pairs", [1, 7168, 12800, 12801, (1 << 24) - 1, 1 << 24, (1 << 25) - 1,
@@ -80,3 +90,29 @@ def test_a_kernels_own_lds_counts_towards_the_limit(rules):
     assert rules.r_align_split_fits(most - 80, 72, most)
     assert not rules.r_align_split_fits(most - 64, 72, most)
     assert not rules.r_align_split_fits(most, 72, most)
+
+
+def test_starts_run_by_themselves_only_where_their_waves_have_samples(rules):
+    split = rules.r_align_splits_starts
+    # 10 and 100 pairs x 16 starts of 2,048 samples; not 500 x 4 of 256
+    assert split(10, 16, 60, 16, 16, 256) and split(100, 16, 60, 16, 16, 256)
+    assert not split(500, 4, 8, 2, 32, 256) and not split(250, 8, 8, 4, 32, 256)
+    assert not split(1000, 1, 0, 2, 9, 256)
+    # never more workgroups than a launch holds
+    for pairs in (1, 1 << 22, (1 << 22) - 1, 1 << 31):
+        for resident in (1, 4, 16):
+            if split(pairs, 1, 8, 16, resident, 256):
+                assert pairs * 1024 < LIMIT
+
+
+@pytest.mark.parametrize("pairs", [1, 300, 767, 768, 2047, 2048, 1 << 23])
+@pytest.mark.parametrize("starts", [1, 3, 4, 8, 9, 20, 65535, 65536, 600000])
+def test_starts_of_a_pair_are_covered_by_a_grid(rules, pairs, starts):
+    for waves in (4, 8):
+        spb = rules.r_align_starts_per_block(pairs, starts, waves, 256)
+        assert spb >= 1 and (starts + spb - 1) // spb <= 65535
+
+
+def test_eight_waves_only_where_the_last_eight_starts_fill_most_of_them(rules):
+    waves = [rules.r_align_waves(5000, s, 1, 0, 256) for s in range(1, 26)]
+    assert waves == [4] * 7 + [8] + [4] * 4 + [8] * 4 + [4] * 4 + [8] * 4 + [4]
