@@ -1278,7 +1278,7 @@ int shape_fo_starts(shape_ctx* c, const shape_mols* A, const shape_mols* B, int3
     if (!pose) return fail(c, SHAPE_E_INVAL, "pose is NULL");
     if ((rc = set_device(c))) return rc;
     HIP_TRY(c, shape::launch_fo_starts(mols_dev(A), mols_dev(B), n_random, key_of(seed), c->flag,
-                                       pose, (hipStream_t)stream),
+                                       pose, c->n_cu, (hipStream_t)stream),
             "alignment starts kernel");
     return SHAPE_OK;
   } catch (...) {

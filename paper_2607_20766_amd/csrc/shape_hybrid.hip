@@ -14,6 +14,7 @@
 // and dT/dq follows from dtheta = 2 (w dv - dw v + v x dv) for q = (w, v).
 #include "shape_kernels.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 #include <math.h>
@@ -92,27 +93,29 @@ __device__ void jacobi3(double a[3][3], double V[9]) {
 // Mixture mean and principal axes of one molecule (weights v_i / Z,
 // v_i = (pi/alpha_i)^(3/2), given as t = pi/alpha_i and its root); axes as
 // columns of U, descending variance, the largest-magnitude component of the
-// first two positive, U right-handed.
-__device__ void principal_frame(const float* xyz, const double2* t_root, int n, double mu[3],
-                                double U[9]) {
+// first two positive, U right-handed.  get(i, xyz) gives atom i's t, root and
+// position.
+template <class Get>
+__device__ __forceinline__ void principal_frame(Get get, int n, double mu[3], double U[9]) {
   double Z = 0.0, m0 = 0.0, m1 = 0.0, m2 = 0.0;
   for (int i = 0; i < n; ++i) {
-    const double2 t = t_root[i];
+    float c[3];
+    const double2 t = get(i, c);
     const double v = t.x * t.y;
     Z = fma(t.x, t.y, Z);
-    m0 = fma(v, (double)xyz[3 * i], m0);
-    m1 = fma(v, (double)xyz[3 * i + 1], m1);
-    m2 = fma(v, (double)xyz[3 * i + 2], m2);
+    m0 = fma(v, (double)c[0], m0);
+    m1 = fma(v, (double)c[1], m1);
+    m2 = fma(v, (double)c[2], m2);
   }
   mu[0] = m0 / Z;
   mu[1] = m1 / Z;
   mu[2] = m2 / Z;
   double C[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
   for (int i = 0; i < n; ++i) {
-    const double2 t = t_root[i];
+    float at[3];
+    const double2 t = get(i, at);
     const double w = t.x * t.y / Z;
-    const double x[3] = {(double)xyz[3 * i] - mu[0], (double)xyz[3 * i + 1] - mu[1],
-                         (double)xyz[3 * i + 2] - mu[2]};
+    const double x[3] = {(double)at[0] - mu[0], (double)at[1] - mu[1], (double)at[2] - mu[2]};
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -175,54 +178,80 @@ __device__ __forceinline__ float4 fo_atom(const MolsDev& M, int i) {
                      M.alpha[i]);
 }
 
-// Eight lanes per pair: even lanes take A's frame, odd lanes B's (the four
-// lanes of a molecule share its weights' roots and divisions through LDS and
-// then form the same sums in atom order), and each lane takes every eighth
-// start.  A chain of FP64 latencies (sums, Jacobi, quaternions) whatever the
-// number of pairs: 10,000 pairs 154 -> 28 us (one lane per pair took two
-// frames and seven starts in turn, with arrays in scratch memory).
-constexpr int kStartLanes = 8;
-constexpr int kStartPairs = kWave / kStartLanes;
-__host__ __device__ inline size_t fo_starts_lds_bytes(int max_atoms) {
-  return (size_t)2 * kStartPairs * max_atoms * (sizeof(double2) + 3 * sizeof(float));
+// kLanes lanes per pair: even lanes take A's frame, odd lanes B's (lanes of one
+// molecule form the same sums in atom order), and each lane takes every kLanes-th
+// start.  A chain of FP64 latencies (sums, Jacobi, quaternions) while there are few
+// pairs: eight lanes share a molecule's weights' roots and divisions through LDS,
+// 10,000 pairs 154 -> 28 us (one lane per pair took two frames and seven starts in
+// turn, with arrays in scratch memory).  Many pairs are bound by FP64 issue, and large
+// molecules by that LDS: two lanes repeat nothing and read the atoms from memory.
+__host__ __device__ inline size_t fo_starts_lds_bytes(int lanes, int max_atoms) {
+  return lanes == 2 ? 0
+                    : (size_t)2 * (kWave / lanes) * max_atoms *
+                          (sizeof(double2) + 3 * sizeof(float));
 }
 
+template <int kLanes>
 __global__ __launch_bounds__(kWave) void k_fo_starts(MolsDev A, MolsDev B, int n_random, uint2 key,
                                                      int* __restrict__ flag,
                                                      float* __restrict__ pose) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x, l = lane % kStartLanes, half = l & 1;
+  constexpr bool kStaged = kLanes > 2;
+  constexpr int kPairs = kWave / kLanes;
+  const int lane = threadIdx.x, l = lane % kLanes, half = l & 1;
   const int max_n = A.max_atoms > B.max_atoms ? A.max_atoms : B.max_atoms;
-  const int set = 2 * (lane / kStartLanes) + half;
+  const int set = 2 * (lane / kLanes) + half;
   double2* t_root = reinterpret_cast<double2*>(smem) + (size_t)set * max_n;
   float* xyz = reinterpret_cast<float*>(reinterpret_cast<double2*>(smem) +
-                                        (size_t)2 * kStartPairs * max_n) +
+                                        (size_t)2 * kPairs * max_n) +
                (size_t)set * 3 * max_n;
-  const int p = blockIdx.x * kStartPairs + lane / kStartLanes;
+  const int p = blockIdx.x * kPairs + lane / kLanes;
   const bool live = p < B.n_mols;
-  int n = 0;
+  const MolsDev& M = half ? B : A;
+  const auto root = [](float alpha) {
+    const double t = M_PI / (double)alpha;
+    return make_double2(t, sqrt(t));
+  };
+  int a0 = 0, n = 0;
   bool bad = false;
   if (live) {
-    const MolsDev& M = half ? B : A;
     const int m = half ? p : (A.n_mols == 1 ? 0 : p);
-    const int a0 = M.off[m], a1 = M.off[m + 1];
+    a0 = M.off[m];
+    const int a1 = M.off[m + 1];
     bad = !fo_range_ok(M, a0, a1);
     n = bad ? 0 : a1 - a0;
-    for (int i = l >> 1; i < n; i += kStartLanes / 2) {
+    for (int i = l >> 1; i < n; i += kLanes / 2) {
       const float4 c = fo_atom(M, a0 + i);
       if (!fo_atom_ok(c)) bad = true;
-      const double t = M_PI / (double)c.w;
-      t_root[i] = make_double2(t, sqrt(t));
-      xyz[3 * i] = c.x;
-      xyz[3 * i + 1] = c.y;
-      xyz[3 * i + 2] = c.z;
+      if constexpr (kStaged) {
+        t_root[i] = root(c.w);
+        xyz[3 * i] = c.x;
+        xyz[3 * i + 1] = c.y;
+        xyz[3 * i + 2] = c.z;
+      }
     }
   }
-  const uint64_t mine = 0xFFull << (lane & ~(kStartLanes - 1));
-  bad = (__ballot(bad) & mine) != 0;
+  constexpr uint64_t kMine = (1ull << kLanes) - 1;
+  bad = (__ballot(bad) & (kMine << (lane & ~(kLanes - 1)))) != 0;
   wave_lds_sync();
   double mu[3] = {0, 0, 0}, U[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
-  if (live && !bad) principal_frame(xyz, t_root, n, mu, U);
+  if (live && !bad) {
+    const auto get = [&](int i, float (&at)[3]) {
+      if constexpr (kStaged) {
+        at[0] = xyz[3 * i];
+        at[1] = xyz[3 * i + 1];
+        at[2] = xyz[3 * i + 2];
+        return t_root[i];
+      } else {
+        const float4 c = fo_atom(M, a0 + i);
+        at[0] = c.x;
+        at[1] = c.y;
+        at[2] = c.z;
+        return root(c.w);
+      }
+    };
+    principal_frame(get, n, mu, U);
+  }
   double muA[3], UA[9], muB[3], UB[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) {
@@ -238,12 +267,12 @@ __global__ __launch_bounds__(kWave) void k_fo_starts(MolsDev A, MolsDev B, int n
   const int n_starts = 5 + n_random;
   float* out = pose + (size_t)p * n_starts * 7;
   if (bad) {
-    for (int c = l; c < n_starts * 7; c += kStartLanes) out[c] = __builtin_nanf("");
+    for (int c = l; c < n_starts * 7; c += kLanes) out[c] = __builtin_nanf("");
     if (l == 0) atomicOr(flag, 1);
     return;
   }
-  if (l < 7) out[l] = l == 0 ? 1.f : 0.f;
-  for (int s = l; s < 4 + n_random; s += kStartLanes) {
+  for (int c = l; c < 7; c += kLanes) out[c] = c == 0 ? 1.f : 0.f;
+  for (int s = l; s < 4 + n_random; s += kLanes) {
     double R[9];
     if (s < 4) {
       // the proper sign matrices diag(1, 1, 1), (1, -1, -1), (-1, 1, -1), (-1, -1, 1)
@@ -936,12 +965,25 @@ __global__ __launch_bounds__(64) void k_apply_pose(MolsDev M, const float* __res
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, int n_random, uint2 key,
-                            int* flag, float* pose, hipStream_t st) {
-  const int max_atoms = A.max_atoms > B.max_atoms ? A.max_atoms : B.max_atoms;
-  hipLaunchKernelGGL(k_fo_starts, dim3((B.n_mols + kStartPairs - 1) / kStartPairs), dim3(kWave),
-                     fo_starts_lds_bytes(max_atoms), st, A, B, n_random, key, flag, pose);
+template <int kLanes>
+static hipError_t launch_fo_starts_t(const MolsDev& A, const MolsDev& B, int n_random, uint2 key,
+                                     int* flag, float* pose, hipStream_t st) {
+  const int64_t blocks = ((int64_t)B.n_mols * kLanes + kWave - 1) / kWave;
+  hipLaunchKernelGGL((k_fo_starts<kLanes>), dim3((unsigned)blocks), dim3(kWave),
+                     fo_starts_lds_bytes(kLanes, std::max(A.max_atoms, B.max_atoms)), st, A, B,
+                     n_random, key, flag, pose);
   return hipGetLastError();
+}
+
+hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, int n_random, uint2 key,
+                            int* flag, float* pose, int n_cu, hipStream_t st) {
+  // eight : two lanes, us, 3 random starts: 10-50 atoms, 10,000 pairs 32 : 45, 20,000 53 :
+  // 47, 10^6 1,645 : 1,180; 150-256 atoms (one wave's LDS per compute unit), 2,000 67 :
+  // 166, 10,000 329 : 276, 100,000 3,560 : 950
+  const bool large = std::max(A.max_atoms, B.max_atoms) > 128;
+  if (B.n_mols > (large ? 24 : 48) * n_cu)
+    return launch_fo_starts_t<2>(A, B, n_random, key, flag, pose, st);
+  return launch_fo_starts_t<8>(A, B, n_random, key, flag, pose, st);
 }
 
 // For s starts per wave.

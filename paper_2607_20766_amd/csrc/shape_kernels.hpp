@@ -164,7 +164,7 @@ hipError_t launch_grid(const float* xa, const float* aa, int na, const float* xb
 // hybrid pipeline (first-order alignment); the caller's arrays are read
 // directly, invalid molecules give NaN and raise *flag
 hipError_t launch_fo_starts(const MolsDev& A, const MolsDev& B, int n_random, uint2 key,
-                            int* flag, float* pose, hipStream_t st);
+                            int* flag, float* pose, int n_cu, hipStream_t st);
 size_t fo_align_lds_bytes(int max_a, int max_b);
 hipError_t launch_fo_align(const MolsDev& A, const MolsDev& B, int n_starts, int n_steps,
                            float lr, int* flag, float* pose, float* T, float* grad,

@@ -59,3 +59,14 @@ def test_alignment_of_few_samples(eng, base):
                  for n in (256, 2048))
     print(f"case: 500 x 4 alignments, 256 samples {few:.3f} ms, 2,048 {many:.3f}", flush=True)
     assert few < 0.35 * many
+
+
+def test_alignment_starts_of_many_pairs_of_large_molecules(eng):
+    """20 times the pairs; with the atoms in LDS, eight pairs of one wave in
+    a compute unit's, 19 times the time (67 against 1,300 us)."""
+    lib = molgen.library(94, 60, 150, 256, workers=4)
+    q = eng.molecules(molgen.molecule(94, 100, 30), mol_id=[1])
+    L = [_library(eng, lib, n) for n in (2000, 40_000)]
+    few, many = (_ms(lambda: eng.shape_fo_starts(q, M, 3, seed=1)) for M in L)
+    print(f"case: starts, 2,000 pairs {few:.3f} ms, 40,000 {many:.3f}", flush=True)
+    assert many < 9 * few

@@ -455,3 +455,32 @@ def test_long_first_order_alignment_in_launch_order_same_bits(eng):
         got = np.concatenate([p[k] for p in parts])
         assert np.array_equal(full.cpu().numpy(), got), k
     assert np.all(np.isfinite(T.cpu().numpy()))
+
+
+@pytest.mark.parametrize("atoms,per_cu", [((1, 2, 3, 50), 48), ((1, 4, 256, 130), 24)])
+@pytest.mark.parametrize("broadcast", [True, False])
+def test_starts_of_few_and_many_pairs_same_bits(eng, atoms, per_cu, broadcast):
+    """Eight lanes per pair up to per_cu pairs per compute unit, two beyond:
+    the first pairs of a long call have the rows of a short one, an invalid
+    molecule's NaN among them, and the last ones the rows of their repeats
+    (but for the random rotations, which go by the pair's number)."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    few, many = per_cu * n_cu, per_cu * n_cu + 37
+    print(f"case: starts of {few} and {many} pairs of up to {max(atoms)} atoms", flush=True)
+    base = molgen.MolSet.concat([molgen.molecule(97, i, n) for i, n in enumerate(atoms)])
+
+    def sets(n):
+        B = eng.molecules(base.subset(np.arange(n) % 4))
+        B.xyz[int(B.offsets[5]), 1] = float("nan")
+        A = (eng.molecules(molgen.molecule(97, 9, 31)) if broadcast
+             else eng.molecules(base.subset(np.arange(3, n + 3) % 4)))
+        return A, B
+
+    short = eng.shape_fo_starts(*sets(few), n_random=6, seed=4)
+    long = eng.shape_fo_starts(*sets(many), n_random=6, seed=4)
+    assert torch.isnan(short[5]).all() and torch.isnan(short).sum() == short[5].numel()
+    assert torch.equal(torch.nan_to_num(long[:few], nan=7.0), torch.nan_to_num(short, nan=7.0))
+    i = torch.arange(few, many, device=long.device)
+    assert torch.equal(long[few:, :5], long[8 + i % 4, :5])
+    with pytest.raises(ShapeError):
+        eng.shape_check_data()
