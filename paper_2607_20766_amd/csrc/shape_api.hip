@@ -18,6 +18,7 @@
 
 #include "shape_is.h"
 #include "shape_kernels.hpp"
+#include "shape_launch.hpp"
 
 #define SHAPE_VERSION_STR "shape_is 0.1.0 (gfx950)"
 
@@ -576,13 +577,15 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   return SHAPE_OK;
 }
 
-// Without a choice by the caller or the tuner: four points per lane on both
-// sides, the fastest variant measured on screens of 500, 7,000, 20,000 and
-// 100,000 drug-sized molecules, fixed and adaptive, i.i.d. and antithetic
-// (100,000, adaptive: 7.15 ms; the next ones 7.22 and 7.32 ms).
-constexpr int kScreenDefaultVariant = 3;
-int screen_variant_of(const shape_ctx* c) {
-  return c->screen_variant < 0 ? kScreenDefaultVariant : c->screen_variant;
+// Without a choice by the caller or the tuner: the tile of screen_points(), four points
+// per lane on both sides with rounds of whole fours (the fastest variant measured on
+// screens of 500, 7,000, 20,000 and 100,000 drug-sized molecules, fixed and adaptive,
+// i.i.d. and antithetic: 100,000, adaptive 7.15 ms, the next ones 7.22 and 7.32), or two;
+// (2, 1) for one slot per lane (40,000 pairs 1.78 ms, two points 2.50).
+int screen_variant_of(const shape_ctx* c, int round_side) {
+  if (c->screen_variant >= 0) return c->screen_variant;
+  const int per_lane = round_side / shape::kWave;
+  return per_lane == 1 ? 5 : (shape::screen_points(per_lane) == 2 ? 1 : 3);
 }
 
 }  // namespace
@@ -867,7 +870,7 @@ int shape_screen(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
     KernelTimer timer(c, st);
     // a variant set by the caller runs as set; the tuner's choice is for
     // screens that take one wave per pair
-    const int variant = screen_variant_of(c);
+    const int variant = screen_variant_of(c, a.round_side);
     HIP_TRY(c, c->variant_set ? shape::launch_screen(a, variant, st)
                               : shape::launch_screen_auto(a, variant, c->n_cu, st),
             "screen kernel");

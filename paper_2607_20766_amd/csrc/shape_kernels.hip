@@ -1364,12 +1364,15 @@ hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStr
     return launch_screen_split(a, st);
   const bool adaptive = a.mode == SHAPE_SCREEN_ADAPTIVE;
   const int64_t n_rounds = (adaptive ? a.cap_pair / 2 : a.n_fixed) / a.round_side;
-  switch (screen_rounds(adaptive, a.n_pairs, n_rounds, a.round_side,
-                        (int64_t)screen_lds_bytes(a.max_q, a.max_b), n_cu)) {
-    case 4: launch_screen_t<4, 4, 4>(a, st); break;
-    case 2: launch_screen_t<4, 4, 2>(a, st); break;
-    default: return launch_screen(a, variant, st);
-  }
+  const int R = screen_rounds(adaptive, a.n_pairs, n_rounds, a.round_side,
+                              (int64_t)screen_lds_bytes(a.max_q, a.max_b), n_cu);
+  const bool two = screen_points(a.round_side / kWave) == 2;
+  if (R == 4)
+    two ? launch_screen_t<2, 2, 4>(a, st) : launch_screen_t<4, 4, 4>(a, st);
+  else if (R == 2)
+    two ? launch_screen_t<2, 2, 2>(a, st) : launch_screen_t<4, 4, 2>(a, st);
+  else
+    return launch_screen(a, variant, st);
   return hipGetLastError();
 }
 

@@ -75,6 +75,14 @@ inline bool align_split_fits(size_t dynamic, size_t own, size_t max_lds) {
   return dynamic + (own + 15) / 16 * 16 <= max_lds;
 }
 
+// Sample points per lane that a screen evaluates together: four, or two where the last
+// four of a lane's slots in a round (per_lane of them) would be half empty or more (one
+// wave per pair, 40,000 pairs, four : two points, ms: 2 slots 2.37 : 1.31, 4 1.27 : 1.31, 5
+// 1.96 : 1.56, 6 1.67 : 1.33, 7 1.47 : 1.54, 22 1.78 : 1.71).
+inline int screen_points(int per_lane) {
+  return per_lane % 4 == 1 || per_lane % 4 == 2 ? 2 : 4;
+}
+
 // Rounds of a pair that its workgroup works on at a time, a wave each, in screens
 // that one wave per pair leaves short of waves: four rounds and two rounds fill the
 // chip up to kFourRoundPairsPerCu (28 pairs per compute unit are fewer than eight

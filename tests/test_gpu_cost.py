@@ -70,3 +70,15 @@ def test_alignment_starts_of_many_pairs_of_large_molecules(eng):
     few, many = (_ms(lambda: eng.shape_fo_starts(q, M, 3, seed=1)) for M in L)
     print(f"case: starts, 2,000 pairs {few:.3f} ms, 40,000 {many:.3f}", flush=True)
     assert many < 9 * few
+
+
+def test_screens_of_short_rounds(eng, base):
+    """The same samples in rounds of 128 per side, two per lane, instead of 256;
+    with tiles of four points, half of them unused, twice the time."""
+    lib = _library(eng, base, 20_000)
+    q = eng.molecules(molgen.molecule(94, 1, 30), mol_id=[1])
+    short, whole = (_ms(lambda: eng.shape_screen(q, lib, mode=SHAPE_SCREEN_ADAPTIVE,
+                                                 round_per_pair=r, cap_per_pair=8192, tau=0.001,
+                                                 seed=1)) for r in (256, 512))
+    print(f"case: 20,000 pairs, rounds of 128 {short:.3f} ms, of 256 {whole:.3f}", flush=True)
+    assert short < 1.4 * whole
