@@ -529,9 +529,17 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   // small one share one: adaptive 300 molecules 102 -> 86 us, 501 102 : 103, 1,000
   // 169 -> 154, 2,000 273 -> 238, 4,000 418 -> 396; fixed, 4,096 per side, 501 74 ->
   // 65, 1,000 122 -> 102, 4,000 330 -> 304 (without the turns 2,000 243, 1,000
-  // fixed 106).
+  // fixed 106).  Not for pairs of little work, about 25,000 evaluations and draws'
+  // worth of them: 3,000 of 1-4 atoms, one round 38 -> 40.
+  const double mean_b = std::max((double)lib->n_atoms / lib->n_mols, 1.0);
+  const double expected = shape::screen_rounds_expected(prm->tau, round_side, query->max_atoms,
+                                                        mean_b);
+  const double side = prm->mode == SHAPE_SCREEN_FIXED
+                          ? (double)n_fixed
+                          : std::min(cap / 2.0, round_side * std::max(1.0, expected));
+  const bool worth = o.n_start || side * (2.0 * mean_b + query->max_atoms + o.w0) >= 25000.0;
   int* short_order = nullptr;
-  if (!wo.order && n_pairs > c->n_cu) {
+  if (!wo.order && n_pairs > c->n_cu && worth) {
     short_order = c->short_order;
     o.per_xcd = 0;
     o.snake = c->n_cu;
@@ -555,6 +563,8 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   a->offL = lib->atom_offset;
   a->n_lib = lib->n_mols;
   a->max_b = lib->max_atoms;
+  a->expected = expected;
+  a->first_rounds = 1;
   a->qs = (const float4*)qs;
   a->qf2 = (const float*)qf2;
   a->pairs = pairs;

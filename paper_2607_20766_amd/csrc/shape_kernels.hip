@@ -493,10 +493,11 @@ struct RoundSums {
 // delta-method SE satisfies
 //   SE(T)^2 = S'^2 (Za^2 Va + Zb^2 Vb) / (4 (n-1) D'^4),
 // so the test is S'^2 (Za^2 Va + Zb^2 Vb) <= 4 tau^2 (n-1) D'^4 with
-// D' != 0 (NaN sums never stop).
+// D' != 0 (NaN sums never stop).  ratio, if given, receives the left side over the
+// right where the test was made, about (SE(T)/tau)^2.
 __device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSums& S,
                                              int64_t n_side, int64_t first_check, bool anti,
-                                             double Za, double Zb) {
+                                             double Za, double Zb, double* ratio = nullptr) {
 #pragma clang fp contract(off)
   if (a.mode != SHAPE_SCREEN_ADAPTIVE) return n_side >= a.n_fixed;
   if (2 * n_side >= a.cap_pair) return true;
@@ -510,7 +511,21 @@ __device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSum
   const double Vb = fmax(n * b11 - b1 * b1, 0.0);
   const double lhs = Sp * Sp * (Za * Za * Va + Zb * Zb * Vb);
   const double D2 = Dp * Dp;
-  return Dp != 0.0 && lhs <= tau2x4 * (n - 1.0) * D2 * D2;
+  const double rhs = tau2x4 * (n - 1.0) * D2 * D2;
+  if (ratio) *ratio = lhs * __builtin_amdgcn_rcp(rhs);
+  return Dp != 0.0 && lhs <= rhs;
+}
+
+// Rounds for an adaptive pair's workgroup to draw together next, at most R, after
+// n_side samples per side whose test left SE(T)^2 at `ratio` times tau^2 (about): as
+// many as the budget or that ratio, which falls as 1/n, still asks for.  What it returns
+// changes no result: rounds past the stop are dropped.
+__device__ __forceinline__ int screen_next(int R, int64_t n_side, int round_side,
+                                           int64_t first_check, double ratio) {
+  const int64_t budget = first_check - 2 * n_side;
+  const float more = budget > 0 ? (float)budget / (float)(2 * round_side)
+                                : (float)n_side / (float)round_side * ((float)ratio - 1.0f);
+  return !(more < (float)R) ? R : max(1, (int)ceilf(more));
 }
 
 // A pair's outputs from its sums (one lane).
@@ -722,10 +737,16 @@ void k_screen(ScreenArgs a) {
   RoundSums S;
   int64_t n_side = 0;
   int buf = 0;
+  int take = 1;  // rounds of this pass
+  if constexpr (kRounds > 1) {
+    take = a.first_rounds;
+    if (a.n_start && take < kRounds)
+      take = max(take, screen_next(kRounds, 0, rs, (int64_t)a.n_start[p], 0.0));
+  }
   for (;;) {
     SideSums<kAnti> A, B;
     const int n0 = (int)n_side + wave * rs;  // this wave's round, if the pair has it
-    if (kRounds == 1 || n0 < screen_limit(screen_args_again())) {
+    if (kRounds == 1 || (wave < take && n0 < screen_limit(screen_args_again()))) {
       // side A: query samples from the cache (query frame), partner = library
       for (int t = 0; t < per_lane; t += kSA) {
         float rx[kSA], ry[kSA], rz[kSA], r2[kSA], w[kSA], f2[kSA], q[kSA];
@@ -778,14 +799,18 @@ void k_screen(ScreenArgs a) {
     } else {
       if (lane < 6) sTot[buf][wave][lane] = v;
       __syncthreads();
-      for (int k = 0; k < kRounds && !stop; ++k) {
+      const int64_t first_check = r.n_start ? (int64_t)r.n_start[p] : 0;
+      double ratio = 0.0;
+      for (int k = 0; k < take && !stop; ++k) {
         S.add(sTot[buf][k][lane < 6 ? lane : 5]);
         n_side += rs;
-        stop = __builtin_amdgcn_readfirstlane(
-            screen_stops(r, S, n_side, r.n_start ? (int64_t)r.n_start[p] : 0, kAnti, r.Q.Z[0],
-                         r.L.Z[m]));
+        stop = __builtin_amdgcn_readfirstlane(screen_stops(r, S, n_side, first_check, kAnti,
+                                                           r.Q.Z[0], r.L.Z[m], &ratio));
       }
       buf ^= 1;
+      if (!stop && r.first_rounds < kRounds)
+        take = __builtin_amdgcn_readfirstlane(
+            screen_next(kRounds, n_side, rs, first_check, ratio));
     }
     if (__builtin_amdgcn_readfirstlane(stop)) break;
   }
@@ -1364,15 +1389,19 @@ hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStr
     return launch_screen_split(a, st);
   const bool adaptive = a.mode == SHAPE_SCREEN_ADAPTIVE;
   const int64_t n_rounds = (adaptive ? a.cap_pair / 2 : a.n_fixed) / a.round_side;
-  const int R = screen_rounds(adaptive, a.n_pairs, n_rounds, a.round_side,
-                              (int64_t)screen_lds_bytes(a.max_q, a.max_b), n_cu);
+  const ScreenShape shape =
+      screen_shape(adaptive, a.n_pairs, n_rounds, a.expected, a.round_side,
+                   (int64_t)screen_lds_bytes(a.max_q, a.max_b), n_cu);
+  const int R = shape.rounds;
+  ScreenArgs s = a;
+  s.first_rounds = shape.first;
   const bool two = screen_points(a.round_side / kWave) == 2;
   if (R == 4)
-    two ? launch_screen_t<2, 2, 4>(a, st) : launch_screen_t<4, 4, 4>(a, st);
+    two ? launch_screen_t<2, 2, 4>(s, st) : launch_screen_t<4, 4, 4>(s, st);
   else if (R == 2)
-    two ? launch_screen_t<2, 2, 2>(a, st) : launch_screen_t<4, 4, 2>(a, st);
+    two ? launch_screen_t<2, 2, 2>(s, st) : launch_screen_t<4, 4, 2>(s, st);
   else
-    return launch_screen(a, variant, st);
+    return launch_screen(s, variant, st);
   return hipGetLastError();
 }
 

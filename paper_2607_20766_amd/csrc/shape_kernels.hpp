@@ -54,6 +54,8 @@ struct ScreenArgs {
   const int* n_start;  // optional per-pair budgets (adaptive)
   int anti;            // antithetic sampling: terms are pair means
   const int* order;    // optional launch order: block b screens pair order[b]
+  int first_rounds;    // rounds of a pair's first pass (set by launch_screen_auto)
+  double expected;     // rounds a pair takes on average, about (for launch_screen_auto)
   float* T;
   float* se_T;
   float* O_ab;
@@ -255,7 +257,7 @@ hipError_t launch_screen(const ScreenArgs& a, int variant, hipStream_t st);
 // per pair up to kSplitPairsPerCu pairs per compute unit (rounds of 256 samples
 // per side), where a pair's chain of rounds bounds the call (256 molecules 0.10
 // ms against 0.12 with four rounds at a time, 1,000 0.190 : 0.185); then several
-// rounds of a pair at a time (screen_rounds); else one wave per pair in the tile
+// rounds of a pair at a time (screen_shape); else one wave per pair in the tile
 // shape `variant`.
 hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStream_t st);
 // Launch order of a grid with one workgroup per pair (blocks along x):

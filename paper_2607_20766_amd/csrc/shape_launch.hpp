@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 namespace shape {
 
@@ -83,39 +84,58 @@ inline int screen_points(int per_lane) {
   return per_lane % 4 == 1 || per_lane % 4 == 2 ? 2 : 4;
 }
 
-// Rounds of a pair that its workgroup works on at a time, a wave each, in screens
-// that one wave per pair leaves short of waves: four rounds and two rounds fill the
-// chip up to kFourRoundPairsPerCu (28 pairs per compute unit are fewer than eight
-// waves per SIMD) and kTwoRoundPairsPerCu, or where a pair's LDS (lds bytes) leaves
-// a compute unit few pairs.  Rounds drawn past an adaptive pair's stop are dropped,
-// (R - 1)/2 on average, so R falls as a round grows; n_rounds is the most a pair
-// takes.  One : two : four rounds, ms:
-//   few pairs          5,000 molecules of 10-50 atoms, adaptive 0.58 : 0.51 :
-//                      0.49; 8,000 0.78 : 0.71 : 0.72; 11,000 1.00 : 0.92 : 0.96;
-//                      13,000 1.09 : 1.07 : 1.14; 16,000 1.29 : 1.30 : 1.37
-//   LDS per pair       20,000 of 50-100 atoms (17 pairs' records in a compute
-//                      unit's LDS) 3.04 : 2.63 : 2.78; 60,000 of 30-70 (25) 6.59
-//                      : 6.53 : 6.90; of 30-60 (28) 6.49 : 6.52 : 6.88; 20,000
-//                      of 100-150 (11) fixed 3.09 : 2.59 : 2.32, of 200-256 (6)
-//                      6.98 : 5.03 : 3.99
-//   long rounds        8,000 pairs, 1,024 samples per side and round 0.81 :
-//                      0.77 : 0.88
-// One workgroup per pair: R also falls until the launch holds them (2^24 pairs of
-// four waves are too many).
+// Rounds that adaptive pairs take to SE(T) <= tau, on average and roughly: 17 rounds of
+// 256 samples per side for 30 atoms against 10-50 at tau 0.005, going as 1/tau^2, fewer
+// where the molecules differ in size (measured : this, tau 0.005, a query of 30 against 1-4
+// atoms 2.2 : 2.5, 4-12 9.0 : 8.2, 50-100 11.9 : 12.2, 150-256 4.9 : 4.6).  Only kernels
+// are chosen by it.
+inline double screen_rounds_expected(double tau, int round_side, double query_atoms,
+                                     double library_atoms) {
+  const double large = std::max(query_atoms, library_atoms);
+  const double alike = std::min(1.0, 1.75 * std::min(query_atoms, library_atoms) / large);
+  return 0.112 / (tau * tau * round_side) * alike * std::pow(std::max(1.0, 25.0 / large), 0.6);
+}
+
+// Rounds of a pair that its workgroup works on at a time, a wave each, and those of its
+// first pass: all of them, and then in every pass (fixed mode, and pairs so few that all
+// waves run at once), or fewer, and then as many as the pair still seems to need.
+// Several rounds where one wave per pair leaves a compute unit short of waves:
+//   LDS per pair       (lds bytes) for the rounds, any number of them: 20,000 molecules of
+//                      50-100 atoms (17 pairs in a compute unit's LDS), one : two : four
+//                      rounds 3.04 : 2.63 : 2.78 ms; 60,000 of 30-70 (25) 6.59 : 6.53 :
+//                      6.90, of 30-60 (28) 6.49 : 6.52 : 6.88; 20,000 of 100-150 (11) fixed
+//                      3.09 : 2.59 : 2.32, of 200-256 (6) 6.98 : 5.03 : 3.99
+//   few pairs          four up to 28 pairs per compute unit (fewer than eight waves per
+//                      SIMD), two up to 50: 5,000 molecules of 10-50 atoms, adaptive 0.58 :
+//                      0.51 : 0.49 ms; 8,000 0.78 : 0.71 : 0.72; 11,000 1.00 : 0.92 : 0.96;
+//                      13,000 1.09 : 1.07 : 1.14.  Adaptive pairs have to need them: a pair
+//                      that stops in its first rounds leaves its other waves idle (one : four,
+//                      us: 3,000 pairs of 10-50 atoms that take 1.0 rounds 47 : 57, 1.5 63 :
+//                      76, 4.7 138 : 126; 7,000 1.5 100 : 129, 4.7 217 : 232, 9 255 : 252;
+//                      1,500 1.6 equal, 2.4 56 : 48), and long rounds do not repay a dropped
+//                      one (8,000 pairs, 1,024 samples per side and round 0.81 : 0.77 : 0.88)
+// One workgroup per pair: the rounds fall until a launch holds them.  n_rounds is the most
+// a pair takes, expected what it takes on average.
 constexpr int kSplitPairsPerCu = 3;  // up to here rounds of 256 samples: eight waves per pair
-constexpr int kFourRoundPairsPerCu = 28;
-constexpr int kTwoRoundPairsPerCu = 50;
-inline int screen_rounds(bool adaptive, int64_t n_pairs, int64_t n_rounds, int round_side,
-                         int64_t lds, int n_cu) {
+struct ScreenShape {
+  int rounds, first;
+};
+inline ScreenShape screen_shape(bool adaptive, int64_t n_pairs, int64_t n_rounds, double expected,
+                                int round_side, int64_t lds, int n_cu) {
   constexpr int64_t kLdsPerCu = 160 * 1024;
   const int64_t resident = kLdsPerCu / lds;
-  int R = 1;
-  if (n_pairs <= (int64_t)kTwoRoundPairsPerCu * n_cu || resident <= 25) R = 2;
-  if (n_pairs <= (int64_t)kFourRoundPairsPerCu * n_cu || resident <= 11) R = 4;
-  if (adaptive && n_pairs > (int64_t)kSplitPairsPerCu * n_cu)
-    while (R > 1 && R * round_side > 1024) R /= 2;
+  const auto up_to = [&](int per_cu) { return n_pairs <= (int64_t)per_cu * n_cu; };
+  int few = up_to(28) ? 4 : (up_to(50) ? 2 : 1);
+  if (adaptive && !up_to(1)) {
+    const double least = up_to(kSplitPairsPerCu) ? 1.0 : (up_to(8) ? 2.0 : (up_to(14) ? 4.0 : 8.0));
+    if (expected < least) few = 1;
+    if (!up_to(kSplitPairsPerCu))
+      while (few > 1 && few * round_side > 1024) few /= 2;
+  }
+  int R = std::max(few, resident <= 11 ? 4 : (resident <= 25 ? 2 : 1));
   while (R > n_rounds || (R > 1 && n_pairs > max_workgroups(R * 64))) R /= 2;
-  return R;
+  const bool all = !adaptive || (few > 1 && up_to(kSplitPairsPerCu));
+  return {R, all ? R : 1};
 }
 
 }  // namespace shape

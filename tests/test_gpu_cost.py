@@ -82,3 +82,18 @@ def test_screens_of_short_rounds(eng, base):
                                                  seed=1)) for r in (256, 512))
     print(f"case: 20,000 pairs, rounds of 128 {short:.3f} ms, of 256 {whole:.3f}", flush=True)
     assert short < 1.4 * whole
+
+
+def test_screens_that_stop_in_their_first_round(eng, base):
+    """Pairs of one round each (tau 0.05), 7,000 of them: with four rounds of
+    every pair drawn at once 1.6 times the time of one wave per pair."""
+    lib = _library(eng, base, 7000)
+    q = eng.molecules(molgen.molecule(94, 1, 30), mol_id=[1])
+    ms = {}
+    for variant in (-1, 3):  # the library's choice, one wave per pair
+        eng.screen_variant(variant)
+        ms[variant] = _ms(lambda: eng.shape_screen(q, lib, mode=SHAPE_SCREEN_ADAPTIVE, tau=0.05,
+                                                   seed=1), repeat=20)
+    eng.screen_variant(-1)
+    print(f"case: 7,000 pairs, tau 0.05, {ms[-1]:.3f} ms, one wave {ms[3]:.3f}", flush=True)
+    assert ms[-1] < 1.25 * ms[3]

@@ -565,3 +565,23 @@ def test_graph_of_long_screen_recomputes_its_order(eng):
             torch.cuda.synchronize()
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("anti", [False, True])
+@pytest.mark.parametrize("pairs_per_cu,atoms,kw", [
+    # adaptive passes of as many rounds as a pair still seems to need: four rounds ...
+    (6, 40, dict(tau=0.005, cap_per_pair=16384)),
+    (6, 40, dict(tau=0.005, cap_per_pair=4608)),                       # cap inside a pass
+    (12, 40, dict(tau=0.004, round_per_pair=256, cap_per_pair=8192)),  # tiles of two points
+    (60, 200, dict(tau=0.02, cap_per_pair=4608)),                      # by LDS, mostly one round
+    # ... and two
+    (40, 40, dict(tau=0.005, cap_per_pair=16384)),
+    (60, 90, dict(tau=0.01, cap_per_pair=3584)),
+    (5, 40, dict(tau=0.003, round_per_pair=1024, cap_per_pair=16384)),
+    # few pairs: every pass of four rounds
+    (1, 40, dict(tau=0.02, round_per_pair=1024, cap_per_pair=5120)),
+    (3, 40, dict(tau=0.003, round_per_pair=1024, cap_per_pair=16384)),
+])
+def test_rounds_as_needed_same_bits(eng, pairs_per_cu, atoms, kw, anti):
+    test_rounds_at_a_time_same_bits(eng, pairs_per_cu, atoms,
+                                    dict(mode=SHAPE_SCREEN_ADAPTIVE, **kw), anti)

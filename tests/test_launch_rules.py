@@ -28,8 +28,14 @@ int r_align_starts_per_block(int64_t pairs, int starts, int waves, int n_cu) {
 int r_align_split_fits(int64_t dynamic, int64_t own, int64_t max_lds) {
   return align_split_fits(dynamic, own, max_lds);
 }
-int r_screen_rounds(int adaptive, int64_t pairs, int64_t rounds, int side, int64_t lds, int n_cu) {
-  return screen_rounds(adaptive, pairs, rounds, side, lds, n_cu);
+int r_screen_shape(int adaptive, int64_t pairs, int64_t rounds, double expected, int side,
+                   int64_t lds, int n_cu, int* first) {
+  const ScreenShape s = screen_shape(adaptive, pairs, rounds, expected, side, lds, n_cu);
+  *first = s.first;
+  return s.rounds;
+}
+double r_expected(double tau, int side, double q, double b) {
+  return screen_rounds_expected(tau, side, q, b);
 }
 }
 """
@@ -52,8 +58,11 @@ def rules(tmp_path_factory):
     L.r_align_splits_starts.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 5
     L.r_align_starts_per_block.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     L.r_align_split_fits.argtypes = [ctypes.c_int64] * 3
-    L.r_screen_rounds.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int,
-                                  ctypes.c_int64, ctypes.c_int]
+    L.r_screen_shape.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_double,
+                                 ctypes.c_int, ctypes.c_int64, ctypes.c_int,
+                                 ctypes.POINTER(ctypes.c_int)]
+    L.r_expected.argtypes = [ctypes.c_double, ctypes.c_int, ctypes.c_double, ctypes.c_double]
+    L.r_expected.restype = ctypes.c_double
     return L
 
 
@@ -81,8 +90,12 @@ def test_alignment_workgroups_fit_a_launch(rules, pairs, starts):
 def test_screen_workgroups_fit_a_launch(rules, pairs, lds, adaptive, side, rounds):
     """Up to 2^26 - 1 pairs, as with one wave per pair throughout, however
     much LDS a pair takes."""
-    R = rules.r_screen_rounds(adaptive, pairs, rounds, side, lds, 256)
-    assert R in (1, 2, 4) and R <= rounds and pairs * R * 64 < LIMIT
+    first = ctypes.c_int()
+    for expected in (0.1, 5.0, 1e9):
+        R = rules.r_screen_shape(adaptive, pairs, rounds, expected, side, lds, 256,
+                                 ctypes.byref(first))
+        assert R in (1, 2, 4) and R <= rounds and pairs * R * 64 < LIMIT
+        assert first.value == R if not adaptive else 1 <= first.value <= R
 
 
 def test_a_kernels_own_lds_counts_towards_the_limit(rules):
@@ -116,3 +129,16 @@ def test_starts_of_a_pair_are_covered_by_a_grid(rules, pairs, starts):
 def test_eight_waves_only_where_the_last_eight_starts_fill_most_of_them(rules):
     waves = [rules.r_align_waves(5000, s, 1, 0, 256) for s in range(1, 26)]
     assert waves == [4] * 7 + [8] + [4] * 4 + [8] * 4 + [4] * 4 + [8] * 4 + [4]
+
+
+def test_pairs_that_need_one_round_get_one_wave(rules):
+    """Adaptive screens at a coarse tau, fewer pairs than fill the chip."""
+    first = ctypes.c_int()
+
+    def R(pairs, tau, atoms):
+        e = rules.r_expected(tau, 256, 30.0, atoms)
+        return rules.r_screen_shape(1, pairs, 128, e, 256, 4000, 256, ctypes.byref(first))
+
+    for pairs in (1000, 3000, 7000, 12500):
+        assert R(pairs, 0.05, 30.0) == 1 and R(pairs, 0.02, 30.0) == 1, pairs
+        assert R(pairs, 0.005, 30.0) > 1 and R(pairs, 0.01, 2.5) == 1, pairs
