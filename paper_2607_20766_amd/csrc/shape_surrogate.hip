@@ -345,6 +345,13 @@ __device__ __forceinline__ float4 fo_phantom_lib() {
   return make_float4(-1e18f, -1e18f, -1e18f, 3e36f);
 }
 
+// Library atoms of a wave's LDS records: padded to whole phases.
+template <int NI>
+__host__ __device__ constexpr int fo_cross_padded(int n) {
+  constexpr int kPhases = kWave / NI;
+  return (n + kPhases - 1) / kPhases * kPhases;
+}
+
 // NI query slots x 64/NI phases; CH chunks of 64 library atoms per lane at
 // most (1 when no library molecule passes 64 atoms).
 template <int NI, int CH>
@@ -352,15 +359,14 @@ __global__ __launch_bounds__(kWave * kFoWaves) void k_fo_cross(
     MolsDev Q, MolsDev L, const int* __restrict__ pairs, int n_pairs, int per_wave,
     int* __restrict__ flag, float* __restrict__ out) {
   constexpr int kPhases = kWave / NI;
-  constexpr int kUnroll = 4;       // terms per lane whose transcendentals are grouped
-  constexpr int kPad = kPhases;    // library atoms padded to a multiple of this
+  constexpr int kUnroll = 4;  // terms per lane whose transcendentals are grouped
   // query records [max_q]; each wave's library atoms [max_b padded], two
   // 16-byte words per atom (c, |c|^2) and (b, 1.5 log2 b, -, -) read from one
   // address; the query's widths (b, b^1.5) [max_q]
   extern __shared__ float4 fo_lds[];
   __shared__ float4 s_cen;  // the query's centroid
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int max_b_pad = (L.max_atoms + kPad - 1) / kPad * kPad;
+  const int max_b_pad = fo_cross_padded<NI>(L.max_atoms);
   float4* sA = fo_lds;
   float4* sB = fo_lds + Q.max_atoms + 2 * w * max_b_pad;
   float2* sAw = reinterpret_cast<float2*>(fo_lds + Q.max_atoms + 2 * kFoWaves * max_b_pad);
@@ -441,7 +447,7 @@ __global__ __launch_bounds__(kWave * kFoWaves) void k_fo_cross(
     for (int k = 0; k < cnt; ++k) {
       const int p = sub + k;
       const int nb = __builtin_amdgcn_readlane(hnb, k), fl = __builtin_amdgcn_readlane(hfl, k);
-      const int nb_pad = (nb + kPad - 1) / kPad * kPad;
+      const int nb_pad = fo_cross_padded<NI>(nb);
       bool a_bad = false;
       if (fl & 1) {
 #pragma unroll
@@ -477,7 +483,7 @@ __global__ __launch_bounds__(kWave * kFoWaves) void k_fo_cross(
         const bool real = i < nq;
         const float4 ci = real ? sA[i] : fo_phantom_query();
         const float2 wi = real ? sAw[i] : make_float2(1.0f, 1.0f);
-        const int n_iter = nb_pad / kPad;  // wave-uniform trip count
+        const int n_iter = nb_pad / kPhases;  // wave-uniform trip count
         float accb = 0.0f;
         const auto terms = [&](int t, auto count) {
           constexpr int V = decltype(count)::value;
@@ -2303,8 +2309,7 @@ template <int NI, int CH>
 static hipError_t launch_fo_cross_t(const MolsDev& Q, const MolsDev& L, const int* pairs,
                                     int n_pairs, int n_cu, int* flag, float* out,
                                     hipStream_t st) {
-  constexpr int kPad = (kWave / NI) * 2;
-  const int max_b_pad = (L.max_atoms + kPad - 1) / kPad * kPad;
+  const int max_b_pad = fo_cross_padded<NI>(L.max_atoms);
   const dim3 block(kWave * kFoWaves);
   const size_t lds = (size_t)Q.max_atoms * (sizeof(float4) + sizeof(float2)) +
                      (size_t)kFoWaves * max_b_pad * 2 * sizeof(float4);
