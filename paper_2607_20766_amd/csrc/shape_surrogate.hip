@@ -345,11 +345,18 @@ __device__ __forceinline__ float4 fo_phantom_lib() {
   return make_float4(-1e18f, -1e18f, -1e18f, 3e36f);
 }
 
-// Library atoms of a wave's LDS records: padded to whole phases.
-template <int NI>
+// Whether the terms' transcendentals are grouped (trans_group).  With queries of 64
+// slots and large molecules LDS leaves few waves, and the grouping would only keep a
+// wave's reads from running ahead (256 x 150-256 atoms, 1,000 pairs 50 us, grouped 56).
+template <int NI, int CH>
+constexpr bool kFoCrossGrouped = NI < 64 || CH == 1;
+
+// Library atoms of a wave's LDS records: padded to whole phases, of two terms each
+// without grouping (the loop then has no remainder).
+template <int NI, int CH>
 __host__ __device__ constexpr int fo_cross_padded(int n) {
-  constexpr int kPhases = kWave / NI;
-  return (n + kPhases - 1) / kPhases * kPhases;
+  constexpr int kPad = kWave / NI * (kFoCrossGrouped<NI, CH> ? 1 : 2);
+  return (n + kPad - 1) / kPad * kPad;
 }
 
 // NI query slots x 64/NI phases; CH chunks of 64 library atoms per lane at
@@ -359,14 +366,15 @@ __global__ __launch_bounds__(kWave * kFoWaves) void k_fo_cross(
     MolsDev Q, MolsDev L, const int* __restrict__ pairs, int n_pairs, int per_wave,
     int* __restrict__ flag, float* __restrict__ out) {
   constexpr int kPhases = kWave / NI;
-  constexpr int kUnroll = 4;  // terms per lane whose transcendentals are grouped
+  constexpr bool kGrouped = kFoCrossGrouped<NI, CH>;
+  constexpr int kUnroll = kGrouped ? 4 : 2;  // terms per lane that go together
   // query records [max_q]; each wave's library atoms [max_b padded], two
   // 16-byte words per atom (c, |c|^2) and (b, 1.5 log2 b, -, -) read from one
   // address; the query's widths (b, b^1.5) [max_q]
   extern __shared__ float4 fo_lds[];
   __shared__ float4 s_cen;  // the query's centroid
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int max_b_pad = fo_cross_padded<NI>(L.max_atoms);
+  const int max_b_pad = fo_cross_padded<NI, CH>(L.max_atoms);
   float4* sA = fo_lds;
   float4* sB = fo_lds + Q.max_atoms + 2 * w * max_b_pad;
   float2* sAw = reinterpret_cast<float2*>(fo_lds + Q.max_atoms + 2 * kFoWaves * max_b_pad);
@@ -447,7 +455,7 @@ __global__ __launch_bounds__(kWave * kFoWaves) void k_fo_cross(
     for (int k = 0; k < cnt; ++k) {
       const int p = sub + k;
       const int nb = __builtin_amdgcn_readlane(hnb, k), fl = __builtin_amdgcn_readlane(hfl, k);
-      const int nb_pad = fo_cross_padded<NI>(nb);
+      const int nb_pad = fo_cross_padded<NI, CH>(nb);
       bool a_bad = false;
       if (fl & 1) {
 #pragma unroll
@@ -508,10 +516,25 @@ __global__ __launch_bounds__(kWave * kFoWaves) void k_fo_cross(
 #pragma unroll
           for (int u = 0; u < V; ++u) accb = fmaf(r[u], e[u], accb);
         };
-        int t = 0;
-        for (; t + kUnroll <= n_iter; t += kUnroll)
-          terms(t, std::integral_constant<int, kUnroll>{});
-        for (; t < n_iter; ++t) terms(t, std::integral_constant<int, 1>{});
+        if constexpr (kGrouped) {
+          int t = 0;
+          for (; t + kUnroll <= n_iter; t += kUnroll)
+            terms(t, std::integral_constant<int, kUnroll>{});
+          for (; t < n_iter; ++t) terms(t, std::integral_constant<int, 1>{});
+        } else {
+          for (int t = 0; t < n_iter; t += kUnroll) {
+            const int j = ph + t * kPhases;
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+              const float4 cj = sB[2 * (j + u * kPhases)];
+              const float4 wj = sB[2 * (j + u * kPhases) + 1];
+              const float d2 = fmaf(ci.x, cj.x, fmaf(ci.y, cj.y, fmaf(ci.z, cj.z, ci.w + cj.w)));
+              const float r = __builtin_amdgcn_rsqf(wi.x + wj.x);  // k^(1/2)
+              const float kk = r * r;
+              accb = fmaf(kk * r, __builtin_amdgcn_exp2f(fmaf(-kk, d2, wj.y)), accb);
+            }
+          }
+        }
         acc = fmaf(accb, wi.y, acc);
       }
       const float sum = 9.64909578231936f * wave_sum_dpp(acc);  // (pi log2(e))^(3/2)
@@ -2309,7 +2332,7 @@ template <int NI, int CH>
 static hipError_t launch_fo_cross_t(const MolsDev& Q, const MolsDev& L, const int* pairs,
                                     int n_pairs, int n_cu, int* flag, float* out,
                                     hipStream_t st) {
-  const int max_b_pad = fo_cross_padded<NI>(L.max_atoms);
+  const int max_b_pad = fo_cross_padded<NI, CH>(L.max_atoms);
   const dim3 block(kWave * kFoWaves);
   const size_t lds = (size_t)Q.max_atoms * (sizeof(float4) + sizeof(float2)) +
                      (size_t)kFoWaves * max_b_pad * 2 * sizeof(float4);

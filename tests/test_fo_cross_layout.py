@@ -14,4 +14,4 @@ def test_kernel_and_launch_pad_alike():
     launch = src[src.index("static hipError_t launch_fo_cross_t("):]
     launch = launch[:launch.index("\n}\n")]
     for part in (kernel, launch):
-        assert re.findall(r"max_b_pad = ([^;]+);", part) == ["fo_cross_padded<NI>(L.max_atoms)"]
+        assert re.findall(r"max_b_pad = ([^;]+);", part) == ["fo_cross_padded<NI, CH>(L.max_atoms)"]
