@@ -91,34 +91,25 @@ __device__ __forceinline__ float row_ror(float v) {
   }
 }
 
-// acc + the terms B_p k^(3/2) exp2(-k d2) of this lane's atom s with the atoms
-// p of the lanes C places back in the row, added in the order of C: their
-// reciprocal roots, then their exponentials, go out as one prioritised group
-// (trans_group; 300,000 molecules 161 -> 155 us: of 1,207 instructions per wave
-// of four molecules about 700 are terms).
+// acc + B_p k^(3/2) exp2(-k d2) for this lane's atom s and the atom p of the
+// lane C places back in the row.  Its transcendentals are not grouped over terms
+// (trans_group): molecules of 150-256 atoms measured 2 to 9 % slower for it, drug-sized
+// ones the same (300,000 of 10-50 atoms 173-181 us, grouped 181).
+template <int C>
+__device__ __forceinline__ float tri_term(const TriAtom& s, const TriAtom& p, float acc) {
+  const float dx = row_ror<C>(p.x) - s.x, dy = row_ror<C>(p.y) - s.y,
+              dz = row_ror<C>(p.z) - s.z;
+  const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+  const float r = __builtin_amdgcn_rsqf(row_ror<C>(p.b) + s.b);
+  const float kk = r * r;
+  const float e = __builtin_amdgcn_exp2f(-kk * d2);
+  return fmaf(row_ror<C>(p.B) * (kk * r), e, acc);
+}
+
 template <int... C>
 __device__ __forceinline__ float tri_terms(const TriAtom& s, const TriAtom& p, float acc,
                                            std::integer_sequence<int, C...>) {
-  constexpr int N = sizeof...(C);
-  float d2[N], r[N], B[N];
-  int i = 0;
-  ((d2[i] = [&] {
-      const float dx = row_ror<C>(p.x) - s.x, dy = row_ror<C>(p.y) - s.y,
-                  dz = row_ror<C>(p.z) - s.z;
-      return fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    }(),
-    r[i] = row_ror<C>(p.b) + s.b, B[i] = row_ror<C>(p.B), ++i),
-   ...);
-  trans_group<N>([&](int k) { r[k] = __builtin_amdgcn_rsqf(r[k]); });
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const float kk = r[k] * r[k];
-    B[k] *= kk * r[k];
-    d2[k] = -kk * d2[k];
-  }
-  trans_group<N>([&](int k) { d2[k] = __builtin_amdgcn_exp2f(d2[k]); });
-#pragma unroll
-  for (int k = 0; k < N; ++k) acc = fmaf(B[k], d2[k], acc);
+  ((acc = tri_term<C>(s, p, acc)), ...);
   return acc;
 }
 
@@ -243,13 +234,11 @@ __global__ __launch_bounds__(64) void k_features(MolsDev in, const int* __restri
     // the diagonal block: rotations 1..7, and 8 on half of the lanes (the
     // pairs at rotation 8 are met twice in the row)
     float acc = tri_terms(own, own, 0.f, std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7>{});
-    const float a8 = tri_terms(own, own, 0.f, std::integer_sequence<int, 8>{});
+    const float a8 = tri_term<8>(own, own, 0.f);
     acc += l16 < 8 ? a8 : 0.f;
     for (int bb = ba + 1; bb < nb; ++bb) {
       const TriAtom other = tri_atom(sC, 16 * bb + l16, n);
-      acc = tri_terms(own, other, acc, std::integer_sequence<int, 0, 1, 2, 3, 4, 5, 6, 7>{});
-      acc = tri_terms(own, other, acc,
-                      std::integer_sequence<int, 8, 9, 10, 11, 12, 13, 14, 15>{});
+      acc = tri_terms(own, other, acc, std::make_integer_sequence<int, 16>{});
     }
     tri = fmaf(own.B, acc, tri);
   }
