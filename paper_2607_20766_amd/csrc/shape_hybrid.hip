@@ -669,6 +669,7 @@ template <int RA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void k_fo_align_rows(FoAlignArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int sBad[kFoRowsStarts / 4];  // per wave: an invalid atom
   constexpr int RA16 = RA * 16;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int l16 = lane & 15, row = lane >> 4;
@@ -687,8 +688,16 @@ void k_fo_align_rows(FoAlignArgs a) {
   float4* sM = sB + a.B.max_atoms;               // [rows][stride] B moved, per start
   float2* tab = reinterpret_cast<float2*>(sM + (size_t)n_rows * stride);  // [max_b][RA16]
   const bool ok = fo_range_ok(a.A, a0, a1) && fo_range_ok(a.B, b0, b_end);
-  if (!fo_stage(a, ok, sA, a0, na, sB, b0, nb, tid, blockDim.x,
-                [](bool b) { return __syncthreads_or(b) != 0; })) {
+  // one barrier: __syncthreads_or takes several, a tenth of a call of few steps
+  const auto any = [&](bool b) {
+    const int mine = __any(b) ? 1 : 0;
+    if (lane == 0) sBad[wave] = mine;
+    __syncthreads();
+    int all = sBad[0];
+    for (int w = 1; w < n_rows / 4; ++w) all |= sBad[w];
+    return all != 0;
+  };
+  if (!fo_stage(a, ok, sA, a0, na, sB, b0, nb, tid, blockDim.x, any)) {
     if (live && l16 == 0) {
       a.T[item] = __builtin_nanf("");
       if (a.grad)
