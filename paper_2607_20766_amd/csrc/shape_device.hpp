@@ -87,36 +87,13 @@ __device__ __forceinline__ void exp2_group(float (&e)[N]) {
 // exponentials (and one loop step) whatever the number of points per lane.
 constexpr int exp_atoms(int S) { return S >= 8 ? 1 : 8 / S; }
 
-// Standard normal from the top 24 bits b of a Philox word: u = (b + 1/2) 2^-24,
+// Standard normals from the top 24 bits b of N Philox words: u = (b + 1/2) 2^-24,
 // z = Phi^-1(u) = sqrt(2) erfinv(x), x = 2u - 1 = b 2^-23 + (2^-24 - 1), which
 // one FP32 fma forms exactly, so the tails are resolved to the last bit.
-// erfinv after Giles (2011): z = x P(L), L = -log2(1 - x^2), with one
-// polynomial in L for L < kSplit and one in sqrt(L) above it (coefficients
-// from gen_normal_poly.py; relative error below 3e-7 over every 24-bit u).
-// The tail branch runs only when some lane of the wave needs it.
-__device__ __forceinline__ float normal_from_bits(uint32_t word) {
-  using namespace normal_poly;
-  const float x = fmaf((float)(word >> 8), 0x1p-23f, 0x1p-24f - 1.0f);
-  const float ax = fabsf(x);
-  const float y = (1.0f - ax) * (1.0f + ax);  // 1 - x^2 >= 2^-24 (1 + 2^-24)
-  const float L = -__builtin_amdgcn_logf(y);
-  float p;
-  if (L < kSplit) {
-    const float t = fmaf(L, kCenScale, kCenOff);
-    p = kCen[8];
-#pragma unroll
-    for (int i = 7; i >= 0; --i) p = fmaf(p, t, kCen[i]);
-  } else {
-    const float t = fmaf(__builtin_amdgcn_sqrtf(L), kTailScale, kTailOff);
-    p = kTail[8];
-#pragma unroll
-    for (int i = 7; i >= 0; --i) p = fmaf(p, t, kTail[i]);
-  }
-  return x * p;
-}
-
-// N inverse normals together (the values normal_from_bits gives): their
-// logarithms are issued as one group at raised priority (see exp2_group), and
+// erfinv after Giles (2011): z = x P(L), L = -log2(1 - x^2) (1 - x^2 >= 2^-24 (1 +
+// 2^-24)), with one polynomial in L for L < kSplit and one in sqrt(L) above it
+// (coefficients from gen_normal_poly.py; relative error below 3e-7 over every 24-bit u).
+// The logarithms are issued as one group at raised priority (see exp2_group), and
 // the tail is evaluated only where a lane of the wave needs it.
 template <int N>
 __device__ __forceinline__ void normals_from_bits(const uint32_t (&word)[N], float (&z)[N]) {
@@ -149,24 +126,10 @@ __device__ __forceinline__ void normals_from_bits(const uint32_t (&word)[N], flo
   }
 }
 
-// Component of a molecule's mixture selected by a Philox word:
+// Components of a molecule's mixture selected by D Philox words:
 // j = #{i < n-1 : word >= thr_i}.  The thresholds are non-decreasing, so the
 // count is found by binary lifting in ceil(log2(n)) steps (the step count is
 // the same for every lane); every index read is below n-1.
-__device__ __forceinline__ int select_component(const AtomSampling* samp, int n, uint32_t word) {
-  const int last = n - 1;
-  int j = 0;
-  if (last > 0) {
-    for (int step = 1 << (31 - __builtin_clz((unsigned)last)); step > 0; step >>= 1) {
-      const int c = j + step;
-      const int idx = (c < last ? c : last) - 1;
-      if (c <= last && word >= samp[idx].thr) j = c;
-    }
-  }
-  return j;
-}
-
-// The components of D words together.
 template <int D>
 __device__ __forceinline__ void select_components(const AtomSampling* samp, int n,
                                                   const uint32_t (&word)[D], int (&j)[D]) {
@@ -188,7 +151,7 @@ __device__ __forceinline__ void select_components(const AtomSampling* samp, int 
 // a word.  Every threshold counted there lies at or below any word whose top
 // bits are g, so that word's count starts at guide[g] and steps only over
 // the thresholds inside its 2^24-wide bucket (on average (n-1)/256 of them):
-// the same count as select_component's, from one table read and a short
+// the same count as select_components', from one table read and a short
 // scan instead of ceil(log2(n)) dependent reads.
 constexpr int kGuideBits = 8;
 constexpr int kGuideSize = 1 << kGuideBits;
@@ -207,15 +170,6 @@ __device__ __forceinline__ void build_guide(const AtomSampling* samp, int n, uin
     }
     guide[g] = (uint8_t)c;  // c <= last < 256
   }
-}
-
-__device__ __forceinline__ int select_component_guided(const AtomSampling* samp,
-                                                       const uint8_t* guide, int n,
-                                                       uint32_t word) {
-  const int last = n - 1;
-  int j = guide[word >> (32 - kGuideBits)];
-  while (j < last && word >= samp[j].thr) ++j;
-  return j;
 }
 
 // The components of D words together: each step reads one threshold per word,
@@ -239,45 +193,46 @@ __device__ __forceinline__ void select_components_guided(const AtomSampling* sam
   }
 }
 
-// Sample point k of a molecule (exact draw from its normalised mixture):
-// component by integer thresholds, then r = c_j + z * sd_j per axis.
-// atoms/samp point at the molecule's own records (LDS or global); guide, if
-// given, is the molecule's guide table (the component is the same).
-__device__ __forceinline__ void sample_point(const Atom* atoms, const AtomSampling* samp,
-                                             int n, uint32_t mol_id, uint64_t k, uint2 key,
-                                             float& rx, float& ry, float& rz,
-                                             const uint8_t* guide = nullptr) {
-  const uint4 x = philox4x32_10(make_uint4((uint32_t)k, (uint32_t)(k >> 32), mol_id, 0u), key);
-  const int j = guide ? select_component_guided(samp, guide, n, x.x)
-                      : select_component(samp, n, x.x);
-  const Atom c = atoms[j];
-  const float sd = samp[j].sd;
-  rx = fmaf(normal_from_bits(x.y), sd, c.x);
-  ry = fmaf(normal_from_bits(x.z), sd, c.y);
-  rz = fmaf(normal_from_bits(x.w), sd, c.z);
+// Samples of a molecule: exact draws from its normalised mixture.  Philox block k of
+// the molecule's stream gives a component by integer thresholds and three normals, and
+// the point r = c_j + z sd_j per axis.  Antithetic samples 2k and 2k + 1 share block k;
+// the odd one is the reflection about its component's centre (z of opposite sign).
+//
+// Components and normals of D blocks x, the steps of all of them interleaved so that
+// their latencies overlap; select(words, j) is select_components or its guided form.
+template <int D, class Select>
+__device__ __forceinline__ void draws_of(const uint4 (&x)[D], Select select, int (&j)[D],
+                                         float (&z)[3 * D]) {
+  uint32_t w0[D], wz[3 * D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    w0[d] = x[d].x;
+    wz[3 * d] = x[d].y;
+    wz[3 * d + 1] = x[d].z;
+    wz[3 * d + 2] = x[d].w;
+  }
+  select(w0, j);
+  normals_from_bits<3 * D>(wz, z);
 }
 
-// D draws together (Philox blocks below 2^32): components and normals, the
-// steps of all of them interleaved so that their latencies overlap.
+__device__ __forceinline__ uint4 philox_block(uint64_t blk, uint32_t mol_id, uint2 key) {
+  return philox4x32_10(make_uint4((uint32_t)blk, (uint32_t)(blk >> 32), mol_id, 0u), key);
+}
+
+// D draws together (blocks below 2^32) by binary lifting.
 template <int D>
 __device__ __forceinline__ void draws(const AtomSampling* samp, int n, uint32_t mol_id,
                                       const uint32_t (&blk)[D], uint2 key, int (&j)[D],
                                       float (&z)[3 * D]) {
-  uint32_t w0[D], wz[3 * D];
+  uint4 x[D];
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    const uint4 x = philox4x32_10(make_uint4(blk[d], 0u, mol_id, 0u), key);
-    w0[d] = x.x;
-    wz[3 * d] = x.y;
-    wz[3 * d + 1] = x.z;
-    wz[3 * d + 2] = x.w;
-  }
-  select_components<D>(samp, n, w0, j);
-  normals_from_bits<3 * D>(wz, z);
+  for (int d = 0; d < D; ++d) x[d] = philox_block(blk[d], mol_id, key);
+  draws_of<D>(x, [&](const uint32_t (&w)[D], int (&c)[D]) { select_components<D>(samp, n, w, c); },
+              j, z);
 }
 
-// The draws' points (sample_point's), or their reflections about the
-// components' centres (sign = -1).
+// The draws' points, or their reflections about the components' centres (sign = -1).
+// atoms/samp point at the molecule's own records (LDS or global).
 template <int D>
 __device__ __forceinline__ void draw_points(const Atom* atoms, const AtomSampling* samp,
                                             const int (&j)[D], const float (&z)[3 * D],
@@ -291,44 +246,6 @@ __device__ __forceinline__ void draw_points(const Atom* atoms, const AtomSamplin
     ry[d] = fmaf(sign * z[3 * d + 1], sd, c.y);
     rz[d] = fmaf(sign * z[3 * d + 2], sd, c.z);
   }
-}
-
-// Antithetic sample k (each draw paired with its reflection about its
-// component's centre): samples 2p and 2p+1 use Philox block p; the odd one
-// takes the normals with the opposite sign.
-__device__ __forceinline__ void sample_point_anti(const Atom* atoms, const AtomSampling* samp,
-                                                  int n, uint32_t mol_id, uint64_t k, uint2 key,
-                                                  float& rx, float& ry, float& rz,
-                                                  const uint8_t* guide = nullptr) {
-  const uint64_t p = k >> 1;
-  const float sg = (k & 1) ? -1.0f : 1.0f;
-  const uint4 x = philox4x32_10(make_uint4((uint32_t)p, (uint32_t)(p >> 32), mol_id, 0u), key);
-  const int j = guide ? select_component_guided(samp, guide, n, x.x)
-                      : select_component(samp, n, x.x);
-  const Atom c = atoms[j];
-  const float sd = samp[j].sd;
-  rx = fmaf(sg * normal_from_bits(x.y), sd, c.x);
-  ry = fmaf(sg * normal_from_bits(x.z), sd, c.y);
-  rz = fmaf(sg * normal_from_bits(x.w), sd, c.z);
-}
-
-// Both members of antithetic pair p from one Philox block.
-__device__ __forceinline__ void sample_pair(const Atom* atoms, const AtomSampling* samp, int n,
-                                            uint32_t mol_id, uint64_t p, uint2 key, float& ax,
-                                            float& ay, float& az, float& bx, float& by,
-                                            float& bz, const uint8_t* guide = nullptr) {
-  const uint4 x = philox4x32_10(make_uint4((uint32_t)p, (uint32_t)(p >> 32), mol_id, 0u), key);
-  const int j = guide ? select_component_guided(samp, guide, n, x.x)
-                      : select_component(samp, n, x.x);
-  const Atom c = atoms[j];
-  const float sd = samp[j].sd;
-  const float zx = normal_from_bits(x.y), zy = normal_from_bits(x.z), zz = normal_from_bits(x.w);
-  ax = fmaf(zx, sd, c.x);
-  ay = fmaf(zy, sd, c.y);
-  az = fmaf(zz, sd, c.z);
-  bx = fmaf(-zx, sd, c.x);
-  by = fmaf(-zy, sd, c.y);
-  bz = fmaf(-zz, sd, c.z);
 }
 
 // First-order density m = sum o_i and union complement q = prod (1 - o_i) of a

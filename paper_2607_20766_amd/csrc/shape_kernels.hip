@@ -406,11 +406,12 @@ __device__ __forceinline__ void query_cache(const Prepared& Qp, const int* __res
   __syncthreads();
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
-  float rx[1], ry[1], rz[1], r2[1];
-  if (anti)
-    sample_point_anti(sF, sS, nq, Qp.id[0], (uint64_t)k, key, rx[0], ry[0], rz[0]);
-  else
-    sample_point(sF, sS, nq, Qp.id[0], (uint64_t)k, key, rx[0], ry[0], rz[0]);
+  // sample numbers stay below 2^32 (at most 2^20)
+  const uint32_t blk[1] = {(uint32_t)(anti ? k >> 1 : k)};
+  int j[1];
+  float z[3], rx[1], ry[1], rz[1], r2[1];
+  draws<1>(sS, nq, Qp.id[0], blk, key, j, z);
+  draw_points<1>(sF, sS, j, z, anti && (k & 1) ? -1.0f : 1.0f, rx, ry, rz);
   r2[0] = norm2(rx[0], ry[0], rz[0]);
   float m[1] = {0.0f}, q[1] = {1.0f};
   eval_density_x<1>(sR, sA, nq, rx, ry, rz, r2, m, q);
@@ -658,20 +659,19 @@ __device__ __forceinline__ void screen_draw(const ScreenLds& lds, int nb, uint32
   constexpr bool kPairs = kAnti && S % 2 == 0;
   constexpr int D = kPairs ? S / 2 : S;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  uint32_t w0[D], wz[3 * D];
+  uint4 x[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     const int s = kPairs ? 2 * d : d;
     const uint32_t i = (t + s) < per_lane ? t + s : t;
     const uint32_t blk = kAnti ? n_side / 2 + lane + kWave * (i >> 1) : n_side + lane + kWave * i;
-    const uint4 x = philox4x32_10(make_uint4(blk, 0u, id, 0u), key);
-    w0[d] = x.x;
-    wz[3 * d] = x.y; wz[3 * d + 1] = x.z; wz[3 * d + 2] = x.w;
+    x[d] = philox_block(blk, id, key);
   }
   int j[D];
-  select_components_guided<D>(lds.BS, lds.guide, nb, w0, j);
   float z[3 * D];
-  normals_from_bits<3 * D>(wz, z);
+  draws_of<D>(x, [&](const uint32_t (&w)[D], int (&c)[D]) {
+    select_components_guided<D>(lds.BS, lds.guide, nb, w, c);
+  }, j, z);
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     const Atom c = lds.BF[j[d]];
@@ -933,43 +933,65 @@ __global__ __launch_bounds__(kSplitThreads) void k_screen_split(ScreenArgs a) {
 // "Importance-sampling estimator": exact draws from the normalised mixture),
 // for exact comparison of the integer steps: the molecule's thresholds, and
 // for samples k0 .. k0+n-1 the Philox block, the selected component (binary
-// lifting, as in the single-pair, query-cache and alignment kernels) and the
-// point (through the guide table, as in the screening kernel), computed by
-// the same device functions as those kernels.  One thread per sample (and
-// per atom for the thresholds); records from HBM.
+// lifting, as in the single-pair, query-cache, self-overlap and alignment kernels) and
+// the point (its component through the guide table, as in the screening kernels),
+// computed by the functions those kernels draw with (draws_of, draw_points), several
+// samples per thread together as there.  kExportDraws samples per thread at a stride of
+// the workgroup, past the end the last one again; one thread per atom for the
+// thresholds; records from HBM.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_sample_points(Prepared P, const int* __restrict__ off,
-                                                       int mol, int64_t k0, int n, uint2 key,
-                                                       int anti, uint32_t* __restrict__ thr,
-                                                       uint32_t* __restrict__ words,
-                                                       int* __restrict__ comp,
-                                                       float* __restrict__ r) {
+constexpr int kExportThreads = 256;
+constexpr int kExportDraws = 4;
+__global__ __launch_bounds__(kExportThreads) void k_sample_points(
+    Prepared P, const int* __restrict__ off, int mol, int64_t k0, int n, uint2 key, int anti,
+    uint32_t* __restrict__ thr, uint32_t* __restrict__ words, int* __restrict__ comp,
+    float* __restrict__ r) {
+  constexpr int D = kExportDraws;
   __shared__ uint8_t guide[kGuideSize];  // the screening kernel's table, one entry per thread
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int a0 = off[mol], na = off[mol + 1] - a0;
   const Atom* atoms = P.atom + a0;
   const AtomSampling* samp = P.samp + a0;
-  if (thr && i < na) thr[i] = samp[i].thr;
+  const int64_t i0 = (int64_t)blockIdx.x * D * kExportThreads + threadIdx.x;
+  if (thr)
+    for (int d = 0; d < D; ++d)
+      if (i0 + d * kExportThreads < na)
+        thr[i0 + d * kExportThreads] = samp[i0 + d * kExportThreads].thr;
   build_guide(samp, na, guide, threadIdx.x, blockDim.x);
   __syncthreads();
-  if (i >= n) return;
-  const uint64_t k = (uint64_t)(k0 + i);
-  const uint64_t blk = anti ? k >> 1 : k;
-  const uint4 x =
-      philox4x32_10(make_uint4((uint32_t)blk, (uint32_t)(blk >> 32), P.id[mol], 0u), key);
-  if (words) reinterpret_cast<uint4*>(words)[i] = x;
-  if (comp) comp[i] = select_component(samp, na, x.x);
-  if (r) {
-    // the point through the guide table: a component other than comp's
-    // would move it far outside the bound of its floating-point steps
-    float rx, ry, rz;
-    if (anti)
-      sample_point_anti(atoms, samp, na, P.id[mol], k, key, rx, ry, rz, guide);
-    else
-      sample_point(atoms, samp, na, P.id[mol], k, key, rx, ry, rz, guide);
-    r[3 * (size_t)i] = rx;
-    r[3 * (size_t)i + 1] = ry;
-    r[3 * (size_t)i + 2] = rz;
+  if (i0 >= n) return;
+  int64_t i[D];
+  uint4 x[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const int64_t at = i0 + d * kExportThreads;
+    i[d] = at < n ? at : n - 1;
+    const uint64_t k = (uint64_t)(k0 + i[d]);
+    x[d] = philox_block(anti ? k >> 1 : k, P.id[mol], key);
+  }
+  int lifted[D], guided[D];
+  float z[3 * D];
+  draws_of<D>(x, [&](const uint32_t (&w)[D], int (&c)[D]) {
+    select_components<D>(samp, na, w, c);
+  }, lifted, z);
+  draws_of<D>(x, [&](const uint32_t (&w)[D], int (&c)[D]) {
+    select_components_guided<D>(samp, guide, na, w, c);
+  }, guided, z);
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    if (words) reinterpret_cast<uint4*>(words)[i[d]] = x[d];
+    if (comp) comp[i[d]] = lifted[d];
+    if (r) {
+      // another component than comp's would move the point far outside the bound of
+      // its floating-point steps
+      const int j[1] = {guided[d]};
+      const float zd[3] = {z[3 * d], z[3 * d + 1], z[3 * d + 2]};
+      const float sign = anti && ((k0 + i[d]) & 1) ? -1.0f : 1.0f;
+      float rx[1], ry[1], rz[1];
+      draw_points<1>(atoms, samp, j, zd, sign, rx, ry, rz);
+      r[3 * i[d]] = rx[0];
+      r[3 * i[d] + 1] = ry[0];
+      r[3 * i[d] + 2] = rz[0];
+    }
   }
 }
 
@@ -1059,9 +1081,10 @@ hipError_t launch_estimate(const Prepared& A, const Prepared& B, const int* offA
 hipError_t launch_sample_points(const Prepared& P, const int* off, int mol, int max_atoms,
                                int64_t k0, int n, uint2 key, int anti, uint32_t* thr,
                                uint32_t* words, int* comp, float* r, hipStream_t st) {
-  const int threads = n > max_atoms ? n : max_atoms;
-  const int blocks = (threads + 255) / 256;
-  hipLaunchKernelGGL(k_sample_points, dim3(blocks), dim3(256), 0, st, P, off, mol, k0, n, key,
+  const int64_t items = n > max_atoms ? n : max_atoms;
+  constexpr int kPer = kExportThreads * kExportDraws;
+  hipLaunchKernelGGL(k_sample_points, dim3((unsigned)((items + kPer - 1) / kPer)),
+                     dim3(kExportThreads), 0, st, P, off, mol, k0, n, key,
                      anti, thr, words, comp, r);
   return hipGetLastError();
 }

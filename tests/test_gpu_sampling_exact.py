@@ -107,3 +107,18 @@ def test_invalid_molecule_and_ranges(eng):
         eng.shape_sample_points(M, 0, 0, 10)
     assert e.value.code == -6
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 255, 256, 257, 769, 1023, 1025])
+def test_sample_counts_around_a_workgroups_share(eng, n):
+    """Four samples per thread, 256 threads apart: counts around those
+    places, i.i.d. and antithetic, the last sample of an odd molecule."""
+    ms = molgen.molecule(74, 0, 33)
+    M = eng.molecules(ms, mol_id=[5])
+    print(f"case: sampling steps, {n} samples", flush=True)
+    for anti in (False, True):
+        eng.sampling(anti)
+        try:
+            _check(eng, ms, M, 0, 5, 11, (1 << 20) - 7, n, anti)
+        finally:
+            eng.sampling(False)
