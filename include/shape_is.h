@@ -300,9 +300,10 @@ int shape_prepare_cache(shape_ctx* ctx, int enable);
  * its index to *best (host pointer, may be NULL) and the measured kernel
  * times to ms[SHAPE_SCREEN_VARIANTS] (host, may be NULL).  Synchronises
  * `stream`.  Errors: as shape_screen; SHAPE_E_UNSUPPORTED during capture.
- * Screens of few pairs (at most 50 per compute unit) or of large molecules
- * spread each pair over several waves instead, whatever the tuner chose, again
- * with the same bits.
+ * The tuner's choice is for screens that take one wave per pair.  Screens of few
+ * pairs (at most 50 per compute unit) whose pairs need many rounds, and of large
+ * molecules, spread each pair over several waves instead, whatever the tuner
+ * chose or measured, again with the same bits.
  * shape_screen_set_variant selects a variant by index, for every later screen
  * of the context (-1 = default: the library chooses);
  * shape_screen_get_variant returns the current one (-1 if ctx is NULL);

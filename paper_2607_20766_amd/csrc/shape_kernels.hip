@@ -1345,7 +1345,7 @@ hipError_t launch_prepare_sets(const PrepSet& a, const PrepSet& b, int* flag, co
                          ((int64_t)b.n + kPrepWaves - 1) / kPrepWaves +
                          (!o ? 0 : (work ? kOrderBlocks : 1));
   if (blocks == 0) return hipSuccess;
-  if (blocks > max_workgroups(256) && a.n > 0) {  // too many for one launch: set by set
+  if (prepare_apart(blocks, a.n, b.n)) {
     const PrepSet none{};
     const hipError_t e = launch_prepare_sets(a, none, flag, o, work, order, st);
     return e != hipSuccess ? e

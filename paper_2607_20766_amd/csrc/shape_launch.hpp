@@ -15,6 +15,12 @@ namespace shape {
 constexpr int64_t kMaxWorkItems = ((int64_t)1 << 32) - 1;
 inline int64_t max_workgroups(int threads) { return kMaxWorkItems / threads; }
 
+// Whether two molecule sets, `blocks` workgroups of 256 threads together, are prepared in
+// a launch each: too many for one, and neither is empty.
+inline bool prepare_apart(int64_t blocks, int n_a, int n_b) {
+  return blocks > max_workgroups(256) && n_a > 0 && n_b > 0;
+}
+
 // Alignments (k_align, k_align_split): how starts are spread over waves and
 // workgroups.  Every shape gives the same bits.
 //

@@ -25,6 +25,7 @@ int r_align_splits_starts(int64_t pairs, int starts, int steps, int busy, int re
 int r_align_starts_per_block(int64_t pairs, int starts, int waves, int n_cu) {
   return align_starts_per_block(pairs, starts, waves, n_cu);
 }
+int r_prepare_apart(int64_t blocks, int a, int b) { return prepare_apart(blocks, a, b); }
 int r_align_split_fits(int64_t dynamic, int64_t own, int64_t max_lds) {
   return align_split_fits(dynamic, own, max_lds);
 }
@@ -57,6 +58,7 @@ def rules(tmp_path_factory):
     L.r_align_waves.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.r_align_splits_starts.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 5
     L.r_align_starts_per_block.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    L.r_prepare_apart.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     L.r_align_split_fits.argtypes = [ctypes.c_int64] * 3
     L.r_screen_shape.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_double,
                                  ctypes.c_int, ctypes.c_int64, ctypes.c_int,
@@ -142,3 +144,12 @@ def test_pairs_that_need_one_round_get_one_wave(rules):
     for pairs in (1000, 3000, 7000, 12500):
         assert R(pairs, 0.05, 30.0) == 1 and R(pairs, 0.02, 30.0) == 1, pairs
         assert R(pairs, 0.005, 30.0) > 1 and R(pairs, 0.01, 2.5) == 1, pairs
+
+
+def test_sets_are_prepared_apart_only_if_that_leaves_less_in_a_launch(rules):
+    most = rules.r_max_workgroups(256)
+    assert not rules.r_prepare_apart(most, 1, 1 << 26)
+    assert rules.r_prepare_apart(most + 1, 1, 1 << 26)
+    # one set alone is left to the driver's refusal
+    assert not rules.r_prepare_apart(most + 1, 1 << 27, 0)
+    assert not rules.r_prepare_apart(most + 1, 0, 1 << 27)
