@@ -532,10 +532,8 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   // fixed 106).  Not for pairs of little work, about 25,000 evaluations and draws'
   // worth of them: 3,000 of 1-4 atoms, one round 38 -> 40.
   const double mean_b = std::max((double)lib->n_atoms / lib->n_mols, 1.0);
-  // (seeded budgets say themselves how many, on the device)
-  const double expected =
-      o.n_start ? 1e9
-                : shape::screen_rounds_expected(prm->tau, round_side, query->max_atoms, mean_b);
+  const double expected = shape::screen_rounds_expected(prm->tau, round_side, query->max_atoms,
+                                                        mean_b);
   const double side = prm->mode == SHAPE_SCREEN_FIXED
                           ? (double)n_fixed
                           : std::min(cap / 2.0, round_side * std::max(1.0, expected));

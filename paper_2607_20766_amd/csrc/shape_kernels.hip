@@ -494,15 +494,14 @@ struct RoundSums {
 // delta-method SE satisfies
 //   SE(T)^2 = S'^2 (Za^2 Va + Zb^2 Vb) / (4 (n-1) D'^4),
 // so the test is S'^2 (Za^2 Va + Zb^2 Vb) <= 4 tau^2 (n-1) D'^4 with
-// D' != 0 (NaN sums never stop).  ratio, if given, receives the left side over the
-// right where the test was made, about (SE(T)/tau)^2.
-__device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSums& S,
-                                             int64_t n_side, int64_t first_check, bool anti,
-                                             double Za, double Zb, double* ratio = nullptr) {
+// D' != 0 (NaN sums never stop).
+struct StopSides {
+  double lhs, rhs, Dp;
+};
+__device__ __forceinline__ StopSides screen_sides(const ScreenArgs& a, const RoundSums& S,
+                                                  int64_t n_side, bool anti, double Za,
+                                                  double Zb) {
 #pragma clang fp contract(off)
-  if (a.mode != SHAPE_SCREEN_ADAPTIVE) return n_side >= a.n_fixed;
-  if (2 * n_side >= a.cap_pair) return true;
-  if (2 * n_side < first_check) return false;  // below the pair's seeded budget: no test yet
   const double tau2x4 = 4.0 * a.tau * a.tau;
   const double n = (double)(anti ? n_side / 2 : n_side);  // independent terms
   const double a1 = S.get(0), a11 = S.get(1), b1 = S.get(3), b11 = S.get(4);
@@ -510,23 +509,34 @@ __device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSum
   const double Dp = Sp - 0.5 * (Za * a1 + Zb * b1);
   const double Va = fmax(n * a11 - a1 * a1, 0.0);
   const double Vb = fmax(n * b11 - b1 * b1, 0.0);
-  const double lhs = Sp * Sp * (Za * Za * Va + Zb * Zb * Vb);
   const double D2 = Dp * Dp;
-  const double rhs = tau2x4 * (n - 1.0) * D2 * D2;
-  if (ratio) *ratio = lhs * __builtin_amdgcn_rcp(rhs);
-  return Dp != 0.0 && lhs <= rhs;
+  return {Sp * Sp * (Za * Za * Va + Zb * Zb * Vb), tau2x4 * (n - 1.0) * D2 * D2, Dp};
+}
+__device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSums& S,
+                                             int64_t n_side, int64_t first_check, bool anti,
+                                             double Za, double Zb) {
+  if (a.mode != SHAPE_SCREEN_ADAPTIVE) return n_side >= a.n_fixed;
+  if (2 * n_side >= a.cap_pair) return true;
+  if (2 * n_side < first_check) return false;  // below the pair's seeded budget: no test yet
+  const StopSides t = screen_sides(a, S, n_side, anti, Za, Zb);
+  return t.Dp != 0.0 && t.lhs <= t.rhs;
 }
 
-// Rounds for an adaptive pair's workgroup to draw together next, at most R, after
-// n_side samples per side whose test left SE(T)^2 at `ratio` times tau^2 (about): as
-// many as the budget or that ratio, which falls as 1/n, still asks for.  What it returns
-// changes no result: rounds past the stop are dropped.
-__device__ __forceinline__ int screen_next(int R, int64_t n_side, int round_side,
-                                           int64_t first_check, double ratio) {
-  const int64_t budget = first_check - 2 * n_side;
-  const float more = budget > 0 ? (float)budget / (float)(2 * round_side)
-                                : (float)n_side / (float)round_side * ((float)ratio - 1.0f);
+// Rounds for an adaptive pair's workgroup to draw together next, at most R, after n_side
+// samples per side: as many as its budget still asks for, or, past that, as SE(T)^2 over
+// tau^2 = lhs / rhs does, which falls as 1/n.  What it returns changes no result: rounds
+// past the stop are dropped.
+__device__ __forceinline__ int screen_rounds_for(int R, float more) {
   return !(more < (float)R) ? R : max(1, (int)ceilf(more));
+}
+__device__ __forceinline__ int screen_next(const ScreenArgs& a, int R, const RoundSums& S,
+                                           int64_t n_side, int64_t first_check, bool anti,
+                                           double Za, double Zb) {
+  const int64_t budget = first_check - 2 * n_side;
+  if (budget > 0) return screen_rounds_for(R, (float)budget / (float)(2 * a.round_side));
+  const StopSides t = screen_sides(a, S, n_side, anti, Za, Zb);
+  const float ratio = (float)(t.lhs * __builtin_amdgcn_rcp(t.rhs));
+  return screen_rounds_for(R, (float)n_side / (float)a.round_side * (ratio - 1.0f));
 }
 
 // A pair's outputs from its sums (one lane).
@@ -741,7 +751,7 @@ void k_screen(ScreenArgs a) {
   if constexpr (kRounds > 1) {
     take = a.first_rounds;
     if (a.n_start && take < kRounds)
-      take = max(take, screen_next(kRounds, 0, rs, (int64_t)a.n_start[p], 0.0));
+      take = max(take, screen_rounds_for(kRounds, (float)a.n_start[p] / (float)(2 * rs)));
   }
   for (;;) {
     SideSums<kAnti> A, B;
@@ -800,17 +810,16 @@ void k_screen(ScreenArgs a) {
       if (lane < 6) sTot[buf][wave][lane] = v;
       __syncthreads();
       const int64_t first_check = r.n_start ? (int64_t)r.n_start[p] : 0;
-      double ratio = 0.0;
       for (int k = 0; k < take && !stop; ++k) {
         S.add(sTot[buf][k][lane < 6 ? lane : 5]);
         n_side += rs;
-        stop = __builtin_amdgcn_readfirstlane(screen_stops(r, S, n_side, first_check, kAnti,
-                                                           r.Q.Z[0], r.L.Z[m], &ratio));
+        stop = __builtin_amdgcn_readfirstlane(
+            screen_stops(r, S, n_side, first_check, kAnti, r.Q.Z[0], r.L.Z[m]));
       }
       buf ^= 1;
       if (!stop && r.first_rounds < kRounds)
-        take = __builtin_amdgcn_readfirstlane(
-            screen_next(kRounds, n_side, rs, first_check, ratio));
+        take = __builtin_amdgcn_readfirstlane(screen_next(r, kRounds, S, n_side, first_check,
+                                                          kAnti, r.Q.Z[0], r.L.Z[m]));
     }
     if (__builtin_amdgcn_readfirstlane(stop)) break;
   }
@@ -1413,7 +1422,7 @@ hipError_t launch_screen_auto(const ScreenArgs& a, int variant, int n_cu, hipStr
   const bool adaptive = a.mode == SHAPE_SCREEN_ADAPTIVE;
   const int64_t n_rounds = (adaptive ? a.cap_pair / 2 : a.n_fixed) / a.round_side;
   const ScreenShape shape =
-      screen_shape(adaptive, a.n_pairs, n_rounds, a.expected, a.round_side,
+      screen_shape(adaptive, a.n_start != nullptr, a.n_pairs, n_rounds, a.expected, a.round_side,
                    (int64_t)screen_lds_bytes(a.max_q, a.max_b), n_cu);
   const int R = shape.rounds;
   ScreenArgs s = a;

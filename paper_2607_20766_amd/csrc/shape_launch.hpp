@@ -103,8 +103,8 @@ inline double screen_rounds_expected(double tau, int round_side, double query_at
 }
 
 // Rounds of a pair that its workgroup works on at a time, a wave each, and those of its
-// first pass: all of them, and then in every pass (fixed mode, and pairs so few that all
-// waves run at once), or fewer, and then as many as the pair still seems to need.
+// first pass: all of them, and then in every pass, or one (or what the pair's budget
+// holds), and then as many as the pair still seems to need.
 // Several rounds where one wave per pair leaves a compute unit short of waves:
 //   LDS per pair       (lds bytes) for the rounds, any number of them: 20,000 molecules of
 //                      50-100 atoms (17 pairs in a compute unit's LDS), one : two : four
@@ -120,27 +120,31 @@ inline double screen_rounds_expected(double tau, int round_side, double query_at
 //                      76, 4.7 138 : 126; 7,000 1.5 100 : 129, 4.7 217 : 232, 9 255 : 252;
 //                      1,500 1.6 equal, 2.4 56 : 48), and long rounds do not repay a dropped
 //                      one (8,000 pairs, 1,024 samples per side and round 0.81 : 0.77 : 0.88)
+// All of them every time in fixed mode, with pairs so few that all waves run at once, and
+// where pairs need many: a pass more costs what a dropped round does not (1,000 pairs of
+// 10-50 atoms, 4.7 rounds 62 : 73 us; 800, 17 rounds 130 : 136).
 // One workgroup per pair: the rounds fall until a launch holds them.  n_rounds is the most
-// a pair takes, expected what it takes on average.
+// a pair takes, expected what it takes on average, unless it has a budget (seeded).
 constexpr int kSplitPairsPerCu = 3;  // up to here rounds of 256 samples: eight waves per pair
 struct ScreenShape {
   int rounds, first;
 };
-inline ScreenShape screen_shape(bool adaptive, int64_t n_pairs, int64_t n_rounds, double expected,
-                                int round_side, int64_t lds, int n_cu) {
+inline ScreenShape screen_shape(bool adaptive, bool seeded, int64_t n_pairs, int64_t n_rounds,
+                                double expected, int round_side, int64_t lds, int n_cu) {
   constexpr int64_t kLdsPerCu = 160 * 1024;
   const int64_t resident = kLdsPerCu / lds;
   const auto up_to = [&](int per_cu) { return n_pairs <= (int64_t)per_cu * n_cu; };
   int few = up_to(28) ? 4 : (up_to(50) ? 2 : 1);
   if (adaptive && !up_to(1)) {
     const double least = up_to(kSplitPairsPerCu) ? 1.0 : (up_to(8) ? 2.0 : (up_to(14) ? 4.0 : 8.0));
-    if (expected < least) few = 1;
+    if (!seeded && expected < least) few = 1;
     if (!up_to(kSplitPairsPerCu))
       while (few > 1 && few * round_side > 1024) few /= 2;
   }
   int R = std::max(few, resident <= 11 ? 4 : (resident <= 25 ? 2 : 1));
   while (R > n_rounds || (R > 1 && n_pairs > max_workgroups(R * 64))) R /= 2;
-  const bool all = !adaptive || (few > 1 && up_to(kSplitPairsPerCu));
+  const bool many = !seeded && expected >= (up_to(14) ? 4.0 : 8.0);
+  const bool all = !adaptive || many || (few > 1 && up_to(kSplitPairsPerCu));
   return {R, all ? R : 1};
 }
 

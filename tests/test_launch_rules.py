@@ -29,9 +29,9 @@ int r_prepare_apart(int64_t blocks, int a, int b) { return prepare_apart(blocks,
 int r_align_split_fits(int64_t dynamic, int64_t own, int64_t max_lds) {
   return align_split_fits(dynamic, own, max_lds);
 }
-int r_screen_shape(int adaptive, int64_t pairs, int64_t rounds, double expected, int side,
-                   int64_t lds, int n_cu, int* first) {
-  const ScreenShape s = screen_shape(adaptive, pairs, rounds, expected, side, lds, n_cu);
+int r_screen_shape(int adaptive, int seeded, int64_t pairs, int64_t rounds, double expected,
+                   int side, int64_t lds, int n_cu, int* first) {
+  const ScreenShape s = screen_shape(adaptive, seeded, pairs, rounds, expected, side, lds, n_cu);
   *first = s.first;
   return s.rounds;
 }
@@ -60,8 +60,8 @@ def rules(tmp_path_factory):
     L.r_align_starts_per_block.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     L.r_prepare_apart.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     L.r_align_split_fits.argtypes = [ctypes.c_int64] * 3
-    L.r_screen_shape.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_double,
-                                 ctypes.c_int, ctypes.c_int64, ctypes.c_int,
+    L.r_screen_shape.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64,
+                                 ctypes.c_double, ctypes.c_int, ctypes.c_int64, ctypes.c_int,
                                  ctypes.POINTER(ctypes.c_int)]
     L.r_expected.argtypes = [ctypes.c_double, ctypes.c_int, ctypes.c_double, ctypes.c_double]
     L.r_expected.restype = ctypes.c_double
@@ -93,8 +93,8 @@ def test_screen_workgroups_fit_a_launch(rules, pairs, lds, adaptive, side, round
     """Up to 2^26 - 1 pairs, as with one wave per pair throughout, however
     much LDS a pair takes."""
     first = ctypes.c_int()
-    for expected in (0.1, 5.0, 1e9):
-        R = rules.r_screen_shape(adaptive, pairs, rounds, expected, side, lds, 256,
+    for expected, seeded in ((0.1, 0), (5.0, 0), (50.0, 0), (0.1, 1), (50.0, 1)):
+        R = rules.r_screen_shape(adaptive, seeded, pairs, rounds, expected, side, lds, 256,
                                  ctypes.byref(first))
         assert R in (1, 2, 4) and R <= rounds and pairs * R * 64 < LIMIT
         assert first.value == R if not adaptive else 1 <= first.value <= R
@@ -139,7 +139,7 @@ def test_pairs_that_need_one_round_get_one_wave(rules):
 
     def R(pairs, tau, atoms):
         e = rules.r_expected(tau, 256, 30.0, atoms)
-        return rules.r_screen_shape(1, pairs, 128, e, 256, 4000, 256, ctypes.byref(first))
+        return rules.r_screen_shape(1, 0, pairs, 128, e, 256, 4000, 256, ctypes.byref(first))
 
     for pairs in (1000, 3000, 7000, 12500):
         assert R(pairs, 0.05, 30.0) == 1 and R(pairs, 0.02, 30.0) == 1, pairs
