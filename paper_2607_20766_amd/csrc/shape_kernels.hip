@@ -495,13 +495,13 @@ struct RoundSums {
 //   SE(T)^2 = S'^2 (Za^2 Va + Zb^2 Vb) / (4 (n-1) D'^4),
 // so the test is S'^2 (Za^2 Va + Zb^2 Vb) <= 4 tau^2 (n-1) D'^4 with
 // D' != 0 (NaN sums never stop).
-struct StopSides {
-  double lhs, rhs, Dp;
-};
-__device__ __forceinline__ StopSides screen_sides(const ScreenArgs& a, const RoundSums& S,
-                                                  int64_t n_side, bool anti, double Za,
-                                                  double Zb) {
+__device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSums& S,
+                                             int64_t n_side, int64_t first_check, bool anti,
+                                             double Za, double Zb) {
 #pragma clang fp contract(off)
+  if (a.mode != SHAPE_SCREEN_ADAPTIVE) return n_side >= a.n_fixed;
+  if (2 * n_side >= a.cap_pair) return true;
+  if (2 * n_side < first_check) return false;  // below the pair's seeded budget: no test yet
   const double tau2x4 = 4.0 * a.tau * a.tau;
   const double n = (double)(anti ? n_side / 2 : n_side);  // independent terms
   const double a1 = S.get(0), a11 = S.get(1), b1 = S.get(3), b11 = S.get(4);
@@ -509,23 +509,15 @@ __device__ __forceinline__ StopSides screen_sides(const ScreenArgs& a, const Rou
   const double Dp = Sp - 0.5 * (Za * a1 + Zb * b1);
   const double Va = fmax(n * a11 - a1 * a1, 0.0);
   const double Vb = fmax(n * b11 - b1 * b1, 0.0);
+  const double lhs = Sp * Sp * (Za * Za * Va + Zb * Zb * Vb);
   const double D2 = Dp * Dp;
-  return {Sp * Sp * (Za * Za * Va + Zb * Zb * Vb), tau2x4 * (n - 1.0) * D2 * D2, Dp};
-}
-__device__ __forceinline__ bool screen_stops(const ScreenArgs& a, const RoundSums& S,
-                                             int64_t n_side, int64_t first_check, bool anti,
-                                             double Za, double Zb) {
-  if (a.mode != SHAPE_SCREEN_ADAPTIVE) return n_side >= a.n_fixed;
-  if (2 * n_side >= a.cap_pair) return true;
-  if (2 * n_side < first_check) return false;  // below the pair's seeded budget: no test yet
-  const StopSides t = screen_sides(a, S, n_side, anti, Za, Zb);
-  return t.Dp != 0.0 && t.lhs <= t.rhs;
+  return Dp != 0.0 && lhs <= tau2x4 * (n - 1.0) * D2 * D2;
 }
 
 // Rounds for an adaptive pair's workgroup to draw together next, at most R, after n_side
-// samples per side: as many as its budget still asks for, or, past that, as SE(T)^2 over
-// tau^2 = lhs / rhs does, which falls as 1/n.  What it returns changes no result: rounds
-// past the stop are dropped.
+// samples per side: as many as its budget still asks for, or, past that, as (SE(T)/tau)^2
+// does, which falls as 1/n.  What it returns changes no result: rounds past the stop are
+// dropped.
 __device__ __forceinline__ int screen_rounds_for(int R, float more) {
   return !(more < (float)R) ? R : max(1, (int)ceilf(more));
 }
@@ -534,9 +526,11 @@ __device__ __forceinline__ int screen_next(const ScreenArgs& a, int R, const Rou
                                            double Za, double Zb) {
   const int64_t budget = first_check - 2 * n_side;
   if (budget > 0) return screen_rounds_for(R, (float)budget / (float)(2 * a.round_side));
-  const StopSides t = screen_sides(a, S, n_side, anti, Za, Zb);
-  const float ratio = (float)(t.lhs * __builtin_amdgcn_rcp(t.rhs));
-  return screen_rounds_for(R, (float)n_side / (float)a.round_side * (ratio - 1.0f));
+  const float r = (float)(se_tanimoto((double)(anti ? n_side / 2 : n_side), Za, Zb, S.get(0),
+                                      S.get(1), S.get(2), S.get(3), S.get(4), S.get(5), nullptr,
+                                      nullptr, nullptr, nullptr) /
+                          a.tau);
+  return screen_rounds_for(R, (float)n_side / (float)a.round_side * (r * r - 1.0f));
 }
 
 // A pair's outputs from its sums (one lane).
