@@ -47,9 +47,10 @@ PEAK_FP32_TFLOPS = 157.3
 # for a given kernel build), from the rocprofv3 summaries in profiles/:
 # HBM bytes (FETCH_SIZE x2.0 + WRITE_SIZE x1.0, scaled by a 1 GiB copy of
 # known size) and executed wave instructions (SQ_INSTS_VALU,
-# SQ_INSTS_VALU_TRANS_F32).  None until taken on the current kernel.
-TRAFFIC_BYTES = 55277.1 * 1024 * 2.0 + 32265.7 * 1024 * 1.0
-VALU_INSTS = 6143575919
+# SQ_INSTS_VALU_TRANS_F32), all with the (4, 4) tile.  None until taken on the
+# current kernel.
+TRAFFIC_BYTES = 55260.0 * 1024 * 2.0 + 32315.3 * 1024 * 1.0
+VALU_INSTS = 6143675919
 TRANS_INSTS = 751965680
 COUNTER_SOURCE = "profiles/k_screen_100k_library_counters.md"
 
@@ -731,6 +732,7 @@ def main():
             "unit": "TFLOP/s",
             "frac": achieved / PEAK_FP32_TFLOPS,
             "traffic": TRAFFIC_BYTES,
+            "counters_of": "k_screen<4, 4>",
             "kernel_ms": kern_ms,
             "atom_evals_per_launch": evals,
             "flops_per_atom_eval": FLOPS_PER_EVAL,

@@ -478,11 +478,11 @@ int shape_fo_starts(shape_ctx* ctx, const shape_mols* A, const shape_mols* B,
  * [n_pairs][n_starts], T_FO at the final poses; grad (device float
  * [n_pairs][n_starts][7] or NULL): dT_FO/dpose there.  n_steps = 0
  * evaluates T_FO and its gradient at the given poses.  FP32, one wave per
- * (pair, start), the whole optimisation in one launch; when A has at most
- * 64 atoms, one workgroup per pair (a start per 16-lane row), and with at
- * least 16 pairs per compute unit those run largest B first (order computed
- * on the device, 4 (pairs + 133120) bytes of context scratch; outputs the
- * same in any order).  Asynchronous.
+ * pair and up to four of its starts, the whole optimisation in one launch;
+ * when A has at most 64 atoms, one workgroup per pair (a start per 16-lane
+ * row), and with at least 16 pairs per compute unit those run largest B first
+ * (order computed on the device, 4 (pairs + 133120) bytes of context scratch;
+ * outputs the same in any order).  Asynchronous.
  * Errors: SHAPE_E_INVAL, SHAPE_E_RANGE (also molecules too large for the
  * kernel's LDS), SHAPE_E_NOMEM, SHAPE_E_HIP. */
 int shape_fo_align(shape_ctx* ctx, const shape_mols* A, const shape_mols* B, int32_t n_starts,

@@ -590,7 +590,8 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
 // Without a choice by the caller or the tuner: the tile of screen_points(), four points
 // per lane on both sides with rounds of whole fours (the fastest variant measured on
 // screens of 500, 7,000, 20,000 and 100,000 drug-sized molecules, fixed and adaptive,
-// i.i.d. and antithetic: 100,000, adaptive 7.15 ms, the next ones 7.22 and 7.32), or two;
+// i.i.d. and antithetic: the 100,000 of the performance cases, adaptive, 7.15 ms, the next
+// ones 7.22 and 7.32), or two;
 // (2, 1) for one slot per lane (40,000 pairs 1.78 ms, two points 2.50).
 int screen_variant_of(const shape_ctx* c, int round_side) {
   if (c->screen_variant >= 0) return c->screen_variant;

@@ -427,7 +427,7 @@ __device__ __forceinline__ void query_cache(const Prepared& Qp, const int* __res
 // broadcast); the hardware dispatcher balances pairs of uneven size.  The
 // workgroup is a single wave, or kRounds waves that each take one of kRounds
 // consecutive rounds and then add the rounds' totals, with the stop test after
-// each, in turn (screen_rounds: where single waves would leave the chip short
+// each, in turn (screen_shape: where single waves would leave the chip short
 // of waves; the same bits).  Pairs are renumbered so that each XCD screens tiles of consecutive
 // library molecules (xcd_chunk).  Per round, `round_side` samples on each side:
 //   side A (query samples, from the cache): f1 = w_A u_B, f2 = w_A u_A
@@ -703,13 +703,14 @@ __device__ __forceinline__ void screen_draw(const ScreenLds& lds, int nb, uint32
 // registers are held to 64, for eight waves per SIMD: the more waves, the
 // more often two of them stand at FP32 instructions that can be issued
 // together (trans_group); a density loop alone measured 21.6, 24.3 and 28.2
-// cycles per evaluation with eight, six and four waves.  100,000 molecules of
-// 10-50 atoms, 30-atom query, SE(T) <= 0.005: 8.07 ms with the exponentials
+// cycles per evaluation with eight, six and four waves.  On the 100,000 molecules
+// of the performance cases (10-50 atoms, 30-atom query, SE(T) <= 0.005; bench.py's
+// library takes 6.14e9 instructions and 7.8 ms): 8.07 ms with the exponentials
 // among the other instructions (76 registers), 7.15 ms with them grouped, 7.07
 // ms with the drawing steps of a lane's points grouped too, 7.00 ms with two
 // atoms per LDS word, no remainder loop and three-way XORs (5.67e9 -> 5.52e9
 // instructions); fixed 4,096 per side, 7,003 molecules: 0.60 -> 0.52 ms, and
-// 0.49 ms with four rounds of a pair at a time (screen_rounds).  Of
+// 0.49 ms with four rounds of a pair at a time (screen_shape).  Of
 // 4-cycle issue slots left by the exponentials, 1.62 of 2 hold an instruction.
 template <int kSA, int kSB, bool kAnti, int kRounds>
 __global__ __launch_bounds__(kRounds * kWave)

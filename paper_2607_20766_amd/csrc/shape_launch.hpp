@@ -119,7 +119,10 @@ inline double screen_rounds_expected(double tau, int round_side, double query_at
 //                      us: 3,000 pairs of 10-50 atoms that take 1.0 rounds 47 : 57, 1.5 63 :
 //                      76, 4.7 138 : 126; 7,000 1.5 100 : 129, 4.7 217 : 232, 9 255 : 252;
 //                      1,500 1.6 equal, 2.4 56 : 48), and long rounds do not repay a dropped
-//                      one (8,000 pairs, 1,024 samples per side and round 0.81 : 0.77 : 0.88)
+//                      one (8,000 pairs, 1,024 samples per side and round 0.81 : 0.77 : 0.88).
+//                      Fixed mode drops none; one : these, 2,048 samples per side: 3,000
+//                      molecules 160 : 140, 7,100 308 : 280, 9,000 (two) 364 : 350, 12,700 480 :
+//                      472; 512 samples equal from 5,000 on
 // All of them every time in fixed mode, with pairs so few that all waves run at once, and
 // where pairs need many: a pass more costs what a dropped round does not (1,000 pairs of
 // 10-50 atoms, 4.7 rounds 62 : 73 us; 800, 17 rounds 130 : 136).
