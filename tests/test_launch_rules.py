@@ -1,6 +1,6 @@
 """The launch rules that depend on sizes alone (csrc/shape_launch.hpp), built
 for the host and checked at sizes no test would launch: a launch holds fewer
-than 2^32 work-items along x, or the driver refuses it."""
+than 2^32 work-items along x, or the runtime refuses it."""
 import ctypes
 import os
 import shutil
@@ -150,6 +150,6 @@ def test_sets_are_prepared_apart_only_if_that_leaves_less_in_a_launch(rules):
     most = rules.r_max_workgroups(256)
     assert not rules.r_prepare_apart(most, 1, 1 << 26)
     assert rules.r_prepare_apart(most + 1, 1, 1 << 26)
-    # one set alone is left to the driver's refusal
+    # one set alone is left to the runtime's refusal
     assert not rules.r_prepare_apart(most + 1, 1 << 27, 0)
     assert not rules.r_prepare_apart(most + 1, 0, 1 << 27)
