@@ -635,19 +635,20 @@ static size_t split_lds_bytes(int n_samples, int max_a, int max_b) {
   return align_lds(n_samples, max_a, max_b, 1, std::min(per_lane, kSplitSlots));
 }
 bool align_splits(int n_pairs, int n_starts, int n_steps, int n_samples, int max_a, int max_b,
-                  int n_cu, size_t max_lds) {
+                  double mean_b, int n_cu, size_t max_lds) {
   const int per_lane = (n_samples + kWave - 1) / kWave;
   const int busy = std::min(kSplitWaves, (per_lane + kSplitS - 1) / kSplitS);
   const int resident = (int)(max_lds / align_lds(n_samples, max_a, max_b, kAlignMinWaves, 0)) *
                        std::min(n_starts, kAlignMinWaves);
-  return align_splits_starts(n_pairs, n_starts, n_steps, busy, resident, n_cu) &&
+  return align_splits_starts(n_pairs, n_starts, n_steps, busy, resident, mean_b, n_cu) &&
          align_split_fits(split_lds_bytes(n_samples, max_a, max_b), sizeof(SplitShared), max_lds);
 }
 
 hipError_t launch_align(const AlignArgs& args, int n_pairs, int n_cu, size_t max_lds,
                         hipStream_t st) {
   AlignArgs a = args;
-  if (align_splits(n_pairs, a.n_starts, a.n_steps, a.n_samples, a.max_a, a.max_b, n_cu, max_lds)) {
+  if (align_splits(n_pairs, a.n_starts, a.n_steps, a.n_samples, a.max_a, a.max_b, a.mean_b, n_cu,
+                   max_lds)) {
     hipLaunchKernelGGL(k_align_split, dim3((unsigned)n_pairs, (unsigned)a.n_starts),
                        dim3(kSplitWaves * kWave), split_lds_bytes(a.n_samples, a.max_a, a.max_b),
                        st, a);

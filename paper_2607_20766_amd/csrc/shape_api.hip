@@ -233,6 +233,11 @@ int check_mols(shape_ctx* c, const shape_mols* m, const char* name, bool single)
   return SHAPE_OK;
 }
 
+// Mean atoms of a set's molecules.
+double mean_atoms(const shape_mols* m) {
+  return std::max((double)m->n_atoms / m->n_mols, 1.0);
+}
+
 shape::MolsDev mols_dev(const shape_mols* m) {
   return shape::MolsDev{m->n_mols, m->max_atoms, m->n_atoms, m->atom_offset, m->xyz, m->alpha,
                         m->mol_id};
@@ -433,7 +438,7 @@ int align_prepare(shape_ctx* c, const shape_mols* A, const shape_mols* B, int n_
                   shape::Prepared* PB, const int** order) {
   int rc;
   if (shape::align_splits(A->n_mols, n_starts, n_steps, n_samples, A->max_atoms, B->max_atoms,
-                          c->n_cu, c->lds_per_block)) {
+                          mean_atoms(B), c->n_cu, c->lds_per_block)) {
     *order = nullptr;
     return prepare_sets(c, A, B, st, PA, PB);
   }
@@ -531,7 +536,7 @@ int screen_setup(shape_ctx* c, const shape_mols* query, const shape_mols* lib,
   // 65, 1,000 122 -> 102, 4,000 330 -> 304 (without the turns 2,000 243, 1,000
   // fixed 106).  Not for pairs of little work, about 25,000 evaluations and draws'
   // worth of them: 3,000 of 1-4 atoms, one round 38 -> 40.
-  const double mean_b = std::max((double)lib->n_atoms / lib->n_mols, 1.0);
+  const double mean_b = mean_atoms(lib);
   const double expected = shape::screen_rounds_expected(prm->tau, round_side, query->max_atoms,
                                                         mean_b);
   const double side = prm->mode == SHAPE_SCREEN_FIXED
@@ -1163,6 +1168,7 @@ int align_launch(shape_ctx* c, const shape_mols* A, const shape_mols* B,
   a.lr = 0.f;
   a.pose_out = nullptr;
   a.order = order;
+  a.mean_b = mean_atoms(B);
   HIP_TRY(c, shape::launch_align(a, A->n_mols, c->n_cu, c->lds_per_block, st), "alignment kernel");
   return SHAPE_OK;
 }
@@ -1259,6 +1265,7 @@ int shape_align(shape_ctx* c, const shape_mols* A, const shape_mols* B, int32_t 
     a.lr = lr;
     a.pose_out = pose;
     a.order = order;
+    a.mean_b = mean_atoms(B);
     KernelTimer timer(c, st);
     HIP_TRY(c, shape::launch_align(a, pairs, c->n_cu, c->lds_per_block, st), "alignment kernel");
     timer.stop();

@@ -87,6 +87,7 @@ struct AlignArgs {
   float* pose_out;    // the pose array again (written when n_steps > 0)
   const int* order;   // optional launch order: block b aligns pair order[b]
   int starts_per_block = 0;  // starts a workgroup takes (set by launch_align)
+  double mean_b = 0.0;       // mean atoms of B's molecules (for launch_align)
 };
 
 // Dense layer C = epilogue(A B) with strided operands (see shape_gemm).
@@ -208,7 +209,7 @@ size_t align_lds_bytes(int n_samples, int max_a, int max_b);
 // max_lds: LDS bytes a workgroup may use.  A call that align_splits runs every
 // start by itself and reads no launch order.
 bool align_splits(int n_pairs, int n_starts, int n_steps, int n_samples, int max_a, int max_b,
-                  int n_cu, size_t max_lds);
+                  double mean_b, int n_cu, size_t max_lds);
 hipError_t launch_align(const AlignArgs& a, int n_pairs, int n_cu, size_t max_lds,
                         hipStream_t st);
 struct SelfSet {

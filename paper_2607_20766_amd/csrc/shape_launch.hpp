@@ -34,17 +34,22 @@ inline bool prepare_apart(int64_t blocks, int n_a, int n_b) {
 //               : 328; 2,048 (sixteen) 160 280 : 520, 2,000 720 : 610
 //   none        256 samples, 550 starts 33 : 27; 512, 550 34 : 29; 1,000, 1,000 54 : 48;
 //               2,048, 1,000 equal
+// Steps of small molecules (mean_b atoms in B on average) are mostly the part that one
+// wave takes by itself, so fewer starts still: 2,048 samples, 8 steps, 1,600 starts of 2-8
+// atoms 286 : 172, 10-20 398 : 321.
 // resident: waves of k_align with a start that a compute unit's LDS holds (the samples
-// take 16 bytes each).  With one per SIMD or less every wave waits for its own chain
-// alone, however many starts there are: 5,000 pairs x 1 start, 8 steps of 4,096 samples
-// 3.4 : 8.0 ms, of 2,048 1.8 : 2.2; 2,000 x 2 of 4,096 2.6 : 3.5 (x 4, 500 pairs 1.3 : 1.2).
+// take 16 bytes each).  With one per SIMD or less (two per compute unit for small molecules
+// and single evaluations) every wave waits for its own chain alone, however many starts
+// there are: 5,000 pairs x 1 start, 8 steps of 4,096 samples 3.4 : 8.0 ms, of 2,048 1.8 :
+// 2.2; 2,000 x 2 of 4,096 2.6 : 3.5 (x 4, 500 pairs 1.3 : 1.2); 20,000 x 1 of 2-8 atoms and
+// 2,048 samples, 2 steps 1.5 : 1.3.
 inline bool align_splits_starts(int64_t n_pairs, int n_starts, int n_steps, int busy,
-                                int resident, int n_cu) {
+                                int resident, double mean_b, int n_cu) {
   if (n_starts > 65535 || n_pairs > max_workgroups(1024)) return false;
-  if (resident <= (n_steps > 0 ? 4 : 2)) return true;
-  // starts per compute unit, times four
-  const int64_t most = n_steps > 0 ? std::min(28, 2 * (busy + 1)) : std::min(16, busy + 4);
-  return 4 * n_pairs * n_starts <= most * n_cu;
+  if (resident <= (n_steps > 0 && mean_b >= 12.0 ? 4 : 2)) return true;
+  const double per_cu = n_steps > 0 ? std::min(7.0, 0.5 * (busy + 1))
+                                    : std::min(4.0, 0.25 * (busy + 4));
+  return (double)n_pairs * n_starts <= per_cu * std::min(1.0, 0.3 + mean_b / 43.0) * n_cu;
 }
 
 // Waves (starts in flight) of a workgroup: eight share the samples of A where that

@@ -19,8 +19,8 @@ int r_align_waves(int64_t pairs, int starts, int fit, int crowded, int n_cu) {
   return align_waves(pairs, starts, fit, crowded, n_cu);
 }
 int r_align_splits_starts(int64_t pairs, int starts, int steps, int busy, int resident,
-                          int n_cu) {
-  return align_splits_starts(pairs, starts, steps, busy, resident, n_cu);
+                          double mean_b, int n_cu) {
+  return align_splits_starts(pairs, starts, steps, busy, resident, mean_b, n_cu);
 }
 int r_align_starts_per_block(int64_t pairs, int starts, int waves, int n_cu) {
   return align_starts_per_block(pairs, starts, waves, n_cu);
@@ -56,7 +56,8 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(str(lib))
     L.r_max_workgroups.restype = ctypes.c_int64
     L.r_align_waves.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
-    L.r_align_splits_starts.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 5
+    L.r_align_splits_starts.argtypes = ([ctypes.c_int64] + [ctypes.c_int] * 4 +
+                                        [ctypes.c_double, ctypes.c_int])
     L.r_align_starts_per_block.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     L.r_prepare_apart.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     L.r_align_split_fits.argtypes = [ctypes.c_int64] * 3
@@ -110,13 +111,16 @@ def test_a_kernels_own_lds_counts_towards_the_limit(rules):
 def test_starts_run_by_themselves_only_where_their_waves_have_samples(rules):
     split = rules.r_align_splits_starts
     # 10 and 100 pairs x 16 starts of 2,048 samples; not 500 x 4 of 256
-    assert split(10, 16, 60, 16, 16, 256) and split(100, 16, 60, 16, 16, 256)
-    assert not split(500, 4, 8, 2, 32, 256) and not split(250, 8, 8, 4, 32, 256)
-    assert not split(1000, 1, 0, 2, 9, 256)
+    assert split(10, 16, 60, 16, 16, 30.0, 256) and split(100, 16, 60, 16, 16, 30.0, 256)
+    assert not split(500, 4, 8, 2, 32, 30.0, 256) and not split(250, 8, 8, 4, 32, 30.0, 256)
+    assert not split(1000, 1, 0, 2, 9, 30.0, 256)
+    # nor small molecules, but for a handful
+    assert split(10, 16, 60, 16, 16, 5.0, 256) and not split(100, 16, 60, 16, 16, 5.0, 256)
+    assert split(20000, 1, 8, 16, 4, 30.0, 256) and not split(20000, 1, 8, 16, 4, 5.0, 256)
     # never more workgroups than a launch holds
     for pairs in (1, 1 << 22, (1 << 22) - 1, 1 << 31):
         for resident in (1, 4, 16):
-            if split(pairs, 1, 8, 16, resident, 256):
+            if split(pairs, 1, 8, 16, resident, 30.0, 256):
                 assert pairs * 1024 < LIMIT
 
 
