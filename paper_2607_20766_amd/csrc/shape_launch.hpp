@@ -130,9 +130,15 @@ inline double screen_rounds_expected(double tau, int round_side, double query_at
 //                      472; 512 samples equal from 5,000 on
 // All of them every time in fixed mode, with pairs so few that all waves run at once, and
 // where pairs need many: a pass more costs what a dropped round does not (1,000 pairs of
-// 10-50 atoms, 4.7 rounds 62 : 73 us; 800, 17 rounds 130 : 136).
+// 10-50 atoms, 4.7 rounds 62 : 73 us; 800, 17 rounds 130 : 136).  A budget only adds to
+// what tau asks for: seeded pairs of such a tau too (a triage's best 8,385 of 167,696
+// molecules, 11-atom query, tau 0.005: 868 us whole, 952 from the budgets; 2,336 of
+// 46,744, 48 atoms 224 : 232).
 // One workgroup per pair: the rounds fall until a launch holds them.  n_rounds is the most
-// a pair takes, expected what it takes on average, unless it has a budget (seeded).
+// a pair takes, expected what tau asks for on average; a budget (seeded) may ask for more,
+// on the device: several rounds then too where tau alone needs few (budgets of 4.7 rounds on
+// average, up to 37, tau 0.02, 3,000 pairs of 10-50 atoms, one : two : four 517 : 268 : 158 us;
+// all budgets one round 73 : 71 : 82).
 constexpr int kSplitPairsPerCu = 3;  // up to here rounds of 256 samples: eight waves per pair
 struct ScreenShape {
   int rounds, first;
@@ -151,7 +157,7 @@ inline ScreenShape screen_shape(bool adaptive, bool seeded, int64_t n_pairs, int
   }
   int R = std::max(few, resident <= 11 ? 4 : (resident <= 25 ? 2 : 1));
   while (R > n_rounds || (R > 1 && n_pairs > max_workgroups(R * 64))) R /= 2;
-  const bool many = !seeded && expected >= (up_to(14) ? 4.0 : 8.0);
+  const bool many = expected >= (up_to(14) ? 4.0 : 8.0);
   const bool all = !adaptive || many || (few > 1 && up_to(kSplitPairsPerCu));
   return {R, all ? R : 1};
 }

@@ -150,6 +150,16 @@ def test_pairs_that_need_one_round_get_one_wave(rules):
         assert R(pairs, 0.005, 30.0) > 1 and R(pairs, 0.01, 2.5) == 1, pairs
 
 
+@pytest.mark.parametrize("seeded", [0, 1])
+def test_pairs_whose_tau_needs_many_rounds_get_whole_passes(rules, seeded):
+    """Budgets add to what tau asks for."""
+    first = ctypes.c_int()
+    for pairs, expected in ((1000, 17.0), (2336, 4.7), (3584, 4.0), (3585, 8.0), (12800, 17.0)):
+        R = rules.r_screen_shape(1, seeded, pairs, 128, expected, 256, 4000, 256,
+                                 ctypes.byref(first))
+        assert first.value == R > 1, pairs
+
+
 def test_sets_are_prepared_apart_only_if_that_leaves_less_in_a_launch(rules):
     most = rules.r_max_workgroups(256)
     assert not rules.r_prepare_apart(most, 1, 1 << 26)
