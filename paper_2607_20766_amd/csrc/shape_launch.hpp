@@ -108,37 +108,50 @@ inline double screen_rounds_expected(double tau, int round_side, double query_at
 }
 
 // Rounds of a pair that its workgroup works on at a time, a wave each, and those of its
-// first pass: all of them, and then in every pass, or one (or what the pair's budget
+// first pass: all of them, and then in every pass, or fewer (but what the pair's budget
 // holds), and then as many as the pair still seems to need.
 // Several rounds where one wave per pair leaves a compute unit short of waves:
-//   LDS per pair       (lds bytes) for the rounds, any number of them: 20,000 molecules of
-//                      50-100 atoms (17 pairs in a compute unit's LDS), one : two : four
-//                      rounds 3.04 : 2.63 : 2.78 ms; 60,000 of 30-70 (25) 6.59 : 6.53 :
-//                      6.90, of 30-60 (28) 6.49 : 6.52 : 6.88; 20,000 of 100-150 (11) fixed
-//                      3.09 : 2.59 : 2.32, of 200-256 (6) 6.98 : 5.03 : 3.99
-//   few pairs          four up to 28 pairs per compute unit (fewer than eight waves per
-//                      SIMD), two up to 50: 5,000 molecules of 10-50 atoms, adaptive 0.58 :
-//                      0.51 : 0.49 ms; 8,000 0.78 : 0.71 : 0.72; 11,000 1.00 : 0.92 : 0.96;
-//                      13,000 1.09 : 1.07 : 1.14.  Adaptive pairs have to need them: a pair
-//                      that stops in its first rounds leaves its other waves idle (one : four,
-//                      us: 3,000 pairs of 10-50 atoms that take 1.0 rounds 47 : 57, 1.5 63 :
-//                      76, 4.7 138 : 126; 7,000 1.5 100 : 129, 4.7 217 : 232, 9 255 : 252;
-//                      1,500 1.6 equal, 2.4 56 : 48), and long rounds do not repay a dropped
-//                      one (8,000 pairs, 1,024 samples per side and round 0.81 : 0.77 : 0.88).
-//                      Fixed mode drops none; one : these, 2,048 samples per side: 3,000
-//                      molecules 160 : 140, 7,100 308 : 280, 9,000 (two) 364 : 350, 12,700 480 :
-//                      472; 512 samples equal from 5,000 on
-// All of them every time in fixed mode, with pairs so few that all waves run at once, and
-// where pairs need many: a pass more costs what a dropped round does not (1,000 pairs of
-// 10-50 atoms, 4.7 rounds 62 : 73 us; 800, 17 rounds 130 : 136).  A budget only adds to
-// what tau asks for: seeded pairs of such a tau too (a triage's best 8,385 of 167,696
-// molecules, 11-atom query, tau 0.005: 868 us whole, 952 from the budgets; 2,336 of
-// 46,744, 48 atoms 224 : 232).
+//   LDS per pair       (lds bytes) for the rounds: 20,000 molecules of 50-100 atoms (17
+//                      pairs in a compute unit's LDS), one : two : four rounds 3.04 : 2.63 :
+//                      2.78 ms; 60,000 of 30-70 (25) 6.59 : 6.53 : 6.90, of 30-60 (28) 6.49 :
+//                      6.52 : 6.88; 20,000 of 100-150 (11) fixed 3.09 : 2.59 : 2.32, of
+//                      200-256 (6) 6.98 : 5.03 : 3.99
+//   few pairs          fixed mode, four up to 28 pairs per compute unit (fewer than eight
+//                      waves per SIMD), two up to 50; 2,048 samples per side, one : these:
+//                      3,000 molecules 160 : 140 us, 7,100 308 : 280, 9,000 (two) 364 :
+//                      350, 12,700 480 : 472; 512 samples equal from 5,000 on
+// Adaptive pairs have to need them, or they leave their other waves idle, and a pass more
+// costs about what two dropped rounds do.  Molecules of 10-50 atoms, 30-atom query (e:
+// expected; one : two : two after a first of one : four : four after a first of one), us:
+//   pairs  800  e 1.1    46 :   41 :   46 :   40 :   46
+//         1500  e 2.2    74 :   61 :   66 :   56 :   66
+//         3500  e 4.4   156 :  141 :  152 :  139 :  152
+//         5000  e 4.4   177 :  166 :  181 :  180 :  195
+//         7000  e 8.9   391 :  359 :  394 :  375 :  413
+//         9000  e 8.9   452 :  435 :  479 :  466 :  513
+//         9000  e 2.2   158 :  168 :  178 :  198 :  218
+// of 50-100 atoms, 64-atom query:
+//          800  e 1.1    69 :   51 :   69 :   62 :   68
+//         9000  e 4.4   473 :  406 :  415 :  419 :  473
+//         9000  e 2.2   295 :  261 :  289 :  365 :  343
+//         9000  e 1.1   198 :  212 :  194 :  366 :  221
+// and of 160-250 atoms, 200-atom query (e 2.2: four after a first of two 689):
+//         9000  e 4.4  1536 : 1234 : 1322 : 1003 : 1210
+//         9000  e 2.2   916 :  711 :  908 :  907 :  905
+//         9000  e 1.1   567 :  645 :  553 :  909 :  542
+// Over 906 such screens (1-250 atoms, 800-20,000 pairs, SE(T) 0.003 to 0.05) this rule
+// takes 1.01 times the fastest of the six shapes and at most 1.06 times one wave per pair.
+// Up to three pairs per compute unit (rounds of other sizes than 256) four from e 1: 700
+// pairs of 150-256 atoms, 1,024 samples per side and round, e 1.2 263 us, two 306, one 480.
+// Otherwise long rounds do not repay a dropped one (8,000 pairs, 1,024 samples per side and
+// round 0.81 : 0.77 : 0.88 ms).
+// A budget (seeded) only adds to what tau asks for, on the device: several rounds then by
+// the number of pairs alone (budgets of 4.7 rounds on average, up to 37, tau 0.02, 3,000
+// pairs of 10-50 atoms, one : two : four 517 : 268 : 158 us; all budgets one round 73 : 71 :
+// 82), whole where tau alone needs many (a triage's best 8,385 of 167,696 molecules,
+// 11-atom query, tau 0.005: 868 us, from the budgets 952).
 // One workgroup per pair: the rounds fall until a launch holds them.  n_rounds is the most
-// a pair takes, expected what tau asks for on average; a budget (seeded) may ask for more,
-// on the device: several rounds then too where tau alone needs few (budgets of 4.7 rounds on
-// average, up to 37, tau 0.02, 3,000 pairs of 10-50 atoms, one : two : four 517 : 268 : 158 us;
-// all budgets one round 73 : 71 : 82).
+// a pair takes, expected what tau asks for on average.
 constexpr int kSplitPairsPerCu = 3;  // up to here rounds of 256 samples: eight waves per pair
 struct ScreenShape {
   int rounds, first;
@@ -148,18 +161,27 @@ inline ScreenShape screen_shape(bool adaptive, bool seeded, int64_t n_pairs, int
   constexpr int64_t kLdsPerCu = 160 * 1024;
   const int64_t resident = kLdsPerCu / lds;
   const auto up_to = [&](int per_cu) { return n_pairs <= (int64_t)per_cu * n_cu; };
+  const double e = expected;
   int few = up_to(28) ? 4 : (up_to(50) ? 2 : 1);
-  if (adaptive && !up_to(1)) {
-    const double least = up_to(kSplitPairsPerCu) ? 1.0 : (up_to(8) ? 2.0 : (up_to(14) ? 4.0 : 8.0));
-    if (!seeded && expected < least) few = 1;
-    if (!up_to(kSplitPairsPerCu))
-      while (few > 1 && few * round_side > 1024) few /= 2;
+  int room = resident <= 11 ? 4 : (resident <= 25 ? 2 : 1);
+  if (adaptive && !seeded && !up_to(1)) {
+    if (e < (up_to(kSplitPairsPerCu) ? 1.0 : (up_to(14) ? 1.9 : 10.0)))
+      few = (up_to(8) && e >= 0.7) || (up_to(28) && e >= 2.5) || (up_to(50) && e >= 5.0) ? 2 : 1;
+    if (e < 1.9) room = std::min(room, 2);
   }
-  int R = std::max(few, resident <= 11 ? 4 : (resident <= 25 ? 2 : 1));
+  if (adaptive && !up_to(kSplitPairsPerCu))
+    while (few > 1 && few * round_side > 1024) few /= 2;
+  int R = std::max(few, room);
   while (R > n_rounds || (R > 1 && n_pairs > max_workgroups(R * 64))) R /= 2;
-  const bool many = expected >= (up_to(14) ? 4.0 : 8.0);
-  const bool all = !adaptive || many || (few > 1 && up_to(kSplitPairsPerCu));
-  return {R, all ? R : 1};
+  int first = 1;
+  // whole passes also where most pairs' waves run at once anyway
+  const bool at_once = up_to(14) && 5 * n_pairs <= 3 * resident * n_cu;
+  if (!adaptive || up_to(1) || e >= 3.5 || (e >= 1.9 && at_once) ||
+      (e >= 1.0 && up_to(kSplitPairsPerCu)))
+    first = R;
+  else if (e >= 1.9 || (e >= 0.7 && up_to(8)))
+    first = std::min(2, R);
+  return {R, first};
 }
 
 }  // namespace shape

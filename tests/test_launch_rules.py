@@ -146,8 +146,24 @@ def test_pairs_that_need_one_round_get_one_wave(rules):
         return rules.r_screen_shape(1, 0, pairs, 128, e, 256, 4000, 256, ctypes.byref(first))
 
     for pairs in (1000, 3000, 7000, 12500):
-        assert R(pairs, 0.05, 30.0) == 1 and R(pairs, 0.02, 30.0) == 1, pairs
+        assert R(pairs, 0.05, 30.0) == 1, pairs
+        # half of them a second round: together where the chip has waves to spare
+        assert R(pairs, 0.02, 30.0) == (2 if pairs == 1000 else 1), pairs
         assert R(pairs, 0.005, 30.0) > 1 and R(pairs, 0.01, 2.5) == 1, pairs
+
+
+def test_large_molecules_that_need_a_few_rounds_get_them_together(rules):
+    """As many in the first pass as their pairs take, where LDS holds few pairs."""
+    first = ctypes.c_int()
+
+    def shape(pairs, expected, lds):
+        return rules.r_screen_shape(1, 0, pairs, 128, expected, 256, lds, 256,
+                                    ctypes.byref(first)), first.value
+
+    assert shape(9000, 4.4, 9600) == (2, 2) and shape(9000, 2.2, 9600) == (2, 2)
+    assert shape(9000, 1.1, 9600) == (2, 1) and shape(800, 1.1, 9600) == (2, 2)
+    assert shape(9000, 4.4, 24000) == (4, 4) and shape(9000, 2.2, 24000) == (4, 2)
+    assert shape(9000, 1.1, 24000) == (2, 1)
 
 
 @pytest.mark.parametrize("seeded", [0, 1])
